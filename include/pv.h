@@ -111,8 +111,8 @@ pv_status pv_select_topk_groups(pv_ctx *ctx, const pv_layout *layout, const floa
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): pv_select_topk_groups with the same
  * arguments and the same results, whose scratch (group scores when group_scores is NULL,
- * radix-select histograms, per-chunk counts) lives in one static device array of about
- * 16.1 MiB that every GPU the library runs on holds until the process ends.  It calls no
+ * radix-select histograms, counts) lives in one static device array of about
+ * 16.5 MiB that every GPU the library runs on holds until the process ends.  It calls no
  * allocation or release routine of any kind, creates no events (timing brackets are off for
  * this call) and enqueues only kernels.  Limit: N <= 4 194 304 groups, else
  * PV_ERR_UNSUPPORTED.  All calls on one GPU share the array: calls that overlap on one GPU

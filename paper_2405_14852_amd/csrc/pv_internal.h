@@ -37,9 +37,10 @@ struct pv_ctx {
 
     // scratch, grown on demand (never shrunk)
     pv_buffer sel_scores;   // f32 [N]            group scores when the caller passes none
-    pv_buffer sel_hist;     // u32 [copies + 2][bins]  radix-select histograms (kept zero between calls)
-    pv_buffer sel_blocks;   // u32 [nblocks][2]   per-block (greater, equal) counts
-    pv_buffer sel_state;    // u32 [4]            threshold key, ties to take
+    pv_buffer sel_hist;     // radix-select histograms, eight copies each (kept zero between calls)
+    pv_buffer sel_blocks;   // u32                counts per wave and per block of the selection
+    pv_buffer sel_list;     // {key, id} [waves][room]  the keys at or above digit 0's range, per wave
+    pv_buffer sel_state;    // u32 [8]            digits found, ranks left
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
     pv_buffer cb_f16;       // prepared codebook operand for the matrix-core filter
     pv_buffer cb_meta;      // u32 [2][8]         two slots of codebook statistics (scale, norms, rounding bound)

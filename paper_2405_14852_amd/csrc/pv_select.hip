@@ -3,69 +3,72 @@
 // score_n = sum_i (T[n,i] - W[n,i])^2 as an fp32 fused-multiply-add chain in
 // index order, so that every implementation of this rule gives the same bits.
 // Scores are non-negative floats, so their bit patterns order like unsigned
-// integers.  The k-th largest key is found by a 3-digit radix select (11 + 12 +
+// integers.  The k-th largest key is found by a 3-digit radix select (12 + 11 +
 // 8 bits below the sign, most significant first); groups above the threshold are taken, groups
 // equal to it are taken lowest id first, and the ids are written in ascending
-// order through a two-level prefix sum.  Nothing returns to the host.
+// order.  Nothing returns to the host.
 //
-// Launches: [scores + digit-0 histogram] [digit-1 histogram] [digit-2 histogram]
-// [per-chunk counts] [ordered write].  Digit 0 (exponent and three mantissa bits: an
-// eighth of an octave - the later passes pay one atomic on device memory for each key
-// that shares the chosen one, the sweep one for each populated bin of each block) is counted in an LDS histogram inside
-// the streaming score kernel, whose
-// blocks are persistent so that clearing and flushing it is paid once per block;
-// the later digits usually see only the few per cent of keys that share the
-// chosen digit 0, but a narrow score distribution (updates of one size, as an
-// optimiser's sign-like step produces) sends nearly all keys there, so they are
-// counted in per-block LDS histograms as well.  Each launch resolves the digit of the histogram before it and
-// publishes it for the launches that follow.
+// Launches: [scores + digit-0 histogram] [collect] [last digit] [ordered write]; up to
+// kSmallGroups groups the last three are one block's work, and for k = N the sweep writes the
+// ids itself.
+// - The sweep counts digit 0 (exponent and four mantissa bits) in an LDS histogram; its blocks
+//   are persistent so that clearing and flushing it is paid once per block.
+// - k_collect is the only pass over all scores after the sweep.  It resolves digit 0, counts
+//   digit 1 of the keys that share it, and copies every key at or above that digit's range, with
+//   its id, into a short list per wave - a little more than the k that will be chosen.
+// - k_last_digit and k_write_ids read those lists only.
+// A list that does not fit (nearly all keys share digit 0, as after an optimiser's sign-like
+// first step, or k is a large part of N) is dropped, and the two kernels read that wave's scores
+// instead: slower, the same result.
+//
+// Histograms in device memory are kept in kCopies copies, block b adding to copy b % kCopies:
+// workgroups are dealt to the eight dies round robin, so the blocks that share a copy share an
+// L2 and their atomics stay in it.  One copy for all moves each line from die to die: 1 M
+// atomics on 2048 counters took 11 us against 1.3 us (512 blocks; 110 and 150 per ns).  That is
+// what makes a 12-bit digit 0 affordable, and a fine digit 0 keeps the lists and the later
+// histograms short.  Every histogram also has a coarse level (sums of 64 counters), so that a
+// reader adds up two rounds of 64 counters and not the whole table.
 #include "pv_internal.h"
 
 #ifndef PV_VOTE_ROUNDS
 #define PV_VOTE_ROUNDS 1   // wave-wide merges before per-lane LDS atomics (guards degenerate inputs)
 #endif
 
-#ifndef PV_LATE_VOTE_ROUNDS
-#define PV_LATE_VOTE_ROUNDS 0   // the same for the later digits: plain LDS atomics are faster on spread-out scores and on the narrow ones of an Adam step; only when EVERY score is equal would the merge win (5.6 M groups: 139 against 157 us for sweep + selection)
-#endif
-
 namespace {
 
 constexpr int kBlock = 256;
-#ifndef PV_REST_BITS
-#define PV_REST_BITS 20
-#endif
-constexpr int kRestBits = PV_REST_BITS;         // bits of a key below digit 0
-#ifndef PV_MID_BITS
-#define PV_MID_BITS (PV_REST_BITS - 8)
-#endif
-constexpr int kMidBits = PV_MID_BITS;
-constexpr int kSlots = 4096;                    // slots of every histogram in device memory
-constexpr int kFirstBins = 1 << (31 - kRestBits);      // digit 0: exponent and 3 mantissa bits (keys are clamped below 2^31)
-constexpr int kBins = 1 << kMidBits;                   // digit 1: the next mantissa bits
-constexpr int kLastBins = 1 << (kRestBits - kMidBits + 1); // digit 2: the remaining low mantissa bits (at most)
-static_assert(kFirstBins <= kSlots && kBins <= kSlots && kLastBins <= kSlots, "a histogram fits its slots");
-constexpr int kItems = 8;                      // groups per thread in the compaction kernels
-constexpr int kChunk = kBlock * kItems;        // groups per chunk there
-static_assert(kChunk < 65536, "the compaction packs two per-chunk counts into 32 bits");
+constexpr int kRestBits = 19;                   // bits of a key below digit 0
+constexpr int kLastBits = 8;                    // bits of digit 2
+constexpr int kFirstBins = 1 << (31 - kRestBits);        // digit 0 (keys are clamped below 2^31)
+constexpr int kMidBins = 1 << (kRestBits - kLastBits);   // digit 1
+constexpr int kLastBins = 1 << kLastBits;                // digit 2
 #ifndef PV_SEL_BLOCKS
 #define PV_SEL_BLOCKS 512
 #endif
 constexpr int kMaxBlocks = PV_SEL_BLOCKS;      // persistent grid of the streaming kernels: two blocks per compute unit (1024 cost 1 us on 2 M groups and 4 to 6 us on 3.7 to 5.6 M, 256 lose a sixth of the bandwidth)
-constexpr int kCompactBlocks = 1024;           // grid of the two compaction kernels
+
+// Histograms in device memory: [copy][bin] and [copy][bin / 64], one after the other.
+constexpr int kCopies = 8;
+constexpr int kFine = 64;                      // counters per coarse counter, one per lane of a wave
+constexpr int hist_words(int bins) { return kCopies * (bins + bins / kFine); }
+constexpr int kHist0 = 0, kHist1 = kHist0 + hist_words(kFirstBins), kHist2 = kHist1 + hist_words(kMidBins);
+constexpr int kHistTotal = kHist2 + hist_words(kLastBins);
+
+// The passes after the sweep: region r of kSelWaves * blocks is the contiguous range of groups
+// that wave r works on in every one of them.
+constexpr int kSelBlock = 1024;
+constexpr int kSelWaves = kSelBlock / 64;
+constexpr int kSelBlocks = 256;                // at most: one block per compute unit (collect on 5.6 M scores: 12.9 us; 128 blocks 15.1, 512 blocks 16.2)
+constexpr int kAhead = 4;                      // 16-byte loads in flight per lane
+constexpr int kSuffix = kLastBins + 8;         // row of a block's suffix counts (kLastBins + 1 used)
+constexpr int kSmallGroups = 32768;            // a single block selects among at most so many
 
 // The key of a score: its bits, which order like the values because scores are sums of squares
 // (never negative); a pattern with the sign bit set can only be a NaN and is clamped to the
 // largest key, so that digit 0 needs no bit for the sign.
 __device__ __forceinline__ unsigned score_key(float s) { return min(__float_as_uint(s), 0x7FFFFFFFu); }
 
-// `mid`: the width of digit 1, which every call fixes when digit 0 is known (see k_hist_next).
-__device__ __forceinline__ int digit_of(unsigned key, int pass, int mid = kMidBits)
-{
-    return pass == 0 ? (int)(key >> kRestBits)
-                     : pass == 1 ? (int)((key >> (kRestBits - mid)) & ((1u << mid) - 1u))
-                                 : (int)(key & ((1u << (kRestBits - mid)) - 1u));
-}
+__device__ __forceinline__ int digit0_of(unsigned key) { return (int)(key >> kRestBits); }
 
 // Add one count per valid lane to an LDS histogram.  Lanes of a wave that hit
 // the same bin as the first pending lane are merged first (catches the
@@ -89,102 +92,82 @@ __device__ __forceinline__ void hist_add(unsigned *hist, int bin, bool valid)
     if (valid) atomicAdd(&hist[bin], 1u);
 }
 
-// Exclusive prefix sum of one value per thread over the block (thread order);
-// *total receives the block sum.  `tmp` needs kBlock / 64 unsigneds of LDS.
-__device__ __forceinline__ unsigned block_excl_scan(unsigned v, unsigned *tmp, unsigned *total)
+// inclusive prefix sum over the lanes of a wave
+__device__ __forceinline__ unsigned wave_incl_scan(unsigned v)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned inc = v;
+    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        unsigned u = __shfl_up(inc, off);
-        if (lane >= off) inc += u;
+        const unsigned u = __shfl_up(v, off);
+        if (lane >= off) v += u;
     }
-    __syncthreads();
-    if (lane == 63) tmp[wave] = inc;
-    __syncthreads();
-    unsigned before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kBlock / 64; ++w) {
-        unsigned x = tmp[w];
-        before += w < wave ? x : 0u;
-        all += x;
-    }
-    __syncthreads();
-    *total = all;
-    return before + inc - v;
+    return v;
 }
 
-// Global histograms are stored so that the scan below reads them coalesced:
-// digit d of a `bins`-digit histogram has rank r = bins - 1 - d from the top and
-// lives at slot (r % kPer) * 256 + r / kPer with kPer = kSlots / 256 ranks per scan thread;
-// thread t of the scan owns ranks [kPer t, kPer t + kPer), i.e. slots t, t + 256, ...
-// Every histogram occupies kSlots slots.
-constexpr int kPer = kSlots / kBlock;
-// The first histogram is fed by every block of the scoring sweep at about the same moment, and
-// most of the counts fall on a dozen bins: its atomics would queue on a dozen addresses (5 to
-// 14 us on 2 M groups, depending on where the scores fall).  It is kept in kSub copies (two
-// already take the queue below the kernel's streaming time; more only cost the readers), block
-// b adds to copy b % kSub, the reader adds the copies.
-#ifndef PV_HIST_COPIES
-#define PV_HIST_COPIES 2
-#endif
-constexpr int kSub = PV_HIST_COPIES;
-constexpr int kHist1 = kSub * kSlots;         // offsets of the second and third histogram
-constexpr int kHist2 = kHist1 + kSlots;
-constexpr int kHistTotal = kHist2 + kSlots;
-__device__ __forceinline__ int hist_slot(int digit, int bins)
+__device__ __forceinline__ unsigned wave_sum(unsigned v)
 {
-    const int r = bins - 1 - digit;
-    return (r % kPer) * kBlock + (r / kPer);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
 }
 
-// Given a histogram of `bins` digits and the rank `kk` (1-based, counted from the
-// largest digit), find the digit d with  count(> d) < kk <= count(>= d)  and
-// return kk - count(> d).  All threads of the block call this; the result goes
-// to all, with the count of that digit if `count` is given.  `tmp` is kBlock + 3 unsigneds of LDS.
-template <int COPIES = 1>
-__device__ void pick_digit(const unsigned *__restrict__ ghist, int bins, unsigned kk,
-                           unsigned *tmp, int *digit, unsigned *kk_rem, unsigned *count = nullptr)
+// One counter per lane, lane 0 holding the LARGEST digit: the lane in which the rank kk (1-based,
+// counted from the top) falls; kk becomes the rank within that lane's counter.
+__device__ __forceinline__ int pick_lane(unsigned count, unsigned &kk)
 {
-    constexpr int per = kPer;            // ranks per thread; thread 0 owns the TOP digits
-    const int tid = threadIdx.x;
-    unsigned cnt[per];
-    unsigned sum = 0;
+    const unsigned inc = wave_incl_scan(count);
+    const unsigned long long at = __ballot(inc >= kk);
+    const int src = at ? __ffsll((long long)at) - 1 : 63;
+    kk -= __shfl(inc - count, src);
+    return src;
+}
+
+// The digit d of the histogram `h` (in device memory, `bins` counters) with
+// count(> d) < kk <= count(>= d); kk becomes kk - count(> d).  Called by all threads of a block of
+// at least kCopies waves: wave c fetches the 64 counters of copy c, every wave adds up all
+// copies (the result needs no broadcast).  `tmp`: 2 * kCopies * 64 unsigneds of LDS.
+__device__ __forceinline__ int pick_digit(const unsigned *__restrict__ h, int bins, unsigned &kk, unsigned *tmp)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ncoarse = bins / kFine;
+    if (wave < kCopies)
+        tmp[wave * 64 + lane] = lane < ncoarse ? h[kCopies * bins + wave * ncoarse + (ncoarse - 1 - lane)] : 0u;
+    __syncthreads();
+    unsigned c = 0;
 #pragma unroll
-    for (int j = 0; j < per; ++j) {
-        unsigned part[COPIES];     // all loads of the copies in flight together
+    for (int i = 0; i < kCopies; ++i) c += tmp[i * 64 + lane];
+    const int top = ncoarse - 1 - pick_lane(c, kk);
+    unsigned *fine = tmp + kCopies * 64;
+    if (wave < kCopies) fine[wave * 64 + lane] = h[wave * bins + top * kFine + (kFine - 1 - lane)];
+    __syncthreads();
+    c = 0;
 #pragma unroll
-        for (int c = 0; c < COPIES; ++c)
-            part[c] = ghist[c * kSlots + j * kBlock + tid];   // ranks beyond `bins`: slots that stay zero
-        cnt[j] = 0u;
-#pragma unroll
-        for (int c = 0; c < COPIES; ++c) cnt[j] += part[c];
-        sum += cnt[j];
-    }
-    unsigned total;
-    unsigned above = block_excl_scan(sum, tmp, &total);
-#pragma unroll
-    for (int j = 0; j < per; ++j) {
-        if (above < kk && kk <= above + cnt[j]) {
-            tmp[kBlock] = (unsigned)(bins - 1 - (tid * per + j));
-            tmp[kBlock + 1] = kk - above;
-            tmp[kBlock + 2] = cnt[j];
+    for (int i = 0; i < kCopies; ++i) c += fine[i * 64 + lane];
+    return top * kFine + (kFine - 1 - pick_lane(c, kk));
+}
+
+// Add a block's LDS histogram to the block's copy in device memory.  An atomic instruction of a
+// wave costs by the cache lines it touches, one after the other per line: the coarse counters
+// go out in one instruction (one per wave that counted something took 5 us, all on one line).
+// `s_coarse`: 64 unsigneds of LDS.
+__device__ __forceinline__ void flush_hist(const unsigned *lh, unsigned *__restrict__ h, int bins,
+                                           unsigned *s_coarse)
+{
+    const int copy = blockIdx.x % kCopies, lane = threadIdx.x & 63;
+    unsigned *fine = h + copy * bins, *coarse = h + kCopies * bins + copy * (bins / kFine);
+    for (int b = threadIdx.x; b < bins; b += blockDim.x) {   // a wave takes the kFine bins of one coarse counter
+        const unsigned v = lh[b];
+        unsigned t = 0;
+        if (__any(v != 0u)) {
+            if (v) atomicAdd(&fine[b], v);
+            t = wave_sum(v);
         }
-        above += cnt[j];
+        if (lane == 0) s_coarse[b / kFine] = t;
     }
     __syncthreads();
-    *digit = (int)tmp[kBlock];
-    *kk_rem = tmp[kBlock + 1];
-    if (count) *count = tmp[kBlock + 2];
-    __syncthreads();
-}
-
-__device__ __forceinline__ void flush_hist(const unsigned *lh, unsigned *__restrict__ gh, int bins)
-{
-    for (int b = threadIdx.x; b < bins; b += kBlock) {
-        unsigned v = lh[b];
-        if (v) atomicAdd(&gh[hist_slot(b, bins)], v);
+    if ((int)threadIdx.x < bins / kFine) {
+        const unsigned t = s_coarse[threadIdx.x];
+        if (t) atomicAdd(&coarse[threadIdx.x], t);
     }
 }
 
@@ -218,9 +201,10 @@ __global__ __launch_bounds__(kBlock) void k_scores_hist0(const float *__restrict
                                                          const float *__restrict__ W,
                                                          float *__restrict__ scores,
                                                          unsigned *__restrict__ hist0, int N, int g,
-                                                         int want_hist)
+                                                         int want_hist, int32_t *__restrict__ all_ids)
 {
     __shared__ unsigned lh[kFirstBins];
+    __shared__ unsigned s_coarse[64];
     if (want_hist)
         for (int b = threadIdx.x; b < kFirstBins; b += kBlock) lh[b] = 0;
     __syncthreads();
@@ -231,12 +215,13 @@ __global__ __launch_bounds__(kBlock) void k_scores_hist0(const float *__restrict
         if (valid) {
             float s = score_group(T + n * g, W + n * g, g);
             scores[n] = s;
+            if (all_ids) all_ids[n] = (int32_t)n;
             key = score_key(s);
         }
-        if (want_hist) hist_add<PV_VOTE_ROUNDS>(lh, digit_of(key, 0), valid);
+        if (want_hist) hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(key), valid);
     }
     __syncthreads();
-    if (want_hist) flush_hist(lh, hist0 + (blockIdx.x % kSub) * kSlots, kFirstBins);
+    if (want_hist) flush_hist(lh, hist0, kFirstBins, s_coarse);
 }
 
 // Pass 0 for g = 4 * PARTS (PARTS a power of two): every lane loads one 16-byte
@@ -264,9 +249,11 @@ __global__ __launch_bounds__(kBlock) void k_scores_hist0_vec(const float *__rest
                                                              const float *__restrict__ W,
                                                              float *__restrict__ scores,
                                                              unsigned *__restrict__ hist0,
-                                                             int64_t nvec, int want_hist, norm_args na)
+                                                             int64_t nvec, int want_hist,
+                                                             int32_t *__restrict__ all_ids, norm_args na)
 {
     __shared__ unsigned lh[kFirstBins];
+    __shared__ unsigned s_coarse[64];
     double nacc = 0.0;
     if (want_hist)
         for (int b = threadIdx.x; b < kFirstBins; b += kBlock) lh[b] = 0;
@@ -333,12 +320,15 @@ __global__ __launch_bounds__(kBlock) void k_scores_hist0_vec(const float *__rest
                 }
             }
             const bool valid = i < nvec && part == PARTS - 1;
-            if (valid) scores[i / PARTS] = s;
-            if (want_hist) hist_add<PV_VOTE_ROUNDS>(lh, digit_of(score_key(s), 0), valid);
+            if (valid) {
+                scores[i / PARTS] = s;
+                if (all_ids) all_ids[i / PARTS] = (int32_t)(i / PARTS);
+            }
+            if (want_hist) hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(score_key(s)), valid);
         }
     }
     __syncthreads();
-    if (want_hist) flush_hist(lh, hist0 + (blockIdx.x % kSub) * kSlots, kFirstBins);
+    if (want_hist) flush_hist(lh, hist0, kFirstBins, s_coarse);
     if constexpr (NORM) {
         __shared__ double ntmp[kBlock / 64];
 #pragma unroll
@@ -363,9 +353,11 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_vec(const float
                                                                      float *__restrict__ scores,
                                                                      unsigned *__restrict__ hist0,
                                                                      int64_t nvec, int want_hist,
+                                                                     int32_t *__restrict__ all_ids,
                                                                      pv_adam_t adam, float *m, float *v)
 {
     __shared__ unsigned lh[kFirstBins];
+    __shared__ unsigned s_coarse[64];
     if (want_hist)
         for (int b = threadIdx.x; b < kFirstBins; b += kBlock) lh[b] = 0;
     __syncthreads();
@@ -440,8 +432,11 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_vec(const float
                 }
             }
             const bool valid = i < nvec && part == PARTS - 1;
-            if (valid) scores[i / PARTS] = s;
-            if (want_hist) hist_add<PV_VOTE_ROUNDS>(lh, digit_of(score_key(s), 0), valid);
+            if (valid) {
+                scores[i / PARTS] = s;
+                if (all_ids) all_ids[i / PARTS] = (int32_t)(i / PARTS);
+            }
+            if (want_hist) hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(score_key(s)), valid);
         }
 #pragma unroll
         for (int u = 0; u < kVecUnroll; ++u) {
@@ -450,7 +445,7 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_vec(const float
         }
     }
     __syncthreads();
-    if (want_hist) flush_hist(lh, hist0 + (blockIdx.x % kSub) * kSlots, kFirstBins);
+    if (want_hist) flush_hist(lh, hist0, kFirstBins, s_coarse);
 }
 
 // The same sweep for group sizes 1 and 2: a 16-byte vector holds 4 / GS whole groups and every
@@ -461,10 +456,12 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_sub(const float
                                                                      float alpha, float *T,
                                                                      float *__restrict__ scores,
                                                                      unsigned *__restrict__ hist0,
-                                                                     int64_t nelem, int want_hist)
+                                                                     int64_t nelem, int want_hist,
+                                                                     int32_t *__restrict__ all_ids)
 {
     constexpr int kPerVec = 4 / GS;               // groups per vector
     __shared__ unsigned lh[kFirstBins];
+    __shared__ unsigned s_coarse[64];
     if (want_hist)
         for (int b = threadIdx.x; b < kFirstBins; b += kBlock) lh[b] = 0;
     __syncthreads();
@@ -509,11 +506,14 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_sub(const float
                 __builtin_nontemporal_store(t, &T4[i]);
 #pragma unroll
                 for (int q = 0; q < kPerVec; ++q) scores[i * kPerVec + q] = sc[q];
+                if (all_ids)
+#pragma unroll
+                    for (int q = 0; q < kPerVec; ++q) all_ids[i * kPerVec + q] = (int32_t)(i * kPerVec + q);
             }
             if (want_hist) {
 #pragma unroll
                 for (int q = 0; q < kPerVec; ++q)
-                    hist_add<PV_VOTE_ROUNDS>(lh, digit_of(score_key(sc[q]), 0), valid);
+                    hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(score_key(sc[q])), valid);
             }
         }
     }
@@ -528,236 +528,390 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_sub(const float
                 s = fmaf(d, d, s);
             }
             scores[i / GS] = s;
-            if (want_hist) atomicAdd(&lh[digit_of(score_key(s), 0)], 1u);
+            if (all_ids) all_ids[i / GS] = (int32_t)(i / GS);
+            if (want_hist) atomicAdd(&lh[digit0_of(score_key(s))], 1u);
         }
     }
     __syncthreads();
-    if (want_hist) flush_hist(lh, hist0 + (blockIdx.x % kSub) * kSlots, kFirstBins);
+    if (want_hist) flush_hist(lh, hist0, kFirstBins, s_coarse);
 }
 
-// Passes 1 and 2: histogram of the next digit among keys that match the digits
-// chosen so far.  Each launch resolves the digit of the previous histogram and
-// block 0 publishes it in `state` for the launches that follow:
-// state[4] = digit 0, state[5] = digit 1, state[6] = rank left after digit 0,
-// state[7] = rank left after digit 1, state[2] = width of digit 1.
-// The width of digit 1 is fixed when digit 0 is known: kMidBits when few keys share digit 0 (a
-// spread-out distribution: every such key costs an atomic on device memory in the flush, and a
-// wide digit 1 leaves few for the last pass), one bit less when more than an eighth of all keys
-// do (a narrow one, as after a sign-like optimiser step: the keys then fall on half as many bins
-// of digit 1 and merge in the block histograms).
-constexpr int kHistBlock = 512;   // measured against 256 and 1024 threads on 2 M and 5.6 M groups
-__global__ __launch_bounds__(kHistBlock) void k_hist_next(const float *__restrict__ scores,
-                                                      const unsigned *__restrict__ hist_all,
-                                                      unsigned *__restrict__ hist_out,
-                                                      unsigned *__restrict__ state, int N,
-                                                      unsigned k, int pass)
+// What a region holds at or above the range of digit 0: `count` entries of `list`, or, if the
+// count exceeds the list's room, the region's scores themselves.
+struct region_t {
+    const uint2 *list;      // {key, id}
+    const float *scores;
+    int64_t base;
+    int n;
+    bool raw;
+};
+__device__ __forceinline__ region_t region_of(int r, const uint2 *list, const unsigned *counts,
+                                              const float *scores, int64_t N, int span, int cap)
 {
-    __shared__ unsigned tmp[kBlock + 3];
-    __shared__ unsigned lh[kBins];
-    int d0, d1 = 0, mid;
-    unsigned kk;
-    if (pass == 1) {
-        unsigned share;
-        pick_digit<kSub>(hist_all, kFirstBins, k, tmp, &d0, &kk, &share);
-        mid = share > (unsigned)N / 8u ? kMidBits - 1 : kMidBits;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            state[4] = (unsigned)d0;
-            state[6] = kk;
-            state[2] = (unsigned)mid;
-        }
-    } else {
-        d0 = (int)state[4];
-        mid = (int)state[2];
-        pick_digit(hist_all + kHist1, 1 << mid, state[6], tmp, &d1, &kk);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            state[5] = (unsigned)d1;
-            state[7] = kk;
-        }
-    }
-    const int bins = pass == 1 ? (1 << mid) : (1 << (kRestBits - mid));
-    // Per-block histogram in LDS, flushed once: a narrow score distribution (all updates of
-    // one size, as after a sign-like optimiser step) puts most keys into a few bins, and that
-    // many atomics on a few global addresses would serialise.
-    for (int b = threadIdx.x; b < bins; b += kHistBlock) lh[b] = 0;
-    __syncthreads();
-    const pv_f4 *s4 = reinterpret_cast<const pv_f4 *>(scores);
-    const int64_t n4 = N >> 2;
-    const int64_t stride = (int64_t)gridDim.x * kHistBlock;
-    // four vectors per thread in flight: with many groups (single-weight units) the loop is
-    // otherwise one memory round trip per vector
-    constexpr int kAhead = 4;
-    for (int64_t base = (int64_t)blockIdx.x * kHistBlock; base < n4; base += stride * kAhead) {
-        pv_f4 v[kAhead];
+    region_t g;
+    const unsigned c = counts[r];
+    g.raw = c > (unsigned)cap;
+    g.base = (int64_t)r * span;
+    const int64_t left = N - g.base;
+    g.list = list + (int64_t)r * cap;
+    g.scores = scores;
+    g.n = g.raw ? (int)(left < span ? (left < 0 ? 0 : left) : span) : (int)c;
+    return g;
+}
+// entry i of the region (i < n); key 0 past its end
+__device__ __forceinline__ uint2 region_at(const region_t &g, int i)
+{
+    if (i >= g.n) return make_uint2(0u, 0u);
+    if (!g.raw) return g.list[i];
+    return make_uint2(score_key(g.scores[g.base + i]), (unsigned)(g.base + i));
+}
+
+// Pass over all scores: digit 0 is resolved, digit 1 of the keys that share it is counted, the
+// keys at or above its range go to the region's list in id order (a wave's 256 keys of a step
+// find their places from four ballots, so nothing is exchanged between waves).
+// Block 0 publishes digit 0 and the rank left after it: state[4], state[6].
+// Bound by the read of the scores: 4 bytes a group.
+__global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__ scores,
+                                                       unsigned *__restrict__ hist_all,
+                                                       unsigned *__restrict__ state, int64_t N,
+                                                       unsigned k, int span, int cap,
+                                                       uint2 *__restrict__ list,
+                                                       unsigned *__restrict__ counts)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kMidBins];
+    const int lane = threadIdx.x & 63;
+    const int r = blockIdx.x * kSelWaves + (threadIdx.x >> 6);
+    const int64_t base = (int64_t)r * span;
+    const float *mine_scores = scores + base;
+    const int n = base >= N ? 0 : (int)(N - base < span ? N - base : span);
+    uint2 *mine = list + (int64_t)r * cap;
+    // keys past the region's end are 0
+    auto load = [&](int at, pv_f4 (&v)[kAhead]) {
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            const int64_t i = base + u * stride + threadIdx.x;
-            v[u] = i < n4 ? s4[i] : pv_f4{0.f, 0.f, 0.f, 0.f};
-        }
+            const int i = at + u * 256 + lane * 4;
+            v[u] = pv_f4{0.f, 0.f, 0.f, 0.f};
+            if (i + 4 <= n) {
+                v[u] = *reinterpret_cast<const pv_f4 *>(mine_scores + i);
+            } else {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int64_t i = base + u * stride + threadIdx.x;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                unsigned key = score_key(v[u][e]);
-                bool valid = i < n4 && digit_of(key, 0) == d0 && (pass == 1 || digit_of(key, 1, mid) == d1);
-                hist_add<PV_LATE_VOTE_ROUNDS>(lh, digit_of(key, pass, mid), valid);
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < n) v[u][e] = mine_scores[i + e];
             }
         }
-    }
-    if (blockIdx.x == 0 && (int)threadIdx.x < (N & 3)) {
-        unsigned key = score_key(scores[(n4 << 2) + threadIdx.x]);
-        if (digit_of(key, 0) == d0 && (pass == 1 || digit_of(key, 1, mid) == d1))
-            atomicAdd(&lh[digit_of(key, pass, mid)], 1u);
-    }
-    __syncthreads();
-    for (int b = threadIdx.x; b < bins; b += kHistBlock) {
-        unsigned v = lh[b];
-        if (v) atomicAdd(&hist_out[hist_slot(b, bins)], v);
-    }
-}
-
-__device__ __forceinline__ unsigned block_sum(unsigned v, unsigned *tmp)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
-    __syncthreads();
-    unsigned total = 0;
-    for (int w = 0; w < kBlock / 64; ++w) total += tmp[w];
-    __syncthreads();
-    return total;
-}
-
-// Threshold key and number of ties to take, then per-chunk (greater, equal) counts.
-__global__ __launch_bounds__(kBlock) void k_chunk_counts(const float *__restrict__ scores,
-                                                         const unsigned *__restrict__ hist_all,
-                                                         unsigned *state,
-                                                         unsigned *__restrict__ chunk_counts, int N,
-                                                         int nchunks)
-{
-    __shared__ unsigned tmp[kBlock + 3];
-    const int d0 = (int)state[4], d1 = (int)state[5], mid = (int)state[2];
-    int d2;
-    unsigned kk;
-    pick_digit(hist_all + kHist2, 1 << (kRestBits - mid), state[7], tmp, &d2, &kk);
-    const unsigned thr = ((unsigned)d0 << kRestBits) | ((unsigned)d1 << (kRestBits - mid)) | (unsigned)d2;
+    };
+    pv_f4 cur[kAhead], nxt[kAhead];
+    load(0, cur);                            // in flight while digit 0 is resolved
+    for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
+    // the last digit's histogram starts at zero (its reader of the call before has run)
+    for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
+        hist_all[z] = 0u;
+    unsigned kk = k;
+    const int d0 = pick_digit(hist_all + kHist0, kFirstBins, kk, tmp);   // its barriers also order the clearing above
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        state[0] = thr;
-        state[1] = kk;  // how many keys equal to thr are selected (lowest ids first)
+        state[4] = (unsigned)d0;
+        state[6] = kk;
     }
-    for (int c = blockIdx.x; c < nchunks; c += gridDim.x) {
-        const int64_t base = (int64_t)c * kChunk + (int64_t)threadIdx.x * kItems;
-        unsigned gt = 0, eq = 0;
-        if (base + kItems <= N) {
-            const pv_f4 *s4 = reinterpret_cast<const pv_f4 *>(scores + base);
+    const unsigned lo = (unsigned)d0 << kRestBits, hi = ((unsigned)d0 + 1u) << kRestBits;
+    unsigned cnt = 0;
+    auto take = [&](const pv_f4 &v, int at, bool whole) {
+        const int i = at + lane * 4;
+        unsigned long long hits[4];
 #pragma unroll
-            for (int v = 0; v < kItems / 4; ++v) {
-                pv_f4 x = s4[v];
+        for (int e = 0; e < 4; ++e)          // (a NaN with its sign bit set is above every range as it is)
+            hits[e] = __ballot(__float_as_uint(v[e]) >= lo && (whole || i + e < n));
+        if (!(hits[0] | hits[1] | hits[2] | hits[3])) return;   // uniform over the wave
+        unsigned pos = cnt;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    unsigned key = score_key(x[e]);
-                    gt += key > thr;
-                    eq += key == thr;
-                }
-            }
-        } else {
-            for (int j = 0; j < kItems; ++j)
-                if (base + j < N) {
-                    unsigned key = score_key(scores[base + j]);
-                    gt += key > thr;
-                    eq += key == thr;
-                }
+        for (int e = 0; e < 4; ++e) {
+            pos = __builtin_amdgcn_mbcnt_hi((unsigned)(hits[e] >> 32),
+                                            __builtin_amdgcn_mbcnt_lo((unsigned)hits[e], pos));
+            cnt += (unsigned)__popcll(hits[e]);
         }
-        gt = block_sum(gt, tmp);
-        eq = block_sum(eq, tmp);
-        if (threadIdx.x == 0) {
-            chunk_counts[2 * c] = gt;
-            chunk_counts[2 * c + 1] = eq;
+        const bool room = cnt <= (unsigned)cap;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((hits[e] >> lane) & 1ull) {
+                const unsigned key = score_key(v[e]);
+                if (room) mine[pos] = make_uint2(key, (unsigned)(base + i + e));
+                ++pos;
+                if (key < hi) atomicAdd(&lh[(key >> kLastBits) & (kMidBins - 1)], 1u);
+            }
+    };
+    for (int at = 0; at < n; at += 256 * kAhead) {
+        if (at + 256 * kAhead < n) load(at + 256 * kAhead, nxt);
+        const bool whole = at + 256 * kAhead <= n;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) take(cur[u], at + u * 256, whole);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
+    }
+    if (lane == 0) counts[r] = cnt;
+    __syncthreads();
+    flush_hist(lh, hist_all + kHist1, kMidBins, tmp);
+}
+
+// Digit 1 is resolved; among the keys collected, those above digits 0 and 1 are counted per
+// block, those equal are counted by digit 2: per block as suffix sums (how many have digit 2 >= d,
+// so that the next kernel reads two numbers a block) and over all blocks in the histogram.
+// Publishes digit 1 and the rank left: state[5], state[7].
+__global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restrict__ scores,
+                                                          unsigned *__restrict__ hist_all,
+                                                          unsigned *__restrict__ state, int64_t N,
+                                                          int span, int cap, const uint2 *__restrict__ list,
+                                                          const unsigned *__restrict__ counts,
+                                                          unsigned *__restrict__ above,
+                                                          unsigned *__restrict__ suffix)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kLastBins];
+    __shared__ unsigned s_above;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < kLastBins) lh[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_above = 0;
+    // digit 0's histogram is done with: zero for the next call
+    for (int z = kHist0 + blockIdx.x * kSelBlock + threadIdx.x; z < kHist1; z += gridDim.x * kSelBlock)
+        hist_all[z] = 0u;
+    const region_t g = region_of(blockIdx.x * kSelWaves + (threadIdx.x >> 6), list, counts, scores, N, span, cap);
+    unsigned kk = state[6];
+    const unsigned d0 = state[4];
+    const unsigned d1 = (unsigned)pick_digit(hist_all + kHist1, kMidBins, kk, tmp);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        state[5] = d1;
+        state[7] = kk;
+    }
+    const unsigned want = (d0 << (kRestBits - kLastBits)) | d1;
+    unsigned gt = 0;
+    for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
+        unsigned key[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) key[u] = region_at(g, i0 + u * 64 + lane).x;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const unsigned p = key[u] >> kLastBits;
+            gt += p > want;
+            if (p == want && i0 + u * 64 + lane < g.n) atomicAdd(&lh[key[u] & (kLastBins - 1)], 1u);
+        }
+    }
+    gt = wave_sum(gt);
+    if (lane == 0 && gt) atomicAdd(&s_above, gt);
+    __syncthreads();
+    flush_hist(lh, hist_all + kHist2, kLastBins, tmp);
+    if (threadIdx.x == 0) above[blockIdx.x] = s_above;
+    if (threadIdx.x < 64) {
+        // four digits a lane, lane 0 the largest
+        unsigned c[kLastBins / 64], sum = 0;
+#pragma unroll
+        for (int q = 0; q < kLastBins / 64; ++q) {
+            c[q] = lh[kLastBins - 1 - (lane * (kLastBins / 64) + q)];
+            sum += c[q];
+        }
+        unsigned run = wave_incl_scan(sum) - sum;
+        unsigned *row = suffix + (int64_t)blockIdx.x * kSuffix;
+#pragma unroll
+        for (int q = 0; q < kLastBins / 64; ++q) {
+            run += c[q];
+            row[kLastBins - 1 - (lane * (kLastBins / 64) + q)] = run;
+        }
+        if (lane == 0) row[kLastBins] = 0u;
+    }
+}
+
+// Digit 2 and with it the threshold and the number of ties to take; then the ids, in order:
+// position of a chosen group = (#greater with a lower id) + min(#equal with a lower id, ties to
+// take).  What the blocks before this one hold comes from their counts.
+__global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict__ scores,
+                                                         unsigned *__restrict__ hist_all,
+                                                         const unsigned *__restrict__ state, int64_t N,
+                                                         int span, int cap, const uint2 *__restrict__ list,
+                                                         const unsigned *__restrict__ counts,
+                                                         const unsigned *__restrict__ above,
+                                                         const unsigned *__restrict__ suffix,
+                                                         int32_t *__restrict__ out_idx)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned s_gt[kSelWaves], s_eq[kSelWaves], s_bg[kSelWaves], s_be[kSelWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // digit 1's histogram is done with: zero for the next call
+    for (int z = kHist1 + blockIdx.x * kSelBlock + threadIdx.x; z < kHist2; z += gridDim.x * kSelBlock)
+        hist_all[z] = 0u;
+    const region_t g = region_of(blockIdx.x * kSelWaves + wave, list, counts, scores, N, span, cap);
+    const unsigned d0 = state[4], d1 = state[5];
+    unsigned need = state[7];
+    const unsigned d2 = (unsigned)pick_digit(hist_all + kHist2, kLastBins, need, tmp);
+    const unsigned thr = (((d0 << (kRestBits - kLastBits)) | d1) << kLastBits) | d2;
+    // the blocks before this one (at most kSelBlocks <= kSelBlock of them, one a thread)
+    unsigned bg = 0, be = 0;
+    if (threadIdx.x < blockIdx.x) {
+        const unsigned *row = suffix + (int64_t)threadIdx.x * kSuffix;
+        const unsigned more = row[d2 + 1];
+        bg = above[threadIdx.x] + more;
+        be = row[d2] - more;
+    }
+    bg = wave_sum(bg);
+    be = wave_sum(be);
+    unsigned gt = 0, eq = 0;
+    for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
+        unsigned key[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) key[u] = region_at(g, i0 + u * 64 + lane).x;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            gt += key[u] > thr;
+            eq += key[u] == thr && i0 + u * 64 + lane < g.n;
+        }
+    }
+    gt = wave_sum(gt);
+    eq = wave_sum(eq);
+    if (lane == 0) {
+        s_gt[wave] = gt;
+        s_eq[wave] = eq;
+        s_bg[wave] = bg;
+        s_be[wave] = be;
+    }
+    __syncthreads();
+    unsigned rg = 0, re = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) {
+        rg += s_bg[w] + (w < wave ? s_gt[w] : 0u);
+        re += s_be[w] + (w < wave ? s_eq[w] : 0u);
+    }
+    for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
+        uint2 en[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) en[u] = region_at(g, i0 + u * 64 + lane);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const bool in = i0 + u * 64 + lane < g.n;
+            const bool isg = en[u].x > thr, ise = in && en[u].x == thr;
+            const unsigned long long bgt = __ballot(isg), beq = __ballot(ise);
+            const unsigned long long below = (1ull << lane) - 1ull;
+            const unsigned pg = rg + __popcll(bgt & below), pe = re + __popcll(beq & below);
+            if (isg || (ise && pe < need)) out_idx[pg + (pe < need ? pe : need)] = (int32_t)en[u].y;
+            rg += __popcll(bgt);
+            re += __popcll(beq);
         }
     }
 }
 
-// Ordered write: position of a selected group = (#greater with a lower id) +
-// min(#equal with a lower id, ties to take).  Also re-zeroes the histograms for
-// the next call.
-__global__ __launch_bounds__(kBlock) void k_compact_write(const float *__restrict__ scores,
-                                                          const unsigned *__restrict__ state,
-                                                          const unsigned *__restrict__ chunk_counts,
-                                                          unsigned *__restrict__ hist_all,
-                                                          int32_t *__restrict__ out_idx, int N,
-                                                          int nchunks)
+// Few groups: one block does what the three kernels above do, every key in a register (thread t
+// holds kSmallPer consecutive groups), digits 1 and 2 counted in LDS.
+constexpr int kSmallPer = kSmallGroups / kSelBlock;
+__global__ __launch_bounds__(kSelBlock) void k_select_small(const float *__restrict__ scores,
+                                                            unsigned *__restrict__ hist_all, int N,
+                                                            unsigned k, int32_t *__restrict__ out_idx)
 {
-    __shared__ unsigned tmp[kBlock + 3];
-    const unsigned thr = state[0], need_eq = state[1];
-    // counts of all earlier chunks: [0, done) is already in (pg, pe), a block that takes several
-    // chunks only adds the ones in between
-    unsigned pg = 0, pe = 0;
-    int done = 0;
-    const uint2 *cc2 = reinterpret_cast<const uint2 *>(chunk_counts);
-    for (int c = blockIdx.x; c < nchunks; c += gridDim.x) {
-        unsigned ag = 0, ae = 0;
-        for (int b = done + threadIdx.x; b < c; b += kBlock) {
-            const uint2 v = cc2[b];
-            ag += v.x;
-            ae += v.y;
-        }
-        pg += block_sum(ag, tmp);
-        pe += block_sum(ae, tmp);
-        done = c;
-        const int64_t base = (int64_t)c * kChunk + (int64_t)threadIdx.x * kItems;
-        unsigned keys[kItems];
-        unsigned gt = 0, eq = 0;
-        if (base + kItems <= N) {
-            const pv_f4 *s4 = reinterpret_cast<const pv_f4 *>(scores + base);
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kMidBins];
+    __shared__ unsigned ll[kLastBins];
+    __shared__ unsigned s_w[kSelWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int per = ((N + kSelBlock - 1) / kSelBlock + 3) & ~3;   // whole 16-byte vectors
+    const int first = threadIdx.x * per;
+    unsigned key[kSmallPer];
 #pragma unroll
-            for (int v = 0; v < kItems / 4; ++v) {
-                const pv_f4 x = s4[v];
+    for (int q = 0; q < kSmallPer; q += 4) {
+        pv_f4 v = {0.f, 0.f, 0.f, 0.f};
+        const int i = first + q;
+        if (q < per && i + 4 <= N) {
+            v = *reinterpret_cast<const pv_f4 *>(scores + i);
+        } else if (q < per) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) keys[v * 4 + e] = score_key(x[e]);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < kItems; ++j) keys[j] = base + j < N ? score_key(scores[base + j]) : 0u;
+            for (int e = 0; e < 4; ++e)
+                if (i + e < N) v[e] = scores[i + e];
         }
 #pragma unroll
-        for (int j = 0; j < kItems; ++j)
-            if (base + j < N) {
-                gt += keys[j] > thr;
-                eq += keys[j] == thr;
-            }
-        // one scan for both counts: a chunk holds kChunk = 2048 keys, so each fits 16 bits
-        unsigned tot;
-        const unsigned both = block_excl_scan(gt | (eq << 16), tmp, &tot);
-        unsigned rg = pg + (both & 0xFFFFu);   // greater keys before this thread's items
-        unsigned re = pe + (both >> 16);       // equal keys before them
-#pragma unroll
-        for (int j = 0; j < kItems; ++j) {
-            int64_t n = base + j;
-            if (n < N) {
-                if (keys[j] > thr) {
-                    out_idx[rg + (re < need_eq ? re : need_eq)] = (int32_t)n;
-                    ++rg;
-                } else if (keys[j] == thr) {
-                    if (re < need_eq) out_idx[rg + re] = (int32_t)n;
-                    ++re;
-                }
-            }
-        }
+        for (int e = 0; e < 4; ++e) key[q + e] = score_key(v[e]);
     }
-    // leave the histograms zero for the next call (all their readers ran in earlier launches)
-    for (int64_t z = (int64_t)blockIdx.x * kBlock + threadIdx.x; z < kHistTotal;
-         z += (int64_t)gridDim.x * kBlock)
-        hist_all[z] = 0;
+    const int have = N - first < per ? (N - first < 0 ? 0 : N - first) : per;   // groups of this thread
+    for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
+    if (threadIdx.x < kLastBins) ll[threadIdx.x] = 0;
+    unsigned kk = k;
+    const unsigned d0 = (unsigned)pick_digit(hist_all + kHist0, kFirstBins, kk, tmp);
+    // a digit of an LDS histogram: 64 coarse sums by the waves, then the chosen 64 (every wave alike)
+    auto pick_lds = [&](const unsigned *h, int bins) {
+        const int nc = bins / kFine;
+        __syncthreads();
+        for (int c = wave; c < nc; c += kSelWaves) {
+            const unsigned t = wave_sum(h[c * kFine + lane]);
+            if (lane == 0) tmp[c] = t;
+        }
+        __syncthreads();
+        const int top = nc - 1 - pick_lane(lane < nc ? tmp[nc - 1 - lane] : 0u, kk);
+        const int d = top * kFine + (kFine - 1 - pick_lane(h[top * kFine + (kFine - 1 - lane)], kk));
+        return (unsigned)d;
+    };
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q)
+        if (q < have && (key[q] >> kRestBits) == d0) atomicAdd(&lh[(key[q] >> kLastBits) & (kMidBins - 1)], 1u);
+    const unsigned want = (d0 << (kRestBits - kLastBits)) | pick_lds(lh, kMidBins);
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q)
+        if (q < have && (key[q] >> kLastBits) == want) atomicAdd(&ll[key[q] & (kLastBins - 1)], 1u);
+    const unsigned thr = (want << kLastBits) | pick_lds(ll, kLastBins);
+    const unsigned need = kk;
+
+    unsigned gt = 0, eq = 0;
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q)
+        if (q < have) {
+            gt += key[q] > thr;
+            eq += key[q] == thr;
+        }
+    const unsigned both = gt | (eq << 16);   // N <= 32768: neither sum reaches 2^16
+    const unsigned inc = wave_incl_scan(both);
+    if (lane == 63) s_w[wave] = inc;
+    __syncthreads();
+    unsigned before = inc - both;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) before += w < wave ? s_w[w] : 0u;
+    unsigned rg = before & 0xFFFFu, re = before >> 16;
+#pragma unroll
+    for (int q = 0; q < kSmallPer; ++q)
+        if (q < have) {
+            if (key[q] > thr) {
+                out_idx[rg + (re < need ? re : need)] = first + q;
+                ++rg;
+            } else if (key[q] == thr) {
+                if (re < need) out_idx[rg + re] = first + q;
+                ++re;
+            }
+        }
+    // digit 0's histogram, the only one this path uses, is left zero (its readers are past their barriers)
+    for (int z = kHist0 + threadIdx.x; z < kHist1; z += kSelBlock) hist_all[z] = 0u;
 }
 
 }  // namespace
 
+// How the groups are dealt to the waves of the passes after the sweep.  A wave needs at least one
+// step of 256 keys; a list has room for a quarter of the wave's keys, twice the largest share
+// of them that a list is asked to hold on average.  With more than an eighth of all groups chosen
+// there are no lists (cap = 0).
+struct sel_plan {
+    int blocks, span, cap;
+};
+static sel_plan make_sel_plan(int64_t N, int64_t k, bool lists)
+{
+    sel_plan p;
+    const int64_t blocks = (N + kSelWaves * 256 - 1) / (kSelWaves * 256);
+    p.blocks = (int)(blocks < kSelBlocks ? (blocks < 1 ? 1 : blocks) : kSelBlocks);
+    const int64_t regions = (int64_t)p.blocks * kSelWaves;
+    p.span = (int)(((N + regions - 1) / regions + 255) & ~INT64_C(255));
+    p.cap = lists && k <= N / 8 ? p.span / 4 : 0;
+    return p;
+}
+// counts per region, keys above digits 0 and 1 per block, suffix counts per block
+constexpr size_t kSelCountWords = (size_t)kSelBlocks * (kSelWaves + 1 + kSuffix);
+
 // The scratch memory of one selection: every group's score (unless the caller keeps them),
-// the radix-select histograms (all zero when a call starts, left zero when it ends), the
-// per-chunk counts of the compaction, the digits and threshold found so far.
+// the radix-select histograms (all zero when a call starts, but for the last digit's, which the
+// call clears itself), the lists and counts of the passes after the sweep, the digits found so far.
 struct sel_bufs {
     float *scores;
-    unsigned *hist, *cc, *state;
+    unsigned *hist, *counts, *state;
+    uint2 *list;
+    sel_plan plan;
     pv_norm_req *norm = nullptr;
 };
 
@@ -784,17 +938,20 @@ pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, cons
         if (st != PV_OK) return st;
         scores = static_cast<float *>(ctx->sel_scores.ptr);
     }
-    const int nchunks = (N + kChunk - 1) / kChunk;
+    sel_bufs bufs;
+    bufs.plan = make_sel_plan(N, k, /*lists=*/true);
     st = pv_ensure(ctx, ctx->sel_hist, (size_t)kHistTotal * sizeof(unsigned), /*zero_new=*/true);
     if (st != PV_OK) return st;
-    st = pv_ensure(ctx, ctx->sel_blocks, (size_t)nchunks * 2 * sizeof(unsigned));
+    st = pv_ensure(ctx, ctx->sel_blocks, kSelCountWords * sizeof(unsigned));
+    if (st != PV_OK) return st;
+    st = pv_ensure(ctx, ctx->sel_list, (size_t)bufs.plan.blocks * kSelWaves * bufs.plan.cap * sizeof(uint2));
     if (st != PV_OK) return st;
     st = pv_ensure(ctx, ctx->sel_state, 8 * sizeof(unsigned));
     if (st != PV_OK) return st;
-    sel_bufs bufs;
     bufs.scores = scores;
     bufs.hist = static_cast<unsigned *>(ctx->sel_hist.ptr);
-    bufs.cc = static_cast<unsigned *>(ctx->sel_blocks.ptr);
+    bufs.counts = static_cast<unsigned *>(ctx->sel_blocks.ptr);
+    bufs.list = static_cast<uint2 *>(ctx->sel_list.ptr);
     bufs.state = static_cast<unsigned *>(ctx->sel_state.ptr);
     bufs.norm = norm;
     return select_run(ctx, l, T, W, k, out_idx, bufs, G, alpha, adam, m, v);
@@ -816,9 +973,8 @@ constexpr int64_t kStaticMaxGroups = INT64_C(1) << 22;            // 4 194 304 g
 constexpr size_t kStaticScoresOff = 0;
 constexpr size_t kStaticHistOff = kStaticScoresOff + (size_t)kStaticMaxGroups * sizeof(float) + 256;
 constexpr size_t kStaticCcOff = kStaticHistOff + (size_t)kHistTotal * sizeof(unsigned);
-constexpr size_t kStaticStateOff =
-    kStaticCcOff + (size_t)((kStaticMaxGroups + kChunk - 1) / kChunk) * 2 * sizeof(unsigned);
-constexpr size_t kStaticBytes = kStaticStateOff + 256;            // about 16.1 MiB
+constexpr size_t kStaticStateOff = kStaticCcOff + kSelCountWords * sizeof(unsigned);
+constexpr size_t kStaticBytes = kStaticStateOff + 256;            // about 16.5 MiB
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 // In host code `scratch` is only a stand-in for the symbol: the memory is reached through the
@@ -855,7 +1011,9 @@ pv_status pv_launch_select_static(pv_ctx *ctx, const pv_layout *l, const float *
     sel_bufs bufs;
     bufs.scores = scores ? scores : reinterpret_cast<float *>(base + kStaticScoresOff);
     bufs.hist = reinterpret_cast<unsigned *>(base + kStaticHistOff);
-    bufs.cc = reinterpret_cast<unsigned *>(base + kStaticCcOff);
+    bufs.counts = reinterpret_cast<unsigned *>(base + kStaticCcOff);
+    bufs.list = nullptr;   // no room for lists: the passes after the sweep read the scores
+    bufs.plan = make_sel_plan(pv_num_groups(l), k, /*lists=*/false);
     bufs.state = reinterpret_cast<unsigned *>(base + kStaticStateOff);
     // the array keeps what the last call (of any context) left: the histograms must start at
     // zero whatever that was (a fill kernel, which a capturing caller may record)
@@ -873,13 +1031,12 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
 {
     const int N = (int)pv_num_groups(l);
     const int g = l->group_size;
-    const int nchunks = (N + kChunk - 1) / kChunk;
     pv_status st;
     float *scores = bufs.scores;
     unsigned *hist = bufs.hist;
-    unsigned *cc = bufs.cc;
     unsigned *state = bufs.state;
-    const int want_hist = k > 0 ? 1 : 0;
+    int32_t *all_ids = k == N ? out_idx : nullptr;   // every group is chosen: the sweep writes the ids as it goes
+    const int want_hist = k > 0 && k < N ? 1 : 0;
     const bool vec_g = g == 4 || g == 8 || g == 16 || g == 32 || g == 64;
     if (G && !adam && (g == 1 || g == 2)) {
         pv_timed t(ctx, PV_K_ENCODE_TARGETS);
@@ -889,10 +1046,10 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
         float *Tw = const_cast<float *>(T);
         if (g == 1)
             hipLaunchKernelGGL(k_targets_scores_hist0_sub<1>, dim3(vblocks), dim3(kBlock), 0, ctx->stream,
-                               W, G, alpha, Tw, scores, hist, nelem, want_hist);
+                               W, G, alpha, Tw, scores, hist, nelem, want_hist, all_ids);
         else
             hipLaunchKernelGGL(k_targets_scores_hist0_sub<2>, dim3(vblocks), dim3(kBlock), 0, ctx->stream,
-                               W, G, alpha, Tw, scores, hist, nelem, want_hist);
+                               W, G, alpha, Tw, scores, hist, nelem, want_hist, all_ids);
     } else {
     if (G && !vec_g) {   // no fused kernel for this group size: form T first
         // (the Adam variant reaches this launcher only for the group sizes that have one)
@@ -912,11 +1069,11 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
     do {                                                                                            \
         if (adam)                                                                                   \
             hipLaunchKernelGGL((k_targets_scores_hist0_vec<PARTS_, true>), dim3(vblocks), dim3(kBlock), \
-                               0, ctx->stream, W, G, alpha, Tw, scores, hist, nvec, want_hist, a, m, v); \
+                               0, ctx->stream, W, G, alpha, Tw, scores, hist, nvec, want_hist, all_ids, a, m, v); \
         else                                                                                        \
             hipLaunchKernelGGL((k_targets_scores_hist0_vec<PARTS_, false>), dim3(vblocks),          \
                                dim3(kBlock), 0, ctx->stream, W, G, alpha, Tw, scores, hist, nvec,   \
-                               want_hist, a, m, v);                                                 \
+                               want_hist, all_ids, a, m, v);                                                 \
     } while (0)
         if (g == 4) PV_FUSED(1);
         else if (g == 8) PV_FUSED(2);
@@ -945,10 +1102,10 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
     do {                                                                                           \
         if (bufs.norm)                                                                             \
             hipLaunchKernelGGL((k_scores_hist0_vec<PARTS_, true>), dim3(vblocks), dim3(kBlock), 0, \
-                               ctx->stream, T, W, scores, hist, nvec, want_hist, na);              \
+                               ctx->stream, T, W, scores, hist, nvec, want_hist, all_ids, na);              \
         else                                                                                       \
             hipLaunchKernelGGL((k_scores_hist0_vec<PARTS_, false>), dim3(vblocks), dim3(kBlock), 0, \
-                               ctx->stream, T, W, scores, hist, nvec, want_hist, na);              \
+                               ctx->stream, T, W, scores, hist, nvec, want_hist, all_ids, na);              \
     } while (0)
         if (g == 4) PV_SCORES(1);
         else if (g == 8) PV_SCORES(2);
@@ -957,23 +1114,26 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
         else if (g == 64) PV_SCORES(16);
         else
             hipLaunchKernelGGL(k_scores_hist0, dim3(sblocks), dim3(kBlock), 0, ctx->stream, T, W,
-                               scores, hist, N, g, want_hist);
+                               scores, hist, N, g, want_hist, all_ids);
 #undef PV_SCORES
     }
     }   // group sizes other than 1 and 2
-    if (k > 0) {
+    if (want_hist && N <= kSmallGroups) {
+        // one block's three phases cost less than three launches up to here
         pv_timed t(ctx, PV_K_SELECT);
-        int64_t hb = ((int64_t)(N >> 2) + kHistBlock - 1) / kHistBlock;
-        const unsigned hblocks = (unsigned)(hb < 512 ? (hb < 1 ? 1 : hb) : 512);
-        const unsigned cblocks = (unsigned)(nchunks < kCompactBlocks ? nchunks : kCompactBlocks);
-        hipLaunchKernelGGL(k_hist_next, dim3(hblocks), dim3(kHistBlock), 0, ctx->stream, scores, hist,
-                           hist + kHist1, state, N, (unsigned)k, 1);
-        hipLaunchKernelGGL(k_hist_next, dim3(hblocks), dim3(kHistBlock), 0, ctx->stream, scores, hist,
-                           hist + kHist2, state, N, (unsigned)k, 2);
-        hipLaunchKernelGGL(k_chunk_counts, dim3(cblocks), dim3(kBlock), 0, ctx->stream, scores, hist,
-                           state, cc, N, nchunks);
-        hipLaunchKernelGGL(k_compact_write, dim3(cblocks), dim3(kBlock), 0, ctx->stream, scores,
-                           state, cc, hist, out_idx, N, nchunks);
+        hipLaunchKernelGGL(k_select_small, dim3(1), dim3(kSelBlock), 0, ctx->stream, scores, hist, N,
+                           (unsigned)k, out_idx);
+    } else if (want_hist) {
+        pv_timed t(ctx, PV_K_SELECT);
+        const sel_plan p = bufs.plan;
+        unsigned *counts = bufs.counts, *above = counts + (size_t)kSelBlocks * kSelWaves;
+        unsigned *suffix = above + kSelBlocks;
+        hipLaunchKernelGGL(k_collect, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, scores, hist, state,
+                           (int64_t)N, (unsigned)k, p.span, p.cap, bufs.list, counts);
+        hipLaunchKernelGGL(k_last_digit, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, scores, hist, state,
+                           (int64_t)N, p.span, p.cap, bufs.list, counts, above, suffix);
+        hipLaunchKernelGGL(k_write_ids, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, scores, hist, state,
+                           (int64_t)N, p.span, p.cap, bufs.list, counts, above, suffix, out_idx);
     }
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;

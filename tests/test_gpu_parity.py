@@ -249,6 +249,30 @@ def test_select_all_zero_scores():
 
 # ------------------------------------------- targets + selection in one sweep
 
+@pytest.mark.parametrize("N", [255, 4097, 32767, 32768, 32769, 40001, 262145, 1050001])
+@pytest.mark.parametrize("values", ["spread", "narrow", "equal", "clustered"])
+def test_select_on_both_sides_of_its_dispatch(N, values):
+    """One block up to 32 768 groups, three kernels beyond; a wave's list of candidates fits,
+    overflows (many keys in one digit, large scores next to each other) or is not kept (large k)."""
+    rng = np.random.default_rng(N)
+    W = np.zeros((1, N), np.float32)
+    if values == "spread":
+        T = rng.standard_normal((1, N)).astype(np.float32)
+    elif values == "narrow":
+        T = (1.0 + 1e-5 * rng.random((1, N))).astype(np.float32)
+    elif values == "equal":
+        T = np.full((1, N), 0.5, np.float32)
+    else:
+        T = (1e-3 * rng.standard_normal((1, N))).astype(np.float32)
+        T[0, N // 3:N // 3 + N // 20] += 1.0
+    wl = workloads.make(1, N, 1, 1, 4, seed=4)
+    run = GpuRun(wl)
+    run.W = dev_f32(W)
+    for k in sorted({1, N // 100 + 1, N // 8, N // 8 + 1, N - 1, N}):
+        idx = run.select(dev_f32(T), k)
+        assert np.array_equal(idx, oracle.select_topk_groups(T, W, 1, k)), (N, values, k)
+
+
 @pytest.mark.parametrize("shape,g", [((256, 256), 8), ((61, 1000), 8), ((33, 4096), 16),
                                      ((129, 4100), 4), ((5, 12), 1), ((100, 36), 6),
                                      ((17, 640), 32), ((9, 1280), 64),
