@@ -44,6 +44,7 @@ struct pv_ctx {
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
     pv_buffer cb_f16;       // prepared codebook operand for the matrix-core filter
     pv_buffer cb_meta;      // u32 [2][8]         two slots of codebook statistics (scale, norms, rounding bound)
+    pv_buffer cells;        // cells of the codebook (pv_cells.h): statistics, thresholds, counts
     pv_buffer x_f16;        // prepared target operand [k_pad / 32][2][32][8] halves
     pv_buffer x_meta;       // f32 [k_pad][4]     per-group bounds and flags
     pv_buffer partials;     // i32 [P][k_pad][2]  best / runner-up keys per partition

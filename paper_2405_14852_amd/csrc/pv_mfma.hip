@@ -293,6 +293,152 @@ __global__ __launch_bounds__(kScanBlock) void k_cb_scan(const unsigned *__restri
     offsets[first + threadIdx.x] = base + inc - v;
 }
 
+// Table position -> tile and row of the operand (see k_prep).
+struct operand_row {
+    int tile, row;
+};
+__device__ __forceinline__ operand_row operand_row_of(int pos)
+{
+    const int q = pos & 15, uu = (pos >> 4) % kU, hw = (pos / (16 * kU)) & 1;
+    return {(pos / (32 * kU)) * kU + uu, 8 * (q >> 2) + 4 * hw + (q & 3)};
+}
+
+// What the preparation of the selected groups reads and writes.
+struct group_args {
+    const float *T, *scales, *codebook;
+    const int32_t *group_idx;
+    const uint16_t *codes;
+    int k, k_pad, gpr, N, csize_mask;
+    h8 *X;
+    float *x_meta, *x_stage;
+    float *reach;          // cells only: squared radius beyond which a cell is left out
+};
+
+// One selected group (position j in the list): x = t / s, its fp16 copy, per-group bounds.
+// CELLS: SHIFT is what makes kv non-negative for every codeword at most as far as the current one
+// (and hardly any other), and reach[j] is that distance's square for the test of whole cells.
+template <int G, bool CELLS>
+__device__ __forceinline__ void prep_group(const group_args &ga, int j, float P, bool ok, const unsigned *meta)
+{
+    // ||c_hi|| <= P max_c ||c|| + rounding
+    const float cmax = P * sqrtf(__uint_as_float(meta[5])) * 1.0001f + kNormMargin;
+    float shift = 0.0f, xx = 0.0f, e1 = 0.0f, dx = -1.0f, reach = -1.0f;
+    h8 chunk[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) chunk[u][e] = (_Float16)0.0f;
+    int n = j < ga.k ? ga.group_idx[j] : -1;
+    if (n >= ga.N) n = -1;
+    // everything is read before anything is written: the loads of one step are in flight together
+    float s = 0.0f;
+    int code = 0;
+    pv_f4 tgt[G / 4], cur[G / 4];
+#pragma unroll
+    for (int v4 = 0; v4 < G / 4; ++v4) tgt[v4] = cur[v4] = pv_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (n >= 0) {
+        code = (int)ga.codes[n] & ga.csize_mask;
+        s = ga.scales[n / ga.gpr];
+        const pv_f4 *src = reinterpret_cast<const pv_f4 *>(ga.T + (int64_t)n * G);
+#pragma unroll
+        for (int v4 = 0; v4 < G / 4; ++v4) tgt[v4] = src[v4];
+        if constexpr (CELLS) {
+            const pv_f4 *cw = reinterpret_cast<const pv_f4 *>(ga.codebook + (int64_t)code * G);
+#pragma unroll
+            for (int v4 = 0; v4 < G / 4; ++v4) cur[v4] = cw[v4];
+        }
+    }
+    {
+        pv_f4 *stage = reinterpret_cast<pv_f4 *>(ga.x_stage + (int64_t)j * (G + 4));
+        pv_f4 tail = {s, __int_as_float(code), __int_as_float(n), 0.0f};
+        stage[G / 4] = tail;
+        if (n >= 0)
+#pragma unroll
+            for (int v4 = 0; v4 < G / 4; ++v4) stage[v4] = tgt[v4];
+    }
+    if (n >= 0 && ok) {
+        bool fits = (s != 0.0f) && (fabsf(s) < 3.0e38f);
+        const float div = fits ? s : 1.0f;
+        float d2 = 0.0f, u2 = 0.0f, p2 = 0.0f;      // p2: squared distance of the current code's codeword, scaled
+#pragma unroll
+        for (int v4 = 0; v4 < G / 4; ++v4) {
+            const pv_f4 raw = tgt[v4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = v4 * 4 + e;
+                float u = P * (raw[e] / div);
+                if (!(fabsf(u) < 240.0f)) fits = false;   // also catches NaN / inf
+                _Float16 hv = to_half_flush(fits ? u : 0.0f);
+                float hf = (float)hv;
+                xx = fmaf(hf, hf, xx);
+                float d = u - hf;
+                d2 = fmaf(d, d, d2);
+                u2 = fmaf(u, u, u2);
+                if constexpr (CELLS) {
+                    const float dp = P * cur[v4][e] - u;
+                    p2 = fmaf(dp, dp, p2);
+                }
+                chunk[i >> 3][i & 7] = hv;
+            }
+        }
+        const float xn = sqrtf(xx) * 1.0001f;
+        // the smallest codeword, scaled: kv of that codeword is then non-negative
+        const float cn0 = P * sqrtf(__uint_as_float(~meta[1])) * 1.0001f + kNormMargin;
+        float want = (xn + cn0) * (xn + cn0) * 1.0001f + 1.0e-3f;
+        if (fits && xx < 57000.0f && want < 60000.0f) {
+            // bound of the fp32 accumulation error of one accumulator (g = 8: products, norm
+            // pieces and SHIFT add up to at most 2 (cmax + xn)^2 in magnitude; g = 16: the
+            // products alone, then two fp32 additions on the vector ALU), plus dropped fp16 pieces
+            const float e1p = (G == 8 ? 2.0f : 1.0f) * kGamma * (cmax + xn) * (cmax + xn) * 1.01f +
+                              (G == 8 ? 5.0e-4f : 4.0e-7f * (cmax + xn) * (cmax + xn));
+            e1 = 1.01f * e1p;
+            // rounding of x to fp16, plus the fp32 division and scaling roundings (2^-22 ||u||)
+            dx = sqrtf(d2) * 1.0001f + 2.4e-7f * sqrtf(u2) + 1.0e-30f;
+            if constexpr (CELLS) {
+                // a codeword that beats the current one has ||P c - u|| <= dp, hence ||c_hi - x_hi|| <=
+                // dp + dx + kNormMargin (rounding of a codeword): kv is non-negative for those.
+                // dp: fp32 differences of elements up to (32 + |u|), each rounded once
+                const float dp = sqrtf(p2) * 1.00001f + 3.0e-7f * (cmax + xn);
+                reach = (dp + dx) * (dp + dx) * 1.0001f;
+                want = (dp + dx + kNormMargin) * (dp + dx + kNormMargin) * 1.0001f + e1 - xx * 0.9999f + 1.0e-3f;
+                if (!(fabsf(want) < 60000.0f)) {     // also NaN: every codeword is looked at instead
+                    dx = reach = -1.0f;
+                    want = 0.0f;
+                }
+            }
+            if (G == 8) {
+                _Float16 pieces[3];
+                split3(want, pieces);
+                shift = ((float)pieces[0] + (float)pieces[1]) + (float)pieces[2];
+                chunk[1][0] = (_Float16)-1.0f;
+                chunk[1][1] = (_Float16)-1.0f;
+                chunk[1][2] = (_Float16)-1.0f;
+                chunk[1][3] = pieces[0];
+                chunk[1][4] = pieces[1];
+                chunk[1][5] = pieces[2];
+            } else {
+                shift = want;
+            }
+        } else {
+            xx = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) chunk[u][e] = (_Float16)0.0f;
+        }
+    }
+    const int gt = j >> 5, col = j & 31;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) ga.X[((int64_t)gt * 2 + u) * 32 + col] = chunk[u];
+    pv_f4 m;
+    m.x = shift;
+    m.y = xx;
+    m.z = e1;
+    m.w = dx;
+    reinterpret_cast<pv_f4 *>(ga.x_meta)[j] = m;
+    if constexpr (CELLS) ga.reach[j] = reach;
+}
+
 // Operand preparation, one launch for both sides.
 //
 // Blocks [0, cb_blocks): one thread per codeword position of the padded table.  A codeword is
@@ -329,13 +475,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(const float *__restrict__ cb, i
                                                  unsigned *__restrict__ bucket_next,
                                                  unsigned *__restrict__ nmin_bits,
                                                  float *__restrict__ cnorm,
-                                                 const float *__restrict__ T,
-                                                 const float *__restrict__ scales,
-                                                 const int32_t *__restrict__ group_idx, int k,
-                                                 int k_pad, int gpr, int N, h8 *__restrict__ X,
-                                                 float *__restrict__ x_meta,
-                                                 const uint16_t *__restrict__ codes, int csize_mask,
-                                                 float *__restrict__ x_stage, int ncyc, int nsplit)
+                                                 group_args ga, int ncyc, int nsplit)
 {
     bool ok;
     const float P = scale_from_maxabs(meta[0], &ok);
@@ -390,11 +530,9 @@ __global__ __launch_bounds__(kBlock) void k_prep(const float *__restrict__ cb, i
                 atomicMin(&nmin_bits[pos / (16 * kU)], 0u);   // padding rows count as norm 0
                 cnorm[pos] = 0.0f;
             }
-            const int q = pos & 15, uu = (pos >> 4) % kU, hw = (pos / (16 * kU)) & 1;
-            const int tile = (pos / (32 * kU)) * kU + uu;
-            const int row = 8 * (q >> 2) + 4 * hw + (q & 3);
+            const operand_row o = operand_row_of(pos);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) A[((int64_t)tile * 2 + u) * 32 + row] = chunk[u];
+            for (int u = 0; u < 2; ++u) A[((int64_t)o.tile * 2 + u) * 32 + o.row] = chunk[u];
         }
         }
         __shared__ float s_d[kBlock / 64];
@@ -410,94 +548,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(const float *__restrict__ cb, i
     }
 
     const int j = ((int)blockIdx.x - cb_blocks) * kBlock + threadIdx.x;
-    if (j >= k_pad) return;
-    ok = ok && meta[3] == 0u && meta[1] != 0u;
-    // ||c_hi|| <= P max_c ||c|| + rounding
-    const float cmax = P * sqrtf(__uint_as_float(meta[5])) * 1.0001f + kNormMargin;
-    float shift = 0.0f, xx = 0.0f, e1 = 0.0f, dx = -1.0f;
-    int n = j < k ? group_idx[j] : -1;
-    if (n >= N) n = -1;
-    pv_f4 *stage = reinterpret_cast<pv_f4 *>(x_stage + (int64_t)j * (G + 4));
-    {
-        pv_f4 tail = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (n >= 0) {
-            tail.x = scales[n / gpr];
-            tail.y = __int_as_float((int)codes[n] & csize_mask);
-        }
-        tail.z = __int_as_float(n);
-        stage[G / 4] = tail;
-    }
-    if (n >= 0) {
-        const pv_f4 *src = reinterpret_cast<const pv_f4 *>(T + (int64_t)n * G);
-#pragma unroll
-        for (int v4 = 0; v4 < G / 4; ++v4) stage[v4] = src[v4];
-    }
-    if (n >= 0 && ok) {
-        const float s = scales[n / gpr];
-        bool fits = (s != 0.0f) && (fabsf(s) < 3.0e38f);
-        const float div = fits ? s : 1.0f;
-        float d2 = 0.0f, u2 = 0.0f;
-        const pv_f4 *src = reinterpret_cast<const pv_f4 *>(T + (int64_t)n * G);
-#pragma unroll
-        for (int v4 = 0; v4 < G / 4; ++v4) {
-            pv_f4 raw = src[v4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = v4 * 4 + e;
-                float u = P * (raw[e] / div);
-                if (!(fabsf(u) < 240.0f)) fits = false;   // also catches NaN / inf
-                _Float16 hv = to_half_flush(fits ? u : 0.0f);
-                float hf = (float)hv;
-                xx = fmaf(hf, hf, xx);
-                float d = u - hf;
-                d2 = fmaf(d, d, d2);
-                u2 = fmaf(u, u, u2);
-                chunk[i >> 3][i & 7] = hv;
-            }
-        }
-        const float xn = sqrtf(xx) * 1.0001f;
-        // the smallest codeword, scaled: kv of that codeword is then non-negative
-        const float cn0 = P * sqrtf(__uint_as_float(~meta[1])) * 1.0001f + kNormMargin;
-        const float want = (xn + cn0) * (xn + cn0) * 1.0001f + 1.0e-3f;
-        if (fits && xx < 57000.0f && want < 60000.0f) {
-            // bound of the fp32 accumulation error of one accumulator (g = 8: products, norm
-            // pieces and SHIFT add up to at most 2 (cmax + xn)^2 in magnitude; g = 16: the
-            // products alone, then two fp32 additions on the vector ALU), plus dropped fp16 pieces
-            const float e1p = (G == 8 ? 2.0f : 1.0f) * kGamma * (cmax + xn) * (cmax + xn) * 1.01f +
-                              (G == 8 ? 5.0e-4f : 4.0e-7f * (cmax + xn) * (cmax + xn));
-            e1 = 1.01f * e1p;
-            // rounding of x to fp16, plus the fp32 division and scaling roundings (2^-22 ||u||)
-            dx = sqrtf(d2) * 1.0001f + 2.4e-7f * sqrtf(u2) + 1.0e-30f;
-            if (G == 8) {
-                _Float16 pieces[3];
-                split3(want, pieces);
-                shift = ((float)pieces[0] + (float)pieces[1]) + (float)pieces[2];
-                chunk[1][0] = (_Float16)-1.0f;
-                chunk[1][1] = (_Float16)-1.0f;
-                chunk[1][2] = (_Float16)-1.0f;
-                chunk[1][3] = pieces[0];
-                chunk[1][4] = pieces[1];
-                chunk[1][5] = pieces[2];
-            } else {
-                shift = want;
-            }
-        } else {
-            xx = 0.0f;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) chunk[u][e] = (_Float16)0.0f;
-        }
-    }
-    const int gt = j >> 5, col = j & 31;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) X[((int64_t)gt * 2 + u) * 32 + col] = chunk[u];
-    pv_f4 m;
-    m.x = shift;
-    m.y = xx;
-    m.z = e1;
-    m.w = dx;
-    reinterpret_cast<pv_f4 *>(x_meta)[j] = m;
+    if (j < ga.k_pad) prep_group<G, false>(ga, j, P, ok && meta[3] == 0u && meta[1] != 0u, meta);
 }
 
 // Plain C so that the compiler sees the reads of MFMA results and inserts the
@@ -570,8 +621,9 @@ template <int G, int NB>
 __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_score_mfma(
     const h8 *__restrict__ A, const h8 *__restrict__ X, const float *__restrict__ x_meta,
     const float *__restrict__ nmin, int2 *__restrict__ partials, int ncyc, int nsplit, int per_half,
-    int gblocks, int k_pad, unsigned *__restrict__ next_item)
+    int gblocks, int k_pad, unsigned *__restrict__ next_item, const float *__restrict__ wanted)
 {
+    if (wanted && *wanted == 0.0f) return;   // the cells do the work (pv_cells.h)
     constexpr int S = PV_STAGE;                                    // tiles per stage
     constexpr int kStageChunks = S * 64;                           // 16-byte chunks per stage
     constexpr int kW = PV_WAVES;                                   // waves per block
@@ -761,6 +813,10 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     }
 }
 
+}  // namespace
+#include "pv_cells.h"
+namespace {
+
 // ---------------------------------------------------------------- exact re-rank
 
 struct cand_t {
@@ -810,7 +866,7 @@ __device__ __forceinline__ float key_upper(int key)
 // (value - bound <= reach), so a generous bound costs a few needless exact evaluations.
 constexpr float kDdAbs = 1.0e-5f;
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-template <int G>
+template <int G, bool CELLS = false>
 __device__ __forceinline__ float approx_dd(const h8 *__restrict__ A, const float *__restrict__ cnorm,
                                            int tile, int row, int pos, const h8 (&xq)[G / 8], float xx)
 {
@@ -829,6 +885,7 @@ __device__ __forceinline__ float approx_dd(const h8 *__restrict__ A, const float
     if (G == 8) {
         const h8 nrm = A[((int64_t)tile * 2 + 1) * 32 + row];
         cc = ((float)nrm[0] + (float)nrm[1]) + (float)nrm[2];
+        if (CELLS && cc > 0.8f * kPadNorm) return __builtin_huge_valf();   // a padding row
     } else {
         cc = cnorm[pos];
     }
@@ -869,10 +926,11 @@ __device__ __forceinline__ float fast_rcp(float v) { return __builtin_amdgcn_rcp
 // applied before the root takes over
 __device__ __forceinline__ float float_above(double v) { return (float)v * 1.0000002f; }
 
-template <int G>
+template <int G, bool CELLS>
 __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
     const float *__restrict__ x_stage, const float *__restrict__ codebook, int k, int k_pad,
     const int2 *__restrict__ partials, int P, int per_half, int ncyc, int nsplit,
+    const int *__restrict__ su_bounds,
     const float *__restrict__ x_meta, const unsigned *__restrict__ cb_meta, const h8 *__restrict__ A,
     const float *__restrict__ cnorm, const h8 *__restrict__ X, const uint16_t *__restrict__ perm,
     uint16_t *__restrict__ codes,
@@ -977,14 +1035,14 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                     pos[uu * kPer + e] = ((su * 2 + hw) * kU + uu) * 16 + qq;
                     // unconditional (the padded table has the row), so that the loads of all the
                     // lane's positions are in flight together
-                    dd[uu * kPer + e] = approx_dd<G>(A, cnorm, su * kU + uu, row, pos[uu * kPer + e], xq, meta.y);
+                    dd[uu * kPer + e] = approx_dd<G, CELLS>(A, cnorm, su * kU + uu, row, pos[uu * kPer + e], xq, meta.y);
                     // the codeword behind the position comes along (g = 8: positions are
                     // codewords), so that an exact evaluation is one more round trip, not two
-                    cwd[uu * kPer + e] = G == 8 ? pos[uu * kPer + e] : (int)perm[pos[uu * kPer + e]];
+                    cwd[uu * kPer + e] = G == 8 && !CELLS ? pos[uu * kPer + e] : (int)perm[pos[uu * kPer + e]];
                 }
 #pragma unroll
             for (int i = 0; i < kMine; ++i)
-                if (pos[i] >= csize) dd[i] = __builtin_huge_valf();
+                if (!CELLS && pos[i] >= csize) dd[i] = __builtin_huge_valf();
         };
         auto exact_at = [&](int cw, cand_t &c) {
             const double o = exact_obj<G>(codebook + (int64_t)cw * G, s, t);
@@ -1047,7 +1105,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
             const float r2f = reach2_of(e_star);
 #pragma unroll
             for (int uu = 0; uu < kMine; ++uu)
-                if (!(chosen && uu == wu) && dd[uu] - dabs <= r2f && pos[uu] < csize) {
+                if (!(chosen && uu == wu) && dd[uu] - dabs <= r2f && dd[uu] < 3.0e38f) {
                     exact_at(cwd[uu], mine);
                     ++exact_evals;
                 }
@@ -1096,7 +1154,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                 level1(key, src + kTeam * u, dd, pos, cwd);
 #pragma unroll
                 for (int uu = 0; uu < kMine; ++uu)
-                    if (dd[uu] - dabs <= reach2f && pos[uu] < csize) {
+                    if (dd[uu] - dabs <= reach2f && dd[uu] < 3.0e38f) {
                         exact_at(cwd[uu], mine);
                         ++exact_evals;
                     }
@@ -1179,8 +1237,8 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
             const int p = __ffsll((long long)left) - 1;
             const int hw = (p / per_half) & 1;
             const int split = p / (2 * per_half);
-            const int su_begin = split_begin(split, ncyc, nsplit) * kResidues;
-            const int su_end = su_begin + split_count(split, ncyc, nsplit) * kResidues;
+            const int su_begin = CELLS ? su_bounds[split] : split_begin(split, ncyc, nsplit) * kResidues;
+            const int su_end = CELLS ? su_bounds[split + 1] : su_begin + split_count(split, ncyc, nsplit) * kResidues;
             const int row = 8 * (qq >> 2) + 4 * hw + (qq & 3);
             // the classes of the record: p % per_half, + per_half, ... (relative to the split's
             // start); kBatch super-units per lane at a time, so that their operand rows are in
@@ -1197,7 +1255,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                     const int su_c = su < su_end ? su : su_end - 1;
 #pragma unroll
                     for (int uu = 0; uu < kU; ++uu)
-                        dd[bb][uu] = approx_dd<G>(A, cnorm, su_c * kU + uu, row,
+                        dd[bb][uu] = approx_dd<G, CELLS>(A, cnorm, su_c * kU + uu, row,
                                                   ((su_c * 2 + hw) * kU + uu) * 16 + qq, xq, xx);
                 }
 #pragma unroll
@@ -1206,8 +1264,9 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
 #pragma unroll
                     for (int uu = 0; uu < kU; ++uu) {
                         const int pos = ((su * 2 + hw) * kU + uu) * 16 + qq;
-                        if (su < su_end && pos < csize && (!test || dd[bb][uu] - dabs <= r2f)) {
-                            const int cw = G == 8 ? pos : (int)perm[pos];
+                        if (su < su_end && (CELLS ? dd[bb][uu] < 3.0e38f : pos < csize) &&
+                            (!test || dd[bb][uu] - dabs <= r2f)) {
+                            const int cw = G == 8 && !CELLS ? pos : (int)perm[pos];
                             const double obj = exact_obj<G>(codebook + (int64_t)cw * G, s, t);
                             if (cand_better(obj, cw, mine.obj, mine.idx)) {
                                 mine.obj = obj;
@@ -1742,7 +1801,39 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
                                 const int32_t *group_idx, int64_t k, uint16_t *codes,
                                 int64_t *num_changed, int32_t power, uint64_t seed)
 {
-    const plan_t p = make_plan(l, k, power > 0);
+    plan_t p = make_plan(l, k, power > 0);
+    // Cells (pv_cells.h): g = 8, the nearest codeword, work enough to pay for cutting the codebook.
+    const int cbits = l->nbits - kCellLog;
+    const bool cells = l->group_size == 8 && power == 0 && l->nbits >= kCellMinBits &&
+                       (k << l->nbits) >= kCellMinWork;
+    int cell_waves = 8, dense_blocks = 0;
+    if (cells) {
+        const int ncells = 1 << cbits;
+        p.cpad = ((1 << l->nbits) + ncells * (kCellPos - 1) + kCellPos - 1) / kCellPos * kCellPos;
+        // Waves per block and number of splits (ranges of runs of 16 cells, at most kItemCells cells
+        // each): the pair with the least work on the fullest compute unit.  An item costs its groups x
+        // its runs, and something besides for each and for itself.  Few splits where that is even: the
+        // re-rank reads four records for each.
+        const int runs = ncells / 16, least = (ncells + kItemCells - 1) / kItemCells;
+        double most = 1e30;
+        for (int n = least; n <= 16 && n <= runs; ++n)
+            for (int w = kCellWavesMax; w >= 4; --w) {
+                const int gb = (int)((k + w * 64 - 1) / (w * 64));
+                const int rounds = (gb * n + 255) / 256, most_runs = (runs + n - 1) / n;
+                const double work = rounds * ((w + 3.0) * (most_runs + 0.5));
+                if (work < most * 0.98) {
+                    most = work;
+                    p.nsplit = n;
+                    cell_waves = w;
+                }
+            }
+        p.gblocks = (int)((k + cell_waves * 64 - 1) / (cell_waves * 64));
+        // the dense contraction takes 512 groups at a time
+        dense_blocks = (int)((k + PV_WAVES * PV_NBX * 32 - 1) / (PV_WAVES * PV_NBX * 32));
+        p.k_pad = (p.gblocks * cell_waves * 64 + 511) & ~511;
+        p.per_half = 2;
+        p.P = p.nsplit * 4;
+    }
     const int g = l->group_size;
     const int csize = 1 << l->nbits;
     const int gpr = (int)(l->in_features / g);
@@ -1758,12 +1849,13 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     const size_t nmin_off = offs_off + (size_t)kNormBins * 4;
     const size_t cnorm_off = (nmin_off + (size_t)nsu_alloc * 4 + 255) & ~(size_t)255;   // g = 16: norm per position
     if ((st = pv_ensure(ctx, ctx->cb_f16, cnorm_off + (size_t)p.cpad * 4)) != PV_OK) return st;
-    if ((st = pv_ensure(ctx, ctx->cb_meta, 16 * sizeof(unsigned), /*zero_new=*/true)) != PV_OK) return st;
+    if ((st = pv_ensure(ctx, ctx->cb_meta, 32 * sizeof(unsigned), /*zero_new=*/true)) != PV_OK) return st;
+    if (cells && (st = pv_ensure(ctx, ctx->cells, kCellWords * 4, /*zero_new=*/true)) != PV_OK) return st;
     if ((st = pv_ensure(ctx, ctx->x_f16, (size_t)p.k_pad * 32)) != PV_OK) return st;
     // per-group bounds, then the staged targets / scale / code / id of each group
     const size_t stage_off = (size_t)p.k_pad * 4 * sizeof(float);
-    if ((st = pv_ensure(ctx, ctx->x_meta, stage_off + (size_t)p.k_pad * (g + 4) * sizeof(float))) != PV_OK)
-        return st;
+    const size_t reach_off = stage_off + (size_t)p.k_pad * (g + 4) * sizeof(float);
+    if ((st = pv_ensure(ctx, ctx->x_meta, reach_off + (cells ? (size_t)p.k_pad * sizeof(float) : 0))) != PV_OK) return st;
     if ((st = pv_ensure(ctx, ctx->partials, (size_t)p.k_pad * p.P * sizeof(int2))) != PV_OK) return st;
     if ((st = pv_ensure(ctx, ctx->fb_list, 64)) != PV_OK) return st;
     const int rr_blocks = (int)((k * rerank_team(l->group_size) + kBlock - 1) / kBlock);
@@ -1790,6 +1882,62 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     unsigned long long *stats = static_cast<unsigned long long *>(ctx->stats.ptr);
     auto nc = reinterpret_cast<unsigned long long *>(num_changed);
     hipStream_t sm = ctx->stream;
+    group_args ga;
+    ga.T = T;
+    ga.scales = scales;
+    ga.codebook = codebooks;
+    ga.group_idx = group_idx;
+    ga.codes = codes;
+    ga.k = (int)k;
+    ga.k_pad = p.k_pad;
+    ga.gpr = gpr;
+    ga.N = N;
+    ga.csize_mask = csize - 1;
+    ga.X = X;
+    ga.x_meta = x_meta;
+    ga.x_stage = x_stage;
+    ga.reach = cells ? reinterpret_cast<float *>(static_cast<char *>(ctx->x_meta.ptr) + reach_off) : nullptr;
+    ctx->rr_blocks_last = rr_blocks;
+    if (cells) {
+        const int cb_blocks = csize / kCellChunk;
+        unsigned *meta = cb_meta + 16;             // written whole by every call: no slots to alternate
+        int *su_bounds = reinterpret_cast<int *>(hist);
+        cell_mem mem;
+        mem.part = static_cast<pv_f4 *>(ctx->cells.ptr);
+        mem.dpart = reinterpret_cast<float *>(mem.part + kCellBlocksMax);
+        mem.theta = mem.dpart + kCellBlocksMax;
+        mem.count = reinterpret_cast<unsigned *>(mem.theta + 16);
+        mem.cursor = mem.count + kCellCopies * kCellsMax;
+        mem.cell_su = reinterpret_cast<int *>(mem.cursor + kCellCopies * kCellsMax);
+        mem.cell_of = reinterpret_cast<uint16_t *>(mem.cell_su + kCellsMax + 8);
+        {
+            pv_timed t(ctx, PV_K_PREP);
+            hipLaunchKernelGGL(k_cells_stats, dim3(cb_blocks + 1), dim3(kBlock), 0, sm, codebooks, csize, cbits, mem,
+                               stats, fb_count, nc, change_slots, nslots, ga);
+            hipLaunchKernelGGL(k_cells_prep, dim3(cb_blocks + (p.k_pad + kBlock - 1) / kBlock), dim3(kBlock), 0, sm,
+                               codebooks, csize, cbits, cb_blocks, mem, meta, A, perm, su_bounds, p.nsplit, ga);
+        }
+        {
+            pv_timed t(ctx, PV_K_SCORE_MFMA);
+            const int items = p.gblocks * p.nsplit;
+            hipLaunchKernelGGL(k_cells_score, dim3(items < 256 ? items : 256), dim3(cell_waves * 64), 0, sm, A, X,
+                               ga.reach, su_bounds, mem, meta, partials, cbits, cb_blocks, p.nsplit, p.gblocks,
+                               p.k_pad, fb_count + 1);
+            const int ditems = dense_blocks * p.nsplit;
+            hipLaunchKernelGGL((k_score_mfma<8, PV_NBX>), dim3(ditems < 256 * PV_OCC ? ditems : 256 * PV_OCC),
+                               dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, (const float *)nullptr, partials,
+                               csize / (32 * kU * kResidues), p.nsplit, p.per_half, dense_blocks, p.k_pad, fb_count + 2,
+                               mem.theta + 15);
+        }
+        {
+            pv_timed t(ctx, PV_K_RERANK);
+            hipLaunchKernelGGL((k_rerank<8, true>), dim3((unsigned)rr_blocks), dim3(kBlock), 0, sm, x_stage, codebooks,
+                               (int)k, p.k_pad, partials, p.P, p.per_half, 0, p.nsplit, su_bounds, x_meta, meta, A,
+                               cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
+        }
+        PV_HIP(ctx, hipGetLastError());
+        return PV_OK;
+    }
     // two statistics slots, used alternately (the first kernel of a call clears the other one)
     unsigned *cb_meta_next = cb_meta + (ctx->meta_phase ? 0 : 8);
     cb_meta += ctx->meta_phase ? 8 : 0;
@@ -1805,7 +1953,6 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             if (fs != PV_OK) return fs;
         }
     }
-    ctx->rr_blocks_last = rr_blocks;
     {
         pv_timed t(ctx, PV_K_PREP);
         int blocks = (csize + kBlock - 1) / kBlock;
@@ -1819,9 +1966,8 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
                                cb_meta, cb_meta_next, stats, fb_count, nc, (unsigned *)nullptr,
                                (unsigned *)nullptr, 0, change_slots, nslots);
             hipLaunchKernelGGL(k_prep<8>, dim3(cb_blocks + x_blocks), dim3(kBlock), 0, sm, codebooks,
-                               csize, p.cpad, cb_blocks, cb_meta, A, perm, bucket, hist, nmin_bits, cnorm, T,
-                               scales, group_idx, (int)k, p.k_pad, gpr, N, X, x_meta, codes, csize - 1,
-                               x_stage, p.ncyc, p.nsplit);
+                               csize, p.cpad, cb_blocks, cb_meta, A, perm, bucket, hist, nmin_bits, cnorm, ga,
+                               p.ncyc, p.nsplit);
         } else {
             hipLaunchKernelGGL(k_cb_stats<16>, dim3(blocks), dim3(kBlock), 0, sm, codebooks, csize,
                                cb_meta, cb_meta_next, stats, fb_count, nc, hist, nmin_bits, nsu_alloc,
@@ -1831,8 +1977,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             hipLaunchKernelGGL(k_cb_scan, dim3(kNormBins / kScanBlock), dim3(kScanBlock), 0, sm, hist, offsets);
             hipLaunchKernelGGL(k_prep<16>, dim3(cb_blocks + x_blocks), dim3(kBlock), 0, sm,
                                codebooks, csize, p.cpad, cb_blocks, cb_meta, A, perm, bucket, offsets,
-                               nmin_bits, cnorm, T, scales, group_idx, (int)k, p.k_pad, gpr, N, X, x_meta,
-                               codes, csize - 1, x_stage, p.ncyc, p.nsplit);
+                               nmin_bits, cnorm, ga, p.ncyc, p.nsplit);
         }
     }
     {
@@ -1842,7 +1987,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
         const float *nmin = reinterpret_cast<const float *>(nmin_bits);
 #define PV_SCORE(G_, NB_)                                                                          \
     hipLaunchKernelGGL((k_score_mfma<G_, NB_>), grid, dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, nmin, \
-                       partials, p.ncyc, p.nsplit, p.per_half, p.gblocks, p.k_pad, fb_count + 1)
+                       partials, p.ncyc, p.nsplit, p.per_half, p.gblocks, p.k_pad, fb_count + 1, (const float *)nullptr)
         if (g == 8) {
             if (p.NB == PV_NBX) PV_SCORE(8, PV_NBX);
             else PV_SCORE(8, 1);
@@ -1865,13 +2010,13 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             else PV_ROUND2(16);
 #undef PV_ROUND2
         } else if (g == 8)
-            hipLaunchKernelGGL(k_rerank<8>, rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
-                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, x_meta, cb_meta, A,
-                               cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
+            hipLaunchKernelGGL((k_rerank<8, false>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
+                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, x_meta,
+                               cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
         else
-            hipLaunchKernelGGL(k_rerank<16>, rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
-                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, x_meta, cb_meta, A,
-                               cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
+            hipLaunchKernelGGL((k_rerank<16, false>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
+                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, x_meta,
+                               cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
     }
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;

@@ -368,6 +368,31 @@ def test_reencode_m1_list_lengths_around_the_launch_plan(g, k):
     assert st["filtered"] + st["fallback"] == k
 
 
+@pytest.mark.parametrize("B,k", [(16, 32768), (16, 34001), (14, 131072)])
+@pytest.mark.parametrize("regime", ["near", "far", "lumps", "degenerate"])
+def test_reencode_m1_cells_of_the_codebook(B, k, regime):
+    """Lists long enough for the search that leaves out whole cells: current codes near the targets,
+    current codes drawn at random (the dense contraction takes over), a codebook of two lumps and
+    constant coordinates (few, crowded cells), groups that the filter does not take."""
+    wl = workloads.make(256, 8 * ((k + 255) // 256 + 3), 8, 1, B, seed=70, sigma_g=4e-3, tau=1.0)
+    if regime == "lumps":
+        wl.codebooks[0, : 1 << (B - 1)] *= np.float32(0.05)
+        wl.codebooks[0, : 1 << (B - 1)] += np.float32(0.06)
+        wl.codebooks[0, :, 2] = np.float32(0.01)
+        wl.codebooks[0, 1:200] = wl.codebooks[0, 0]
+    if regime == "degenerate":
+        wl.scales[::5] = 0.0
+        wl.scales[1::5] *= np.float32(-1e-3)
+    if regime != "far":
+        wl.W = oracle.dequantize(wl.codes, wl.codebooks, wl.scales)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    if regime == "degenerate":
+        T_np[3, ::7] = np.float32(1e30)
+    N = wl.layout.num_groups
+    idx = np.sort(np.random.default_rng(k).choice(N, size=k, replace=False)).astype(np.int32)
+    reencode_case(wl, 0, idx=idx, T_np=T_np)
+
+
 @pytest.mark.parametrize("B", [5, 6, 9, 13, 16])
 def test_reencode_m1_codebook_sizes_with_long_lists(B):
     """More than 4096 listed groups (two group tiles per wave) at every codebook size class."""
