@@ -37,9 +37,6 @@ constexpr int kCellMinBits = 14;              // smallest codebook that is cut i
 // nothing and the dense contraction runs after all, the way there costs 10 us.
 constexpr int64_t kCellMinWork = INT64_C(1) << 31;
 constexpr int kCellsMax = 1 << (16 - kCellLog);
-constexpr int kCellChunk = 4 * kBlock;        // codewords a block of the two preparation kernels takes
-constexpr int kCellBlocksMax = 65536 / kCellChunk;
-constexpr int kCellCopies = 8;                // counters per die (block b adds to copy b % 8: workgroups go round robin)
 constexpr int kCellPos = 32 * kU;             // a cell is padded to whole super-units
 constexpr int kCellSample = kBlock;           // codewords behind the thresholds
 constexpr float kPadNorm = 50000.0f;          // norm of a padding row (a codeword's is at most 8 * 32^2)
@@ -56,29 +53,16 @@ extern "C" __device__ int pv_writelane(int value, int lane, int old) __asm("llvm
 
 // Device scratch of the path (words).
 struct cell_mem {
-    pv_f4 *part;          // [kCellBlocksMax] {max |c|, min norm^2, max norm^2, bad}
-    float *dpart;         // [kCellBlocksMax] largest rounding error ||P c - c_hi||^2 of a block's codewords
+    pv_f4 *part;          // [kCbParts] {max |c|, min norm^2, max norm^2, bad}
+    float *dpart;         // [kCbParts] largest rounding error ||P c - c_hi||^2 of a block's codewords
     float *theta;         // [16] thresholds 0..7, then the two outer ones of the last dimension; [15] != 0: dense
     unsigned *count;      // [copies][cells], zero between calls
     unsigned *cursor;     // [copies][cells]
     int *cell_su;         // [cells + 1] first super-unit of a cell
     uint16_t *cell_of;    // [codewords]
 };
-constexpr size_t kCellWords = kCellBlocksMax * 4 + kCellBlocksMax + 16 + 2 * kCellCopies * kCellsMax +
+constexpr size_t kCellWords = kCbParts * 4 + kCbParts + 16 + 2 * kCbCopies * kCellsMax +
                               (kCellsMax + 8) + 65536 / 2;
-
-__device__ __forceinline__ float wave_min_f(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off));
-    return v;
-}
-__device__ __forceinline__ float wave_max_f(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
-}
 
 // Bit i of a cell: the side of theta_i.  A 16-bit codebook has nine bits for eight dimensions: two of
 // them say between which thresholds of dimension 7 the coordinate lies, and stand at bits 4 and 5, so
@@ -140,18 +124,13 @@ struct cell_bounds {
 // Every block takes the same sample and so the same thresholds.  Results leave as plain stores
 // per block (the next kernel adds up 64 of them; atomics of all blocks on one line took 3 us).
 __global__ __launch_bounds__(kBlock) void k_cells_stats(const float *__restrict__ cb, int csize, int cbits,
-                                                        cell_mem mem,
-                                                        unsigned long long *__restrict__ stats,
-                                                        unsigned *__restrict__ fb_count,
-                                                        unsigned long long *__restrict__ num_changed,
-                                                        unsigned long long *__restrict__ change_slots,
-                                                        int nslots, group_args ga)
+                                                        cell_mem mem, clear_args ca, group_args ga)
 {
     __shared__ float s_v[kCellSample * 9];          // row stride 9: conflict-free columns
     __shared__ float s_p[4][2][8];
     __shared__ float s_theta[16];
     __shared__ unsigned s_hist[kCellsMax];
-    __shared__ float s_r[kBlock / 64][4];
+    __shared__ pv_f4 s_tmp[kBlock / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ncells = 1 << cbits;
     const pv_f4 *cb4 = reinterpret_cast<const pv_f4 *>(cb);
@@ -188,19 +167,14 @@ __global__ __launch_bounds__(kBlock) void k_cells_stats(const float *__restrict_
     pv_f4 own[4][2];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int c = (sampler ? 0 : blockIdx.x) * kCellChunk + r * kBlock + tid;   // csize is a multiple of kCellChunk
+        const int c = (sampler ? 0 : blockIdx.x) * kCbChunk + r * kBlock + tid;   // csize is a multiple of kCbChunk
         own[r][0] = cb4[c * 2];
         own[r][1] = cb4[c * 2 + 1];
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) s_v[tid * 9 + e] = smp[e >> 2][e & 3];
-    for (int i = blockIdx.x * kBlock + tid; i < nslots; i += gridDim.x * kBlock) change_slots[i] = 0ull;
-    for (int i = blockIdx.x * kBlock + tid; i < kCellCopies * ncells; i += gridDim.x * kBlock) mem.cursor[i] = 0u;
-    if (blockIdx.x == 0) {
-        if (tid < 8) stats[tid] = 0ull;
-        if (tid < 4) fb_count[tid] = 0u;
-        if (tid == 0 && num_changed) *num_changed = 0ull;
-    }
+    clear_counters(ca, blockIdx.x, gridDim.x);
+    for (int i = blockIdx.x * kBlock + tid; i < kCbCopies * ncells; i += gridDim.x * kBlock) mem.cursor[i] = 0u;
     for (int b = tid; b < ncells; b += kBlock) s_hist[b] = 0u;
     __syncthreads();
     {
@@ -253,87 +227,33 @@ __global__ __launch_bounds__(kBlock) void k_cells_stats(const float *__restrict_
         // (a group that the filter does not take, or whose distance is not a number, keeps nothing here)
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) kept += __shfl_xor(kept, off);
-        if (lane == 0) s_r[wave][0] = (float)kept;
+        if (lane == 0) s_tmp[wave].x = (float)kept;
         __syncthreads();
         if (tid == 0) {
-            const float all = s_r[0][0] + s_r[1][0] + s_r[2][0] + s_r[3][0];
+            const float all = s_tmp[0].x + s_tmp[1].x + s_tmp[2].x + s_tmp[3].x;
             mem.theta[15] = all > kDenseShare * (float)ncells * kSampleGroups ? 1.0f : 0.0f;
         }
         return;
     }
-    float m = 0.0f, nmin = __builtin_huge_valf(), nmax = 0.0f;
-    bool bad = false;
+    cb_stat st;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        float v[8], n2 = 0.0f;
+        stat_add<8>(st, own[r]);
+        float v[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            v[i] = own[r][i >> 2][i & 3];
-            bad |= !(fabsf(v[i]) <= 3.0e38f);
-            m = fmaxf(m, fabsf(v[i]));
-            n2 = fmaf(v[i], v[i], n2);
-        }
-        nmin = fminf(nmin, n2);
-        nmax = fmaxf(nmax, n2);
+        for (int i = 0; i < 8; ++i) v[i] = own[r][i >> 2][i & 3];
         const int cell = cell_of_codeword(v, s_theta, cbits);
-        mem.cell_of[blockIdx.x * kCellChunk + r * kBlock + tid] = (uint16_t)cell;
+        mem.cell_of[blockIdx.x * kCbChunk + r * kBlock + tid] = (uint16_t)cell;
         atomicAdd(&s_hist[cell], 1u);
     }
-    m = wave_max_f(m);
-    nmin = wave_min_f(nmin);
-    nmax = wave_max_f(nmax);
-    const bool anybad = __any(bad);
-    if (lane == 0) {
-        s_r[wave][0] = m;
-        s_r[wave][1] = nmin;
-        s_r[wave][2] = nmax;
-        s_r[wave][3] = anybad ? 1.0f : 0.0f;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        pv_f4 p = {s_r[0][0], s_r[0][1], s_r[0][2], s_r[0][3]};
-#pragma unroll
-        for (int w = 1; w < kBlock / 64; ++w) {
-            p.x = fmaxf(p.x, s_r[w][0]);
-            p.y = fminf(p.y, s_r[w][1]);
-            p.z = fmaxf(p.z, s_r[w][2]);
-            p.w = fmaxf(p.w, s_r[w][3]);
-        }
-        mem.part[blockIdx.x] = p;
-    }
-    unsigned *count = mem.count + (blockIdx.x % kCellCopies) * ncells;
+    const pv_f4 p = stat_block(st, s_tmp);      // its barrier also ends the counting
+    if (tid == 0) mem.part[blockIdx.x] = p;
+    unsigned *count = mem.count + (blockIdx.x % kCbCopies) * ncells;
     for (int b = tid; b < ncells; b += kBlock) {
         const unsigned v = s_hist[b];
         if (v) atomicAdd(&count[b], v);
     }
 }
-
-// The codebook's statistics from the blocks' parts, in the form the other kernels keep them:
-// [0] bits of max|C|, [1] ~bits of min norm^2, [3] bad flag, [5] bits of max norm^2.  Called by
-// all threads of a block; `out`: 8 unsigneds of LDS.
-__device__ __forceinline__ void cells_meta(const cell_mem &mem, int nparts, unsigned *out)
-{
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        pv_f4 p = {0.0f, __builtin_huge_valf(), 0.0f, 0.0f};
-        if (lane < nparts) p = mem.part[lane];      // nparts <= kCellBlocksMax = 64
-        p.x = wave_max_f(p.x);
-        p.y = wave_min_f(p.y);
-        p.z = wave_max_f(p.z);
-        const bool bad = __any(p.w != 0.0f) || !(p.z < 3.0e38f);
-        if (lane == 0) {
-            out[0] = __float_as_uint(p.x);
-            out[1] = p.y >= 0.0f && p.y < 3.0e38f ? ~__float_as_uint(p.y) : 0u;
-            out[2] = 0u;
-            out[3] = bad ? 1u : 0u;
-            out[4] = 0u;
-            out[5] = __float_as_uint(p.z);
-            out[6] = out[7] = 0u;
-        }
-    }
-    __syncthreads();
-}
-static_assert(kCellBlocksMax <= 64, "one wave reduces the parts");
 
 // Blocks [0, cb_blocks): the chunk of codewords that the same block counted is placed: the
 // cell's first super-unit, then the codewords of the copies before this one, then those that
@@ -347,7 +267,7 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
                                                        group_args ga)
 {
     __shared__ unsigned s_meta[8];
-    cells_meta(mem, csize / kCellChunk, s_meta);
+    meta_of_parts(mem.part, csize / kCbChunk, s_meta);
     bool ok;
     const float P = scale_from_maxabs(s_meta[0], &ok);
     const int tid = threadIdx.x;
@@ -356,17 +276,17 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
         if (j < ga.k_pad) prep_group<8, true>(ga, j, P, ok && s_meta[3] == 0u && s_meta[1] != 0u, s_meta);
         return;
     }
-    constexpr int kPadCells = kCellChunk >> kCellLog;
+    constexpr int kPadCells = kCbChunk >> kCellLog;
     __shared__ unsigned s_cnt[kCellsMax], s_base[kCellsMax], s_w[kBlock / 64], s_pad[kPadCells][2];
     const int ncells = 1 << cbits, lane = tid & 63, wave = tid >> 6;
-    const int copy = blockIdx.x % kCellCopies;
+    const int copy = blockIdx.x % kCbCopies;
     const bool dense = mem.theta[15] != 0.0f;   // cells follow one another without padding
     int cell[4];
     unsigned rank[4];
     pv_f4 own[4][2];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int c = blockIdx.x * kCellChunk + r * kBlock + tid;
+        const int c = blockIdx.x * kCbChunk + r * kBlock + tid;
         cell[r] = mem.cell_of[c];
         own[r][0] = reinterpret_cast<const pv_f4 *>(cb)[c * 2];
         own[r][1] = reinterpret_cast<const pv_f4 *>(cb)[c * 2 + 1];
@@ -378,13 +298,13 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
     // two cells a thread: their codewords, in all copies and in the copies before this one
     unsigned all[2] = {0u, 0u}, before[2] = {0u, 0u};
     {
-        unsigned v[kCellCopies][2];
+        unsigned v[kCbCopies][2];
 #pragma unroll
-        for (int q = 0; q < kCellCopies; ++q)
+        for (int q = 0; q < kCbCopies; ++q)
 #pragma unroll
             for (int e = 0; e < 2; ++e) v[q][e] = 2 * tid + e < ncells ? mem.count[q * ncells + 2 * tid + e] : 0u;
 #pragma unroll
-        for (int q = 0; q < kCellCopies; ++q)
+        for (int q = 0; q < kCbCopies; ++q)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 before[e] += q < copy ? v[q][e] : 0u;
@@ -434,7 +354,7 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
         su_bounds[tid] = split_begin(tid, csize / (kCellPos * kResidues), nsplit) * kResidues;
     if (blockIdx.x == 0 && tid < 8) meta[tid] = s_meta[tid];
     __syncthreads();
-    // cb_blocks = csize / kCellChunk blocks share csize / 2^kCellLog cells: kCellChunk / 2^kCellLog each
+    // cb_blocks = csize / kCbChunk blocks share csize / 2^kCellLog cells: kCbChunk / 2^kCellLog each
     for (int i = tid; i < kPadCells * kCellPos; i += kBlock) {
         const unsigned pos = s_pad[i / kCellPos][0] + i % kCellPos;
         if (pos < s_pad[i / kCellPos][1]) {
@@ -452,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
     float d2 = 0.0f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int c = blockIdx.x * kCellChunk + r * kBlock + tid;
+        const int c = blockIdx.x * kCbChunk + r * kBlock + tid;
         const int pos = (int)(s_base[cell[r]] + rank[r]);
         h8 chunk[2];
         float n2 = 0.0f, d2c = 0.0f;
@@ -522,7 +442,7 @@ __global__ __launch_bounds__(kCellWavesMax * 64, kCellWavesMax / 4) void k_cells
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ncells = 1 << cbits, runs = ncells / 16, waves = blockDim.x >> 6, groups = blockDim.x;
     // the counts are done with: zero for the next call; the largest rounding error of the codebook
-    for (int i = blockIdx.x * groups + tid; i < kCellCopies * ncells; i += gridDim.x * groups) mem.count[i] = 0u;
+    for (int i = blockIdx.x * groups + tid; i < kCbCopies * ncells; i += gridDim.x * groups) mem.count[i] = 0u;
     if (blockIdx.x == 0 && tid < 64) {
         const float d = wave_max_f(tid < cb_parts ? mem.dpart[tid] : 0.0f);
         if (tid == 0) meta[2] = __float_as_uint(d);

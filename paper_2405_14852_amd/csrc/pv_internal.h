@@ -29,7 +29,6 @@ struct pv_ctx {
     hipStream_t stream = nullptr;
     char err[256] = {0};
     int search_mode = 0;
-    int meta_phase = 0;        // which of the two statistics slots of cb_meta the next filter call uses
     int rr_blocks_last = 0;    // blocks of the last call's re-rank kernel (their counters are summed on request)
     bool timing = false;
     pv_timer timers[PV_K_COUNT];
@@ -43,7 +42,7 @@ struct pv_ctx {
     pv_buffer sel_state;    // u32 [8]            digits found, ranks left
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
     pv_buffer cb_f16;       // prepared codebook operand for the matrix-core filter
-    pv_buffer cb_meta;      // u32 [2][8]         two slots of codebook statistics (scale, norms, rounding bound)
+    pv_buffer cb_meta;      // statistics of the codebook (scale, norms, rounding bound), counters of its norm ordering
     pv_buffer cells;        // cells of the codebook (pv_cells.h): statistics, thresholds, counts
     pv_buffer x_f16;        // prepared target operand [k_pad / 32][2][32][8] halves
     pv_buffer x_meta;       // f32 [k_pad][4]     per-group bounds and flags

@@ -78,10 +78,13 @@ constexpr int kNoKey = (int)0x80000000;             // "no key": below every key
 constexpr float kHalfMinNormal = 6.103515625e-05f;  // 2^-14
 constexpr float kGamma = 7.62939453125e-06f;        // 2^-17: fp32 accumulation bound per unit of sum|terms|
 constexpr float kNormMargin = 0.04f;                // >= max_c | ||c_hi|| - ||P c|| | (half an fp16 ulp below 32, 16 dims)
-constexpr int kNormBins = 65536;                    // buckets of the norm ordering (g = 16)
+constexpr int kNormFine = 5 * 2048;                 // buckets of the norm ordering (g = 16): five octaves finely,
+constexpr int kNormCoarse = 1024;                   // the octaves below and those above coarsely
+constexpr int kNormBins = kNormFine + 2 * kNormCoarse;
+constexpr int kCbCopies = 8;                        // copies of the bucket counters, one per die
 
 // cb_meta layout (unsigned[8]): [0] bits of max|C|, [1] ~bits of min_c ||c||^2 (unscaled),
-// [2] bits of max ||P c - c_hi||^2, [3] bad-codebook flag, [4] blocks of the re-rank kernel done,
+// [2] bits of max ||P c - c_hi||^2 (written by the scoring kernel), [3] bad-codebook flag,
 // [5] bits of max_c ||c||^2 (unscaled)
 // x_meta layout (float[4] per selected group): SHIFT as the kernel adds it, ||x_hi||^2, E1,
 // dx (negative: the filter is skipped for this group)
@@ -109,16 +112,6 @@ __device__ __forceinline__ void split3(float v, _Float16 *p)
     p[1] = to_half_flush(r);
     r = r - (float)p[1];
     p[2] = to_half_flush(r);
-}
-
-// Bucket of a squared norm of scaled fp16 codeword entries (at most 16 * 32^2): the 32 octaves
-// below 2^15, 2048 buckets each; ascending in the norm.
-__device__ __forceinline__ int norm_bucket(float n2)
-{
-    const int e = (int)(__float_as_uint(n2) >> 12);
-    const int top = (int)(0x47000000u >> 12);      // bits of 32768.0f
-    const int key = e - (top - (kNormBins - 1));
-    return key < 0 ? 0 : (key > kNormBins - 1 ? kNormBins - 1 : key);
 }
 
 // Residue cycles of the table owned by codeword split `split` of `nsplit`: cycles are dealt to
@@ -159,138 +152,219 @@ __device__ __forceinline__ void round_codeword(const float *__restrict__ cw, flo
     }
 }
 
-// Codebook statistics, one thread per codeword: largest |entry| (fixes the common scale P),
-// smallest squared norm, non-finite entries.  Block 0 also clears the per-call counters, and
-// the grid clears the tables of the norm ordering (g = 16), which only later launches touch.
-// The statistics live in one of two slots, alternating from call to call: this kernel clears
-// the slot of the next call (nothing of this call reads it), so no kernel has to run last.
-template <int G>
-__global__ __launch_bounds__(kBlock) void k_cb_stats(const float *__restrict__ cb, int csize,
-                                                     unsigned *__restrict__ meta,
-                                                     unsigned *__restrict__ meta_next,
-                                                     unsigned long long *__restrict__ stats,
-                                                     unsigned *__restrict__ fb_count,
-                                                     unsigned long long *__restrict__ num_changed,
-                                                     unsigned *__restrict__ hist,
-                                                     unsigned *__restrict__ nmin_bits, int nsu_alloc,
-                                                     unsigned long long *__restrict__ change_slots,
-                                                     int nslots)
+// ---------------------------------------------------------------- the codebook's statistics
+//
+// Codebooks beyond kOneBlock codewords: k_cb_stats, one block per kCbChunk codewords, leaves its
+// part as a plain store, and whoever needs the whole adds up at most 64 parts (atomics of all
+// blocks end up on one cache line, one after the other: 3 us).  Up to kOneBlock codewords there is
+// no such launch: every block of k_prep takes the statistics of the whole codebook itself.
+constexpr int kCbPer = 4;                     // codewords a thread of the codebook part
+constexpr int kCbChunk = kBlock * kCbPer;     // codewords a block
+constexpr int kCbParts = 65536 / kCbChunk;    // blocks of the largest codebook
+constexpr int kOneBlock = kCbChunk;
+static_assert(kCbParts <= 64, "one wave reduces the parts");
+
+// Device scratch of the preparation.
+struct cb_mem {
+    pv_f4 *part;          // [kCbParts] {max |c|, min norm^2, max norm^2, bad}
+    float *dpart;         // [kCbParts] largest rounding error ||P c - c_hi||^2 of a block's codewords
+    float *anchor;        // [1] g = 16: norm that the buckets are counted from
+    unsigned *count;      // [copies][kNormBins / 2] g = 16: codewords per bucket (two in a word: a copy
+                          // has at most 65536 / kCbCopies), zero between calls
+    unsigned *cursor;     // [copies][kNormBins / 2] g = 16: codewords of a bucket placed so far
+};
+constexpr size_t kCbWords = kCbParts * 4 + kCbParts + 16 + (size_t)kCbCopies * kNormBins;
+
+__device__ __forceinline__ float wave_min_f(float v)
 {
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < nslots; i += gridDim.x * kBlock) change_slots[i] = 0ull;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < 8) stats[threadIdx.x] = 0ull;
-        if (threadIdx.x < 8) meta_next[threadIdx.x] = 0u;   // the statistics slot of the next call
-        if (threadIdx.x < 4) fb_count[threadIdx.x] = 0u;
-        if (threadIdx.x == 0 && num_changed) *num_changed = 0ull;
-    }
-    const int tid = blockIdx.x * kBlock + threadIdx.x, nthreads = gridDim.x * kBlock;
-    if (hist) {
-        for (int i = tid; i < kNormBins; i += nthreads) hist[i] = 0u;
-        for (int i = tid; i < nsu_alloc; i += nthreads) nmin_bits[i] = 0x7F800000u;   // +inf
-    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off));
+    return v;
+}
+__device__ __forceinline__ float wave_max_f(float v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+    return v;
+}
+
+struct cb_stat {
     float m = 0.0f, nmin = __builtin_huge_valf(), nmax = 0.0f;
     bool bad = false;
-    for (int c = tid; c < csize; c += nthreads) {
-        const pv_f4 *src = reinterpret_cast<const pv_f4 *>(cb + (int64_t)c * G);
-        float n2 = 0.0f;
+};
+
+// statistics of one codeword
+template <int G>
+__device__ __forceinline__ void stat_add(cb_stat &s, const pv_f4 (&cw)[G / 4])
+{
+    float n2 = 0.0f;
 #pragma unroll
-        for (int v4 = 0; v4 < G / 4; ++v4) {
-            pv_f4 v = src[v4];
+    for (int v4 = 0; v4 < G / 4; ++v4)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float a = fabsf(v[e]);
-                bad |= !(a <= 3.0e38f);
-                m = fmaxf(m, a);
-                n2 = fmaf(v[e], v[e], n2);
-            }
+        for (int e = 0; e < 4; ++e) {
+            const float a = fabsf(cw[v4][e]);
+            s.bad |= !(a <= 3.0e38f);
+            s.m = fmaxf(s.m, a);
+            n2 = fmaf(cw[v4][e], cw[v4][e], n2);
         }
-        nmin = fminf(nmin, n2);
-        nmax = fmaxf(nmax, n2);
-    }
-    __shared__ float s_m[kBlock / 64], s_n[kBlock / 64], s_x[kBlock / 64];
-    for (int off = 32; off > 0; off >>= 1) {
-        m = fmaxf(m, __shfl_down(m, off));
-        nmin = fminf(nmin, __shfl_down(nmin, off));
-        nmax = fmaxf(nmax, __shfl_down(nmax, off));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        s_m[threadIdx.x >> 6] = m;
-        s_n[threadIdx.x >> 6] = nmin;
-        s_x[threadIdx.x >> 6] = nmax;
-    }
+    s.nmin = fminf(s.nmin, n2);
+    s.nmax = fmaxf(s.nmax, n2);
+}
+
+// a block's statistics, in thread 0; `tmp`: one pv_f4 a wave of LDS
+__device__ __forceinline__ pv_f4 stat_block(const cb_stat &s, pv_f4 *tmp)
+{
+    pv_f4 p = {wave_max_f(s.m), wave_min_f(s.nmin), wave_max_f(s.nmax), __any(s.bad) ? 1.0f : 0.0f};
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = p;
     __syncthreads();
-    if (threadIdx.x == 0) {   // one atomic per block: same-address atomics serialise
+    if (threadIdx.x == 0)
 #pragma unroll
         for (int w = 1; w < kBlock / 64; ++w) {
-            m = fmaxf(m, s_m[w]);
-            nmin = fminf(nmin, s_n[w]);
-            nmax = fmaxf(nmax, s_x[w]);
+            p.x = fmaxf(p.x, tmp[w].x);
+            p.y = fminf(p.y, tmp[w].y);
+            p.z = fmaxf(p.z, tmp[w].z);
+            p.w = fmaxf(p.w, tmp[w].w);
         }
-        atomicMax(&meta[0], __float_as_uint(m));
-        if (nmin >= 0.0f && nmin < 3.0e38f) atomicMax(&meta[1], ~__float_as_uint(nmin));
-        if (nmax >= 0.0f && nmax < 3.0e38f) atomicMax(&meta[5], __float_as_uint(nmax));
-        else bad = true;
-    }
-    if (bad) atomicMax(&meta[3], 1u);
+    return p;
 }
 
-// Norm ordering, step 1 (g = 16): bucket of every codeword's ||c_hi||^2 and the bucket counts.
+// statistics -> the words that the other kernels read (see cb_meta)
+__device__ __forceinline__ void meta_words(const pv_f4 &p, unsigned *out)
+{
+    out[0] = __float_as_uint(p.x);
+    out[1] = p.y >= 0.0f && p.y < 3.0e38f ? ~__float_as_uint(p.y) : 0u;
+    out[2] = 0u;
+    out[3] = p.w != 0.0f || !(p.z < 3.0e38f) ? 1u : 0u;
+    out[4] = 0u;
+    out[5] = __float_as_uint(p.z);
+    out[6] = out[7] = 0u;
+}
+
+// ... of all blocks' parts, to `out` (8 unsigneds of LDS); called by all threads of a block
+__device__ __forceinline__ void meta_of_parts(const pv_f4 *part, int nparts, unsigned *out)
+{
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        pv_f4 p = {0.0f, __builtin_huge_valf(), 0.0f, 0.0f};
+        if (lane < nparts) p = part[lane];
+        p.x = wave_max_f(p.x);
+        p.y = wave_min_f(p.y);
+        p.z = wave_max_f(p.z);
+        p.w = wave_max_f(p.w);
+        if (lane == 0) meta_words(p, out);
+    }
+    __syncthreads();
+}
+
+// What a call counts in starts at zero: done by the call's first kernel.
+struct clear_args {
+    unsigned long long *stats, *num_changed, *change_slots;
+    unsigned *fb_count;
+    int nslots;
+};
+__device__ __forceinline__ void clear_counters(const clear_args &a, int block, int nblocks)
+{
+    for (int i = block * kBlock + threadIdx.x; i < a.nslots; i += nblocks * kBlock) a.change_slots[i] = 0ull;
+    if (block == 0) {
+        if (threadIdx.x < 8) a.stats[threadIdx.x] = 0ull;
+        if (threadIdx.x < 4) a.fb_count[threadIdx.x] = 0u;
+        if (threadIdx.x == 0 && a.num_changed) *a.num_changed = 0ull;
+    }
+}
+
+// Norm ordering (g = 16): buckets of ||c_hi||^2.  A key's bound lies off by up to the width of its
+// bucket, and that decides how many groups the re-rank has to search again: 2048 buckets an octave
+// where most norms lie (four octaves below `anchor`, the largest norm of a sample, and one above), 32
+// an octave beyond.  P is a power of two, so ||c_hi|| / P is known before P is: the entries rounded to
+// fp16's 11 bits (those that P c leaves below fp16's normal range count as zero in c_hi, see
+// norm_bucket_floor).
+constexpr int kNormShift = 12;
 template <int G>
-__global__ __launch_bounds__(kBlock) void k_cb_bucket(const float *__restrict__ cb, int csize,
-                                                      const unsigned *__restrict__ meta,
-                                                      uint16_t *__restrict__ bucket,
-                                                      unsigned *__restrict__ hist)
+__device__ __forceinline__ float norm_rounded(const pv_f4 (&cw)[G / 4])
 {
-    bool ok;
-    const float P = scale_from_maxabs(meta[0], &ok);
-    const int c = blockIdx.x * kBlock + threadIdx.x;
-    if (c >= csize) return;
-    float hf[G], n2, d2;
-    round_codeword<G>(cb + (int64_t)c * G, P, ok, hf, n2, d2);
-    const int b = norm_bucket(n2);
-    bucket[c] = (uint16_t)b;
-    atomicAdd(&hist[b], 1u);
+    float n2 = 0.0f;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        unsigned u = __float_as_uint(cw[i >> 2][i & 3]);
+        u = (u + 0xFFFu + ((u >> 13) & 1u)) & ~0x1FFFu;
+        const float v = __uint_as_float(u);
+        n2 = fmaf(v, v, n2);
+    }
+    return n2;
 }
-
-// Step 2: exclusive prefix sum of the bucket counts.  Block b owns 1024 buckets; it adds up
-// everything before them itself (coalesced reads of a table that sits in L2: cheaper than any
-// exchange between blocks) and scans its own.
-constexpr int kScanBlock = 1024;
-__global__ __launch_bounds__(kScanBlock) void k_cb_scan(const unsigned *__restrict__ hist,
-                                                        unsigned *__restrict__ offsets)
+__device__ __forceinline__ int norm_fine(float v) { return (int)((__float_as_uint(v) & 0x7FFFFFFFu) >> kNormShift); }
+__device__ __forceinline__ int norm_bucket(float n2, float anchor)
 {
-    __shared__ unsigned s_w[kScanBlock / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int first = blockIdx.x * kScanBlock;
-    unsigned before = 0;
-    for (int i0 = 0; i0 < first; i0 += 8 * kScanBlock) {   // eight loads in flight per thread
-        unsigned v8[8];
+    const int d = norm_fine(n2) - norm_fine(anchor) + 4 * 2048;
+    const int key = kNormCoarse + (d < 0 ? d >> 6 : d < kNormFine ? d : kNormFine + ((d - kNormFine) >> 6));
+    return key < 0 ? 0 : (key > kNormBins - 1 ? kNormBins - 1 : key);
+}
+// A bound from below for the computed ||c_hi||^2 of the bucket's codewords: its edge, less the
+// rounding of two fp32 sums of 16 terms (2 * 16 * 2^-24 of the sum) and 16 flushed entries (2^-28 each).
+__device__ __forceinline__ float norm_bucket_floor(int bucket, float anchor, float P)
+{
+    const int key = bucket - kNormCoarse;
+    const int d = key < 0 ? key * 64 : key < kNormFine ? key : kNormFine + (key - kNormFine) * 64;
+    const int e = d + norm_fine(anchor) - 4 * 2048;
+    const float edge = __uint_as_float(bucket == 0 || e <= 0 ? 0u : (unsigned)e << kNormShift);
+    // (below 1e-30 the squares of the entries have lost bits to the bottom of fp32's range)
+    return edge < 1.0e-30f ? 0.0f : fmaxf(edge * P * P * 0.999997f - 6.0e-8f, 0.0f);
+}
+// two 16-bit counters a word
+__device__ __forceinline__ unsigned half_of(unsigned w, int e) { return e & 1 ? w >> 16 : w & 0xFFFFu; }
+__device__ __forceinline__ unsigned half_one(int e) { return 1u << (16 * (e & 1)); }
+
+// Codebook statistics, one block per kCbChunk codewords; g = 16 also counts the norm buckets (the
+// anchor from a sample that every block takes alike; block b counts into copy b % kCbCopies:
+// workgroups are dealt to the dies round robin, so a copy's atomics stay in one L2).  Latency: 65536
+// codewords, g = 16, 7.2 us; statistics, buckets and their scan as three kernels took 23 us.
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_cb_stats(const float *__restrict__ cb, int csize, cb_mem mem,
+                                                     uint16_t *__restrict__ bucket, clear_args ca)
+{
+    __shared__ pv_f4 s_tmp[kBlock / 64];
+    __shared__ float s_n[kBlock / 64];
+    __shared__ unsigned s_hist[G == 16 ? kNormBins / 2 : 1];     // as in mem.count
+    const int tid = threadIdx.x;
+    const pv_f4 *cb4 = reinterpret_cast<const pv_f4 *>(cb);
+    pv_f4 own[kCbPer][G / 4], smp[G / 4];
+    if (G == 16)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = i0 + u * kScanBlock + threadIdx.x;
-            v8[u] = i < first ? hist[i] : 0u;
+        for (int v = 0; v < G / 4; ++v) smp[v] = cb4[(int64_t)tid * (csize / kBlock) * (G / 4) + v];
+#pragma unroll
+    for (int r = 0; r < kCbPer; ++r)      // csize is a multiple of kCbChunk here
+#pragma unroll
+        for (int v = 0; v < G / 4; ++v) own[r][v] = cb4[(int64_t)(blockIdx.x * kCbChunk + r * kBlock + tid) * (G / 4) + v];
+    clear_counters(ca, blockIdx.x, gridDim.x);
+    float anchor = 0.0f;
+    if (G == 16) {
+        for (int i = blockIdx.x * kBlock + tid; i < kCbCopies * (kNormBins / 2); i += gridDim.x * kBlock) mem.cursor[i] = 0u;
+        for (int b = tid; b < kNormBins / 2; b += kBlock) s_hist[b] = 0u;
+        const float n = wave_max_f(norm_rounded<G>(smp));
+        if ((tid & 63) == 0) s_n[tid >> 6] = n;
+        __syncthreads();
+        anchor = fmaxf(fmaxf(s_n[0], s_n[1]), fmaxf(s_n[2], s_n[3]));
+        if (blockIdx.x == 0 && tid == 0) *mem.anchor = anchor;
+    }
+    cb_stat s;
+#pragma unroll
+    for (int r = 0; r < kCbPer; ++r) {
+        stat_add<G>(s, own[r]);
+        if constexpr (G == 16) {
+            const int b = norm_bucket(norm_rounded<G>(own[r]), anchor);
+            bucket[blockIdx.x * kCbChunk + r * kBlock + tid] = (uint16_t)b;
+            atomicAdd(&s_hist[b >> 1], half_one(b));
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) before += v8[u];
     }
-    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
-    if (lane == 0) s_w[wave] = before;
-    __syncthreads();
-    unsigned base = 0;
-#pragma unroll
-    for (int w = 0; w < kScanBlock / 64; ++w) base += s_w[w];
-    __syncthreads();
-    const unsigned v = hist[first + threadIdx.x];
-    unsigned inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        unsigned u = __shfl_up(inc, off);
-        if (lane >= off) inc += u;
+    const pv_f4 p = stat_block(s, s_tmp);       // its barrier also ends the counting
+    if (tid == 0) mem.part[blockIdx.x] = p;
+    if (G == 16) {
+        unsigned *count = mem.count + (blockIdx.x % kCbCopies) * (kNormBins / 2);
+        for (int b = tid; b < kNormBins / 2; b += kBlock) {
+            const unsigned v = s_hist[b];
+            if (v) atomicAdd(&count[b], v);
+        }
     }
-    if (lane == 63) s_w[wave] = inc;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) base += s_w[w];
-    offsets[first + threadIdx.x] = base + inc - v;
 }
 
 // Table position -> tile and row of the operand (see k_prep).
@@ -441,15 +515,16 @@ __device__ __forceinline__ void prep_group(const group_args &ga, int j, float P,
 
 // Operand preparation, one launch for both sides.
 //
-// Blocks [0, cb_blocks): one thread per codeword position of the padded table.  A codeword is
-// placed at position pos (g = 8: its own index; g = 16: the next free rank of its norm bucket,
-// ranks ascending in ||c_hi||^2 up to the bucket width, and the residue cycles of the ranking
+// Blocks [0, cb_blocks): kCbPer codeword positions of the padded table a thread.  A codeword is
+// placed at position pos (g = 8: its own index; g = 16: the next free rank of its norm bucket -
+// what the buckets before hold, what the copies of the counters before this block's hold, what
+// blocks of the same copy placed already - and the residue cycles of the ranking
 // dealt round robin to the codeword splits), perm[pos] names it.  The 32 U
 // positions of super-unit su are split in two runs of 16 U, one per half wave hw, each run in
 // U pieces of 16, one per tile: position pos = ((su * 2 + hw) * U + uu) * 16 + q sits in tile
 // su * U + uu at row 8*(q/4) + 4*hw + q%4, so that accumulator q of half wave hw is that
 // position, and the 16 U positions behind one key of a lane are consecutive (for g = 16: in
-// norm order, their smallest norm is nmin[su * 2 + hw]).  Operand A of tile t, k-half h, row r
+// norm order, none of their norms is below nmin[su * 2 + hw]).  Operand A of tile t, k-half h, row r
 // is the 16-byte chunk A[(t * 2 + h) * 32 + r]:
 //   g = 8:  k-half 0 = 2 c_hi, k-half 1 = { three pieces of ||c_hi||^2, 1, 1, 1, 0, 0 }
 //   g = 16: k-half 0 = 2 c_hi[0..8), k-half 1 = 2 c_hi[8..16)
@@ -463,92 +538,201 @@ __device__ __forceinline__ void prep_group(const group_args &ga, int j, float P,
 // and x_stage[j] = { the g target values, the row scale, the current code, the group id } is
 // what the re-rank kernel needs of the group, in one place (its loads then depend on nothing
 // but the list position).
-#ifndef PV_CB_PER
-#define PV_CB_PER 4
-#endif
-constexpr int kCbPer = PV_CB_PER;   // codeword positions a thread of the codebook part
-template <int G>
+//
+// The codebook's blocks are a chain of latencies (parts, counters, codewords, stores) that runs
+// beside the groups' blocks, so what can go out early does: the claim of a place in a bucket needs
+// only the bucket.  Code runs once per block, cold: the loop over the counters stays rolled, and
+// the key bounds come from the codeword that got a key's first rank (written out per bucket they
+// cost 5 us of instruction fetch).  65536 codewords, g = 16: codebook alone 16 us, 183k groups alone
+// 16 us, both 21 us.
+template <int G, bool ONE>
 __global__ __launch_bounds__(kBlock) void k_prep(const float *__restrict__ cb, int csize, int cpad,
-                                                 int cb_blocks, unsigned *__restrict__ meta,
+                                                 int cb_blocks, unsigned *__restrict__ meta, cb_mem mem,
                                                  h8 *__restrict__ A, uint16_t *__restrict__ perm,
                                                  const uint16_t *__restrict__ bucket,
-                                                 unsigned *__restrict__ bucket_next,
-                                                 unsigned *__restrict__ nmin_bits,
-                                                 float *__restrict__ cnorm,
-                                                 group_args ga, int ncyc, int nsplit)
+                                                 float *__restrict__ nmin, float *__restrict__ cnorm,
+                                                 group_args ga, int ncyc, int nsplit, clear_args ca)
 {
-    bool ok;
-    const float P = scale_from_maxabs(meta[0], &ok);
-    h8 chunk[2];
+    __shared__ unsigned s_meta[8];
+    __shared__ pv_f4 s_tmp[kBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const pv_f4 *cb4 = reinterpret_cast<const pv_f4 *>(cb);
+    if (ONE) {           // no k_cb_stats before: this block looks at the whole codebook
+        cb_stat s;
+        pv_f4 cw[kCbPer][G / 4];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+        for (int r = 0; r < kCbPer; ++r)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) chunk[u][e] = (_Float16)0.0f;
-
-    if ((int)blockIdx.x < cb_blocks) {
-        float d2 = 0.0f;
-        // kCbPer codeword positions a thread: a quarter of the blocks, and of the atomics on the
-        // one address that takes the largest rounding error
-#pragma unroll 1
-        for (int rep = 0; rep < kCbPer; ++rep) {
-        const int c = (blockIdx.x * kCbPer + rep) * kBlock + threadIdx.x;
-        if (rep > 0) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) chunk[u][e] = (_Float16)0.0f;
-        }
-        if (c < cpad) {
-            int pos = c;
-            if (c < csize) {
-                float hf[G], n2, d2c;
-                round_codeword<G>(cb + (int64_t)c * G, P, ok, hf, n2, d2c);
-                d2 = fmaxf(d2, d2c);
-#pragma unroll
-                for (int i = 0; i < G; ++i) chunk[i >> 3][i & 7] = (_Float16)(2.0f * hf[i]);
-                if (G == 8) {
-                    _Float16 pieces[3];
-                    split3(n2, pieces);
-                    chunk[1][0] = pieces[0];
-                    chunk[1][1] = pieces[1];
-                    chunk[1][2] = pieces[2];
-                    chunk[1][3] = (_Float16)1.0f;
-                    chunk[1][4] = (_Float16)1.0f;
-                    chunk[1][5] = (_Float16)1.0f;
-                } else {
-                    // rank in norm order -> place in memory: cycle rc of the ranking is cycle
-                    // rc / nsplit of split rc % nsplit
-                    const int rank = (int)atomicAdd(&bucket_next[bucket[c]], 1u);
-                    constexpr int per_cycle = 32 * kU * kResidues;
-                    const int rc = rank / per_cycle;
-                    pos = (split_begin(rc % nsplit, ncyc, nsplit) + rc / nsplit) * per_cycle + rank % per_cycle;
-                    atomicMin(&nmin_bits[pos / (16 * kU)], __float_as_uint(n2));
-                    cnorm[pos] = n2;           // for the re-rank kernel's cheap distances
-                }
-                perm[pos] = (uint16_t)c;
-            } else if (G == 16) {
-                atomicMin(&nmin_bits[pos / (16 * kU)], 0u);   // padding rows count as norm 0
-                cnorm[pos] = 0.0f;
+            for (int v = 0; v < G / 4; ++v) {
+                const int c = r * kBlock + tid;
+                cw[r][v] = cb4[(int64_t)(c < csize ? c : csize - 1) * (G / 4) + v];
             }
-            const operand_row o = operand_row_of(pos);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) A[((int64_t)o.tile * 2 + u) * 32 + o.row] = chunk[u];
-        }
-        }
-        __shared__ float s_d[kBlock / 64];
-        for (int off = 32; off > 0; off >>= 1) d2 = fmaxf(d2, __shfl_down(d2, off));
-        if ((threadIdx.x & 63) == 0) s_d[threadIdx.x >> 6] = d2;
+        for (int r = 0; r < kCbPer; ++r) stat_add<G>(s, cw[r]);
+        const pv_f4 p = stat_block(s, s_tmp);
+        if (tid == 0) meta_words(p, s_meta);
         __syncthreads();
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int w = 1; w < kBlock / 64; ++w) d2 = fmaxf(d2, s_d[w]);
-            atomicMax(&meta[2], __float_as_uint(d2));
-        }
+        clear_counters(ca, blockIdx.x, gridDim.x);
+    } else {
+        meta_of_parts(mem.part, csize / kCbChunk, s_meta);
+    }
+    bool ok;
+    const float P = scale_from_maxabs(s_meta[0], &ok);
+    if (blockIdx.x == 0 && tid < 8) meta[tid] = s_meta[tid];
+    if ((int)blockIdx.x >= cb_blocks) {
+        const int j = ((int)blockIdx.x - cb_blocks) * kBlock + tid;
+        if (j < ga.k_pad) prep_group<G, false>(ga, j, P, ok && s_meta[3] == 0u && s_meta[1] != 0u, s_meta);
         return;
     }
 
-    const int j = ((int)blockIdx.x - cb_blocks) * kBlock + threadIdx.x;
-    if (j < ga.k_pad) prep_group<G, false>(ga, j, P, ok && meta[3] == 0u && meta[1] != 0u, meta);
+    // ranks of the codewords in norm order (g = 16)
+    constexpr int kRun = 16, kRuns = kNormBins / (kBlock * kRun);      // buckets a thread looks at together
+    __shared__ unsigned s_base[G == 16 ? kNormBins / 2 : 1], s_w[2][kBlock / 64];
+    int bkt[kCbPer];
+    unsigned placed[kCbPer];
+    float anchor = 0.0f;
+    const int copy = blockIdx.x % kCbCopies;
+    auto place_of = [&](int rank) {       // cycle rc of the ranking is cycle rc / nsplit of split rc % nsplit
+        constexpr int per_cycle = 32 * kU * kResidues;
+        const int rc = rank / per_cycle;
+        return (split_begin(rc % nsplit, ncyc, nsplit) + rc / nsplit) * per_cycle + rank % per_cycle;
+    };
+    if constexpr (G == 16) {
+        anchor = ONE ? __uint_as_float(s_meta[5]) : *mem.anchor;
+        if constexpr (ONE) {
+            for (int b = tid; b < kNormBins / 2; b += kBlock) s_base[b] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kCbPer; ++r) {
+                const int c = r * kBlock + tid;
+                if (c < csize) {
+                    pv_f4 cw[G / 4];
+#pragma unroll
+                    for (int v = 0; v < G / 4; ++v) cw[v] = cb4[(int64_t)c * (G / 4) + v];
+                    bkt[r] = norm_bucket(norm_rounded<G>(cw), anchor);
+                    atomicAdd(&s_base[bkt[r] >> 1], half_one(bkt[r]));
+                }
+            }
+            __syncthreads();
+        } else {
+#pragma unroll
+            for (int r = 0; r < kCbPer; ++r) bkt[r] = bucket[blockIdx.x * kCbChunk + r * kBlock + tid];
+#pragma unroll
+            for (int r = 0; r < kCbPer; ++r)
+                placed[r] = atomicAdd(&mem.cursor[copy * (kNormBins / 2) + (bkt[r] >> 1)], half_one(bkt[r]));
+        }
+        unsigned first = 0;
+#pragma unroll 1
+        for (int run = 0; run < kRuns; ++run) {
+            // the buckets' codewords in copies 0 - 3, in the others, in those before this block's
+            const int w0 = (run * kBlock + tid) * (kRun / 2);
+            unsigned lo[kRun / 2], hi[kRun / 2], before[kRun / 2], sum = 0;
+#pragma unroll
+            for (int e = 0; e < kRun / 2; ++e) {
+                lo[e] = ONE ? s_base[w0 + e] : 0u;
+                hi[e] = before[e] = 0u;
+            }
+            if (!ONE) {
+#pragma unroll
+                for (int q = 0; q < kCbCopies; ++q) {
+                    const uint4 *src = reinterpret_cast<const uint4 *>(mem.count + q * (kNormBins / 2) + w0);
+#pragma unroll
+                    for (int v = 0; v < kRun / 8; ++v) {
+                        const uint4 x = src[v];
+                        const unsigned n4[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            (q < kCbCopies / 2 ? lo : hi)[v * 4 + e] += n4[e];
+                            before[v * 4 + e] += q < copy ? n4[e] : 0u;
+                        }
+                    }
+                }
+            }
+            auto all = [&](int e) { return half_of(lo[e >> 1], e) + half_of(hi[e >> 1], e); };
+#pragma unroll
+            for (int e = 0; e < kRun; ++e) sum += all(e);
+            unsigned inc = sum;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const unsigned u = __shfl_up(inc, off);
+                if (lane >= off) inc += u;
+            }
+            if (lane == 63) s_w[run & 1][wave] = inc;
+            __syncthreads();
+            unsigned rank = first + inc - sum;
+#pragma unroll
+            for (int w = 0; w < kBlock / 64; ++w) {
+                const unsigned n = s_w[run & 1][w];
+                rank += w < wave ? n : 0u;
+                first += n;
+            }
+#pragma unroll
+            for (int e = 0; e < kRun; ++e) {
+                const unsigned at = rank + half_of(before[e >> 1], e);
+                // (a bucket behind the last codeword may be at 65536, which no one asks for)
+                if (e & 1) s_base[w0 + (e >> 1)] |= at << 16;
+                else s_base[w0 + (e >> 1)] = at & 0xFFFFu;
+                rank += all(e);
+            }
+        }
+        // keys with nothing but padding behind them
+        if (blockIdx.x == 0)
+            for (int h = (csize + 16 * kU - 1) / (16 * kU) + tid; h < cpad / (16 * kU); h += kBlock) nmin[place_of(h * (16 * kU)) / (16 * kU)] = 3.0e38f;
+        __syncthreads();
+    }
+
+    float d2 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < kCbPer; ++r) {
+        const int c = blockIdx.x * kCbChunk + r * kBlock + tid;
+        if (ONE && c >= cpad) continue;
+        h8 chunk[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) chunk[u][e] = (_Float16)0.0f;
+        int pos = c;                          // (padding exists only where the ranks are places already)
+        if (!ONE || c < csize) {        // (larger codebooks are whole chunks)
+            float hf[G], n2, d2c;
+            round_codeword<G>(cb + (int64_t)c * G, P, ok, hf, n2, d2c);
+            d2 = fmaxf(d2, d2c);
+#pragma unroll
+            for (int i = 0; i < G; ++i) chunk[i >> 3][i & 7] = (_Float16)(2.0f * hf[i]);
+            if constexpr (G == 8) {
+                _Float16 pieces[3];
+                split3(n2, pieces);
+                chunk[1][0] = pieces[0];
+                chunk[1][1] = pieces[1];
+                chunk[1][2] = pieces[2];
+                chunk[1][3] = (_Float16)1.0f;
+                chunk[1][4] = (_Float16)1.0f;
+                chunk[1][5] = (_Float16)1.0f;
+            } else {
+                const int b = bkt[r];
+                unsigned rank;
+                if (ONE) {
+                    rank = half_of(atomicAdd(&s_base[b >> 1], half_one(b)), b);
+                } else {
+                    rank = half_of(s_base[b >> 1], b) + half_of(placed[r], b);
+                }
+                pos = place_of((int)rank);
+                cnorm[pos] = n2;           // for the re-rank kernel's cheap distances
+                // the ranks of a key's positions lie in the bucket of the first of them, or above it
+                if (rank % (16 * kU) == 0) nmin[pos / (16 * kU)] = norm_bucket_floor(b, anchor, P);
+            }
+            perm[pos] = (uint16_t)c;
+        } else if (G == 16) {
+            cnorm[pos] = 0.0f;
+        }
+        const operand_row o = operand_row_of(pos);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) A[((int64_t)o.tile * 2 + u) * 32 + o.row] = chunk[u];
+    }
+    d2 = wave_max_f(d2);
+    __syncthreads();
+    if (lane == 0) s_tmp[wave].x = d2;
+    __syncthreads();
+    if (tid == 0) mem.dpart[blockIdx.x] = fmaxf(fmaxf(s_tmp[0].x, s_tmp[1].x), fmaxf(s_tmp[2].x, s_tmp[3].x));
 }
 
 // Plain C so that the compiler sees the reads of MFMA results and inserts the
@@ -621,9 +805,20 @@ template <int G, int NB>
 __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_score_mfma(
     const h8 *__restrict__ A, const h8 *__restrict__ X, const float *__restrict__ x_meta,
     const float *__restrict__ nmin, int2 *__restrict__ partials, int ncyc, int nsplit, int per_half,
-    int gblocks, int k_pad, unsigned *__restrict__ next_item, const float *__restrict__ wanted)
+    int gblocks, int k_pad, unsigned *__restrict__ next_item, const float *__restrict__ wanted,
+    cb_mem mem, int cb_parts, unsigned *__restrict__ meta)
 {
     if (wanted && *wanted == 0.0f) return;   // the cells do the work (pv_cells.h)
+    if (!wanted) {
+        // the largest rounding error of the codebook, for the re-rank; the bucket counts are done with
+        if (blockIdx.x == 0 && threadIdx.x < 64) {
+            const float d = wave_max_f((int)threadIdx.x < cb_parts ? mem.dpart[threadIdx.x] : 0.0f);
+            if (threadIdx.x == 0) meta[2] = __float_as_uint(d);
+        }
+        if (G == 16)
+            for (int i = blockIdx.x * (PV_WAVES * 64) + threadIdx.x; i < kCbCopies * (kNormBins / 2); i += gridDim.x * (PV_WAVES * 64))
+                mem.count[i] = 0u;
+    }
     constexpr int S = PV_STAGE;                                    // tiles per stage
     constexpr int kStageChunks = S * 64;                           // 16-byte chunks per stage
     constexpr int kW = PV_WAVES;                                   // waves per block
@@ -1840,16 +2035,14 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     const int N = (int)pv_num_groups(l);
     const int nsu_alloc = 2 * p.nsu + 64;    // two norms per super-unit; the scoring kernel stages 64 at a time
     pv_status st;
-    // codebook operand, then: position -> codeword, norm buckets, bucket counts / offsets,
-    // smallest norm per super-unit
+    // codebook operand, then: position -> codeword, norm buckets, smallest norm per super-unit
     const size_t a_bytes = (size_t)p.cpad * 32;
     const size_t perm_off = a_bytes, bucket_off = perm_off + (size_t)p.cpad * 2;
-    const size_t hist_off = (bucket_off + (size_t)csize * 2 + 255) & ~(size_t)255;
-    const size_t offs_off = hist_off + (size_t)kNormBins * 4;
-    const size_t nmin_off = offs_off + (size_t)kNormBins * 4;
+    const size_t bounds_off = (bucket_off + (size_t)csize * 2 + 255) & ~(size_t)255;     // splits of a table of cells
+    const size_t nmin_off = bounds_off + 256;
     const size_t cnorm_off = (nmin_off + (size_t)nsu_alloc * 4 + 255) & ~(size_t)255;   // g = 16: norm per position
     if ((st = pv_ensure(ctx, ctx->cb_f16, cnorm_off + (size_t)p.cpad * 4)) != PV_OK) return st;
-    if ((st = pv_ensure(ctx, ctx->cb_meta, 32 * sizeof(unsigned), /*zero_new=*/true)) != PV_OK) return st;
+    if ((st = pv_ensure(ctx, ctx->cb_meta, (kCbWords + 8) * sizeof(unsigned), /*zero_new=*/true)) != PV_OK) return st;
     if (cells && (st = pv_ensure(ctx, ctx->cells, kCellWords * 4, /*zero_new=*/true)) != PV_OK) return st;
     if ((st = pv_ensure(ctx, ctx->x_f16, (size_t)p.k_pad * 32)) != PV_OK) return st;
     // per-group bounds, then the staged targets / scale / code / id of each group
@@ -1869,12 +2062,16 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     h8 *A = reinterpret_cast<h8 *>(cbase);
     uint16_t *perm = reinterpret_cast<uint16_t *>(cbase + perm_off);
     uint16_t *bucket = reinterpret_cast<uint16_t *>(cbase + bucket_off);
-    unsigned *hist = reinterpret_cast<unsigned *>(cbase + hist_off);
-    unsigned *offsets = reinterpret_cast<unsigned *>(cbase + offs_off);
-    unsigned *nmin_bits = reinterpret_cast<unsigned *>(cbase + nmin_off);
+    float *nmin = reinterpret_cast<float *>(cbase + nmin_off);
     float *cnorm = reinterpret_cast<float *>(cbase + cnorm_off);
     h8 *X = static_cast<h8 *>(ctx->x_f16.ptr);
-    unsigned *cb_meta = static_cast<unsigned *>(ctx->cb_meta.ptr);
+    cb_mem mem;
+    mem.part = static_cast<pv_f4 *>(ctx->cb_meta.ptr);
+    mem.dpart = reinterpret_cast<float *>(mem.part + kCbParts);
+    mem.anchor = mem.dpart + kCbParts;
+    mem.count = reinterpret_cast<unsigned *>(mem.anchor + 16);
+    mem.cursor = mem.count + kCbCopies * (kNormBins / 2);
+    unsigned *cb_meta = mem.cursor + kCbCopies * (kNormBins / 2);
     float *x_meta = static_cast<float *>(ctx->x_meta.ptr);
     float *x_stage = x_meta + (size_t)p.k_pad * 4;
     int2 *partials = static_cast<int2 *>(ctx->partials.ptr);
@@ -1898,36 +2095,42 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     ga.x_stage = x_stage;
     ga.reach = cells ? reinterpret_cast<float *>(static_cast<char *>(ctx->x_meta.ptr) + reach_off) : nullptr;
     ctx->rr_blocks_last = rr_blocks;
+    clear_args ca;
+    ca.stats = stats;
+    ca.num_changed = nc;
+    ca.change_slots = change_slots;
+    ca.fb_count = fb_count;
+    ca.nslots = nslots;
     if (cells) {
-        const int cb_blocks = csize / kCellChunk;
-        unsigned *meta = cb_meta + 16;             // written whole by every call: no slots to alternate
-        int *su_bounds = reinterpret_cast<int *>(hist);
-        cell_mem mem;
-        mem.part = static_cast<pv_f4 *>(ctx->cells.ptr);
-        mem.dpart = reinterpret_cast<float *>(mem.part + kCellBlocksMax);
-        mem.theta = mem.dpart + kCellBlocksMax;
-        mem.count = reinterpret_cast<unsigned *>(mem.theta + 16);
-        mem.cursor = mem.count + kCellCopies * kCellsMax;
-        mem.cell_su = reinterpret_cast<int *>(mem.cursor + kCellCopies * kCellsMax);
-        mem.cell_of = reinterpret_cast<uint16_t *>(mem.cell_su + kCellsMax + 8);
+        const int cb_blocks = csize / kCbChunk;
+        unsigned *meta = cb_meta;
+        int *su_bounds = reinterpret_cast<int *>(cbase + bounds_off);
+        cell_mem cm;
+        cm.part = static_cast<pv_f4 *>(ctx->cells.ptr);
+        cm.dpart = reinterpret_cast<float *>(cm.part + kCbParts);
+        cm.theta = cm.dpart + kCbParts;
+        cm.count = reinterpret_cast<unsigned *>(cm.theta + 16);
+        cm.cursor = cm.count + kCbCopies * kCellsMax;
+        cm.cell_su = reinterpret_cast<int *>(cm.cursor + kCbCopies * kCellsMax);
+        cm.cell_of = reinterpret_cast<uint16_t *>(cm.cell_su + kCellsMax + 8);
         {
             pv_timed t(ctx, PV_K_PREP);
-            hipLaunchKernelGGL(k_cells_stats, dim3(cb_blocks + 1), dim3(kBlock), 0, sm, codebooks, csize, cbits, mem,
-                               stats, fb_count, nc, change_slots, nslots, ga);
+            hipLaunchKernelGGL(k_cells_stats, dim3(cb_blocks + 1), dim3(kBlock), 0, sm, codebooks, csize, cbits, cm,
+                               ca, ga);
             hipLaunchKernelGGL(k_cells_prep, dim3(cb_blocks + (p.k_pad + kBlock - 1) / kBlock), dim3(kBlock), 0, sm,
-                               codebooks, csize, cbits, cb_blocks, mem, meta, A, perm, su_bounds, p.nsplit, ga);
+                               codebooks, csize, cbits, cb_blocks, cm, meta, A, perm, su_bounds, p.nsplit, ga);
         }
         {
             pv_timed t(ctx, PV_K_SCORE_MFMA);
             const int items = p.gblocks * p.nsplit;
             hipLaunchKernelGGL(k_cells_score, dim3(items < 256 ? items : 256), dim3(cell_waves * 64), 0, sm, A, X,
-                               ga.reach, su_bounds, mem, meta, partials, cbits, cb_blocks, p.nsplit, p.gblocks,
+                               ga.reach, su_bounds, cm, meta, partials, cbits, cb_blocks, p.nsplit, p.gblocks,
                                p.k_pad, fb_count + 1);
             const int ditems = dense_blocks * p.nsplit;
             hipLaunchKernelGGL((k_score_mfma<8, PV_NBX>), dim3(ditems < 256 * PV_OCC ? ditems : 256 * PV_OCC),
                                dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, (const float *)nullptr, partials,
                                csize / (32 * kU * kResidues), p.nsplit, p.per_half, dense_blocks, p.k_pad, fb_count + 2,
-                               mem.theta + 15);
+                               cm.theta + 15, mem, 0, meta);
         }
         {
             pv_timed t(ctx, PV_K_RERANK);
@@ -1938,56 +2141,35 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
         PV_HIP(ctx, hipGetLastError());
         return PV_OK;
     }
-    // two statistics slots, used alternately (the first kernel of a call clears the other one)
-    unsigned *cb_meta_next = cb_meta + (ctx->meta_phase ? 0 : 8);
-    cb_meta += ctx->meta_phase ? 8 : 0;
-    ctx->meta_phase ^= 1;
-    {
-        // Under graph capture the slots do not alternate from replay to replay (the graph keeps
-        // the pointers of the captured call), so the slot this call accumulates into still holds
-        // what the last replay left: clear it first (a fill kernel, not a memset node).
-        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-        PV_HIP(ctx, hipStreamIsCapturing(sm, &capturing));
-        if (capturing != hipStreamCaptureStatusNone) {
-            pv_status fs = pv_launch_fill_f32(ctx, reinterpret_cast<float *>(cb_meta), 8, 0.0f);
-            if (fs != PV_OK) return fs;
-        }
-    }
+    const int cb_blocks = (p.cpad + kCbChunk - 1) / kCbChunk;
     {
         pv_timed t(ctx, PV_K_PREP);
-        int blocks = (csize + kBlock - 1) / kBlock;
-        // every block ends with three atomics, each on one address: 64 blocks measured best (32
-        // are as good, 128 cost 1.6 us more, 256 another 4)
-        if (blocks > 64) blocks = 64;
-        const int cb_blocks = (p.cpad + kBlock * kCbPer - 1) / (kBlock * kCbPer);
         const int x_blocks = (p.k_pad + kBlock - 1) / kBlock;
-        if (g == 8) {
-            hipLaunchKernelGGL(k_cb_stats<8>, dim3(blocks), dim3(kBlock), 0, sm, codebooks, csize,
-                               cb_meta, cb_meta_next, stats, fb_count, nc, (unsigned *)nullptr,
-                               (unsigned *)nullptr, 0, change_slots, nslots);
-            hipLaunchKernelGGL(k_prep<8>, dim3(cb_blocks + x_blocks), dim3(kBlock), 0, sm, codebooks,
-                               csize, p.cpad, cb_blocks, cb_meta, A, perm, bucket, hist, nmin_bits, cnorm, ga,
-                               p.ncyc, p.nsplit);
+#define PV_PREP(G_, ONE_)                                                                                \
+    do {                                                                                           \
+        if (!ONE_)                                                                                 \
+            hipLaunchKernelGGL(k_cb_stats<G_>, dim3(csize / kCbChunk), dim3(kBlock), 0, sm, codebooks, csize, mem, \
+                               bucket, ca);                                                        \
+        hipLaunchKernelGGL((k_prep<G_, ONE_>), dim3(cb_blocks + x_blocks), dim3(kBlock), 0, sm, codebooks, csize, p.cpad, \
+                           cb_blocks, cb_meta, mem, A, perm, bucket, nmin, cnorm, ga, p.ncyc, p.nsplit, ca); \
+    } while (0)
+        if (csize <= kOneBlock) {
+            if (g == 8) PV_PREP(8, true);
+            else PV_PREP(16, true);
         } else {
-            hipLaunchKernelGGL(k_cb_stats<16>, dim3(blocks), dim3(kBlock), 0, sm, codebooks, csize,
-                               cb_meta, cb_meta_next, stats, fb_count, nc, hist, nmin_bits, nsu_alloc,
-                               change_slots, nslots);
-            hipLaunchKernelGGL(k_cb_bucket<16>, dim3((csize + kBlock - 1) / kBlock), dim3(kBlock), 0,
-                               sm, codebooks, csize, cb_meta, bucket, hist);
-            hipLaunchKernelGGL(k_cb_scan, dim3(kNormBins / kScanBlock), dim3(kScanBlock), 0, sm, hist, offsets);
-            hipLaunchKernelGGL(k_prep<16>, dim3(cb_blocks + x_blocks), dim3(kBlock), 0, sm,
-                               codebooks, csize, p.cpad, cb_blocks, cb_meta, A, perm, bucket, offsets,
-                               nmin_bits, cnorm, ga, p.ncyc, p.nsplit);
+            if (g == 8) PV_PREP(8, false);
+            else PV_PREP(16, false);
         }
+#undef PV_PREP
     }
     {
         pv_timed t(ctx, PV_K_SCORE_MFMA);
         const int items = p.gblocks * p.nsplit;
         dim3 grid(items < 256 * PV_OCC ? items : 256 * PV_OCC);
-        const float *nmin = reinterpret_cast<const float *>(nmin_bits);
 #define PV_SCORE(G_, NB_)                                                                          \
     hipLaunchKernelGGL((k_score_mfma<G_, NB_>), grid, dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, nmin, \
-                       partials, p.ncyc, p.nsplit, p.per_half, p.gblocks, p.k_pad, fb_count + 1, (const float *)nullptr)
+                       partials, p.ncyc, p.nsplit, p.per_half, p.gblocks, p.k_pad, fb_count + 1, (const float *)nullptr, mem, \
+                       cb_blocks, cb_meta)
         if (g == 8) {
             if (p.NB == PV_NBX) PV_SCORE(8, PV_NBX);
             else PV_SCORE(8, 1);

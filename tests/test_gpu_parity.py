@@ -393,6 +393,25 @@ def test_reencode_m1_cells_of_the_codebook(B, k, regime):
     reencode_case(wl, 0, idx=idx, T_np=T_np)
 
 
+@pytest.mark.parametrize("g", [8, 16])
+@pytest.mark.parametrize("B", [5, 10, 11, 14])
+@pytest.mark.parametrize("norms", ["one", "spread", "tiny"])
+def test_reencode_m1_codebook_preparation(g, B, norms):
+    """Both ways of taking the codebook's statistics (1024 codewords, and more), and norms on which
+    the norm ordering is put to the test: all alike, far beyond a sample's, at the bottom of float32."""
+    wl = workloads.make(64, 64 * g, g, 1, B, seed=71, sigma_g=4e-3, tau=0.5)
+    if norms == "one":
+        wl.codebooks[:] = np.float32(0.02) * np.sign(wl.codebooks)
+    if norms == "spread":
+        wl.codebooks[0, 3::41] *= np.float32(30.0)
+        wl.codebooks[0, 5::43] *= np.float32(1e-3)
+        wl.codebooks[0, 7] = np.float32(0.0)
+    if norms == "tiny":
+        wl.codebooks *= np.float32(1e-14)
+        wl.scales *= np.float32(1e14)
+    reencode_case(wl, 0)
+
+
 @pytest.mark.parametrize("B", [5, 6, 9, 13, 16])
 def test_reencode_m1_codebook_sizes_with_long_lists(B):
     """More than 4096 listed groups (two group tiles per wave) at every codebook size class."""
