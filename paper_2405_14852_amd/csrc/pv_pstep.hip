@@ -16,9 +16,10 @@
 // plain loop over the groups.  Segments longer than kLong groups are cut into pieces of kLong
 // that are summed by the teams of one block and added in piece order (a different
 // association from the plain loop: reproducible from run to run, but no longer the sequential
-// rounding).  Small codebooks take another route (k_pg_small below).  The scale gradient is
-// one block-wide tree sum per row.
+// rounding).  Small codebooks take another route (k_pg_small below), which takes the scale
+// gradient along; otherwise that is one block-wide tree sum per row.
 #include "pv_internal.h"
+#include "pv_dpp.h"
 #include "pv_radix.h"
 
 namespace {
@@ -186,63 +187,37 @@ __global__ __launch_bounds__(kBlock) void k_pg_long(const int32_t *__restrict__ 
 }
 
 // Small codebooks (all M * 2^B * g sums fit one block's LDS): every codeword is shared by
-// thousands of groups, so sorting buys nothing.  Each block sweeps a contiguous range of
-// groups once, 16 bytes of G per thread, and adds s_o * G into its own LDS table with LDS
-// atomics.  To make the result independent of the order in which the atomics land, the
-// table is kept in 64-bit FIXED POINT: with X = max|s| * max|G| (both maxima are taken
-// beforehand, the product of two floats is exact in double) every term is scaled by a power
-// of two that leaves `headroom` bits for the number of terms one block can add, and rounded
-// to an integer once; integer addition is associative, so a table is a function of the
-// block's inputs only.  The tables are added over the blocks as integers too (exactly) and
-// the total is scaled back and rounded to fp32.  A term keeps min(62 - headroom, 50) bits
-// below X (>= 39 for the largest matrices), so a sum differs from the exact one by far less
-// than the rounding of a sequential double loop does.  Gradients or scales that are not
-// finite make every entry NaN.  The kernel is bound by the LDS atomics (sixteen per group and
-// codebook), not by reading G: indices are kept in 32 bits relative to the block's range and
-// the conversion to an integer is one addition, so that the vector ALU stays out of the way.
+// thousands of groups, so sorting buys nothing.  One pass over G: every wave streams its own
+// consecutive vectors, adds s_o * G into the block's LDS table with LDS atomics and, from the same
+// registers, the products with the codewords for the scale gradient.
+// To make the result independent of the order in which the atomics land, the table is kept in 64-bit
+// FIXED POINT: every term is scaled by a power of two that leaves room for the number of terms
+// one block can add, and rounded to an integer once; integer addition is associative, so a
+// table is a function of the block's inputs only.  The unit comes from the block's FIRST vectors (16
+// places spread over its range), with kSmallSlack bits to spare, instead of a pass of its own for
+// the largest |G|; the largest product met is taken on the way, and a block that met one beyond
+// the room (rows of zeros first, a gradient that grows 64-fold) clears its table and sweeps its
+// range again with the unit of what it met.  A term keeps at least min(62 - headroom, 50) - 6
+// bits (41 for 2^14 groups a block) below the block's largest product, so a sum differs from the
+// exact one by far less than the rounding of a sequential double loop to fp32 does.  The blocks'
+// tables are added in double in a fixed order.  Gradients or scales that are not finite make every
+// entry NaN.  A row's products are summed by the waves that meet it, lanes first, and added in
+// order of the waves.
+// Bound by the LDS atomics (sixteen per group and codebook: 53 us at 11008 x 4096, 2 x 8, where
+// reading G takes 36); the vector ALU works meanwhile (23 M instructions, 37 us).  There, with the
+// scale gradient (and the maxima) as a kernel of its own that read G first: 98.7 us a step, in one
+// pass 68.3.  Ordering tiles of groups by code in LDS and summing in registers, without these
+// atomics, was tried: 112 us, one block of 16 waves per compute unit waiting at its barriers.
 constexpr int kSmallBlock = 1024;                         // one table serves sixteen waves
+constexpr int kSmallWaves = kSmallBlock / 64;
 constexpr int kSmallAhead = 2;                            // vectors of a thread in flight
-// The power of two that turns a term s_o * G into a 64-bit integer (see k_pg_small): from the
-// largest |scale| and the largest |G| (as bits: NaN > inf > every finite value), leaving
-// `headroom` bits for the terms one block adds to an entry.  Block 0 leaves the inverse factor
-// and the poison flag (some input not finite) in meta[0], meta[1].  All threads of a
-// kSmallBlock-wide block call this; s_max is 2 * kSmallBlock / 64 unsigneds of LDS.
-__device__ __forceinline__ double fixed_point_unit(const float *__restrict__ scales, int out_features,
-                                                   const unsigned *__restrict__ gmax_bits, int nmax,
-                                                   int headroom, unsigned *s_max,
-                                                   double *__restrict__ meta)
-{
-    constexpr int kW = kSmallBlock / 64;
-    unsigned sb = 0u, gb = 0u;
-    for (int o = threadIdx.x; o < out_features; o += kSmallBlock) sb = max(sb, __float_as_uint(fabsf(scales[o])));
-    for (int o = threadIdx.x; o < nmax; o += kSmallBlock) gb = max(gb, gmax_bits[o]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        sb = max(sb, (unsigned)__shfl_down(sb, off));
-        gb = max(gb, (unsigned)__shfl_down(gb, off));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        s_max[threadIdx.x >> 6] = sb;
-        s_max[kW + (threadIdx.x >> 6)] = gb;
-    }
-    __syncthreads();
-    sb = gb = 0u;
-#pragma unroll
-    for (int w = 0; w < kW; ++w) {
-        sb = max(sb, s_max[w]);
-        gb = max(gb, s_max[kW + w]);
-    }
-    const double X = (double)__uint_as_float(sb) * (double)__uint_as_float(gb);
-    const bool poison = !(X < __builtin_huge_val());
-    int ex = 0;
-    (void)frexp(X, &ex);                                  // X < 2^ex
-    const int kbits = 62 - headroom < 50 ? 62 - headroom : 50;   // bits of a term below 2^ex
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        meta[0] = (X > 0.0 && !poison) ? ldexp(1.0, -(kbits - ex)) : 0.0;
-        meta[1] = poison ? 1.0 : 0.0;
-    }
-    return (X > 0.0 && !poison) ? ldexp(1.0, kbits - ex) : 0.0;
-}
+constexpr int kSmallSlack = 6;                            // bits of room above the first vectors' largest product
+
+struct small_mem {
+    double *partial;     // [blocks][entries]
+    double *rows;        // [rows + waves] part of row r that wave w met, at r + w
+    unsigned *poison;    // [blocks]
+};
 
 // x + 1.5 * 2^52 holds the integer nearest to x (ties to even) in its low mantissa bits for
 // |x| < 2^51; the terms stay below 2^50
@@ -252,136 +227,238 @@ __device__ __forceinline__ unsigned long long fixed_point_term(double x)
     return (unsigned long long)(__double_as_longlong(x + kMagic) - __double_as_longlong(kMagic));
 }
 
-// VPG: 16-byte vectors per group when that is 1, 2 or 4 (a shift finds the group), else 0
-template <int VPG>
-__global__ __launch_bounds__(kSmallBlock) void k_pg_small(
-    const float *__restrict__ G, const uint16_t *__restrict__ codes,
-    const float *__restrict__ scales, int64_t N, int64_t per_block, int g, int M, int nbits,
-    int gpr, int out_features, const unsigned *__restrict__ gmax_bits, int nmax, int headroom,
-    long long *__restrict__ partial, double *__restrict__ meta)
+// sums and maxima over a wave through the lane-permute paths of the vector unit; uniform results
+__device__ __forceinline__ double wave_lane_f64(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    pv_team_stages<16>([&](auto c) { v = v + pv_dpp_f64<decltype(c)::value>(v); });
+    return (wave_lane_f64(v, 0) + wave_lane_f64(v, 16)) + (wave_lane_f64(v, 32) + wave_lane_f64(v, 48));
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v)
+{
+    pv_team_stages<16>([&](auto c) { v = max(v, (unsigned)pv_dpp<decltype(c)::value>((int)v)); });
+    const unsigned a = __builtin_amdgcn_readlane((int)v, 0), b = __builtin_amdgcn_readlane((int)v, 16);
+    const unsigned d = __builtin_amdgcn_readlane((int)v, 32), e = __builtin_amdgcn_readlane((int)v, 48);
+    return max(max(a, b), max(d, e));
+}
+
+// largest |scale| times largest |G| of a block, from each wave's own (as bits: NaN > inf > every
+// finite value); all threads call this, s_max is 2 * kSmallWaves unsigneds of LDS
+__device__ __forceinline__ double block_bound(unsigned gb, unsigned sb, unsigned *s_max)
+{
+    gb = wave_max_u32(gb);
+    sb = wave_max_u32(sb);
+    __syncthreads();                                       // the last call's values were read
+    if ((threadIdx.x & 63) == 0) {
+        s_max[threadIdx.x >> 6] = gb;
+        s_max[kSmallWaves + (threadIdx.x >> 6)] = sb;
+    }
+    __syncthreads();
+    gb = sb = 0u;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+        gb = max(gb, s_max[w]);
+        sb = max(sb, s_max[kSmallWaves + w]);
+    }
+    return (double)__uint_as_float(sb) * (double)__uint_as_float(gb);
+}
+
+// VPG: 16-byte vectors per group when that is 1, 2 or 4 (a shift finds the group), else 0.
+// ROWS: the scale gradient too (rows of at least 64 vectors).  A wave takes `per_wave` consecutive
+// vectors, a multiple of 64 that begins with a group.
+template <int VPG, bool ROWS>
+__global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
+    const float *__restrict__ G, const uint16_t *__restrict__ codes, const float *__restrict__ codebooks,
+    const float *__restrict__ scales, int64_t nvec, int per_wave, int g, int M, int nbits, int gpr,
+    int out_features, int kbits, small_mem mem)
 {
     extern __shared__ unsigned long long tab[];         // [M][2^B][g]
-    __shared__ unsigned s_max[2 * (kSmallBlock / 64)];
+    __shared__ unsigned s_max[2 * kSmallWaves];
     const int csize = 1 << nbits;
     const unsigned mask = (unsigned)csize - 1u;
     const int entries = M * csize * g;
-    for (int e = threadIdx.x; e < entries; e += kSmallBlock) tab[e] = 0ull;
-    const double up = fixed_point_unit(scales, out_features, gmax_bits, nmax, headroom, s_max, meta);
     const unsigned vpg = VPG > 0 ? (unsigned)VPG : (unsigned)(g / 4);   // 16-byte vectors per group
-    const int64_t lo = (int64_t)blockIdx.x * per_block;
-    const int64_t hi = lo + per_block < N ? lo + per_block : N;
-    // everything inside the block's range is counted from its first group in 32 bits
-    const unsigned nvec = hi > lo ? (unsigned)(hi - lo) * vpg : 0u;
-    const unsigned row0 = (unsigned)(lo / gpr), rem0 = (unsigned)(lo - (int64_t)row0 * gpr);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kSmallWaves + (threadIdx.x >> 6)));
+    const int64_t v_lo = (int64_t)wave * per_wave;
+    const int64_t left = nvec - v_lo;
+    const int len = left <= 0 ? 0 : left < per_wave ? (int)left : per_wave;
+    // everything inside the wave's range is counted from its first group in 32 bits
+    const int64_t n_lo = v_lo / vpg;
+    const unsigned row0 = (unsigned)(n_lo / gpr), rem0 = (unsigned)(n_lo - (int64_t)row0 * gpr);
     const double inv_gpr = 1.0 / (double)gpr;
-    const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(G) + lo * vpg;
-    const uint16_t *codes0 = codes + lo * M;
+    const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(G) + v_lo;
+    const pv_f4 *C4 = reinterpret_cast<const pv_f4 *>(codebooks);
+    const uint16_t *codes0 = codes + n_lo * M;
     // Within a codeword's row the elements are permuted by bits of the code (power-of-two
     // groups): for a given element the 64 lanes of an atomic then spread over all LDS banks
     // instead of the few that a row stride of 8 g bytes leaves them.
     const unsigned swm = (g & (g - 1)) == 0 ? (unsigned)g - 1u : 0u;
-    for (unsigned v0 = threadIdx.x; v0 < nvec; v0 += kSmallBlock * kSmallAhead) {
-        pv_f4 gv[kSmallAhead];
-        float sf[kSmallAhead];
-        unsigned nl[kSmallAhead], q4[kSmallAhead], c01[kSmallAhead][2];
+
+    // the first vectors of each wave say what to expect; they are read again (from a cache) below
+    unsigned gb = 0u, sb = 0u;
+    for (int u = 0; u < kSmallAhead; ++u) {
+        const int v = lane + u * 64;
+        if (v < len) {
+            const pv_f4 x = G4[v];
 #pragma unroll
-        for (int u = 0; u < kSmallAhead; ++u) {
-            const unsigned v = v0 + (unsigned)u * kSmallBlock;
-            const unsigned vc = v < nvec ? v : nvec - 1u;   // clamped: the loads of a batch go out together
-            nl[u] = vc / vpg;
-            q4[u] = vc - nl[u] * vpg;
-            gv[u] = __builtin_nontemporal_load(&G4[vc]);
-            sf[u] = scales[row0 + pv_row_of(rem0 + nl[u], inv_gpr)];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) c01[u][m] = m < M ? codes0[(size_t)nl[u] * M + m] & mask : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < kSmallAhead; ++u) {
-            if (v0 + (unsigned)u * kSmallBlock >= nvec) break;
-            const double ss = (double)sf[u] * up;           // a power of two: exact
-            unsigned long long term[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                term[e] = fixed_point_term(ss * (double)gv[u][e]);
-            for (int m = 0; m < M; ++m) {
-                const unsigned c = m < 2 ? c01[u][m] : codes0[(size_t)nl[u] * M + m] & mask;
-                unsigned long long *row = tab + ((size_t)m * csize + c) * g;
-                const unsigned sw = (c >> 2) & swm;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) atomicAdd(&row[(q4[u] * 4u + e) ^ sw], term[e]);
-            }
+            for (int e = 0; e < 4; ++e) gb = max(gb, __float_as_uint(fabsf(x[e])));
+            sb = max(sb, __float_as_uint(fabsf(scales[row0 + pv_row_of(rem0 + (unsigned)v / vpg, inv_gpr)])));
         }
     }
-    __syncthreads();
-    long long *out = partial + (int64_t)blockIdx.x * entries;
+    double X = block_bound(gb, sb, s_max);
+    int ex = 0;
+    double down = 0.0;
+    unsigned bad = 0u;
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        const bool some = X > 0.0 && X < __builtin_huge_val();
+        (void)frexp(some ? X : 0.0, &ex);                  // X < 2^ex
+        if (attempt == 0) ex += kSmallSlack;
+        const double limit = some ? ldexp(1.0, ex) : 0.0;
+        const double up = some ? ldexp(1.0, kbits - ex) : 0.0;
+        down = some ? ldexp(1.0, ex - kbits) : 0.0;
+        for (int e = threadIdx.x; e < entries; e += kSmallBlock) tab[e] = 0ull;
+        __syncthreads();
+        const bool rows = ROWS && attempt == 0;
+        unsigned cur = row0;
+        int row_end = (int)((unsigned)gpr - rem0) * (int)vpg;
+        double acc = 0.0;
+        gb = sb = 0u;
+        for (int v0 = 0; v0 < len; v0 += 64 * kSmallAhead) {
+            pv_f4 gv[kSmallAhead];
+            unsigned nl[kSmallAhead], q4[kSmallAhead], c01[kSmallAhead][2];
+#pragma unroll
+            for (int u = 0; u < kSmallAhead; ++u) {
+                const unsigned vc = (unsigned)min(v0 + u * 64 + lane, len - 1);   // clamped: the loads of a batch go out together
+                nl[u] = vc / vpg;
+                q4[u] = vc - nl[u] * vpg;
+                gv[u] = __builtin_nontemporal_load(&G4[vc]);
+#pragma unroll
+                for (int m = 0; m < 2; ++m) c01[u][m] = m < M ? codes0[(size_t)nl[u] * M + m] & mask : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < kSmallAhead; ++u) {
+                const int at = v0 + u * 64;                // uniform
+                if (at >= len) break;
+                const bool in = at + lane < len;
+                float sf;
+                bool next = false;
+                if constexpr (ROWS) {                      // at least 64 vectors a row: two rows at most
+                    next = at + lane >= row_end;
+                    const float sa = scales[cur], sx = scales[min(cur + 1u, (unsigned)out_features - 1u)];
+                    sf = next ? sx : sa;
+                } else {
+                    sf = scales[row0 + pv_row_of(rem0 + nl[u], inv_gpr)];
+                }
+                gb = max(max(gb, __float_as_uint(fabsf(gv[u].x))), __float_as_uint(fabsf(gv[u].y)));
+                gb = max(max(gb, __float_as_uint(fabsf(gv[u].z))), __float_as_uint(fabsf(gv[u].w)));
+                sb = max(sb, in ? __float_as_uint(fabsf(sf)) : 0u);
+                if (in) {
+                    const double ss = (double)sf * up;     // a power of two: exact
+                    unsigned long long term[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) term[e] = fixed_point_term(ss * (double)gv[u][e]);
+                    for (int m = 0; m < M; ++m) {
+                        const unsigned c = m < 2 ? c01[u][m] : codes0[(size_t)nl[u] * M + m] & mask;
+                        unsigned long long *row = tab + ((size_t)m * csize + c) * g;
+                        const unsigned sw = (c >> 2) & swm;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) atomicAdd(&row[(q4[u] * 4u + e) ^ sw], term[e]);
+                    }
+                }
+                if constexpr (ROWS) {
+                    const bool ends = at + 64 > row_end;
+                    if (rows) {
+                        pv_f4 q = C4[c01[u][0] * vpg + q4[u]];
+                        for (int m = 1; m < M; ++m) {
+                            const unsigned c = m < 2 ? c01[u][m] : codes0[(size_t)nl[u] * M + m] & mask;
+                            const pv_f4 cw = C4[((unsigned)m * csize + c) * vpg + q4[u]];
+                            q.x = q.x + cw.x;
+                            q.y = q.y + cw.y;
+                            q.z = q.z + cw.z;
+                            q.w = q.w + cw.w;
+                        }
+                        // a product of two floats is exact in double: one rounding a term
+                        double d = (double)gv[u].x * (double)q.x;
+                        d = fma((double)gv[u].y, (double)q.y, d);
+                        d = fma((double)gv[u].z, (double)q.z, d);
+                        d = fma((double)gv[u].w, (double)q.w, d);
+                        if (!in) d = 0.0;
+                        if (ends) {
+                            const double total = wave_sum_f64(acc + (next ? 0.0 : d));
+                            if (lane == 0) mem.rows[(size_t)cur + wave] = total;
+                            acc = next ? d : 0.0;
+                        } else {
+                            acc = acc + d;
+                        }
+                    }
+                    if (ends) {
+                        ++cur;
+                        row_end += gpr * (int)vpg;
+                    }
+                }
+            }
+        }
+        if (ROWS && rows && len > 0) {                     // the row that goes on: zero if none of it was met
+            const double total = wave_sum_f64(acc);
+            if (lane == 0) mem.rows[(size_t)cur + wave] = total;
+        }
+        X = block_bound(gb, sb, s_max);                    // what the block did meet
+        bad = X < __builtin_huge_val() ? 0u : 1u;
+        if (bad || X <= limit) break;
+    }
+    double *out = mem.partial + (int64_t)blockIdx.x * entries;
     for (int e = threadIdx.x; e < entries; e += kSmallBlock) {
         const unsigned sw = ((((unsigned)e / (unsigned)g) & mask) >> 2) & swm;   // the code within its codebook, as on the way in
-        out[e] = (long long)tab[(unsigned)e ^ sw];
+        out[e] = (double)(long long)tab[(unsigned)e ^ sw] * down;
     }
+    if (threadIdx.x == 0) mem.poison[blockIdx.x] = bad;
 }
 
-// adds the per-block tables as integers (16 threads per entry, each a slice of the blocks),
-// scales back and rounds once
+// adds the blocks' tables (16 threads per entry, each a slice of the blocks, in an order of their own)
+// and rounds once; the blocks from `eblocks` on add the waves' parts of a row each thread
 constexpr int kSlices = 16;
-__global__ __launch_bounds__(kBlock) void k_pg_small_final(const long long *__restrict__ partial,
-                                                           int blocks, int entries,
-                                                           const double *__restrict__ meta,
-                                                           float *__restrict__ out)
+__global__ __launch_bounds__(kBlock) void k_pg_small_final(small_mem mem, int blocks, int entries, int eblocks,
+                                                           int rows, int64_t row_vecs, int per_wave,
+                                                           float *__restrict__ out,
+                                                           float *__restrict__ grad_scales)
 {
-    __shared__ long long s_hi[kSlices][kBlock / kSlices];
-    __shared__ long long s_lo[kSlices][kBlock / kSlices];
+    if ((int)blockIdx.x >= eblocks) {
+        const int64_t r = (int64_t)((int)blockIdx.x - eblocks) * kBlock + threadIdx.x;
+        if (r >= rows) return;
+        const int w1 = (int)(((r + 1) * row_vecs - 1) / per_wave);
+        double total = 0.0;
+        for (int w = (int)(r * row_vecs / per_wave); w <= w1; ++w) total = total + mem.rows[r + w];
+        grad_scales[r] = (float)total;
+        return;
+    }
+    __shared__ double s_sum[kSlices][kBlock / kSlices];
     const int col = threadIdx.x % (kBlock / kSlices), sl = threadIdx.x / (kBlock / kSlices);
     const int e = blockIdx.x * (kBlock / kSlices) + col;
-    long long hi = 0, lo = 0;                           // total = hi * 2^32 + lo
+    double total = 0.0;
     if (e < entries) {
-        for (int b0 = sl; b0 < blocks; b0 += kSlices * 4) {
-            long long p[4];
+        for (int b0 = sl; b0 < blocks; b0 += kSlices * 8) {
+            double p[8];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 8; ++u) {
                 const int b = b0 + u * kSlices;
-                p[u] = b < blocks ? partial[(int64_t)b * entries + e] : 0;
+                p[u] = b < blocks ? mem.partial[(int64_t)b * entries + e] : 0.0;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                hi += p[u] >> 32;
-                lo += p[u] & 0xffffffffll;
-            }
+            for (int u = 0; u < 8; ++u) total = total + p[u];
         }
     }
-    s_hi[sl][col] = hi;
-    s_lo[sl][col] = lo;
-    __syncthreads();
+    s_sum[sl][col] = total;
+    unsigned bad = 0u;
+    for (int b = threadIdx.x; b < blocks; b += kBlock) bad |= mem.poison[b];
+    bad = (unsigned)__syncthreads_or((int)bad);
     if (sl == 0 && e < entries) {
-        for (int q = 1; q < kSlices; ++q) {
-            hi += s_hi[q][col];
-            lo += s_lo[q][col];
-        }
-        // |hi| < 2^40 and 0 <= lo < 2^41: both conversions are exact, the sum rounds once
-        const double total = (double)hi * 4294967296.0 + (double)lo;
-        out[e] = meta[1] != 0.0 ? __builtin_nanf("") : (float)(total * meta[0]);
-    }
-}
-
-// largest |G| seen by each block, as bits, for callers that do not ask for the scale gradient
-// (whose kernel takes the maximum of each row on its way)
-__global__ __launch_bounds__(kBlock) void k_pg_absmax(const float *__restrict__ G, int64_t n4,
-                                                      unsigned *__restrict__ gmax_bits)
-{
-    const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(G);
-    unsigned mb = 0u;
-    for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < n4; v += (int64_t)gridDim.x * kBlock) {
-        const pv_f4 x = G4[v];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) mb = max(mb, __float_as_uint(fabsf(x[e])));
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mb = max(mb, (unsigned)__shfl_down(mb, off));
-    __shared__ unsigned tmp_max[kBlock / 64];
-    if ((threadIdx.x & 63) == 0) tmp_max[threadIdx.x >> 6] = mb;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w) mb = max(mb, tmp_max[w]);
-        gmax_bits[blockIdx.x] = mb;
+        for (int q = 1; q < kSlices; ++q) total = total + s_sum[q][col];
+        out[e] = bad ? __builtin_nanf("") : (float)total;
     }
 }
 
@@ -391,11 +468,9 @@ __global__ __launch_bounds__(kBlock) void k_pg_scales(const float *__restrict__ 
                                                       const uint16_t *__restrict__ codes,
                                                       const float *__restrict__ codebooks, int g,
                                                       int M, int nbits, int gpr,
-                                                      float *__restrict__ grad_scales,
-                                                      unsigned *__restrict__ gmax_bits /* [rows], NULL ok */)
+                                                      float *__restrict__ grad_scales)
 {
     __shared__ double tmp[kBlock / 64];
-    unsigned mb = 0u;                     // largest |G| of the row, as bits
     const int64_t o = blockIdx.x;
     const int64_t csize = (int64_t)1 << nbits;
     const unsigned mask = (unsigned)csize - 1u;
@@ -446,8 +521,6 @@ __global__ __launch_bounds__(kBlock) void k_pg_scales(const float *__restrict__ 
                     acc = acc + (double)gv[u].y * (double)q[u].y;
                     acc = acc + (double)gv[u].z * (double)q[u].z;
                     acc = acc + (double)gv[u].w * (double)q[u].w;
-                    mb = max(max(mb, __float_as_uint(fabsf(gv[u].x))), __float_as_uint(fabsf(gv[u].y)));
-                    mb = max(max(mb, __float_as_uint(fabsf(gv[u].z))), __float_as_uint(fabsf(gv[u].w)));
                 }
             }
         }
@@ -460,14 +533,7 @@ __global__ __launch_bounds__(kBlock) void k_pg_scales(const float *__restrict__ 
                 q = q + codebooks[(m * csize + (codes[n * M + m] & mask)) * g + i];
             const float gv = G[o * in_features + e];
             acc = acc + (double)gv * (double)q;
-            mb = max(mb, __float_as_uint(fabsf(gv)));
         }
-    }
-    __shared__ unsigned tmp_max[kBlock / 64];
-    if (gmax_bits) {     // one plain store per row: atomics on one device address would queue up
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mb = max(mb, (unsigned)__shfl_down(mb, off));
-        if ((threadIdx.x & 63) == 0) tmp_max[threadIdx.x >> 6] = mb;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc = acc + __shfl_down(acc, off);
@@ -477,11 +543,6 @@ __global__ __launch_bounds__(kBlock) void k_pg_scales(const float *__restrict__ 
         double t = 0.0;
         for (int w = 0; w < kBlock / 64; ++w) t = t + tmp[w];
         grad_scales[o] = (float)t;
-        if (gmax_bits) {
-            unsigned m4 = 0u;
-            for (int w = 0; w < kBlock / 64; ++w) m4 = max(m4, tmp_max[w]);
-            gmax_bits[o] = m4;
-        }
     }
 }
 
@@ -503,41 +564,49 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
     // small codebooks: per-block LDS tables instead of a sort
     const int64_t entries = (int64_t)M * csize * g;
     if (g % 4 == 0 && entries * 8 <= 64 * 1024 && N / csize >= 64) {
-        int blocks = (int)((N + 4095) / 4096);
-        if (blocks > 512) blocks = 512;
-        if (blocks < 1) blocks = 1;
-        const int64_t per_block = (N + blocks - 1) / blocks;
+        const int vpg = g / 4;
+        const int64_t nvec = N * vpg;
+        int64_t blocks64 = (N + 4095) / 4096;
+        if (blocks64 > 512) blocks64 = 512;
+        const int blocks = (int)blocks64, waves = blocks * kSmallWaves;
+        const int unit = 64 * vpg;
+        const int per_wave = (int)((nvec + (int64_t)waves * unit - 1) / ((int64_t)waves * unit)) * unit;
         int headroom = 1;                                 // 2^headroom > terms one block adds to an entry
-        while (((int64_t)1 << headroom) <= per_block) ++headroom;
-        const int64_t n4 = N * g / 4;
-        int64_t mblocks = (n4 + kBlock * 8 - 1) / (kBlock * 8);
-        if (mblocks > 2048) mblocks = 2048;
-        const int nmax = grad_scales ? (int)l->out_features : (int)mblocks;
-        const size_t o_meta = align_up((size_t)blocks * entries * 8);
-        const size_t o_gmax = o_meta + 256;
-        pv_status st2 = pv_ensure(ctx, ctx->pstep, o_gmax + (size_t)nmax * 4);
+        while (((int64_t)1 << headroom) <= (int64_t)per_wave / vpg * kSmallWaves) ++headroom;
+        const int kbits = 62 - headroom < 50 ? 62 - headroom : 50;   // bits of a term below the bound
+        const bool rows = grad_scales && l->in_features >= 256;      // 64 vectors a row
+        const size_t o_rows = align_up((size_t)blocks * entries * 8);
+        const size_t o_bad = o_rows + align_up(((size_t)l->out_features + waves) * 8);
+        pv_status st2 = pv_ensure(ctx, ctx->pstep, o_bad + (size_t)blocks * 4);
         if (st2 != PV_OK) return st2;
-        long long *partial = static_cast<long long *>(ctx->pstep.ptr);
-        double *meta = reinterpret_cast<double *>(static_cast<char *>(ctx->pstep.ptr) + o_meta);
-        unsigned *gmax = reinterpret_cast<unsigned *>(static_cast<char *>(ctx->pstep.ptr) + o_gmax);
+        char *p = static_cast<char *>(ctx->pstep.ptr);
+        const small_mem mem{reinterpret_cast<double *>(p), reinterpret_cast<double *>(p + o_rows),
+                            reinterpret_cast<unsigned *>(p + o_bad)};
         pv_timed t(ctx, PV_K_PSTEP);
-        if (grad_scales)     // first: it reads all of G anyway and takes max|G| of each row on its way
+        if (grad_scales && !rows)
             hipLaunchKernelGGL(k_pg_scales<true>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,
-                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales, gmax);
-        else
-            hipLaunchKernelGGL(k_pg_absmax, dim3((unsigned)mblocks), dim3(kBlock), 0, sm, G, n4, gmax);
+                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales);
 #define PV_SMALL(V_)                                                                             \
-    hipLaunchKernelGGL(k_pg_small<V_>, dim3(blocks), dim3(kSmallBlock), (size_t)entries * 8, sm, G, \
-                       codes, scales, N, per_block, g, M, l->nbits, gpr, (int)l->out_features,  \
-                       gmax, nmax, headroom, partial, meta)
+    do {                                                                                         \
+        if (rows)                                                                                \
+            hipLaunchKernelGGL((k_pg_small<V_, true>), dim3(blocks), dim3(kSmallBlock), (size_t)entries * 8, \
+                               sm, G, codes, codebooks, scales, nvec, per_wave, g, M, l->nbits, gpr, \
+                               (int)l->out_features, kbits, mem);                                \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_pg_small<V_, false>), dim3(blocks), dim3(kSmallBlock), (size_t)entries * 8, \
+                               sm, G, codes, codebooks, scales, nvec, per_wave, g, M, l->nbits, gpr, \
+                               (int)l->out_features, kbits, mem);                                \
+    } while (0)
         if (g == 8) PV_SMALL(2);
         else if (g == 16) PV_SMALL(4);
         else if (g == 4) PV_SMALL(1);
         else PV_SMALL(0);
 #undef PV_SMALL
-        hipLaunchKernelGGL(k_pg_small_final,
-                           dim3((unsigned)((entries + kBlock / kSlices - 1) / (kBlock / kSlices))),
-                           dim3(kBlock), 0, sm, partial, blocks, (int)entries, meta, grad_codebooks);
+        const int eblocks = (int)((entries + kBlock / kSlices - 1) / (kBlock / kSlices));
+        const int rblocks = rows ? (int)((l->out_features + kBlock - 1) / kBlock) : 0;
+        hipLaunchKernelGGL(k_pg_small_final, dim3((unsigned)(eblocks + rblocks)), dim3(kBlock), 0, sm, mem, blocks,
+                           (int)entries, eblocks, (int)l->out_features, l->in_features / 4, per_wave,
+                           grad_codebooks, grad_scales);
         PV_HIP(ctx, hipGetLastError());
         return PV_OK;
     }
@@ -623,10 +692,10 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
     if (grad_scales) {
         if (g % 4 == 0)
             hipLaunchKernelGGL(k_pg_scales<true>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,
-                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales, (unsigned *)nullptr);
+                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales);
         else
             hipLaunchKernelGGL(k_pg_scales<false>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,
-                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales, (unsigned *)nullptr);
+                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales);
     }
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;

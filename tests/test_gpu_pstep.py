@@ -171,6 +171,33 @@ def test_codebook_grads_small_codebook_route_shapes(g, M, B, shape):
     assert np.array_equal(gs.view(np.uint32), gs2.view(np.uint32))
 
 
+@pytest.mark.parametrize("g,M,B,shape", [(8, 2, 4, (64, 248)),      # 62 vectors a row: the scale gradient apart
+                                         (8, 2, 4, (64, 256)),      # 64: a row ends with every wave step
+                                         (4, 1, 5, (67, 260)),      # 65: nearly every step meets two rows
+                                         (16, 1, 8, (70, 4080)),    # rows longer than a wave's range, a ragged end
+                                         (12, 2, 3, (33, 1200)),
+                                         (8, 1, 8, (4099, 512))])
+@pytest.mark.parametrize("head", ["plain", "zero", "small"])
+def test_codebook_grads_small_codebook_route_unit_and_rows(g, M, B, shape, head):
+    """The unit of a block's sums is set by its first vectors: rows of zeros there, or values 2^40
+    below the rest, make the block sweep again.  Rows that end inside, at and beyond a wave step.
+    Bounds: a term is rounded at 2^-41 of the largest product, sums of up to 2^20 terms."""
+    wl = workloads.make(shape[0], shape[1], g, M, B, seed=90, sigma_g=1e-2)
+    if head != "plain":
+        flat = wl.G.reshape(-1)
+        flat[:flat.size - 64] *= np.float32(0.0 if head == "zero" else 2.0 ** -40)
+    gc, gs, gc_ref, gs_ref = run_case(wl)
+    top = np.abs(wl.G).max() * np.abs(wl.scales).max()
+    terms = np.bincount(wl.codes[..., 0].ravel(), minlength=1 << B).max()
+    tol = 2 * np.spacing(np.abs(gc_ref)) + 2.0 ** -41 * top * terms
+    assert (np.abs(gc.astype(np.float64) - gc_ref.astype(np.float64)) <= tol).all()
+    q = oracle.dequantize(wl.codes, wl.codebooks, np.ones_like(wl.scales))
+    assert close_sum(gs, gs_ref, np.abs(wl.G * q).sum(axis=1))
+    again, gs2, _, _ = run_case(wl)
+    assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
+    assert np.array_equal(gs.view(np.uint32), gs2.view(np.uint32))
+
+
 def test_codebook_grads_of_an_empty_matrix_are_zero():
     from paper_2405_14852_amd import Layout, PVContext
     ctx = PVContext(0)
