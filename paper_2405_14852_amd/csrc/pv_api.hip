@@ -126,8 +126,8 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->sel_scores, &c->sel_hist, &c->sel_blocks, &c->sel_list, &c->sel_state, &c->stats,
-                         &c->cb_f16,     &c->cb_meta, &c->cells,  &c->x_f16,      &c->x_meta,    &c->partials,
+    pv_buffer *bufs[] = {&c->sel_scores, &c->sel_hist, &c->sel_list, &c->stats,
+                         &c->cb_f16,     &c->cb_meta,  &c->x_f16,    &c->partials,
                          &c->fb_list, &c->rr_counts, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);

@@ -36,16 +36,15 @@ struct pv_ctx {
 
     // scratch, grown on demand (never shrunk)
     pv_buffer sel_scores;   // f32 [N]            group scores when the caller passes none
-    pv_buffer sel_hist;     // radix-select histograms, eight copies each (kept zero between calls)
-    pv_buffer sel_blocks;   // u32                counts per wave and per block of the selection
+    pv_buffer sel_hist;     // radix-select histograms, eight copies each (kept zero between calls), counts per
+                            // wave and per block, digits found, ranks left
     pv_buffer sel_list;     // {key, id} [waves][room]  the keys at or above digit 0's range, per wave
-    pv_buffer sel_state;    // u32 [8]            digits found, ranks left
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
     pv_buffer cb_f16;       // prepared codebook operand for the matrix-core filter
-    pv_buffer cb_meta;      // statistics of the codebook (scale, norms, rounding bound), counters of its norm ordering
-    pv_buffer cells;        // cells of the codebook (pv_cells.h): statistics, thresholds, counts
-    pv_buffer x_f16;        // prepared target operand [k_pad / 32][2][32][8] halves
-    pv_buffer x_meta;       // f32 [k_pad][4]     per-group bounds and flags
+    pv_buffer cb_meta;      // statistics of the codebook (scale, norms, rounding bound), counters of its norm ordering;
+                            // those of its cells (pv_cells.h)
+    pv_buffer x_f16;        // prepared target operand [k_pad / 32][2][32][8] halves, bounds and flags f32 [k_pad][4],
+                            // staged rows f32 [k_pad][g + 4], squared reach f32 [k_pad]
     pv_buffer partials;     // i32 [P][k_pad][2]  best / runner-up keys per partition
     pv_buffer fb_list;      // counters (work-item hand-out) and, for the beam path, the groups left to the exact kernel
     pv_buffer rr_counts;    // u32 [blocks][4]    per-block counters of the re-rank kernel

@@ -2042,13 +2042,15 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     const size_t nmin_off = bounds_off + 256;
     const size_t cnorm_off = (nmin_off + (size_t)nsu_alloc * 4 + 255) & ~(size_t)255;   // g = 16: norm per position
     if ((st = pv_ensure(ctx, ctx->cb_f16, cnorm_off + (size_t)p.cpad * 4)) != PV_OK) return st;
-    if ((st = pv_ensure(ctx, ctx->cb_meta, (kCbWords + 8) * sizeof(unsigned), /*zero_new=*/true)) != PV_OK) return st;
-    if (cells && (st = pv_ensure(ctx, ctx->cells, kCellWords * 4, /*zero_new=*/true)) != PV_OK) return st;
-    if ((st = pv_ensure(ctx, ctx->x_f16, (size_t)p.k_pad * 32)) != PV_OK) return st;
-    // per-group bounds, then the staged targets / scale / code / id of each group
-    const size_t stage_off = (size_t)p.k_pad * 4 * sizeof(float);
+    // one allocation for what is zeroed once, one for what each group needs: every new buffer costs
+    // the first call of a context about 10 us
+    const size_t cells_off = ((kCbWords + 8) * sizeof(unsigned) + 255) & ~(size_t)255;
+    if ((st = pv_ensure(ctx, ctx->cb_meta, cells_off + kCellWords * 4, /*zero_new=*/true)) != PV_OK) return st;
+    // operands, per-group bounds, the staged targets / scale / code / id of each group
+    const size_t meta_off = (size_t)p.k_pad * 32;
+    const size_t stage_off = meta_off + (size_t)p.k_pad * 4 * sizeof(float);
     const size_t reach_off = stage_off + (size_t)p.k_pad * (g + 4) * sizeof(float);
-    if ((st = pv_ensure(ctx, ctx->x_meta, reach_off + (cells ? (size_t)p.k_pad * sizeof(float) : 0))) != PV_OK) return st;
+    if ((st = pv_ensure(ctx, ctx->x_f16, reach_off + (cells ? (size_t)p.k_pad * sizeof(float) : 0))) != PV_OK) return st;
     if ((st = pv_ensure(ctx, ctx->partials, (size_t)p.k_pad * p.P * sizeof(int2))) != PV_OK) return st;
     if ((st = pv_ensure(ctx, ctx->fb_list, 64)) != PV_OK) return st;
     const int rr_blocks = (int)((k * rerank_team(l->group_size) + kBlock - 1) / kBlock);
@@ -2072,7 +2074,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     mem.count = reinterpret_cast<unsigned *>(mem.anchor + 16);
     mem.cursor = mem.count + kCbCopies * (kNormBins / 2);
     unsigned *cb_meta = mem.cursor + kCbCopies * (kNormBins / 2);
-    float *x_meta = static_cast<float *>(ctx->x_meta.ptr);
+    float *x_meta = reinterpret_cast<float *>(static_cast<char *>(ctx->x_f16.ptr) + meta_off);
     float *x_stage = x_meta + (size_t)p.k_pad * 4;
     int2 *partials = static_cast<int2 *>(ctx->partials.ptr);
     unsigned *fb_count = reinterpret_cast<unsigned *>(ctx->fb_list.ptr);       // 4 counters
@@ -2093,7 +2095,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     ga.X = X;
     ga.x_meta = x_meta;
     ga.x_stage = x_stage;
-    ga.reach = cells ? reinterpret_cast<float *>(static_cast<char *>(ctx->x_meta.ptr) + reach_off) : nullptr;
+    ga.reach = cells ? reinterpret_cast<float *>(static_cast<char *>(ctx->x_f16.ptr) + reach_off) : nullptr;
     ctx->rr_blocks_last = rr_blocks;
     clear_args ca;
     ca.stats = stats;
@@ -2106,7 +2108,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
         unsigned *meta = cb_meta;
         int *su_bounds = reinterpret_cast<int *>(cbase + bounds_off);
         cell_mem cm;
-        cm.part = static_cast<pv_f4 *>(ctx->cells.ptr);
+        cm.part = reinterpret_cast<pv_f4 *>(static_cast<char *>(ctx->cb_meta.ptr) + cells_off);
         cm.dpart = reinterpret_cast<float *>(cm.part + kCbParts);
         cm.theta = cm.dpart + kCbParts;
         cm.count = reinterpret_cast<unsigned *>(cm.theta + 16);

@@ -940,19 +940,16 @@ pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, cons
     }
     sel_bufs bufs;
     bufs.plan = make_sel_plan(N, k, /*lists=*/true);
-    st = pv_ensure(ctx, ctx->sel_hist, (size_t)kHistTotal * sizeof(unsigned), /*zero_new=*/true);
+    // histograms, counts and state have fixed sizes: one allocation
+    st = pv_ensure(ctx, ctx->sel_hist, (kHistTotal + kSelCountWords + 8) * sizeof(unsigned), /*zero_new=*/true);
     if (st != PV_OK) return st;
-    st = pv_ensure(ctx, ctx->sel_blocks, kSelCountWords * sizeof(unsigned));
-    if (st != PV_OK) return st;
-    st = pv_ensure(ctx, ctx->sel_list, (size_t)bufs.plan.blocks * kSelWaves * bufs.plan.cap * sizeof(uint2));
-    if (st != PV_OK) return st;
-    st = pv_ensure(ctx, ctx->sel_state, 8 * sizeof(unsigned));
-    if (st != PV_OK) return st;
+    const size_t list_bytes = (size_t)bufs.plan.blocks * kSelWaves * bufs.plan.cap * sizeof(uint2);
+    if (list_bytes && (st = pv_ensure(ctx, ctx->sel_list, list_bytes)) != PV_OK) return st;
     bufs.scores = scores;
     bufs.hist = static_cast<unsigned *>(ctx->sel_hist.ptr);
-    bufs.counts = static_cast<unsigned *>(ctx->sel_blocks.ptr);
+    bufs.counts = bufs.hist + kHistTotal;
     bufs.list = static_cast<uint2 *>(ctx->sel_list.ptr);
-    bufs.state = static_cast<unsigned *>(ctx->sel_state.ptr);
+    bufs.state = bufs.counts + kSelCountWords;
     bufs.norm = norm;
     return select_run(ctx, l, T, W, k, out_idx, bufs, G, alpha, adam, m, v);
 }
