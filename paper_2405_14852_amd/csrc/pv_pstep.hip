@@ -291,6 +291,12 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
     const int64_t n_lo = v_lo / vpg;
     const unsigned row0 = (unsigned)(n_lo / gpr), rem0 = (unsigned)(n_lo - (int64_t)row0 * gpr);
     const double inv_gpr = 1.0 / (double)gpr;
+    // vectors of so many groups of a row, as a 32-bit number: a row beyond 2^30 vectors has no end in
+    // the wave's range (per_wave is below 2^30: G would not fit the memory otherwise)
+    auto row_vecs = [&](int groups) {
+        const int64_t n = (int64_t)groups * vpg;
+        return n < (1 << 30) ? (int)n : 1 << 30;
+    };
     const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(G) + v_lo;
     const pv_f4 *C4 = reinterpret_cast<const pv_f4 *>(codebooks);
     const uint16_t *codes0 = codes + n_lo * M;
@@ -325,7 +331,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
         __syncthreads();
         const bool rows = ROWS && attempt == 0;
         unsigned cur = row0;
-        int row_end = (int)((unsigned)gpr - rem0) * (int)vpg;
+        int row_end = row_vecs(gpr - (int)rem0);           // in vectors from the wave's first
         double acc = 0.0;
         gb = sb = 0u;
         for (int v0 = 0; v0 < len; v0 += 64 * kSmallAhead) {
@@ -398,7 +404,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
                     }
                     if (ends) {
                         ++cur;
-                        row_end += gpr * (int)vpg;
+                        row_end += row_vecs(gpr);
                     }
                 }
             }

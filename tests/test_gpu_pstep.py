@@ -198,6 +198,42 @@ def test_codebook_grads_small_codebook_route_unit_and_rows(g, M, B, shape, head)
     assert np.array_equal(gs.view(np.uint32), gs2.view(np.uint32))
 
 
+@pytest.mark.parametrize("rows,columns", [(1, 1 << 33), (2, 1 << 32)])
+def test_codebook_grads_small_codebook_route_of_a_row_beyond_32_bit_vectors(rows, columns):
+    """2^31 vectors of 16 bytes in a row: no 32-bit count of a row's vectors holds it.  (2 x 2^32 is
+    the largest row that fits, and the row's end lies between two waves.)"""
+    from paper_2405_14852_amd import Layout, PVContext
+    if torch.cuda.mem_get_info()[0] < 48 << 30:
+        pytest.skip("needs 48 GiB of device memory")
+    lay = Layout(rows, columns, 8, 1, 4)
+    rng = np.random.default_rng(91)
+    at = np.unique(np.concatenate([rng.integers(0, rows * columns, 4000), [0, rows * columns - 1, columns - 1]]))
+    val = rng.standard_normal(at.size).astype(np.float32)
+    G = torch.zeros(rows * columns, device=DEV)
+    at_d = torch.from_numpy(at).to(DEV)
+    G[at_d] = dev_f32(val)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(91)
+    codes = torch.randint(0, 16, (rows * columns // 8,), generator=gen, device=DEV, dtype=torch.int16)
+    cb = rng.standard_normal((1, 16, 8)).astype(np.float32)
+    sc = (rng.random(rows) + 0.5).astype(np.float32)
+    gc = torch.full((1, 16, 8), 7.0, device=DEV)
+    gs = torch.full((rows,), 7.0, device=DEV)
+    ctx = PVContext(0)
+    ctx.pv_codebook_grads(lay, G.view(rows, columns), codes.view(torch.uint16).view(rows, columns // 8, 1),
+                          dev_f32(cb), dev_f32(sc), gc, gs)
+    torch.cuda.synchronize()
+    code, row, e = codes[at_d // 8].cpu().numpy(), at // columns, at % 8
+    want = np.zeros((16, 8))
+    np.add.at(want, (code, e), sc[row].astype(np.float64) * val)
+    want_s = np.zeros(rows)
+    np.add.at(want_s, row, val.astype(np.float64) * cb[0, code, e])
+    # a term is rounded at 2^-41 of the block's bound, at most 4000 of them an entry
+    assert (np.abs(gc.cpu().numpy()[0] - want) <= 2 * np.spacing(np.abs(want).astype(np.float32)) + 1e-8).all()
+    assert close_sum(gs.cpu().numpy(), want_s, np.abs(val).sum() * np.abs(cb).max())
+    ctx.close()
+
+
 def test_codebook_grads_of_an_empty_matrix_are_zero():
     from paper_2405_14852_amd import Layout, PVContext
     ctx = PVContext(0)
