@@ -194,29 +194,32 @@ __global__ __launch_bounds__(kBlock) void k_pg_long(const int32_t *__restrict__ 
 // FIXED POINT: every term is scaled by a power of two that leaves room for the number of terms
 // one block can add, and rounded to an integer once; integer addition is associative, so a
 // table is a function of the block's inputs only.  The unit comes from the block's FIRST vectors (16
-// places spread over its range), with kSmallSlack bits to spare, instead of a pass of its own for
-// the largest |G|; the largest product met is taken on the way, and a block that met one beyond
-// the room (rows of zeros first, a gradient that grows 64-fold) clears its table and sweeps its
-// range again with the unit of what it met.  A term keeps at least min(62 - headroom, 50) - 6
-// bits (41 for 2^14 groups a block) below the block's largest product, so a sum differs from the
-// exact one by far less than the rounding of a sequential double loop to fp32 does.  The blocks'
-// tables are added in double in a fixed order.  Gradients or scales that are not finite make every
-// entry NaN.  A row's products are summed by the waves that meet it, lanes first, and added in
-// order of the waves.
+// places spread over its range) instead of a pass of its own: the bound is the block's largest |scale|
+// times its largest |G|, 2^ex, and a term keeps kbits = min(62 - headroom, 50) bits below it (48 for 2^14
+// groups a block).  Up to twice 2^ex everything still fits 64 bits.  The sweep takes the true bound on
+// its way: a block that met more looks for the vectors beyond the room, takes away what they added
+// (wrapped integers, but the same ones again), shifts the table to the unit of the true bound, once, and adds them in that.
+// 11008 x 4096: no block for bell-shaped gradients, one or two vectors in a third of the blocks for
+// Student's t with three degrees of freedom.  Only where they are more than a short list holds or the
+// first vectors were all zero the block sweeps its range again.  So no term is
+// rounded more coarsely than with the unit of the whole matrix's bound.  The blocks' tables are
+// added with the rounding errors carried along, and the total is rounded to fp32.  Gradients or
+// scales that are not finite make every entry NaN.  A row's products are summed by the waves that
+// meet it, lanes first, and added in order of the waves.
 // Bound by the LDS atomics (sixteen per group and codebook: 53 us at 11008 x 4096, 2 x 8, where
 // reading G takes 36); the vector ALU works meanwhile (23 M instructions, 37 us).  There, with the
 // scale gradient (and the maxima) as a kernel of its own that read G first: 98.7 us a step, in one
-// pass 68.3.  Ordering tiles of groups by code in LDS and summing in registers, without these
+// pass 71.  Gradients with heavy tails (cubed normal, Student's t): 78 and 84.  Ordering tiles of groups by code in LDS and summing in registers, without these
 // atomics, was tried: 112 us, one block of 16 waves per compute unit waiting at its barriers.
 constexpr int kSmallBlock = 1024;                         // one table serves sixteen waves
 constexpr int kSmallWaves = kSmallBlock / 64;
 constexpr int kSmallAhead = 2;                            // vectors of a thread in flight
-constexpr int kSmallSlack = 6;                            // bits of room above the first vectors' largest product
+constexpr unsigned kSmallOver = 512;                      // vectors beyond the unit's room that a block lists
 
 struct small_mem {
-    double *partial;     // [blocks][entries]
+    long long *partial;  // [blocks][entries]
     double *rows;        // [rows + waves] part of row r that wave w met, at r + w
-    unsigned *poison;    // [blocks]
+    double *unit;        // [blocks] what one in `partial` stands for; NaN: some input was not finite
 };
 
 // x + 1.5 * 2^52 holds the integer nearest to x (ties to even) in its low mantissa bits for
@@ -278,6 +281,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
 {
     extern __shared__ unsigned long long tab[];         // [M][2^B][g]
     __shared__ unsigned s_max[2 * kSmallWaves];
+    __shared__ unsigned s_over, s_list[kSmallOver];     // places in the block's range
     const int csize = 1 << nbits;
     const unsigned mask = (unsigned)csize - 1u;
     const int entries = M * csize * g;
@@ -316,18 +320,34 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
             sb = max(sb, __float_as_uint(fabsf(scales[row0 + pv_row_of(rem0 + (unsigned)v / vpg, inv_gpr)])));
         }
     }
+    // adds one vector to the table: elements q4 * 4 .. of a group (its first two codes fetched already)
+    // (scale and unit in ss: a power of two, exact); NEGATE: takes away what the same call added
+    auto add_terms = [&](const pv_f4 &x, double ss, unsigned q4, const unsigned (&c01)[2], const uint16_t *group_codes,
+                         bool negate = false) {
+        unsigned long long term[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            term[e] = fixed_point_term(ss * (double)x[e]);
+            if (negate) term[e] = 0ull - term[e];
+        }
+        for (int m = 0; m < M; ++m) {
+            const unsigned c = m < 2 ? c01[m] : group_codes[m] & mask;
+            unsigned long long *row = tab + ((size_t)m * csize + c) * g;
+            const unsigned sw = (c >> 2) & swm;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) atomicAdd(&row[(q4 * 4u + e) ^ sw], term[e]);
+        }
+    };
     double X = block_bound(gb, sb, s_max);
     int ex = 0;
-    double down = 0.0;
-    unsigned bad = 0u;
+    double unit = 0.0;
     for (int attempt = 0; attempt < 2; ++attempt) {
         const bool some = X > 0.0 && X < __builtin_huge_val();
         (void)frexp(some ? X : 0.0, &ex);                  // X < 2^ex
-        if (attempt == 0) ex += kSmallSlack;
-        const double limit = some ? ldexp(1.0, ex) : 0.0;
         const double up = some ? ldexp(1.0, kbits - ex) : 0.0;
-        down = some ? ldexp(1.0, ex - kbits) : 0.0;
+        unit = some ? ldexp(1.0, ex - kbits) : 0.0;
         for (int e = threadIdx.x; e < entries; e += kSmallBlock) tab[e] = 0ull;
+        if (threadIdx.x == 0) s_over = 0u;
         __syncthreads();
         const bool rows = ROWS && attempt == 0;
         unsigned cur = row0;
@@ -363,19 +383,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
                 gb = max(max(gb, __float_as_uint(fabsf(gv[u].x))), __float_as_uint(fabsf(gv[u].y)));
                 gb = max(max(gb, __float_as_uint(fabsf(gv[u].z))), __float_as_uint(fabsf(gv[u].w)));
                 sb = max(sb, in ? __float_as_uint(fabsf(sf)) : 0u);
-                if (in) {
-                    const double ss = (double)sf * up;     // a power of two: exact
-                    unsigned long long term[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) term[e] = fixed_point_term(ss * (double)gv[u][e]);
-                    for (int m = 0; m < M; ++m) {
-                        const unsigned c = m < 2 ? c01[u][m] : codes0[(size_t)nl[u] * M + m] & mask;
-                        unsigned long long *row = tab + ((size_t)m * csize + c) * g;
-                        const unsigned sw = (c >> 2) & swm;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) atomicAdd(&row[(q4[u] * 4u + e) ^ sw], term[e]);
-                    }
-                }
+                if (in) add_terms(gv[u], (double)sf * up, q4[u], c01[u], codes0 + (size_t)nl[u] * M);
                 if constexpr (ROWS) {
                     const bool ends = at + 64 > row_end;
                     if (rows) {
@@ -414,19 +422,74 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
             if (lane == 0) mem.rows[(size_t)cur + wave] = total;
         }
         X = block_bound(gb, sb, s_max);                    // what the block did meet
-        bad = X < __builtin_huge_val() ? 0u : 1u;
-        if (bad || X <= limit) break;
+        if (!(X < __builtin_huge_val())) unit = __builtin_nan("");
+        // terms up to the limit stay below 2^51 and their sums below 2^63
+        if (__builtin_expect(unit != unit || X <= unit * ldexp(1.99, kbits), 1)) break;
+        if (some) {
+            const double limit = ldexp(1.99, kbits);
+            for (int v = lane; v < len; v += 64) {
+                const unsigned n = (unsigned)v / vpg;
+                const pv_f4 x = G4[v];
+                const double ss = (double)scales[row0 + pv_row_of(rem0 + n, inv_gpr)] * up;
+                if (fabs(ss) * (double)fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) > limit) {
+                    const unsigned i = atomicAdd(&s_over, 1u);
+                    unsigned c[2];
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) c[m] = m < M ? codes0[(size_t)n * M + m] & mask : 0u;
+                    if (i < kSmallOver) {
+                        s_list[i] = (threadIdx.x >> 6) * (unsigned)per_wave + (unsigned)v;
+                        add_terms(x, ss, (unsigned)v - n * vpg, c, codes0 + (size_t)n * M, true);
+                    }
+                }
+            }
+            __syncthreads();
+            const unsigned over = s_over;
+            if (over <= kSmallOver) {
+                // the unit of the true bound (2^shift of the old): the table is rounded to it, the list added
+                int to = 0;
+                (void)frexp(X, &to);
+                const int shift = to - ex;
+                for (int e = threadIdx.x; e < entries; e += kSmallBlock) {
+                    const long long t = (long long)tab[e];
+                    tab[e] = shift < 64 ? (unsigned long long)((t >> shift) + ((t >> (shift - 1)) & 1)) : 0ull;
+                }
+                unit = ldexp(1.0, to - kbits);
+                __syncthreads();
+                for (unsigned i = threadIdx.x; i < over; i += kSmallBlock) {
+                    const int64_t v = (int64_t)blockIdx.x * kSmallWaves * per_wave + s_list[i];
+                    const int64_t n = v / vpg;
+                    unsigned c[2];
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) c[m] = m < M ? codes[n * M + m] & mask : 0u;
+                    const pv_f4 x = reinterpret_cast<const pv_f4 *>(G)[v];
+                    add_terms(x, (double)scales[n / gpr] * ldexp(1.0, kbits - to), (unsigned)(v - n * vpg), c, codes + n * M);
+                }
+                __syncthreads();
+                break;
+            }
+        }
+        __syncthreads();                                   // s_over was read
     }
-    double *out = mem.partial + (int64_t)blockIdx.x * entries;
+    long long *out = mem.partial + (int64_t)blockIdx.x * entries;
     for (int e = threadIdx.x; e < entries; e += kSmallBlock) {
         const unsigned sw = ((((unsigned)e / (unsigned)g) & mask) >> 2) & swm;   // the code within its codebook, as on the way in
-        out[e] = (double)(long long)tab[(unsigned)e ^ sw] * down;
+        out[e] = (long long)tab[(unsigned)e ^ sw];
     }
-    if (threadIdx.x == 0) mem.poison[blockIdx.x] = bad;
+    if (threadIdx.x == 0) mem.unit[blockIdx.x] = unit;
 }
 
-// adds the blocks' tables (16 threads per entry, each a slice of the blocks, in an order of their own)
-// and rounds once; the blocks from `eblocks` on add the waves' parts of a row each thread
+// sum + error, the rounding error of the addition kept (Knuth)
+__device__ __forceinline__ void add_keeping_error(double &sum, double &error, double v)
+{
+    const double t = sum + v, b = t - sum;
+    error = error + ((sum - (t - b)) + (v - b));
+    sum = t;
+}
+
+// adds the blocks' tables (16 threads per entry, each a slice of the blocks) and rounds once: upper
+// and lower half of an integer are exact as doubles, the upper halves' sum keeps its rounding errors
+// and the lower halves' sum has bits to spare.  The blocks from `eblocks` on add the waves' parts of a
+// row each thread.
 constexpr int kSlices = 16;
 __global__ __launch_bounds__(kBlock) void k_pg_small_final(small_mem mem, int blocks, int entries, int eblocks,
                                                            int rows, int64_t row_vecs, int per_wave,
@@ -442,29 +505,37 @@ __global__ __launch_bounds__(kBlock) void k_pg_small_final(small_mem mem, int bl
         grad_scales[r] = (float)total;
         return;
     }
-    __shared__ double s_sum[kSlices][kBlock / kSlices];
+    __shared__ double s_sum[kSlices][kBlock / kSlices], s_err[kSlices][kBlock / kSlices];
     const int col = threadIdx.x % (kBlock / kSlices), sl = threadIdx.x / (kBlock / kSlices);
     const int e = blockIdx.x * (kBlock / kSlices) + col;
-    double total = 0.0;
+    double total = 0.0, error = 0.0;
     if (e < entries) {
         for (int b0 = sl; b0 < blocks; b0 += kSlices * 8) {
-            double p[8];
+            long long p[8];
+            double unit[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int b = b0 + u * kSlices;
-                p[u] = b < blocks ? mem.partial[(int64_t)b * entries + e] : 0.0;
+                p[u] = b < blocks ? mem.partial[(int64_t)b * entries + e] : 0;
+                unit[u] = b < blocks ? mem.unit[b] : 0.0;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) total = total + p[u];
+            for (int u = 0; u < 8; ++u) {
+                add_keeping_error(total, error, (double)(int)(p[u] >> 32) * (unit[u] * 4294967296.0));
+                error = error + (double)(unsigned)p[u] * unit[u];
+            }
         }
     }
     s_sum[sl][col] = total;
-    unsigned bad = 0u;
-    for (int b = threadIdx.x; b < blocks; b += kBlock) bad |= mem.poison[b];
-    bad = (unsigned)__syncthreads_or((int)bad);
+    s_err[sl][col] = error;
+    __syncthreads();
     if (sl == 0 && e < entries) {
-        for (int q = 1; q < kSlices; ++q) total = total + s_sum[q][col];
-        out[e] = bad ? __builtin_nanf("") : (float)total;
+        for (int q = 1; q < kSlices; ++q) {
+            add_keeping_error(total, error, s_sum[q][col]);
+            error = error + s_err[q][col];
+        }
+        total = total + error;
+        out[e] = total == total ? (float)total : __builtin_nanf("");
     }
 }
 
@@ -577,17 +648,18 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
         const int blocks = (int)blocks64, waves = blocks * kSmallWaves;
         const int unit = 64 * vpg;
         const int per_wave = (int)((nvec + (int64_t)waves * unit - 1) / ((int64_t)waves * unit)) * unit;
-        int headroom = 1;                                 // 2^headroom > terms one block adds to an entry
-        while (((int64_t)1 << headroom) <= (int64_t)per_wave / vpg * kSmallWaves) ++headroom;
+        const int64_t most = (int64_t)per_wave / vpg * kSmallWaves;  // terms one block adds to an entry
+        int headroom = 1;
+        while (((int64_t)1 << headroom) < (most < N ? most : N)) ++headroom;
         const int kbits = 62 - headroom < 50 ? 62 - headroom : 50;   // bits of a term below the bound
         const bool rows = grad_scales && l->in_features >= 256;      // 64 vectors a row
         const size_t o_rows = align_up((size_t)blocks * entries * 8);
-        const size_t o_bad = o_rows + align_up(((size_t)l->out_features + waves) * 8);
-        pv_status st2 = pv_ensure(ctx, ctx->pstep, o_bad + (size_t)blocks * 4);
+        const size_t o_unit = o_rows + align_up(((size_t)l->out_features + waves) * 8);
+        pv_status st2 = pv_ensure(ctx, ctx->pstep, o_unit + (size_t)blocks * 8);
         if (st2 != PV_OK) return st2;
         char *p = static_cast<char *>(ctx->pstep.ptr);
-        const small_mem mem{reinterpret_cast<double *>(p), reinterpret_cast<double *>(p + o_rows),
-                            reinterpret_cast<unsigned *>(p + o_bad)};
+        const small_mem mem{reinterpret_cast<long long *>(p), reinterpret_cast<double *>(p + o_rows),
+                            reinterpret_cast<double *>(p + o_unit)};
         pv_timed t(ctx, PV_K_PSTEP);
         if (grad_scales && !rows)
             hipLaunchKernelGGL(k_pg_scales<true>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,

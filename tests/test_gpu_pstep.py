@@ -180,22 +180,100 @@ def test_codebook_grads_small_codebook_route_shapes(g, M, B, shape):
 @pytest.mark.parametrize("head", ["plain", "zero", "small"])
 def test_codebook_grads_small_codebook_route_unit_and_rows(g, M, B, shape, head):
     """The unit of a block's sums is set by its first vectors: rows of zeros there, or values 2^40
-    below the rest, make the block sweep again.  Rows that end inside, at and beyond a wave step.
-    Bounds: a term is rounded at 2^-41 of the largest product, sums of up to 2^20 terms."""
+    below the rest.  Rows that end inside, at and beyond a wave step."""
     wl = workloads.make(shape[0], shape[1], g, M, B, seed=90, sigma_g=1e-2)
     if head != "plain":
         flat = wl.G.reshape(-1)
         flat[:flat.size - 64] *= np.float32(0.0 if head == "zero" else 2.0 ** -40)
     gc, gs, gc_ref, gs_ref = run_case(wl)
-    top = np.abs(wl.G).max() * np.abs(wl.scales).max()
-    terms = np.bincount(wl.codes[..., 0].ravel(), minlength=1 << B).max()
-    tol = 2 * np.spacing(np.abs(gc_ref)) + 2.0 ** -41 * top * terms
-    assert (np.abs(gc.astype(np.float64) - gc_ref.astype(np.float64)) <= tol).all()
+    want, tol = exact_small_route(wl)
+    assert (np.abs(gc - want) <= tol).all()
+    if head == "small" and wl.layout.num_groups > 8192:     # a block of its own for most of the head
+        lost = wl.G.copy()
+        lost.reshape(-1)[:-64] = 0.0
+        assert (np.abs(exact_small_route(wl, lost)[0] - want) > tol).any()
     q = oracle.dequantize(wl.codes, wl.codebooks, np.ones_like(wl.scales))
     assert close_sum(gs, gs_ref, np.abs(wl.G * q).sum(axis=1))
     again, gs2, _, _ = run_case(wl)
     assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
     assert np.array_equal(gs.view(np.uint32), gs2.view(np.uint32))
+
+
+def small_route_blocks(wl):
+    """Vectors of 16 bytes that a wave takes, and the block of every group (of the route that keeps
+    its sums in blocks: at most 512 of them, 4096 groups or more each, 16 waves)."""
+    N, vpg = wl.layout.num_groups, wl.layout.group_size // 4
+    blocks = min((N + 4095) // 4096, 512)
+    step = blocks * 16 * 64 * vpg
+    per_wave = (N * vpg + step - 1) // step * 64 * vpg
+    return per_wave, np.arange(N) * vpg // (16 * per_wave)
+
+
+def exact_small_route(wl, G=None):
+    """The codebook gradient in extended precision, and how far from it the route may be: half an ulp
+    of the result, and a term's rounding: half a unit, 2^-48 of the bound of its block (max |s| times
+    max |G|) at up to 2^14 groups a block, twice where the table is shifted to a larger unit."""
+    lay, M, (_, csize, g) = wl.layout, wl.codebooks.shape[0], wl.codebooks.shape
+    G = (wl.G if G is None else G).reshape(lay.num_groups, g)
+    s = np.repeat(wl.scales, lay.groups_per_row).astype(np.longdouble)
+    block = small_route_blocks(wl)[1]
+    bound = np.zeros(block.max() + 1)
+    size = np.zeros_like(bound)
+    np.maximum.at(bound, block, np.abs(G).max(axis=1).astype(np.float64))
+    np.maximum.at(size, block, s.astype(np.float64))
+    want = np.zeros((M, csize, g), np.longdouble)
+    tol = np.zeros((M, csize, 1))
+    for m in range(M):
+        c = wl.codes.reshape(-1, M)[:, m]
+        np.add.at(want[m], c, s[:, None] * G)
+        np.add.at(tol[m], c, (2.0 ** -47 * bound * size)[block][:, None])
+    return want, tol + 0.501 * np.spacing(np.abs(want).astype(np.float32))
+
+
+@pytest.mark.parametrize("rows", [8, 64])     # one block, four blocks
+def test_codebook_grads_small_codebook_route_keeps_what_cancels(rows):
+    """Large terms that cancel exactly, in one block and from block to block, beside terms 2^-44 of
+    their size: a unit 2^-50 of the bound keeps six bits of those (2^14 groups: kbits = 50)."""
+    wl = workloads.make(rows, 2048, 8, 1, 3 if rows == 8 else 4, seed=92, sigma_g=1e-2)
+    rng = np.random.default_rng(92)
+    wl.scales[:] = 1.0
+    n = rows // 2 - rows // 8
+    wl.G[:n] = rng.uniform(0.5, 0.99, (n, 2048))
+    wl.G[n:2 * n] = -wl.G[:n]
+    wl.codes[n:2 * n] = wl.codes[:n]
+    wl.G[2 * n:] = rng.standard_normal((rows - 2 * n, 2048)) * 2.0 ** -44
+    want = np.zeros(wl.codebooks.shape[1:], np.float64)
+    np.add.at(want, wl.codes[2 * n:].ravel(), wl.G[2 * n:].reshape(-1, 8).astype(np.float64))
+    terms = np.bincount(wl.codes[2 * n:].ravel(), minlength=want.shape[0])[:, None]
+    order = rng.permutation(rows)
+    wl.G[:], wl.codes[:] = wl.G[order], wl.codes[order]
+    gc, _, _, _ = run_case(wl)
+    assert (np.abs(gc[0] - want) <= terms * 2.0 ** -51 + np.spacing(np.abs(want).astype(np.float32))).all()
+
+
+@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 4, (64, 2048)), (8, 3, 5, (65, 2040)), (16, 1, 6, (128, 1024))])
+@pytest.mark.parametrize("kind", ["few", "huge", "full", "many"])
+def test_codebook_grads_small_codebook_route_terms_beyond_the_room(g, M, B, shape, kind):
+    """Vectors whose terms exceed what the first vectors announced: a few (listed, the table shifted to
+    their unit, by more than 63 bits at the most), as many as the list holds, more (a second sweep)."""
+    wl = workloads.make(shape[0], shape[1], g, M, B, seed=93, sigma_g=1e-2)
+    rng = np.random.default_rng(93)
+    per_wave, _ = small_route_blocks(wl)
+    vec = wl.G.reshape(-1, 4)
+    later = np.nonzero(np.arange(len(vec)) % per_wave >= 128)[0]
+    if kind == "full":      # 512 in the first block
+        pick = rng.choice(later[later < 16 * per_wave], 512, replace=False)
+    else:
+        pick = rng.choice(later, len(later) // 2 if kind == "many" else 20, replace=False)
+    vec[pick, 1] *= np.float32(2.0 ** (75 if kind == "huge" else 9))
+    vec[pick, 1] += np.float32(4.0) * np.sign(vec[pick, 1])
+    gc, gs, _, gs_ref = run_case(wl)
+    want, tol = exact_small_route(wl)
+    assert (np.abs(gc - want) <= tol).all()
+    q = oracle.dequantize(wl.codes, wl.codebooks, np.ones_like(wl.scales))
+    assert close_sum(gs, gs_ref, np.abs(wl.G * q).sum(axis=1))
+    again, _, _, _ = run_case(wl)
+    assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
 
 
 @pytest.mark.parametrize("rows,columns", [(1, 1 << 33), (2, 1 << 32)])
@@ -228,7 +306,7 @@ def test_codebook_grads_small_codebook_route_of_a_row_beyond_32_bit_vectors(rows
     np.add.at(want, (code, e), sc[row].astype(np.float64) * val)
     want_s = np.zeros(rows)
     np.add.at(want_s, row, val.astype(np.float64) * cb[0, code, e])
-    # a term is rounded at 2^-41 of the block's bound, at most 4000 of them an entry
+    # a term is rounded at 2^-48 of the block's bound, at most 4000 of them an entry
     assert (np.abs(gc.cpu().numpy()[0] - want) <= 2 * np.spacing(np.abs(want).astype(np.float32)) + 1e-8).all()
     assert close_sum(gs.cpu().numpy(), want_s, np.abs(val).sum() * np.abs(cb).max())
     ctx.close()
