@@ -21,7 +21,7 @@ pv_status pv_fail(pv_ctx *ctx, pv_status st, const char *fmt, ...)
     return st;
 }
 
-pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, bool zero_new)
+pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head)
 {
     if (buf.bytes >= bytes && buf.ptr) return PV_OK;
     size_t want = bytes < 256 ? 256 : bytes;
@@ -34,13 +34,15 @@ pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, bool zero_new)
         want += want / 4;
     }
     void *p = nullptr;
-    if (hipMalloc(&p, want) != hipSuccess) {
+    hipError_t e = hipMalloc(&p, want);
+    if (e != hipSuccess && want > bytes) e = hipMalloc(&p, want = bytes);     // without the reserve for growth
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         return pv_fail(ctx, PV_ERR_ALLOC, "scratch allocation of %zu bytes failed", want);
     }
     buf.ptr = p;
     buf.bytes = want;
-    if (zero_new) PV_HIP(ctx, hipMemsetAsync(p, 0, want, ctx->stream));
+    if (zero_head) PV_HIP(ctx, hipMemsetAsync(p, 0, zero_head, ctx->stream));
     return PV_OK;
 }
 
@@ -126,7 +128,7 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->sel_scores, &c->sel_hist, &c->sel_list, &c->stats,
+    pv_buffer *bufs[] = {&c->select, &c->stats,
                          &c->cb_f16,     &c->cb_meta,  &c->x_f16,    &c->partials,
                          &c->fb_list, &c->rr_counts, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)

@@ -35,10 +35,9 @@ struct pv_ctx {
     std::vector<hipEvent_t> event_pool;
 
     // scratch, grown on demand (never shrunk)
-    pv_buffer sel_scores;   // f32 [N]            group scores when the caller passes none
-    pv_buffer sel_hist;     // radix-select histograms, eight copies each (kept zero between calls), counts per
-                            // wave and per block, digits found, ranks left
-    pv_buffer sel_list;     // {key, id} [waves][room]  the keys at or above digit 0's range, per wave
+    pv_buffer select;       // the selection's: histograms (kept zero between calls), counts, lists, group scores
+                            // when the caller passes none (see sel_scratch)
+    size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
     pv_buffer cb_f16;       // prepared codebook operand for the matrix-core filter
     pv_buffer cb_meta;      // statistics of the codebook (scale, norms, rounding bound), counters of its norm ordering;
@@ -62,7 +61,8 @@ struct pv_timed {
 };
 
 pv_status pv_fail(pv_ctx *ctx, pv_status st, const char *fmt, ...);
-pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, bool zero_new = false);
+// A buffer of at least `bytes`; the first `zero_head` bytes of a new block are cleared on the stream.
+pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head = 0);
 
 #define PV_HIP(ctx, call)                                                              \
     do {                                                                               \
@@ -138,6 +138,8 @@ struct pv_norm_req {
 };
 bool pv_select_norm_supported(const pv_layout *l);
 int pv_select_norm_parts();
+// where a selection among N groups without a buffer of the caller's leaves the scores
+pv_status pv_select_scores(pv_ctx *ctx, int64_t N, float **scores);
 // G != nullptr: T is an output, formed in the scoring sweep as W - alpha * G, or, with adam and
 // the moments m, v given, as W minus one Adam update of G
 pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, const float *W,

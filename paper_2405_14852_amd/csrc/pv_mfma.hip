@@ -2045,7 +2045,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     // one allocation for what is zeroed once, one for what each group needs: every new buffer costs
     // the first call of a context about 10 us
     const size_t cells_off = ((kCbWords + 8) * sizeof(unsigned) + 255) & ~(size_t)255;
-    if ((st = pv_ensure(ctx, ctx->cb_meta, cells_off + kCellWords * 4, /*zero_new=*/true)) != PV_OK) return st;
+    if ((st = pv_ensure(ctx, ctx->cb_meta, cells_off + kCellWords * 4, cells_off + kCellWords * 4)) != PV_OK) return st;
     // operands, per-group bounds, the staged targets / scale / code / id of each group
     const size_t meta_off = (size_t)p.k_pad * 32;
     const size_t stage_off = meta_off + (size_t)p.k_pad * 4 * sizeof(float);

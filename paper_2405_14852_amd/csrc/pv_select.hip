@@ -887,7 +887,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_small(const float *__restr
 // How the groups are dealt to the waves of the passes after the sweep.  A wave needs at least one
 // step of 256 keys; a list has room for a quarter of the wave's keys, twice the largest share
 // of them that a list is asked to hold on average.  With more than an eighth of all groups chosen
-// there are no lists (cap = 0).
+// there are no lists (cap = 0), nor where there is no memory for them.
 struct sel_plan {
     int blocks, span, cap;
 };
@@ -901,6 +901,12 @@ static sel_plan make_sel_plan(int64_t N, int64_t k, bool lists)
     p.cap = lists && k <= N / 8 ? p.span / 4 : 0;
     return p;
 }
+static size_t sel_list_bytes(int64_t N)      // whatever k: a later call with another k finds the same block
+{
+    if (N <= kSmallGroups) return 0;
+    const sel_plan p = make_sel_plan(N, 0, true);
+    return (size_t)p.blocks * kSelWaves * p.cap * sizeof(uint2);
+}
 // counts per region, keys above digits 0 and 1 per block, suffix counts per block
 constexpr size_t kSelCountWords = (size_t)kSelBlocks * (kSelWaves + 1 + kSuffix);
 
@@ -908,10 +914,10 @@ constexpr size_t kSelCountWords = (size_t)kSelBlocks * (kSelWaves + 1 + kSuffix)
 // the radix-select histograms (all zero when a call starts, but for the last digit's, which the
 // call clears itself), the lists and counts of the passes after the sweep, the digits found so far.
 struct sel_bufs {
-    float *scores;
-    unsigned *hist, *counts, *state;
-    uint2 *list;
-    sel_plan plan;
+    float *scores = nullptr;
+    unsigned *hist = nullptr, *counts = nullptr, *state = nullptr;
+    uint2 *list = nullptr;
+    sel_plan plan{};
     pv_norm_req *norm = nullptr;
 };
 
@@ -924,6 +930,39 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
                             int64_t k, int32_t *out_idx, const sel_bufs &bufs, const float *G,
                             float alpha, const pv_adam_t *adam, float *m, float *v);
 
+// A context's scratch, one block: histograms, counts and state | lists | scores.  Lists are
+// left out where the device has no room for them (then, and for that size from then on: a call of
+// a size that was seen before does not allocate).
+static pv_status sel_scratch(pv_ctx *ctx, int64_t N, bool own_scores, sel_bufs *b, bool *lists)
+{
+    constexpr size_t head = ((kHistTotal + kSelCountWords + 8) * sizeof(unsigned) + 255) & ~(size_t)255;
+    const size_t list = sel_list_bytes(N), rest = own_scores ? (size_t)N * sizeof(float) + 16 : 0;
+    *lists = list == 0 || ctx->select.bytes >= head + list + rest;
+    if (!*lists && head + list + rest < ctx->select_refused) {
+        *lists = pv_ensure(ctx, ctx->select, head + list + rest, kHistTotal * sizeof(unsigned)) == PV_OK;
+        if (!*lists) ctx->select_refused = head + list + rest;
+    }
+    const size_t scores_at = head + (*lists ? list : 0);
+    const pv_status st = pv_ensure(ctx, ctx->select, scores_at + rest, kHistTotal * sizeof(unsigned));
+    if (st != PV_OK) return st;
+    char *base = static_cast<char *>(ctx->select.ptr);
+    b->hist = reinterpret_cast<unsigned *>(base);
+    b->counts = b->hist + kHistTotal;
+    b->state = b->counts + kSelCountWords;
+    b->list = *lists ? reinterpret_cast<uint2 *>(base + head) : nullptr;
+    b->scores = own_scores ? reinterpret_cast<float *>(base + scores_at) : nullptr;
+    return PV_OK;
+}
+
+pv_status pv_select_scores(pv_ctx *ctx, int64_t N, float **scores)
+{
+    sel_bufs b;
+    bool lists;
+    const pv_status st = sel_scratch(ctx, N, /*own_scores=*/true, &b, &lists);
+    *scores = b.scores;
+    return st;
+}
+
 // G != nullptr: T is an OUTPUT, formed here as W - alpha * G in the same pass that scores it.
 pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, const float *W,
                            int64_t k, int32_t *out_idx, float *scores, const float *G, float alpha,
@@ -933,23 +972,12 @@ pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, cons
     pv_status st;
     if (norm && (G || !pv_select_norm_supported(l)))
         return pv_fail(ctx, PV_ERR_UNSUPPORTED, "norm request: scores-only sweep, one codebook, g = 8 or 16");
-    if (!scores) {
-        st = pv_ensure(ctx, ctx->sel_scores, (size_t)N * sizeof(float) + 16);
-        if (st != PV_OK) return st;
-        scores = static_cast<float *>(ctx->sel_scores.ptr);
-    }
     sel_bufs bufs;
-    bufs.plan = make_sel_plan(N, k, /*lists=*/true);
-    // histograms, counts and state have fixed sizes: one allocation
-    st = pv_ensure(ctx, ctx->sel_hist, (kHistTotal + kSelCountWords + 8) * sizeof(unsigned), /*zero_new=*/true);
+    bool lists;
+    st = sel_scratch(ctx, N, /*own_scores=*/!scores, &bufs, &lists);
     if (st != PV_OK) return st;
-    const size_t list_bytes = (size_t)bufs.plan.blocks * kSelWaves * bufs.plan.cap * sizeof(uint2);
-    if (list_bytes && (st = pv_ensure(ctx, ctx->sel_list, list_bytes)) != PV_OK) return st;
-    bufs.scores = scores;
-    bufs.hist = static_cast<unsigned *>(ctx->sel_hist.ptr);
-    bufs.counts = bufs.hist + kHistTotal;
-    bufs.list = static_cast<uint2 *>(ctx->sel_list.ptr);
-    bufs.state = bufs.counts + kSelCountWords;
+    bufs.plan = make_sel_plan(N, k, lists);
+    if (scores) bufs.scores = scores;
     bufs.norm = norm;
     return select_run(ctx, l, T, W, k, out_idx, bufs, G, alpha, adam, m, v);
 }

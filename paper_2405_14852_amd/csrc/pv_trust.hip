@@ -635,7 +635,8 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     size_t total = o_totals + 1024;
     pv_status st = pv_ensure(ctx, ctx->trust, total);
     if (st != PV_OK) return st;
-    st = pv_ensure(ctx, ctx->sel_scores, (size_t)N * sizeof(float) + 16);
+    float *scores = nullptr;
+    st = pv_select_scores(ctx, N, &scores);
     if (st != PV_OK) return st;
     char *base = static_cast<char *>(ctx->trust.ptr);
     tr_state *state = reinterpret_cast<tr_state *>(base + o_state);
@@ -655,7 +656,6 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     unsigned *hist = reinterpret_cast<unsigned *>(base + o_hist);
     unsigned *rowpre = reinterpret_cast<unsigned *>(base + o_rowpre);
     unsigned *totals = reinterpret_cast<unsigned *>(base + o_totals);
-    float *scores = static_cast<float *>(ctx->sel_scores.ptr);
     hipStream_t sm = ctx->stream;
 
     // ||x^k||^2 of the codes as they are now (partial sums; the gather kernel adds them up).
@@ -678,7 +678,8 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
                                codebooks, scales, N, per_block, g, M, l->nbits, gpr, norm_partial);
     }
     // candidates: the k_max groups of the selection rule (ascending ids) and every score
-    st = pv_launch_select(ctx, l, T, W, k, idx, scores, nullptr, 0.0f, nullptr, nullptr, nullptr,
+    // (into the context's own scores, at the address above)
+    st = pv_launch_select(ctx, l, T, W, k, idx, nullptr, nullptr, 0.0f, nullptr, nullptr, nullptr,
                           fused_norm ? &norm_req : nullptr);
     if (st != PV_OK) return st;
     if (fused_norm) norm_blocks = norm_req.parts;

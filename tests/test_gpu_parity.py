@@ -12,11 +12,11 @@ import torch
 
 import oracle
 import workloads
-from gpu_util import DEV, GpuRun, check_codes_on, dev_f32, dev_u16, host_u16
+from gpu_util import DEV, GpuRun, check_codes_on, dev_f32, dev_i32, dev_u16, host_u16
 
 pytestmark = pytest.mark.gpu
 
-RECON_REL = 1e-5      # spec tolerance for reconstructed weights (relative L2)
+RECON_REL = 1e-5      # tolerance for reconstructed weights (relative L2)
 
 
 def check_codes(wl, T_np, idx, got, want, info):
@@ -245,6 +245,49 @@ def test_select_all_zero_scores():
     run = GpuRun(wl)
     idx = run.select(run.W, 10)          # T == W: every score is +0
     assert np.array_equal(idx, np.arange(10, dtype=np.int32))
+
+
+def test_select_scratch_does_not_depend_on_k():
+    """A smaller k on a shape that was seen before allocates nothing (a caller may be capturing)."""
+    run = GpuRun(workloads.make(4, 64, 8, 1, 4, seed=4))
+    lay = type(run.lay)(2048, 16384, 8, 1, 4)
+    W = torch.zeros(2048, 16384, device=DEV)
+    T = torch.rand(2048, 16384, device=DEV)
+    idx = torch.empty(lay.num_groups, dtype=torch.int32, device=DEV)
+    free = []
+    for k in (lay.num_groups // 2, lay.num_groups // 100, lay.num_groups, 1):
+        run.ctx.pv_select_topk_groups(lay, T, W, k, idx)
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+    assert min(free) == max(free), free
+
+
+def test_select_without_memory_for_its_lists():
+    """The lists of candidates take 2 bytes a group: where the device has no room for them the
+    selection does without, also in later calls."""
+    run = GpuRun(workloads.make(4, 64, 8, 1, 4, seed=4))
+    rows = columns = 1 << 14
+    lay, small = type(run.lay)(rows, columns, 1, 1, 4), type(run.lay)(256, 256, 1, 1, 4)
+    W = torch.zeros(rows, columns, device=DEV)
+    T = torch.zeros(rows, columns, device=DEV)
+    scores = torch.empty(rows * columns, device=DEV)
+    rng = np.random.default_rng(5)
+    at = np.unique(rng.integers(0, rows * columns, 4000)).astype(np.int32)
+    T.view(-1)[dev_i32(at).long()] = dev_f32(rng.uniform(1.0, 2.0, at.size))
+    idx = torch.empty(at.size, dtype=torch.int32, device=DEV)
+    run.ctx.pv_select_topk_groups(small, T, W, 256, idx, scores)       # loads the kernels
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    fill = torch.empty(torch.cuda.mem_get_info()[0] - (300 << 20), dtype=torch.uint8, device=DEV)
+    try:
+        for _ in range(2):
+            idx.fill_(-1)
+            run.ctx.pv_select_topk_groups(lay, T, W, at.size, idx, scores)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), at)
+    finally:
+        del fill
+        torch.cuda.empty_cache()
 
 
 # ------------------------------------------- targets + selection in one sweep
