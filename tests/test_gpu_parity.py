@@ -278,7 +278,9 @@ def test_select_without_memory_for_its_lists():
     run.ctx.pv_select_topk_groups(small, T, W, 256, idx, scores)       # loads the kernels
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
-    fill = torch.empty(torch.cuda.mem_get_info()[0] - (300 << 20), dtype=torch.uint8, device=DEV)
+    fill = []
+    while torch.cuda.mem_get_info()[0] > 400 << 20:       # the lists of 2^28 groups take 512 MiB
+        fill.append(torch.empty(torch.cuda.mem_get_info()[0] - (300 << 20), dtype=torch.uint8, device=DEV))
     try:
         for _ in range(2):
             idx.fill_(-1)
