@@ -128,9 +128,7 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->select, &c->stats,
-                         &c->cb_f16,     &c->cb_meta,  &c->x_f16,    &c->partials,
-                         &c->fb_list, &c->rr_counts, &c->trust, &c->pstep};
+    pv_buffer *bufs[] = {&c->select, &c->stats, &c->search, &c->fb_list, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     for (auto &t : c->timers)
@@ -612,11 +610,11 @@ extern "C" pv_status pv_reencode_stats(pv_ctx *ctx, int64_t stats[4])
     int64_t host[8];
     PV_HIP(ctx, hipMemcpy(host, ctx->stats.ptr, sizeof(host), hipMemcpyDeviceToHost));
     for (int i = 0; i < 4; ++i) stats[i] = host[i];
-    if (ctx->rr_blocks_last > 0 && ctx->rr_counts.ptr) {
+    if (ctx->rr_blocks_last > 0 && ctx->rr_counts) {
         // the one-codebook filter leaves its counters per block of the re-rank kernel:
         // {decided by the filter, codes changed, candidates evaluated, finished by a scan}
         std::vector<uint32_t> per_block((size_t)ctx->rr_blocks_last * 4);
-        PV_HIP(ctx, hipMemcpy(per_block.data(), ctx->rr_counts.ptr, per_block.size() * sizeof(uint32_t),
+        PV_HIP(ctx, hipMemcpy(per_block.data(), ctx->rr_counts, per_block.size() * sizeof(uint32_t),
                               hipMemcpyDeviceToHost));
         for (int b = 0; b < ctx->rr_blocks_last; ++b) {
             stats[0] += per_block[4 * (size_t)b + 0];

@@ -61,8 +61,8 @@ struct cell_mem {
     int *cell_su;         // [cells + 1] first super-unit of a cell
     uint16_t *cell_of;    // [codewords]
 };
-constexpr size_t kCellWords = kCbParts * 4 + kCbParts + 16 + 2 * kCbCopies * kCellsMax +
-                              (kCellsMax + 8) + 65536 / 2;
+constexpr size_t kCellWords = kCbParts * 4 + kCbParts + 16 + kCbCopies * kCellsMax +
+                              (kCellsMax + 8) + 65536 / 2;     // without `count`
 
 // Bit i of a cell: the side of theta_i.  A 16-bit codebook has nine bits for eight dimensions: two of
 // them say between which thresholds of dimension 7 the coordinate lies, and stand at bits 4 and 5, so

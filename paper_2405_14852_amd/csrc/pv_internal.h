@@ -39,14 +39,9 @@ struct pv_ctx {
                             // when the caller passes none (see sel_scratch)
     size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
-    pv_buffer cb_f16;       // prepared codebook operand for the matrix-core filter
-    pv_buffer cb_meta;      // statistics of the codebook (scale, norms, rounding bound), counters of its norm ordering;
-                            // those of its cells (pv_cells.h)
-    pv_buffer x_f16;        // prepared target operand [k_pad / 32][2][32][8] halves, bounds and flags f32 [k_pad][4],
-                            // staged rows f32 [k_pad][g + 4], squared reach f32 [k_pad]
-    pv_buffer partials;     // i32 [P][k_pad][2]  best / runner-up keys per partition
-    pv_buffer fb_list;      // counters (work-item hand-out) and, for the beam path, the groups left to the exact kernel
-    pv_buffer rr_counts;    // u32 [blocks][4]    per-block counters of the re-rank kernel
+    pv_buffer search;       // the matrix-core filter's: statistics, operands, records, counters (see pv_launch_mfma_search)
+    const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel
+    pv_buffer fb_list;      // beam path: the groups left to the exact kernel
     pv_buffer trust;        // scratch of the trust-ratio call (saved codes, keys, prefix sums, sort space)
     pv_buffer pstep;        // scratch of the P-step gradients (digit histograms, keys and group ids of the sorting passes, segment starts, piece sums)
 };

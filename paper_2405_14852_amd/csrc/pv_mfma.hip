@@ -173,7 +173,7 @@ struct cb_mem {
                           // has at most 65536 / kCbCopies), zero between calls
     unsigned *cursor;     // [copies][kNormBins / 2] g = 16: codewords of a bucket placed so far
 };
-constexpr size_t kCbWords = kCbParts * 4 + kCbParts + 16 + (size_t)kCbCopies * kNormBins;
+constexpr size_t kCbWords = kCbParts * 4 + kCbParts + 16 + (size_t)kCbCopies * (kNormBins / 2);     // without `count`
 
 __device__ __forceinline__ float wave_min_f(float v)
 {
@@ -256,6 +256,10 @@ __device__ __forceinline__ void meta_of_parts(const pv_f4 *part, int nparts, uns
     __syncthreads();
 }
 
+// A slot of the changed codes' count has a line of its own: the atomics of different slots would
+// queue on a shared one (406 blocks, seven slots in one line: 1.5 us of the re-rank's 13).
+constexpr int kSlotStride = 16;
+
 // What a call counts in starts at zero: done by the call's first kernel.
 struct clear_args {
     unsigned long long *stats, *num_changed, *change_slots;
@@ -264,7 +268,7 @@ struct clear_args {
 };
 __device__ __forceinline__ void clear_counters(const clear_args &a, int block, int nblocks)
 {
-    for (int i = block * kBlock + threadIdx.x; i < a.nslots; i += nblocks * kBlock) a.change_slots[i] = 0ull;
+    for (int i = block * kBlock + threadIdx.x; i < a.nslots; i += nblocks * kBlock) a.change_slots[i * kSlotStride] = 0ull;
     if (block == 0) {
         if (threadIdx.x < 8) a.stats[threadIdx.x] = 0ull;
         if (threadIdx.x < 4) a.fb_count[threadIdx.x] = 0u;
@@ -1517,7 +1521,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
         const unsigned first = (blockIdx.x >> 6) << 6;
         const unsigned members = gridDim.x - first < 64u ? gridDim.x - first : 64u;
         const unsigned long long old =
-            atomicAdd(&change_slots[blockIdx.x >> 6], (1ull << 40) | (unsigned long long)s_cnt[1]);
+            atomicAdd(&change_slots[(blockIdx.x >> 6) * kSlotStride], (1ull << 40) | (unsigned long long)s_cnt[1]);
         if ((unsigned)(old >> 40) == members - 1u) {
             const unsigned long long total = (old & ((1ull << 40) - 1ull)) + s_cnt[1];
             if (total) atomicAdd(num_changed, total);
@@ -1885,7 +1889,7 @@ __global__ __launch_bounds__(kBlock) void k_round_top2(
         const unsigned first = (blockIdx.x >> 6) << 6;
         const unsigned members = gridDim.x - first < 64u ? gridDim.x - first : 64u;
         const unsigned long long old =
-            atomicAdd(&change_slots[blockIdx.x >> 6], (1ull << 40) | (unsigned long long)s_cnt[1]);
+            atomicAdd(&change_slots[(blockIdx.x >> 6) * kSlotStride], (1ull << 40) | (unsigned long long)s_cnt[1]);
         if ((unsigned)(old >> 40) == members - 1u) {
             const unsigned long long total = (old & ((1ull << 40) - 1ull)) + s_cnt[1];
             if (total) atomicAdd(num_changed, total);
@@ -2035,49 +2039,52 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     const int N = (int)pv_num_groups(l);
     const int nsu_alloc = 2 * p.nsu + 64;    // two norms per super-unit; the scoring kernel stages 64 at a time
     pv_status st;
-    // codebook operand, then: position -> codeword, norm buckets, smallest norm per super-unit
-    const size_t a_bytes = (size_t)p.cpad * 32;
-    const size_t perm_off = a_bytes, bucket_off = perm_off + (size_t)p.cpad * 2;
-    const size_t bounds_off = (bucket_off + (size_t)csize * 2 + 255) & ~(size_t)255;     // splits of a table of cells
-    const size_t nmin_off = bounds_off + 256;
-    const size_t cnorm_off = (nmin_off + (size_t)nsu_alloc * 4 + 255) & ~(size_t)255;   // g = 16: norm per position
-    if ((st = pv_ensure(ctx, ctx->cb_f16, cnorm_off + (size_t)p.cpad * 4)) != PV_OK) return st;
-    // one allocation for what is zeroed once, one for what each group needs: every new buffer costs
-    // the first call of a context about 10 us
-    const size_t cells_off = ((kCbWords + 8) * sizeof(unsigned) + 255) & ~(size_t)255;
-    if ((st = pv_ensure(ctx, ctx->cb_meta, cells_off + kCellWords * 4, cells_off + kCellWords * 4)) != PV_OK) return st;
-    // operands, per-group bounds, the staged targets / scale / code / id of each group
-    const size_t meta_off = (size_t)p.k_pad * 32;
-    const size_t stage_off = meta_off + (size_t)p.k_pad * 4 * sizeof(float);
-    const size_t reach_off = stage_off + (size_t)p.k_pad * (g + 4) * sizeof(float);
-    if ((st = pv_ensure(ctx, ctx->x_f16, reach_off + (cells ? (size_t)p.k_pad * sizeof(float) : 0))) != PV_OK) return st;
-    if ((st = pv_ensure(ctx, ctx->partials, (size_t)p.k_pad * p.P * sizeof(int2))) != PV_OK) return st;
-    if ((st = pv_ensure(ctx, ctx->fb_list, 64)) != PV_OK) return st;
+    // All scratch is one block (each new one costs the first call of a context about 10 us):
+    //   bucket counts, cells' counts (zero between calls: cleared once) | the rest of their tables
+    //   codebook operand, position -> codeword, norm buckets, bounds of the splits, smallest norm per
+    //   super-unit, g = 16: norm per position
+    //   groups' operands, bounds, staged targets / scale / code / id, squared reach
+    //   records | counters
+    size_t used = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = used;
+        used = (used + bytes + 255) & ~(size_t)255;
+        return at;
+    };
     const int rr_blocks = (int)((k * rerank_team(l->group_size) + kBlock - 1) / kBlock);
     const int nslots = (rr_blocks + 63) / 64;
-    if ((st = pv_ensure(ctx, ctx->rr_counts, (size_t)rr_blocks * 4 * sizeof(unsigned) + (size_t)nslots * 8 + 16)) != PV_OK)
-        return st;
-    unsigned *rr_counts = static_cast<unsigned *>(ctx->rr_counts.ptr);
-    unsigned long long *change_slots = reinterpret_cast<unsigned long long *>(
-        static_cast<char *>(ctx->rr_counts.ptr) + (((size_t)rr_blocks * 4 * sizeof(unsigned) + 7) & ~(size_t)7));
-    char *cbase = static_cast<char *>(ctx->cb_f16.ptr);
-    h8 *A = reinterpret_cast<h8 *>(cbase);
-    uint16_t *perm = reinterpret_cast<uint16_t *>(cbase + perm_off);
-    uint16_t *bucket = reinterpret_cast<uint16_t *>(cbase + bucket_off);
-    float *nmin = reinterpret_cast<float *>(cbase + nmin_off);
-    float *cnorm = reinterpret_cast<float *>(cbase + cnorm_off);
-    h8 *X = static_cast<h8 *>(ctx->x_f16.ptr);
+    const size_t count_off = take((size_t)kCbCopies * (kNormBins / 2) * 4);
+    const size_t cell_count_off = take((size_t)kCbCopies * kCellsMax * 4);
+    const size_t zero_head = used;
+    const size_t cb_off = take((kCbWords + 8) * 4), cells_off = take(kCellWords * 4);
+    const size_t a_off = take((size_t)p.cpad * 32), perm_off = take((size_t)p.cpad * 2);
+    const size_t bucket_off = take((size_t)csize * 2), bounds_off = take(256);
+    const size_t nmin_off = take((size_t)nsu_alloc * 4), cnorm_off = take((size_t)p.cpad * 4);
+    const size_t x_off = take((size_t)p.k_pad * 32), x_meta_off = take((size_t)p.k_pad * 16);
+    const size_t stage_off = take((size_t)p.k_pad * (g + 4) * 4), reach_off = take(cells ? (size_t)p.k_pad * 4 : 0);
+    const size_t partials_off = take((size_t)p.k_pad * p.P * sizeof(int2));
+    const size_t fb_off = take(64), rr_off = take((size_t)rr_blocks * 16), slots_off = take((size_t)nslots * kSlotStride * 8);
+    if ((st = pv_ensure(ctx, ctx->search, used, zero_head)) != PV_OK) return st;
+    char *base = static_cast<char *>(ctx->search.ptr);
+    unsigned *rr_counts = reinterpret_cast<unsigned *>(base + rr_off);
+    unsigned long long *change_slots = reinterpret_cast<unsigned long long *>(base + slots_off);
+    h8 *A = reinterpret_cast<h8 *>(base + a_off);
+    uint16_t *perm = reinterpret_cast<uint16_t *>(base + perm_off);
+    uint16_t *bucket = reinterpret_cast<uint16_t *>(base + bucket_off);
+    float *nmin = reinterpret_cast<float *>(base + nmin_off);
+    float *cnorm = reinterpret_cast<float *>(base + cnorm_off);
+    h8 *X = reinterpret_cast<h8 *>(base + x_off);
     cb_mem mem;
-    mem.part = static_cast<pv_f4 *>(ctx->cb_meta.ptr);
+    mem.part = reinterpret_cast<pv_f4 *>(base + cb_off);
     mem.dpart = reinterpret_cast<float *>(mem.part + kCbParts);
     mem.anchor = mem.dpart + kCbParts;
-    mem.count = reinterpret_cast<unsigned *>(mem.anchor + 16);
-    mem.cursor = mem.count + kCbCopies * (kNormBins / 2);
+    mem.cursor = reinterpret_cast<unsigned *>(mem.anchor + 16);
+    mem.count = reinterpret_cast<unsigned *>(base + count_off);
     unsigned *cb_meta = mem.cursor + kCbCopies * (kNormBins / 2);
-    float *x_meta = reinterpret_cast<float *>(static_cast<char *>(ctx->x_f16.ptr) + meta_off);
-    float *x_stage = x_meta + (size_t)p.k_pad * 4;
-    int2 *partials = static_cast<int2 *>(ctx->partials.ptr);
-    unsigned *fb_count = reinterpret_cast<unsigned *>(ctx->fb_list.ptr);       // 4 counters
+    float *x_meta = reinterpret_cast<float *>(base + x_meta_off);
+    float *x_stage = reinterpret_cast<float *>(base + stage_off);
+    int2 *partials = reinterpret_cast<int2 *>(base + partials_off);
+    unsigned *fb_count = reinterpret_cast<unsigned *>(base + fb_off);          // 4 counters
     unsigned long long *stats = static_cast<unsigned long long *>(ctx->stats.ptr);
     auto nc = reinterpret_cast<unsigned long long *>(num_changed);
     hipStream_t sm = ctx->stream;
@@ -2095,8 +2102,9 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     ga.X = X;
     ga.x_meta = x_meta;
     ga.x_stage = x_stage;
-    ga.reach = cells ? reinterpret_cast<float *>(static_cast<char *>(ctx->x_f16.ptr) + reach_off) : nullptr;
+    ga.reach = reinterpret_cast<float *>(base + reach_off);      // cells only
     ctx->rr_blocks_last = rr_blocks;
+    ctx->rr_counts = rr_counts;
     clear_args ca;
     ca.stats = stats;
     ca.num_changed = nc;
@@ -2106,13 +2114,13 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     if (cells) {
         const int cb_blocks = csize / kCbChunk;
         unsigned *meta = cb_meta;
-        int *su_bounds = reinterpret_cast<int *>(cbase + bounds_off);
+        int *su_bounds = reinterpret_cast<int *>(base + bounds_off);
         cell_mem cm;
-        cm.part = reinterpret_cast<pv_f4 *>(static_cast<char *>(ctx->cb_meta.ptr) + cells_off);
+        cm.part = reinterpret_cast<pv_f4 *>(base + cells_off);
         cm.dpart = reinterpret_cast<float *>(cm.part + kCbParts);
         cm.theta = cm.dpart + kCbParts;
-        cm.count = reinterpret_cast<unsigned *>(cm.theta + 16);
-        cm.cursor = cm.count + kCbCopies * kCellsMax;
+        cm.count = reinterpret_cast<unsigned *>(base + cell_count_off);
+        cm.cursor = reinterpret_cast<unsigned *>(cm.theta + 16);
         cm.cell_su = reinterpret_cast<int *>(cm.cursor + kCbCopies * kCellsMax);
         cm.cell_of = reinterpret_cast<uint16_t *>(cm.cell_su + kCellsMax + 8);
         {
