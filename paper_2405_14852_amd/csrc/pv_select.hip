@@ -61,7 +61,9 @@ constexpr int kSelWaves = kSelBlock / 64;
 constexpr int kSelBlocks = 256;                // at most: one block per compute unit (collect on 5.6 M scores: 12.9 us; 128 blocks 15.1, 512 blocks 16.2)
 constexpr int kAhead = 4;                      // 16-byte loads in flight per lane
 constexpr int kSuffix = kLastBins + 8;         // row of a block's suffix counts (kLastBins + 1 used)
-constexpr int kSmallGroups = 32768;            // a single block selects among at most so many
+// A single block selects among at most so many: a call with 24 576 groups 21.3 us against 22.9 by three
+// kernels, with 32 768 24.0 against 22.8 (every key is in a register: the code grows with the limit too).
+constexpr int kSmallGroups = 24576;
 
 // The key of a score: its bits, which order like the values because scores are sums of squares
 // (never negative); a pattern with the sign bit set can only be a NaN and is clamped to the
@@ -91,6 +93,27 @@ __device__ __forceinline__ void hist_add(unsigned *hist, int bin, bool valid)
     }
     if (valid) atomicAdd(&hist[bin], 1u);
 }
+
+// The later digits: few keys count as a rule, but all of them in a few bins where scores are alike (a
+// sign-like optimiser step, equal scores), and the atomics of one instruction on one address queue
+// up in the LDS.  Such a histogram is kept in 2^log copies, lane l adding to copy l % 2^log: eight
+// lanes at most on an address.  (One block, 32 768 equal scores, a whole call: 76 -> 29 us; merging the lanes
+// of a bin by ballots instead took 38, and 2.7 us more on scores that are not alike.)
+constexpr int kSpreadLog = 3;
+__device__ __forceinline__ void spread_add(unsigned *hist, unsigned bin, int log)
+{
+    atomicAdd(&hist[(bin << log) + (threadIdx.x & ((1u << log) - 1u))], 1u);
+}
+__device__ __forceinline__ unsigned spread_at(const unsigned *hist, int bin, int log)
+{
+    if (log == 0) return hist[bin];
+    unsigned t = 0;
+#pragma unroll
+    for (int c = 0; c < 1 << kSpreadLog; ++c) t += hist[(bin << kSpreadLog) + c];
+    return t;
+}
+// copies of digit 1's histogram: more than one where the keys that share digit 0 are many
+__device__ __forceinline__ int mid_log(unsigned share, int64_t N) { return (int64_t)share * 8 > N ? kSpreadLog : 0; }
 
 // inclusive prefix sum over the lanes of a wave
 __device__ __forceinline__ unsigned wave_incl_scan(unsigned v)
@@ -126,7 +149,9 @@ __device__ __forceinline__ int pick_lane(unsigned count, unsigned &kk)
 // count(> d) < kk <= count(>= d); kk becomes kk - count(> d).  Called by all threads of a block of
 // at least kCopies waves: wave c fetches the 64 counters of copy c, every wave adds up all
 // copies (the result needs no broadcast).  `tmp`: 2 * kCopies * 64 unsigneds of LDS.
-__device__ __forceinline__ int pick_digit(const unsigned *__restrict__ h, int bins, unsigned &kk, unsigned *tmp)
+// `share`: the count of the digit.
+__device__ __forceinline__ int pick_digit(const unsigned *__restrict__ h, int bins, unsigned &kk, unsigned *tmp,
+                                          unsigned *share = nullptr)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncoarse = bins / kFine;
@@ -143,20 +168,22 @@ __device__ __forceinline__ int pick_digit(const unsigned *__restrict__ h, int bi
     c = 0;
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) c += fine[i * 64 + lane];
-    return top * kFine + (kFine - 1 - pick_lane(c, kk));
+    const int at = pick_lane(c, kk);
+    if (share) *share = __shfl(c, at);
+    return top * kFine + (kFine - 1 - at);
 }
 
 // Add a block's LDS histogram to the block's copy in device memory.  An atomic instruction of a
 // wave costs by the cache lines it touches, one after the other per line: the coarse counters
 // go out in one instruction (one per wave that counted something took 5 us, all on one line).
-// `s_coarse`: 64 unsigneds of LDS.
+// `s_coarse`: 64 unsigneds of LDS; log: see spread_add.
 __device__ __forceinline__ void flush_hist(const unsigned *lh, unsigned *__restrict__ h, int bins,
-                                           unsigned *s_coarse)
+                                           unsigned *s_coarse, int log = 0)
 {
     const int copy = blockIdx.x % kCopies, lane = threadIdx.x & 63;
     unsigned *fine = h + copy * bins, *coarse = h + kCopies * bins + copy * (bins / kFine);
     for (int b = threadIdx.x; b < bins; b += blockDim.x) {   // a wave takes the kFine bins of one coarse counter
-        const unsigned v = lh[b];
+        const unsigned v = spread_at(lh, b, log);
         unsigned t = 0;
         if (__any(v != 0u)) {
             if (v) atomicAdd(&fine[b], v);
@@ -558,12 +585,43 @@ __device__ __forceinline__ region_t region_of(int r, const uint2 *list, const un
     g.n = g.raw ? (int)(left < span ? (left < 0 ? 0 : left) : span) : (int)c;
     return g;
 }
-// entry i of the region (i < n); key 0 past its end
-__device__ __forceinline__ uint2 region_at(const region_t &g, int i)
+// entry i of the region's list (i < n); key 0 past its end
+__device__ __forceinline__ uint2 list_at(const region_t &g, int i)
 {
-    if (i >= g.n) return make_uint2(0u, 0u);
-    if (!g.raw) return g.list[i];
-    return make_uint2(score_key(g.scores[g.base + i]), (unsigned)(g.base + i));
+    return i < g.n ? g.list[i] : make_uint2(0u, 0u);
+}
+// kAhead steps of a wave through scores: four consecutive ones a lane, 256 a step; 0 past the n-th
+__device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4 (&v)[kAhead])
+{
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+        const int i = at + u * 256 + (int)(threadIdx.x & 63) * 4;
+        v[u] = pv_f4{0.f, 0.f, 0.f, 0.f};
+        if (i + 4 <= n) {
+            v[u] = *reinterpret_cast<const pv_f4 *>(s + i);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e < n) v[u][e] = s[i + e];
+        }
+    }
+}
+// f(scores, place of the step's first one) for every step of a wave through n scores, the next
+// kAhead steps on their way (four bytes a lane instead: 45 M single weights, lists that do not fit, 541 us
+// a call against 426)
+template <class F>
+__device__ __forceinline__ void for_scores(const float *s, int n, pv_f4 (&cur)[kAhead], F f)
+{
+    pv_f4 nxt[kAhead];
+    for (int at = 0; at < n; at += 256 * kAhead) {
+        const bool more = at + 256 * kAhead < n;
+        if (more) load_scores(s, at + 256 * kAhead, n, nxt);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) f(cur[u], at + u * 256);
+        if (more)
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
+    }
 }
 
 // Pass over all scores: digit 0 is resolved, digit 1 of the keys that share it is counted, the
@@ -579,48 +637,39 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
                                                        unsigned *__restrict__ counts)
 {
     __shared__ unsigned tmp[2 * kCopies * 64];
-    __shared__ unsigned lh[kMidBins];
+    __shared__ unsigned lh[kMidBins << kSpreadLog];
     const int lane = threadIdx.x & 63;
     const int r = blockIdx.x * kSelWaves + (threadIdx.x >> 6);
     const int64_t base = (int64_t)r * span;
     const float *mine_scores = scores + base;
     const int n = base >= N ? 0 : (int)(N - base < span ? N - base : span);
     uint2 *mine = list + (int64_t)r * cap;
-    // keys past the region's end are 0
-    auto load = [&](int at, pv_f4 (&v)[kAhead]) {
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int i = at + u * 256 + lane * 4;
-            v[u] = pv_f4{0.f, 0.f, 0.f, 0.f};
-            if (i + 4 <= n) {
-                v[u] = *reinterpret_cast<const pv_f4 *>(mine_scores + i);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (i + e < n) v[u][e] = mine_scores[i + e];
-            }
-        }
-    };
-    pv_f4 cur[kAhead], nxt[kAhead];
-    load(0, cur);                            // in flight while digit 0 is resolved
+    pv_f4 cur[kAhead];
+    load_scores(mine_scores, 0, n, cur);     // in flight while digit 0 is resolved
     for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
     // the last digit's histogram starts at zero (its reader of the call before has run)
     for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
         hist_all[z] = 0u;
     unsigned kk = k;
-    const int d0 = pick_digit(hist_all + kHist0, kFirstBins, kk, tmp);   // its barriers also order the clearing above
+    unsigned share;
+    const int d0 = pick_digit(hist_all + kHist0, kFirstBins, kk, tmp, &share);   // its barriers also order the clearing above
+    const int log = mid_log(share, N);                       // the same in every thread
+    if (log) {
+        for (int b = kMidBins + threadIdx.x; b < kMidBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
+        __syncthreads();
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         state[4] = (unsigned)d0;
         state[6] = kk;
     }
     const unsigned lo = (unsigned)d0 << kRestBits, hi = ((unsigned)d0 + 1u) << kRestBits;
     unsigned cnt = 0;
-    auto take = [&](const pv_f4 &v, int at, bool whole) {
+    for_scores(mine_scores, n, cur, [&](const pv_f4 &v, int at) {
         const int i = at + lane * 4;
         unsigned long long hits[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)          // (a NaN with its sign bit set is above every range as it is)
-            hits[e] = __ballot(__float_as_uint(v[e]) >= lo && (whole || i + e < n));
+            hits[e] = __ballot(__float_as_uint(v[e]) >= lo && i + e < n);
         if (!(hits[0] | hits[1] | hits[2] | hits[3])) return;   // uniform over the wave
         unsigned pos = cnt;
 #pragma unroll
@@ -636,20 +685,12 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
                 const unsigned key = score_key(v[e]);
                 if (room) mine[pos] = make_uint2(key, (unsigned)(base + i + e));
                 ++pos;
-                if (key < hi) atomicAdd(&lh[(key >> kLastBits) & (kMidBins - 1)], 1u);
+                if (key < hi) spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
             }
-    };
-    for (int at = 0; at < n; at += 256 * kAhead) {
-        if (at + 256 * kAhead < n) load(at + 256 * kAhead, nxt);
-        const bool whole = at + 256 * kAhead <= n;
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) take(cur[u], at + u * 256, whole);
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
-    }
+    });
     if (lane == 0) counts[r] = cnt;
     __syncthreads();
-    flush_hist(lh, hist_all + kHist1, kMidBins, tmp);
+    flush_hist(lh, hist_all + kHist1, kMidBins, tmp, log);
 }
 
 // Digit 1 is resolved; among the keys collected, those above digits 0 and 1 are counted per
@@ -665,10 +706,10 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
                                                           unsigned *__restrict__ suffix)
 {
     __shared__ unsigned tmp[2 * kCopies * 64];
-    __shared__ unsigned lh[kLastBins];
+    __shared__ unsigned lh[kLastBins << kSpreadLog];
     __shared__ unsigned s_above;
     const int lane = threadIdx.x & 63;
-    if (threadIdx.x < kLastBins) lh[threadIdx.x] = 0;
+    for (int b = threadIdx.x; b < kLastBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
     if (threadIdx.x == 0) s_above = 0;
     // digit 0's histogram is done with: zero for the next call
     for (int z = kHist0 + blockIdx.x * kSelBlock + threadIdx.x; z < kHist1; z += gridDim.x * kSelBlock)
@@ -683,28 +724,38 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
     }
     const unsigned want = (d0 << (kRestBits - kLastBits)) | d1;
     unsigned gt = 0;
-    for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
-        unsigned key[kAhead];
+    auto count = [&](unsigned key, bool in) {
+        const unsigned p = key >> kLastBits;
+        gt += p > want;
+        if (p == want && in) spread_add(lh, key & (kLastBins - 1), kSpreadLog);
+    };
+    if (g.raw) {
+        pv_f4 cur[kAhead];
+        load_scores(g.scores + g.base, 0, g.n, cur);
+        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at) {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) key[u] = region_at(g, i0 + u * 64 + lane).x;
+            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
+        });
+    } else {
+        for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
+            unsigned key[kAhead];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const unsigned p = key[u] >> kLastBits;
-            gt += p > want;
-            if (p == want && i0 + u * 64 + lane < g.n) atomicAdd(&lh[key[u] & (kLastBins - 1)], 1u);
+            for (int u = 0; u < kAhead; ++u) key[u] = list_at(g, i0 + u * 64 + lane).x;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) count(key[u], i0 + u * 64 + lane < g.n);
         }
     }
     gt = wave_sum(gt);
     if (lane == 0 && gt) atomicAdd(&s_above, gt);
     __syncthreads();
-    flush_hist(lh, hist_all + kHist2, kLastBins, tmp);
+    flush_hist(lh, hist_all + kHist2, kLastBins, tmp, kSpreadLog);
     if (threadIdx.x == 0) above[blockIdx.x] = s_above;
     if (threadIdx.x < 64) {
         // four digits a lane, lane 0 the largest
         unsigned c[kLastBins / 64], sum = 0;
 #pragma unroll
         for (int q = 0; q < kLastBins / 64; ++q) {
-            c[q] = lh[kLastBins - 1 - (lane * (kLastBins / 64) + q)];
+            c[q] = spread_at(lh, kLastBins - 1 - (lane * (kLastBins / 64) + q), kSpreadLog);
             sum += c[q];
         }
         unsigned run = wave_incl_scan(sum) - sum;
@@ -752,14 +803,25 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
     bg = wave_sum(bg);
     be = wave_sum(be);
     unsigned gt = 0, eq = 0;
-    for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
-        unsigned key[kAhead];
+    auto count = [&](unsigned key, bool in) {
+        gt += key > thr;
+        eq += key == thr && in;
+    };
+    pv_f4 cur[kAhead];
+    if (g.raw) {
+        load_scores(g.scores + g.base, 0, g.n, cur);
+        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at) {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) key[u] = region_at(g, i0 + u * 64 + lane).x;
+            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
+        });
+        if (g.n > 256 * kAhead) load_scores(g.scores + g.base, 0, g.n, cur);   // for the second trip
+    } else {
+        for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
+            unsigned key[kAhead];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            gt += key[u] > thr;
-            eq += key[u] == thr && i0 + u * 64 + lane < g.n;
+            for (int u = 0; u < kAhead; ++u) key[u] = list_at(g, i0 + u * 64 + lane).x;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) count(key[u], i0 + u * 64 + lane < g.n);
         }
     }
     gt = wave_sum(gt);
@@ -777,10 +839,38 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
         rg += s_bg[w] + (w < wave ? s_gt[w] : 0u);
         re += s_be[w] + (w < wave ? s_eq[w] : 0u);
     }
+    if (g.raw) {
+        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at) {
+            unsigned long long bgt[4], beq[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned key = score_key(v[e]);
+                bgt[e] = __ballot(key > thr);
+                beq[e] = __ballot(key == thr && at + lane * 4 + e < g.n);
+            }
+            if (!(bgt[0] | bgt[1] | bgt[2] | bgt[3] | beq[0] | beq[1] | beq[2] | beq[3])) return;   // uniform over the wave
+            unsigned pg = rg, pe = re;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                pg = __builtin_amdgcn_mbcnt_hi((unsigned)(bgt[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bgt[e], pg));
+                pe = __builtin_amdgcn_mbcnt_hi((unsigned)(beq[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)beq[e], pe));
+                rg += (unsigned)__popcll(bgt[e]);
+                re += (unsigned)__popcll(beq[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool isg = (bgt[e] >> lane) & 1ull, ise = (beq[e] >> lane) & 1ull;
+                if (isg || (ise && pe < need)) out_idx[pg + (pe < need ? pe : need)] = (int32_t)(g.base + at + lane * 4 + e);
+                pg += isg;
+                pe += ise;
+            }
+        });
+        return;
+    }
     for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
         uint2 en[kAhead];
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) en[u] = region_at(g, i0 + u * 64 + lane);
+        for (int u = 0; u < kAhead; ++u) en[u] = list_at(g, i0 + u * 64 + lane);
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             const bool in = i0 + u * 64 + lane < g.n;
@@ -803,8 +893,8 @@ __global__ __launch_bounds__(kSelBlock) void k_select_small(const float *__restr
                                                             unsigned k, int32_t *__restrict__ out_idx)
 {
     __shared__ unsigned tmp[2 * kCopies * 64];
-    __shared__ unsigned lh[kMidBins];
-    __shared__ unsigned ll[kLastBins];
+    __shared__ unsigned lh[kMidBins << kSpreadLog];
+    __shared__ unsigned ll[kLastBins << kSpreadLog];
     __shared__ unsigned s_w[kSelWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int per = ((N + kSelBlock - 1) / kSelBlock + 3) & ~3;   // whole 16-byte vectors
@@ -827,28 +917,34 @@ __global__ __launch_bounds__(kSelBlock) void k_select_small(const float *__restr
     const int have = N - first < per ? (N - first < 0 ? 0 : N - first) : per;   // groups of this thread
     for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
     if (threadIdx.x < kLastBins) ll[threadIdx.x] = 0;
-    unsigned kk = k;
-    const unsigned d0 = (unsigned)pick_digit(hist_all + kHist0, kFirstBins, kk, tmp);
+    unsigned kk = k, share;
+    const unsigned d0 = (unsigned)pick_digit(hist_all + kHist0, kFirstBins, kk, tmp, &share);
+    const int log = mid_log(share, N);                       // the same in every thread
+    if (log) {
+        for (int b = kMidBins + threadIdx.x; b < kMidBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
+        for (int b = kLastBins + threadIdx.x; b < kLastBins << kSpreadLog; b += kSelBlock) ll[b] = 0;
+        __syncthreads();
+    }
     // a digit of an LDS histogram: 64 coarse sums by the waves, then the chosen 64 (every wave alike)
     auto pick_lds = [&](const unsigned *h, int bins) {
         const int nc = bins / kFine;
         __syncthreads();
         for (int c = wave; c < nc; c += kSelWaves) {
-            const unsigned t = wave_sum(h[c * kFine + lane]);
+            const unsigned t = wave_sum(spread_at(h, c * kFine + lane, log));
             if (lane == 0) tmp[c] = t;
         }
         __syncthreads();
         const int top = nc - 1 - pick_lane(lane < nc ? tmp[nc - 1 - lane] : 0u, kk);
-        const int d = top * kFine + (kFine - 1 - pick_lane(h[top * kFine + (kFine - 1 - lane)], kk));
+        const int d = top * kFine + (kFine - 1 - pick_lane(spread_at(h, top * kFine + (kFine - 1 - lane), log), kk));
         return (unsigned)d;
     };
 #pragma unroll
     for (int q = 0; q < kSmallPer; ++q)
-        if (q < have && (key[q] >> kRestBits) == d0) atomicAdd(&lh[(key[q] >> kLastBits) & (kMidBins - 1)], 1u);
+        if (q < have && (key[q] >> kRestBits) == d0) spread_add(lh, (key[q] >> kLastBits) & (kMidBins - 1), log);
     const unsigned want = (d0 << (kRestBits - kLastBits)) | pick_lds(lh, kMidBins);
 #pragma unroll
     for (int q = 0; q < kSmallPer; ++q)
-        if (q < have && (key[q] >> kLastBits) == want) atomicAdd(&ll[key[q] & (kLastBins - 1)], 1u);
+        if (q < have && (key[q] >> kLastBits) == want) spread_add(ll, key[q] & (kLastBins - 1), log);
     const unsigned thr = (want << kLastBits) | pick_lds(ll, kLastBins);
     const unsigned need = kk;
 
@@ -859,7 +955,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_small(const float *__restr
             gt += key[q] > thr;
             eq += key[q] == thr;
         }
-    const unsigned both = gt | (eq << 16);   // N <= 32768: neither sum reaches 2^16
+    const unsigned both = gt | (eq << 16);   // N < 2^16: neither sum reaches it
     const unsigned inc = wave_incl_scan(both);
     if (lane == 63) s_w[wave] = inc;
     __syncthreads();

@@ -294,10 +294,10 @@ def test_select_without_memory_for_its_lists():
 
 # ------------------------------------------- targets + selection in one sweep
 
-@pytest.mark.parametrize("N", [255, 4097, 32767, 32768, 32769, 40001, 262145, 1050001])
+@pytest.mark.parametrize("N", [255, 4097, 24575, 24576, 24577, 32767, 32768, 32769, 40001, 262145, 1050001, 9000001])
 @pytest.mark.parametrize("values", ["spread", "narrow", "equal", "clustered"])
 def test_select_on_both_sides_of_its_dispatch(N, values):
-    """One block up to 32 768 groups, three kernels beyond; a wave's list of candidates fits,
+    """One block up to 24 576 groups, three kernels beyond; a wave's list of candidates fits,
     overflows (many keys in one digit, large scores next to each other) or is not kept (large k)."""
     rng = np.random.default_rng(N)
     W = np.zeros((1, N), np.float32)
