@@ -18,8 +18,8 @@
 // Where the current code says little (codes drawn at random, a step of many codeword spacings) a
 // group keeps most cells and the dense contraction is faster: k_cells_stats counts the cells that
 // 64 groups spread over the list would keep, and above kDenseShare the table is laid out without
-// padding and k_score_mfma contracts it (of the two kernels the one that is not needed returns at
-// once; both ways in one kernel left too few registers to either).
+// padding and k_score_mfma contracts it, cut into splits as without cells (of the two kernels the one
+// that is not needed returns at once; both ways in one kernel left too few registers to either).
 // k_rerank        (pv_mfma.hip) decides from the records as it does for the dense contraction
 //
 // The accumulator is kv = R2 - ||c_hi - x_hi||^2 with R2 a little above (P d_p)^2: a negative kv
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
                                                        unsigned *__restrict__ meta, h8 *__restrict__ A,
                                                        uint16_t *__restrict__ perm,
                                                        int *__restrict__ su_bounds, int nsplit,
-                                                       group_args ga)
+                                                       int dense_splits, group_args ga)
 {
     __shared__ unsigned s_meta[8];
     meta_of_parts(mem.part, csize / kCbChunk, s_meta);
@@ -350,8 +350,8 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
             if (blockIdx.x == 0 && b == ncells - 1 && !dense) su_bounds[nsplit] = (int)(end / kCellPos);
         }
     }
-    if (blockIdx.x == 0 && dense && tid <= nsplit)
-        su_bounds[tid] = split_begin(tid, csize / (kCellPos * kResidues), nsplit) * kResidues;
+    if (blockIdx.x == 0 && dense && tid <= dense_splits)
+        su_bounds[tid] = split_begin(tid, csize / (kCellPos * kResidues), dense_splits) * kResidues;
     if (blockIdx.x == 0 && tid < 8) meta[tid] = s_meta[tid];
     __syncthreads();
     // cb_blocks = csize / kCbChunk blocks share csize / 2^kCellLog cells: kCbChunk / 2^kCellLog each

@@ -1129,7 +1129,7 @@ template <int G, bool CELLS>
 __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
     const float *__restrict__ x_stage, const float *__restrict__ codebook, int k, int k_pad,
     const int2 *__restrict__ partials, int P, int per_half, int ncyc, int nsplit,
-    const int *__restrict__ su_bounds,
+    const int *__restrict__ su_bounds, const float *__restrict__ dense, int dense_P, int dense_per_half,
     const float *__restrict__ x_meta, const unsigned *__restrict__ cb_meta, const h8 *__restrict__ A,
     const float *__restrict__ cnorm, const h8 *__restrict__ X, const uint16_t *__restrict__ perm,
     uint16_t *__restrict__ codes,
@@ -1146,6 +1146,10 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
     if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) s_nopen = 0;
     __syncthreads();
+    if (CELLS && *dense != 0.0f) {           // the dense contraction filled the records, in its own partitions
+        P = dense_P;
+        per_half = dense_per_half;
+    }
     const int csize = 1 << nbits;
     const int gid = blockIdx.x * kBlock + threadIdx.x;
     const int j = gid / kTeam, q = gid % kTeam;
@@ -2001,11 +2005,12 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
                                 int64_t *num_changed, int32_t power, uint64_t seed)
 {
     plan_t p = make_plan(l, k, power > 0);
+    const plan_t dense = p;      // with cells: the plan of the dense contraction, should it be needed
     // Cells (pv_cells.h): g = 8, the nearest codeword, work enough to pay for cutting the codebook.
     const int cbits = l->nbits - kCellLog;
     const bool cells = l->group_size == 8 && power == 0 && l->nbits >= kCellMinBits &&
                        (k << l->nbits) >= kCellMinWork;
-    int cell_waves = 8, dense_blocks = 0;
+    int cell_waves = 8;
     if (cells) {
         const int ncells = 1 << cbits;
         p.cpad = ((1 << l->nbits) + ncells * (kCellPos - 1) + kCellPos - 1) / kCellPos * kCellPos;
@@ -2027,8 +2032,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
                 }
             }
         p.gblocks = (int)((k + cell_waves * 64 - 1) / (cell_waves * 64));
-        // the dense contraction takes 512 groups at a time
-        dense_blocks = (int)((k + PV_WAVES * PV_NBX * 32 - 1) / (PV_WAVES * PV_NBX * 32));
+        // (the dense contraction takes 512 groups at a time: a list this long has two group tiles a wave)
         p.k_pad = (p.gblocks * cell_waves * 64 + 511) & ~511;
         p.per_half = 2;
         p.P = p.nsplit * 4;
@@ -2062,7 +2066,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
     const size_t nmin_off = take((size_t)nsu_alloc * 4), cnorm_off = take((size_t)p.cpad * 4);
     const size_t x_off = take((size_t)p.k_pad * 32), x_meta_off = take((size_t)p.k_pad * 16);
     const size_t stage_off = take((size_t)p.k_pad * (g + 4) * 4), reach_off = take(cells ? (size_t)p.k_pad * 4 : 0);
-    const size_t partials_off = take((size_t)p.k_pad * p.P * sizeof(int2));
+    const size_t partials_off = take((size_t)p.k_pad * (p.P > dense.P ? p.P : dense.P) * sizeof(int2));
     const size_t fb_off = take(64), rr_off = take((size_t)rr_blocks * 16), slots_off = take((size_t)nslots * kSlotStride * 8);
     if ((st = pv_ensure(ctx, ctx->search, used, zero_head)) != PV_OK) return st;
     char *base = static_cast<char *>(ctx->search.ptr);
@@ -2128,7 +2132,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             hipLaunchKernelGGL(k_cells_stats, dim3(cb_blocks + 1), dim3(kBlock), 0, sm, codebooks, csize, cbits, cm,
                                ca, ga);
             hipLaunchKernelGGL(k_cells_prep, dim3(cb_blocks + (p.k_pad + kBlock - 1) / kBlock), dim3(kBlock), 0, sm,
-                               codebooks, csize, cbits, cb_blocks, cm, meta, A, perm, su_bounds, p.nsplit, ga);
+                               codebooks, csize, cbits, cb_blocks, cm, meta, A, perm, su_bounds, p.nsplit, dense.nsplit, ga);
         }
         {
             pv_timed t(ctx, PV_K_SCORE_MFMA);
@@ -2136,16 +2140,17 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             hipLaunchKernelGGL(k_cells_score, dim3(items < 256 ? items : 256), dim3(cell_waves * 64), 0, sm, A, X,
                                ga.reach, su_bounds, cm, meta, partials, cbits, cb_blocks, p.nsplit, p.gblocks,
                                p.k_pad, fb_count + 1);
-            const int ditems = dense_blocks * p.nsplit;
+            const int ditems = dense.gblocks * dense.nsplit;
             hipLaunchKernelGGL((k_score_mfma<8, PV_NBX>), dim3(ditems < 256 * PV_OCC ? ditems : 256 * PV_OCC),
                                dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, (const float *)nullptr, partials,
-                               csize / (32 * kU * kResidues), p.nsplit, p.per_half, dense_blocks, p.k_pad, fb_count + 2,
+                               dense.ncyc, dense.nsplit, dense.per_half, dense.gblocks, p.k_pad, fb_count + 2,
                                cm.theta + 15, mem, 0, meta);
         }
         {
             pv_timed t(ctx, PV_K_RERANK);
             hipLaunchKernelGGL((k_rerank<8, true>), dim3((unsigned)rr_blocks), dim3(kBlock), 0, sm, x_stage, codebooks,
-                               (int)k, p.k_pad, partials, p.P, p.per_half, 0, p.nsplit, su_bounds, x_meta, meta, A,
+                               (int)k, p.k_pad, partials, p.P, p.per_half, 0, p.nsplit, su_bounds, cm.theta + 15, dense.P,
+                               dense.per_half, x_meta, meta, A,
                                cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
         }
         PV_HIP(ctx, hipGetLastError());
@@ -2203,11 +2208,11 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
 #undef PV_ROUND2
         } else if (g == 8)
             hipLaunchKernelGGL((k_rerank<8, false>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
-                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, x_meta,
+                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, (const float *)nullptr, 0, 0, x_meta,
                                cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
         else
             hipLaunchKernelGGL((k_rerank<16, false>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
-                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, x_meta,
+                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, (const float *)nullptr, 0, 0, x_meta,
                                cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
     }
     PV_HIP(ctx, hipGetLastError());
