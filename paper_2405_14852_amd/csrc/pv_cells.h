@@ -441,6 +441,7 @@ __global__ __launch_bounds__(kCellWavesMax * 64, kCellWavesMax / 4) void k_cells
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ncells = 1 << cbits, runs = ncells / 16, waves = blockDim.x >> 6, groups = blockDim.x;
+    if (mem.theta[15] != 0.0f) return;      // dense: k_score_mfma does the work, and what follows
     // the counts are done with: zero for the next call; the largest rounding error of the codebook
     for (int i = blockIdx.x * groups + tid; i < kCbCopies * ncells; i += gridDim.x * groups) mem.count[i] = 0u;
     if (blockIdx.x == 0 && tid < 64) {
@@ -455,7 +456,6 @@ __global__ __launch_bounds__(kCellWavesMax * 64, kCellWavesMax / 4) void k_cells
     }
     bool okP;
     const float P = scale_from_maxabs(meta[0], &okP);
-    if (mem.theta[15] != 0.0f) return;      // dense: k_score_mfma does the work
     unsigned vmask = ~kKeyMask;
     asm volatile("" : "+v"(vmask));   // keep the mask in a vector register
     const unsigned items = (unsigned)gblocks * (unsigned)nsplit;

@@ -810,19 +810,16 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     const h8 *__restrict__ A, const h8 *__restrict__ X, const float *__restrict__ x_meta,
     const float *__restrict__ nmin, int2 *__restrict__ partials, int ncyc, int nsplit, int per_half,
     int gblocks, int k_pad, unsigned *__restrict__ next_item, const float *__restrict__ wanted,
-    cb_mem mem, int cb_parts, unsigned *__restrict__ meta)
+    const float *__restrict__ dpart, int cb_parts, unsigned *__restrict__ counts, int ncounts,
+    unsigned *__restrict__ meta)
 {
     if (wanted && *wanted == 0.0f) return;   // the cells do the work (pv_cells.h)
-    if (!wanted) {
-        // the largest rounding error of the codebook, for the re-rank; the bucket counts are done with
-        if (blockIdx.x == 0 && threadIdx.x < 64) {
-            const float d = wave_max_f((int)threadIdx.x < cb_parts ? mem.dpart[threadIdx.x] : 0.0f);
-            if (threadIdx.x == 0) meta[2] = __float_as_uint(d);
-        }
-        if (G == 16)
-            for (int i = blockIdx.x * (PV_WAVES * 64) + threadIdx.x; i < kCbCopies * (kNormBins / 2); i += gridDim.x * (PV_WAVES * 64))
-                mem.count[i] = 0u;
+    // the largest rounding error of the codebook, for the re-rank; the counts are done with
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        const float d = wave_max_f((int)threadIdx.x < cb_parts ? dpart[threadIdx.x] : 0.0f);
+        if (threadIdx.x == 0) meta[2] = __float_as_uint(d);
     }
+    for (int i = blockIdx.x * (PV_WAVES * 64) + threadIdx.x; i < ncounts; i += gridDim.x * (PV_WAVES * 64)) counts[i] = 0u;
     constexpr int S = PV_STAGE;                                    // tiles per stage
     constexpr int kStageChunks = S * 64;                           // 16-byte chunks per stage
     constexpr int kW = PV_WAVES;                                   // waves per block
@@ -2144,7 +2141,7 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             hipLaunchKernelGGL((k_score_mfma<8, PV_NBX>), dim3(ditems < 256 * PV_OCC ? ditems : 256 * PV_OCC),
                                dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, (const float *)nullptr, partials,
                                dense.ncyc, dense.nsplit, dense.per_half, dense.gblocks, p.k_pad, fb_count + 2,
-                               cm.theta + 15, mem, 0, meta);
+                               cm.theta + 15, cm.dpart, cb_blocks, cm.count, kCbCopies << cbits, meta);
         }
         {
             pv_timed t(ctx, PV_K_RERANK);
@@ -2183,8 +2180,8 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
         dim3 grid(items < 256 * PV_OCC ? items : 256 * PV_OCC);
 #define PV_SCORE(G_, NB_)                                                                          \
     hipLaunchKernelGGL((k_score_mfma<G_, NB_>), grid, dim3(PV_WAVES * 64), 0, sm, A, X, x_meta, nmin, \
-                       partials, p.ncyc, p.nsplit, p.per_half, p.gblocks, p.k_pad, fb_count + 1, (const float *)nullptr, mem, \
-                       cb_blocks, cb_meta)
+                       partials, p.ncyc, p.nsplit, p.per_half, p.gblocks, p.k_pad, fb_count + 1, (const float *)nullptr, mem.dpart, \
+                       cb_blocks, mem.count, G_ == 16 ? kCbCopies * (kNormBins / 2) : 0, cb_meta)
         if (g == 8) {
             if (p.NB == PV_NBX) PV_SCORE(8, PV_NBX);
             else PV_SCORE(8, 1);
