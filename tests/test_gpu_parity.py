@@ -413,7 +413,7 @@ def test_reencode_m1_list_lengths_around_the_launch_plan(g, k):
     assert st["filtered"] + st["fallback"] == k
 
 
-@pytest.mark.parametrize("B,k", [(16, 32768), (16, 34001), (14, 131072)])
+@pytest.mark.parametrize("B,k", [(16, 32768), (16, 34001), (15, 65536), (14, 131072)])
 @pytest.mark.parametrize("regime", ["near", "far", "lumps", "degenerate"])
 def test_reencode_m1_cells_of_the_codebook(B, k, regime):
     """Lists long enough for the search that leaves out whole cells: current codes near the targets,
@@ -436,6 +436,52 @@ def test_reencode_m1_cells_of_the_codebook(B, k, regime):
     N = wl.layout.num_groups
     idx = np.sort(np.random.default_rng(k).choice(N, size=k, replace=False)).astype(np.int32)
     reencode_case(wl, 0, idx=idx, T_np=T_np)
+
+
+def _cells_case(k, B, regime, seed, g=8):
+    wl = workloads.make(512, g * ((k + 511) // 512 + 3), g, 1, B, seed=seed, sigma_g=4e-3, tau=1.0)
+    if regime == "near":
+        wl.W = oracle.dequantize(wl.codes, wl.codebooks, wl.scales)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    idx = np.sort(np.random.default_rng(k).choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    return wl, T_np, idx
+
+
+@pytest.mark.parametrize("B,k", [(16, 112721), (15, 150001), (14, 262145)])
+@pytest.mark.parametrize("regime", ["near", "far"])
+def test_reencode_m1_cells_with_more_items_than_blocks(B, k, regime):
+    """Lists so long that a scoring block takes several work items, of cells (more than 256: near) and of
+    the dense contraction (more than 512: far).  A sample of the groups is checked."""
+    wl, T_np, idx = _cells_case(k, B, regime, 72)
+    run = GpuRun(wl)
+    got, nch = run.reencode(dev_f32(T_np), idx)
+    sub = idx[::k // 4000]
+    want, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, sub, wl.codes)
+    check_codes_on(wl, T_np, sub, got, want, info)
+    mask = np.ones(wl.layout.num_groups, bool)
+    mask[idx] = False
+    assert np.array_equal(got.ravel()[mask], wl.codes.ravel()[mask])
+    assert nch == (got != wl.codes).sum()
+
+
+def test_reencode_m1_on_one_context_equals_fresh_contexts():
+    """What a context keeps between calls (counters of cells and of norm buckets that are left at zero,
+    scratch that grows) makes no difference, whichever of the ways through the search comes next."""
+    from paper_2405_14852_amd import PVContext
+    cases = [(8, 16, 40000, "near"), (8, 16, 40000, "far"), (8, 16, 33000, "near"), (8, 14, 140000, "near"),
+             (16, 12, 6000, "far"), (8, 15, 70000, "near"), (8, 8, 3000, "near"), (16, 16, 5000, "near"),
+             (8, 14, 140000, "far"), (16, 10, 700, "far"), (8, 12, 5000, "near"), (16, 12, 6000, "far"),
+             (8, 16, 40000, "near")]
+    shared = PVContext(0)
+    known = {}
+    for case in cases:
+        g, B, k, regime = case
+        wl, T_np, idx = _cells_case(k, B, regime, 73, g)
+        if case not in known:
+            known[case] = GpuRun(wl).reencode(dev_f32(T_np), idx)
+        got, nch = GpuRun(wl, shared).reencode(dev_f32(T_np), idx)
+        assert np.array_equal(got, known[case][0]) and nch == known[case][1], case
+    shared.close()
 
 
 @pytest.mark.parametrize("g", [8, 16])

@@ -232,11 +232,17 @@ def test_stochastic_rounding_on_inputs_that_strain_the_filter(g, B):
 
 
 @pytest.mark.parametrize("g,M,B,beam,stochastic", [(8, 1, 12, 1, False), (16, 1, 11, 1, False), (8, 2, 8, 8, False),
-                                                   (8, 1, 12, 1, True), (16, 1, 10, 1, True)])
+                                                   (8, 1, 12, 1, True), (16, 1, 10, 1, True),
+                                                   (16, 1, 10, 1, False), (8, 1, 8, 1, False),
+                                                   (8, 1, 16, 1, False)])      # the last: cells
 def test_repeated_calls_from_the_same_state_give_the_same_codes(g, M, B, beam, stochastic):
-    """Thirty calls from the same codes, on one context (scratch, alternating statistics slots
-    and counters are reused): every result is the first one, bit for bit, and num_changed too."""
-    wl = workloads.make(192, 64 * g, g, M, B, beam_width=beam, sigma_g=5e-3, tau=0.5, seed=900 + B + g)
+    """Thirty calls from the same codes, on one context (scratch is reused, with counts of norm buckets
+    and of cells that the scoring kernels leave at zero and cursors that the first kernel clears): every
+    result is the first one, bit for bit, and num_changed too."""
+    rows = 1088 if B == 16 else 192
+    wl = workloads.make(rows, 64 * g, g, M, B, beam_width=beam, sigma_g=5e-3, tau=0.5, seed=900 + B + g)
+    if B == 16:
+        wl.W = oracle.dequantize(wl.codes, wl.codebooks, wl.scales)
     lay = lay_of(wl)
     T = oracle.encode_targets(wl.W, wl.G, wl.alpha)
     k = wl.k
