@@ -597,6 +597,7 @@ __device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4
     for (int u = 0; u < kAhead; ++u) {
         const int i = at + u * 256 + (int)(threadIdx.x & 63) * 4;
         v[u] = pv_f4{0.f, 0.f, 0.f, 0.f};
+        if (at + u * 256 >= n) continue;          // uniform over the wave
         if (i + 4 <= n) {
             v[u] = *reinterpret_cast<const pv_f4 *>(s + i);
         } else {
@@ -617,7 +618,8 @@ __device__ __forceinline__ void for_scores(const float *s, int n, pv_f4 (&cur)[k
         const bool more = at + 256 * kAhead < n;
         if (more) load_scores(s, at + 256 * kAhead, n, nxt);
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) f(cur[u], at + u * 256);
+        for (int u = 0; u < kAhead; ++u)
+            if (at + u * 256 < n) f(cur[u], at + u * 256);      // uniform over the wave
         if (more)
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
