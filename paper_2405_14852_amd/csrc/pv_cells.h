@@ -30,11 +30,13 @@ namespace {
 
 constexpr int kCellLog = 7;                   // log2 of the codewords a cell has on average
 constexpr int kCellMinBits = 14;              // smallest codebook that is cut into cells
-// Groups x codewords from which on cells are used.  Measured against the dense contraction, whole search
-// (preparation, scoring, re-rank), update of about the codeword spacing: 16 bits 21k groups 77 against 84 us,
-// 56k 130 against 172, 367k 474 against 842; 15 bits 56k 93 against 110; 14 bits 84k 104 against 113; 13 bits
-// 367k 231 against 243, fewer groups lose.  The line lies a little above break-even: where the current codes say
-// nothing and the dense contraction runs after all, the way there costs 10 us.
+// Groups x codewords from which on cells are used.  Whole search (preparation, scoring, re-rank) against
+// the dense contraction alone.  Update of about the codeword spacing: 16 bits 21k groups 77 against 84 us,
+// 40k 85 against 114, 56k 87 against 145, 184k 188 against 435; 15 bits 66k 85 against 110; 14 bits 140k 110
+// against 122; 13 bits 367k 231 against 243, fewer groups lose.  Current codes that say nothing, so that
+// the dense contraction runs after all: 16 bits 40k 121 against 114, 56k 155 against 145, 184k 455 against
+// 435; 15 bits 66k 118 against 110 (a launch that does nothing, and the cells' preparation).  The line lies
+// above break-even of the first kind for the sake of the second.
 constexpr int64_t kCellMinWork = INT64_C(1) << 31;
 constexpr int kCellsMax = 1 << (16 - kCellLog);
 constexpr int kCellPos = 32 * kU;             // a cell is padded to whole super-units
@@ -415,8 +417,9 @@ __global__ __launch_bounds__(kBlock) void k_cells_prep(const float *__restrict__
 //    A key goes to the group's record by LDS maxima if it is above the second largest there: few
 //    lanes have one.
 // 4. The records leave: partition = (split, half wave, parity of the super-unit).
-// Bound by vector-ALU issue, like the dense contraction (8 maxima a matrix instruction); what a
-// list costs is spread over more groups the larger the block is: up to 16 waves (the launch picks
+// No unit is full: for the Adam step below, vector-ALU issue takes 58 of 109 thousand cycles (14.9 M
+// instructions), the LDS 33, the matrix cores 17; the rest are waits at the start of a list and at the
+// two barriers of an item.  What a list costs is spread over more groups the larger the block is: up to 16 waves (the launch picks
 // the number that fills the chip), one block per compute unit.  56 360 groups, 16 bits: 75 us where the
 // update is the codeword spacing of the widest groups (35 us for an Adam step, whose updates are more even)
 // against 122 us for the dense contraction.

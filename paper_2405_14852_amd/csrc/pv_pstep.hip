@@ -206,11 +206,13 @@ __global__ __launch_bounds__(kBlock) void k_pg_long(const int32_t *__restrict__ 
 // added with the rounding errors carried along, and the total is rounded to fp32.  Gradients or
 // scales that are not finite make every entry NaN.  A row's products are summed by the waves that
 // meet it, lanes first, and added in order of the waves.
-// Bound by the LDS atomics (sixteen per group and codebook: 53 us at 11008 x 4096, 2 x 8, where
-// reading G takes 36); the vector ALU works meanwhile (23 M instructions, 37 us).  There, with the
+// 11008 x 4096, 2 x 8: vector-ALU issue fills 91 of the kernel's 141 thousand cycles (23.4 M instructions,
+// much of it the conversion to integers), the LDS 60 (sixteen 64-bit atomics a group and codebook; 35 of
+// them bank conflicts), reading G takes 75; none alone is the bound, their overlap is.  There, with the
 // scale gradient (and the maxima) as a kernel of its own that read G first: 98.7 us a step, in one
-// pass 71.  Gradients with heavy tails (cubed normal, Student's t): 78 and 84.  Ordering tiles of groups by code in LDS and summing in registers, without these
-// atomics, was tried: 112 us, one block of 16 waves per compute unit waiting at its barriers.
+// pass 73.  Gradients with heavy tails (cubed normal, Student's t): 82 and 86.  Ordering tiles of
+// groups by code in LDS and summing in registers, without these atomics, was tried: 112 us, one
+// block of 16 waves per compute unit waiting at its barriers.
 constexpr int kSmallBlock = 1024;                         // one table serves sixteen waves
 constexpr int kSmallWaves = kSmallBlock / 64;
 constexpr int kSmallAhead = 2;                            // vectors of a thread in flight

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape,g,M,B,beam", [((128, 1024), 8, 1, 16, 1), ((64, 1024), 16, 1, 12, 1),
-                                             ((96, 512), 8, 2, 8, 8), ((48, 384), 8, 1, 7, 1)])
+                                             ((96, 512), 8, 2, 8, 8), ((48, 384), 8, 1, 7, 1),
+                                             ((384, 8192), 8, 1, 16, 1)])     # the last: cells
 def test_captured_step_replays_like_the_eager_one(shape, g, M, B, beam):
     wl = workloads.make(shape[0], shape[1], g, M, B, beam_width=beam, tau=0.1, sigma_g=5e-3, seed=700 + B)
     lay = lay_of(wl)
@@ -122,9 +123,8 @@ def test_captured_step_follows_a_codebook_that_changes_between_replays(factor):
 
 
 def test_captured_step_forgets_the_statistics_of_the_last_replay():
-    """The codebook statistics of a call are accumulated with atomics in a slot that eager calls
-    alternate; a replayed graph keeps its slot, so the call clears it first when it is being
-    captured.  Seen from outside: a codebook with a non-finite entry switches the filter off (every
+    """The codebook statistics of a call come from that call alone, also in a replay, which works on the
+    same memory as the replay before.  Seen from outside: a codebook with a non-finite entry switches the filter off (every
     group is scanned exactly); once the entry is repaired in place the next replay must use the
     filter again."""
     wl = workloads.make(128, 1024, 8, 1, 16, tau=0.1, sigma_g=5e-3, seed=733)

@@ -464,6 +464,29 @@ def test_reencode_m1_cells_with_more_items_than_blocks(B, k, regime):
     assert nch == (got != wl.codes).sum()
 
 
+@pytest.mark.parametrize("codewords", ["finite", "some_not"])
+def test_reencode_m1_cells_non_finite_inputs(codewords):
+    """Targets, scales and codewords that are not finite, in lists that the cells take: such groups are
+    searched in full, as the oracle does, and the others as ever."""
+    wl, T_np, idx = _cells_case(33000, 16, "near", 74)
+    T_np[3, ::11] = np.nan
+    T_np[5, ::9] = np.inf
+    T_np[7, ::9] = -3e38
+    wl.scales[[9, 11, 13, 15]] = [np.inf, np.nan, 0.0, 1e-38]
+    if codewords == "some_not":
+        wl.codebooks[0, 7, 2] = np.nan
+        wl.codebooks[0, 300, 5] = np.inf
+        wl.codebooks[0, 65535, 0] = -np.inf
+        wl.codes[20:24, :8] = np.uint16(300)
+        wl.codes[24:28, :8] = np.uint16(7)
+    got, _ = GpuRun(wl).reencode(dev_f32(T_np), idx)
+    gpr = wl.layout.groups_per_row
+    odd = [n for n in idx if n // gpr < 30]
+    sub = np.sort(np.unique(np.concatenate([np.array(odd, np.int32), idx[::16]])))
+    want, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, sub, wl.codes)
+    check_codes_on(wl, T_np, sub, got, want, info)
+
+
 def test_reencode_m1_on_one_context_equals_fresh_contexts():
     """What a context keeps between calls (counters of cells and of norm buckets that are left at zero,
     scratch that grows) makes no difference, whichever of the ways through the search comes next."""

@@ -251,7 +251,8 @@ def test_codebook_grads_small_codebook_route_keeps_what_cancels(rows):
     assert (np.abs(gc[0] - want) <= terms * 2.0 ** -51 + np.spacing(np.abs(want).astype(np.float32))).all()
 
 
-@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 4, (64, 2048)), (8, 3, 5, (65, 2040)), (16, 1, 6, (128, 1024))])
+@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 4, (64, 2048)), (8, 3, 5, (65, 2040)), (16, 1, 6, (128, 1024)),
+                                         (8, 1, 10, (256, 2048))])     # the last: the largest table, 64 KiB
 @pytest.mark.parametrize("kind", ["few", "huge", "full", "many"])
 def test_codebook_grads_small_codebook_route_terms_beyond_the_room(g, M, B, shape, kind):
     """Vectors whose terms exceed what the first vectors announced: a few (listed, the table shifted to
