@@ -645,7 +645,12 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
     if (g % 4 == 0 && entries * 8 <= 64 * 1024 && N / csize >= 64) {
         const int vpg = g / 4;
         const int64_t nvec = N * vpg;
-        int64_t blocks64 = (N + 4095) / 4096;
+        // Groups of a block: up to 2^20 groups as few thousands as leave at most 256 blocks, one per compute
+        // unit (a wave takes whole steps, 1024 groups a block), then 4096.  With 4096 throughout, 256 x 1024 at
+        // g = 16 took 22 us (1024 a block: 12), 1024 x 1024 2 x 8 20 (13); with 512
+        // blocks of fewer groups at 2^20 27 instead of 21.
+        const int64_t groups = N <= 1 << 20 ? ((N + (1 << 18) - 1) >> 18) * 1024 : 4096;
+        int64_t blocks64 = (N + groups - 1) / groups;
         if (blocks64 > 512) blocks64 = 512;
         const int blocks = (int)blocks64, waves = blocks * kSmallWaves;
         const int unit = 64 * vpg;

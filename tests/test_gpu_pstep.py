@@ -201,9 +201,10 @@ def test_codebook_grads_small_codebook_route_unit_and_rows(g, M, B, shape, head)
 
 def small_route_blocks(wl):
     """Vectors of 16 bytes that a wave takes, and the block of every group (of the route that keeps
-    its sums in blocks: at most 512 of them, 4096 groups or more each, 16 waves)."""
+    its sums in blocks of 16 waves: 256 at most up to 2^20 groups, 512 beyond)."""
     N, vpg = wl.layout.num_groups, wl.layout.group_size // 4
-    blocks = min((N + 4095) // 4096, 512)
+    groups = -(-N // (1 << 18)) * 1024 if N <= 1 << 20 else 4096
+    blocks = min(-(-N // groups), 512)
     step = blocks * 16 * 64 * vpg
     per_wave = (N * vpg + step - 1) // step * 64 * vpg
     return per_wave, np.arange(N) * vpg // (16 * per_wave)
@@ -230,18 +231,18 @@ def exact_small_route(wl, G=None):
     return want, tol + 0.501 * np.spacing(np.abs(want).astype(np.float32))
 
 
-@pytest.mark.parametrize("rows", [8, 64])     # one block, four blocks
-def test_codebook_grads_small_codebook_route_keeps_what_cancels(rows):
+@pytest.mark.parametrize("rows,columns,B", [(8, 1024, 3), (64, 2048, 4), (192, 16384, 4)])  # 1, 16, 192 blocks
+def test_codebook_grads_small_codebook_route_keeps_what_cancels(rows, columns, B):
     """Large terms that cancel exactly, in one block and from block to block, beside terms 2^-44 of
-    their size: a unit 2^-50 of the bound keeps six bits of those (2^14 groups: kbits = 50)."""
-    wl = workloads.make(rows, 2048, 8, 1, 3 if rows == 8 else 4, seed=92, sigma_g=1e-2)
+    their size: a unit 2^-50 of the bound (as it is up to 2^12 groups a block) keeps six bits of those."""
+    wl = workloads.make(rows, columns, 8, 1, B, seed=92, sigma_g=1e-2)
     rng = np.random.default_rng(92)
     wl.scales[:] = 1.0
     n = rows // 2 - rows // 8
-    wl.G[:n] = rng.uniform(0.5, 0.99, (n, 2048))
+    wl.G[:n] = rng.uniform(0.5, 0.99, (n, columns))
     wl.G[n:2 * n] = -wl.G[:n]
     wl.codes[n:2 * n] = wl.codes[:n]
-    wl.G[2 * n:] = rng.standard_normal((rows - 2 * n, 2048)) * 2.0 ** -44
+    wl.G[2 * n:] = rng.standard_normal((rows - 2 * n, columns)) * 2.0 ** -44
     want = np.zeros(wl.codebooks.shape[1:], np.float64)
     np.add.at(want, wl.codes[2 * n:].ravel(), wl.G[2 * n:].reshape(-1, 8).astype(np.float64))
     terms = np.bincount(wl.codes[2 * n:].ravel(), minlength=want.shape[0])[:, None]
@@ -251,8 +252,8 @@ def test_codebook_grads_small_codebook_route_keeps_what_cancels(rows):
     assert (np.abs(gc[0] - want) <= terms * 2.0 ** -51 + np.spacing(np.abs(want).astype(np.float32))).all()
 
 
-@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 4, (64, 2048)), (8, 3, 5, (65, 2040)), (16, 1, 6, (128, 1024)),
-                                         (8, 1, 10, (256, 2048))])     # the last: the largest table, 64 KiB
+@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 4, (520, 4096)), (8, 3, 5, (521, 4088)), (16, 1, 6, (128, 1024)),
+                                         (8, 1, 10, (520, 4096))])     # the last: the largest table, 64 KiB
 @pytest.mark.parametrize("kind", ["few", "huge", "full", "many"])
 def test_codebook_grads_small_codebook_route_terms_beyond_the_room(g, M, B, shape, kind):
     """Vectors whose terms exceed what the first vectors announced: a few (listed, the table shifted to
