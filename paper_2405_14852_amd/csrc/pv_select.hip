@@ -591,13 +591,14 @@ __device__ __forceinline__ uint2 list_at(const region_t &g, int i)
     return i < g.n ? g.list[i] : make_uint2(0u, 0u);
 }
 // kAhead steps of a wave through scores: four consecutive ones a lane, 256 a step; 0 past the n-th
+template <bool SKIP = false>      // SKIP: no instructions for steps past the n-th score
 __device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4 (&v)[kAhead])
 {
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
         const int i = at + u * 256 + (int)(threadIdx.x & 63) * 4;
         v[u] = pv_f4{0.f, 0.f, 0.f, 0.f};
-        if (at + u * 256 >= n) continue;          // uniform over the wave
+        if (SKIP && at + u * 256 >= n) continue;          // uniform over the wave
         if (i + 4 <= n) {
             v[u] = *reinterpret_cast<const pv_f4 *>(s + i);
         } else {
@@ -607,22 +608,26 @@ __device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4
         }
     }
 }
-// f(scores, place of the step's first one) for every step of a wave through n scores, the next
+// f(scores, place of the step's first one, whether all are there) for every step of a wave through n scores, the next
 // kAhead steps on their way (four bytes a lane instead: 45 M single weights, lists that do not fit, 541 us
 // a call against 426)
-template <class F>
+template <bool ONE_CHUNK = true, class F>
 __device__ __forceinline__ void for_scores(const float *s, int n, pv_f4 (&cur)[kAhead], F f)
 {
-    pv_f4 nxt[kAhead];
-    for (int at = 0; at < n; at += 256 * kAhead) {
-        const bool more = at + 256 * kAhead < n;
-        if (more) load_scores(s, at + 256 * kAhead, n, nxt);
+    if (ONE_CHUNK && n <= 256 * kAhead) {         // cur stays as it is
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
-            if (at + u * 256 < n) f(cur[u], at + u * 256);      // uniform over the wave
-        if (more)
+            if (u * 256 < n) f(cur[u], u * 256, u * 256 + 256 <= n);      // uniform over the wave
+        return;
+    }
+    pv_f4 nxt[kAhead];
+    for (int at = 0; at < n; at += 256 * kAhead) {
+        if (at + 256 * kAhead < n) load_scores(s, at + 256 * kAhead, n, nxt);
+        const bool whole = at + 256 * kAhead <= n;
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
+        for (int u = 0; u < kAhead; ++u) f(cur[u], at + u * 256, whole);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
     }
 }
 
@@ -666,12 +671,12 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
     }
     const unsigned lo = (unsigned)d0 << kRestBits, hi = ((unsigned)d0 + 1u) << kRestBits;
     unsigned cnt = 0;
-    for_scores(mine_scores, n, cur, [&](const pv_f4 &v, int at) {
+    for_scores<false>(mine_scores, n, cur, [&](const pv_f4 &v, int at, bool whole) {
         const int i = at + lane * 4;
         unsigned long long hits[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)          // (a NaN with its sign bit set is above every range as it is)
-            hits[e] = __ballot(__float_as_uint(v[e]) >= lo && i + e < n);
+            hits[e] = __ballot(__float_as_uint(v[e]) >= lo && (whole || i + e < n));
         if (!(hits[0] | hits[1] | hits[2] | hits[3])) return;   // uniform over the wave
         unsigned pos = cnt;
 #pragma unroll
@@ -733,10 +738,10 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
     };
     if (g.raw) {
         pv_f4 cur[kAhead];
-        load_scores(g.scores + g.base, 0, g.n, cur);
-        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at) {
+        load_scores<true>(g.scores + g.base, 0, g.n, cur);
+        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at, bool whole) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
+            for (int e = 0; e < 4; ++e) count(score_key(v[e]), whole || at + lane * 4 + e < g.n);
         });
     } else {
         for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
@@ -811,10 +816,10 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
     };
     pv_f4 cur[kAhead];
     if (g.raw) {
-        load_scores(g.scores + g.base, 0, g.n, cur);
-        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at) {
+        load_scores<true>(g.scores + g.base, 0, g.n, cur);
+        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at, bool whole) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
+            for (int e = 0; e < 4; ++e) count(score_key(v[e]), whole || at + lane * 4 + e < g.n);
         });
         if (g.n > 256 * kAhead) load_scores(g.scores + g.base, 0, g.n, cur);   // for the second trip
     } else {
@@ -842,13 +847,13 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
         re += s_be[w] + (w < wave ? s_eq[w] : 0u);
     }
     if (g.raw) {
-        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at) {
+        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at, bool whole) {
             unsigned long long bgt[4], beq[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const unsigned key = score_key(v[e]);
                 bgt[e] = __ballot(key > thr);
-                beq[e] = __ballot(key == thr && at + lane * 4 + e < g.n);
+                beq[e] = __ballot(key == thr && (whole || at + lane * 4 + e < g.n));
             }
             if (!(bgt[0] | bgt[1] | bgt[2] | bgt[3] | beq[0] | beq[1] | beq[2] | beq[3])) return;   // uniform over the wave
             unsigned pg = rg, pe = re;
