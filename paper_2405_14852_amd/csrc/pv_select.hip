@@ -590,8 +590,9 @@ __device__ __forceinline__ uint2 list_at(const region_t &g, int i)
 {
     return i < g.n ? g.list[i] : make_uint2(0u, 0u);
 }
-// kAhead steps of a wave through scores: four consecutive ones a lane, 256 a step; 0 past the n-th
-template <bool SKIP = false>      // SKIP: no instructions for steps past the n-th score
+// kAhead steps of a wave through scores: four consecutive ones a lane, 256 a step; 0 past the n-th.
+// SKIP: no instructions for steps past the n-th score.
+template <bool SKIP>
 __device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4 (&v)[kAhead])
 {
 #pragma unroll
@@ -608,26 +609,20 @@ __device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4
         }
     }
 }
-// f(scores, place of the step's first one, whether all are there) for every step of a wave through n scores, the next
-// kAhead steps on their way (four bytes a lane instead: 45 M single weights, lists that do not fit, 541 us
-// a call against 426)
-template <bool ONE_CHUNK = true, class F>
-__device__ __forceinline__ void for_scores(const float *s, int n, pv_f4 (&cur)[kAhead], F f)
+// f(scores, place of the first one) for every step of a wave through the n scores of a region whose list
+// does not fit.  Sixteen bytes a lane (with four: 45 M single weights 541 us a call against 430).  Short code
+// rather than the next steps' loads ahead: it lies between the instructions of the kernels' usual way,
+// and their registers decide what fits beside them (a 224-matrix sweep on four streams: 1 %).
+template <class F>
+__device__ __forceinline__ void for_scores(const float *s, int n, F f)
 {
-    if (ONE_CHUNK && n <= 256 * kAhead) {         // cur stays as it is
+#pragma unroll 1
+    for (int at = 0; at < n; at += 256 * kAhead) {
+        pv_f4 v[kAhead];
+        load_scores<true>(s, at, n, v);
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
-            if (u * 256 < n) f(cur[u], u * 256, u * 256 + 256 <= n);      // uniform over the wave
-        return;
-    }
-    pv_f4 nxt[kAhead];
-    for (int at = 0; at < n; at += 256 * kAhead) {
-        if (at + 256 * kAhead < n) load_scores(s, at + 256 * kAhead, n, nxt);
-        const bool whole = at + 256 * kAhead <= n;
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) f(cur[u], at + u * 256, whole);
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
+            if (at + u * 256 < n) f(v[u], at + u * 256);      // uniform over the wave
     }
 }
 
@@ -651,8 +646,8 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
     const float *mine_scores = scores + base;
     const int n = base >= N ? 0 : (int)(N - base < span ? N - base : span);
     uint2 *mine = list + (int64_t)r * cap;
-    pv_f4 cur[kAhead];
-    load_scores(mine_scores, 0, n, cur);     // in flight while digit 0 is resolved
+    pv_f4 cur[kAhead], nxt[kAhead];
+    load_scores<false>(mine_scores, 0, n, cur);     // in flight while digit 0 is resolved
     for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
     // the last digit's histogram starts at zero (its reader of the call before has run)
     for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
@@ -671,7 +666,7 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
     }
     const unsigned lo = (unsigned)d0 << kRestBits, hi = ((unsigned)d0 + 1u) << kRestBits;
     unsigned cnt = 0;
-    for_scores<false>(mine_scores, n, cur, [&](const pv_f4 &v, int at, bool whole) {
+    auto take = [&](const pv_f4 &v, int at, bool whole) {
         const int i = at + lane * 4;
         unsigned long long hits[4];
 #pragma unroll
@@ -694,7 +689,15 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
                 ++pos;
                 if (key < hi) spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
             }
-    });
+    };
+    for (int at = 0; at < n; at += 256 * kAhead) {
+        if (at + 256 * kAhead < n) load_scores<false>(mine_scores, at + 256 * kAhead, n, nxt);
+        const bool whole = at + 256 * kAhead <= n;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) take(cur[u], at + u * 256, whole);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) cur[u] = nxt[u];
+    }
     if (lane == 0) counts[r] = cnt;
     __syncthreads();
     flush_hist(lh, hist_all + kHist1, kMidBins, tmp, log);
@@ -737,11 +740,9 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
         if (p == want && in) spread_add(lh, key & (kLastBins - 1), kSpreadLog);
     };
     if (g.raw) {
-        pv_f4 cur[kAhead];
-        load_scores<true>(g.scores + g.base, 0, g.n, cur);
-        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at, bool whole) {
+        for_scores(g.scores + g.base, g.n, [&](const pv_f4 &v, int at) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) count(score_key(v[e]), whole || at + lane * 4 + e < g.n);
+            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
         });
     } else {
         for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
@@ -814,14 +815,11 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
         gt += key > thr;
         eq += key == thr && in;
     };
-    pv_f4 cur[kAhead];
     if (g.raw) {
-        load_scores<true>(g.scores + g.base, 0, g.n, cur);
-        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at, bool whole) {
+        for_scores(g.scores + g.base, g.n, [&](const pv_f4 &v, int at) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) count(score_key(v[e]), whole || at + lane * 4 + e < g.n);
+            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
         });
-        if (g.n > 256 * kAhead) load_scores(g.scores + g.base, 0, g.n, cur);   // for the second trip
     } else {
         for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
             unsigned key[kAhead];
@@ -847,13 +845,13 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
         re += s_be[w] + (w < wave ? s_eq[w] : 0u);
     }
     if (g.raw) {
-        for_scores(g.scores + g.base, g.n, cur, [&](const pv_f4 &v, int at, bool whole) {
+        for_scores(g.scores + g.base, g.n, [&](const pv_f4 &v, int at) {
             unsigned long long bgt[4], beq[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const unsigned key = score_key(v[e]);
                 bgt[e] = __ballot(key > thr);
-                beq[e] = __ballot(key == thr && (whole || at + lane * 4 + e < g.n));
+                beq[e] = __ballot(key == thr && at + lane * 4 + e < g.n);
             }
             if (!(bgt[0] | bgt[1] | bgt[2] | bgt[3] | beq[0] | beq[1] | beq[2] | beq[3])) return;   // uniform over the wave
             unsigned pg = rg, pe = re;
