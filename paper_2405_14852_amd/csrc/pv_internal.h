@@ -43,7 +43,7 @@ struct pv_ctx {
     const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel
     pv_buffer fb_list;      // beam path: the groups left to the exact kernel
     pv_buffer trust;        // scratch of the trust-ratio call (saved codes, keys, prefix sums, sort space)
-    pv_buffer pstep;        // scratch of the P-step gradients (digit histograms, keys and group ids of the sorting passes, segment starts, piece sums)
+    pv_buffer pstep;        // scratch of the P-step gradients (tiles in bucket order and where their buckets start, sums that go on; or the blocks' tables)
 };
 
 // RAII bracket that records HIP events around a group of launches when timing is on.

@@ -8,181 +8,533 @@
 // The codebook gradient is a scatter-add of N * g values into 2^B * g sums.  Floating-point
 // atomics would serialise on popular codewords and give run-dependent roundings (and atomics
 // on device memory are slow on a part whose L2 is split over several dies); instead the
-// groups are SORTED by code with a stable radix sort written for this key width - 8 bits a
-// pass, so at most two passes of histogram, prefix sum and scatter, with ranks taken from
-// wave ballots and per-wave counters in LDS so that equal codes keep ascending group order
-// and no atomic touches device memory - and every codeword's segment is summed by g
-// lanes in that order, in double, with exact products: the same sum, in the same order, as a
-// plain loop over the groups.  Segments longer than kLong groups are cut into pieces of kLong
-// that are summed by the teams of one block and added in piece order (a different
-// association from the plain loop: reproducible from run to run, but no longer the sequential
-// rounding).  Small codebooks take another route (k_pg_small below), which takes the scale
-// gradient along; otherwise that is one block-wide tree sum per row.
+// groups are put in code order by two launches that exchange 4 bytes a group and no atomics:
+// - k_pg_tiles puts every tile of 8192 groups in the order of up to 512 buckets of consecutive
+//   codes and writes the tile where it was read, with the places where its buckets start; no
+//   counts over the whole matrix are needed.  Blocks of the same launch take the scale gradient,
+//   a tree sum per row.
+// - k_pg_buckets gives a block to a bucket: it lays the tiles' runs end to end in LDS, puts them in
+//   code order there, and sums every codeword's groups by a team of lanes in ascending group order,
+//   in double with exact products: the same sum, in the same order, as a plain loop over the
+//   groups.  Codewords with more than kLong groups in a chunk of the bucket are summed in pieces that are
+//   added in order (a different association from the plain loop: reproducible from run to run,
+//   but no longer the sequential rounding).
+// Bound by the gathers: 32 bytes of G (g = 8) bring a line of 128, and 2^21 of them in random order
+// take 41 us of k_pg_buckets' 54 whatever the kind of load (plain, nontemporal, device scope) and
+// whether G was read shortly before.  4096 x 4096, 1 x 16: 107 -> 83 us a call against a radix sort of
+// (code, group) in two passes of three kernels, segment starts, sums and scales (nine launches);
+// 354 x 384, 1 x 12 40 -> 20; 4096 x 4096, 1 x 12 118 -> 90.  Scales as a launch of their own: 84; beside the
+// sums instead of the order: 82.  Buckets of 256 or tiles of 4096 groups: 1 to 8 us more.
+// Small codebooks take another route (k_pg_small below), which takes the scale gradient along.
 #include "pv_internal.h"
 #include "pv_dpp.h"
-#include "pv_radix.h"
 
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kLong = 128;       // groups per piece: a segment up to this long is summed by one team alone
-// the codes of codebook m as sort keys, masked to B bits
-struct code_keys {
+constexpr int kLong = 128;       // groups of a codeword in a chunk that one team sums alone, in order
+
+// ---- large codebooks: tiles put in bucket order, then a block for every bucket
+
+// A bucket is a range of 2^low consecutive codes, at most 512 buckets a codebook.
+constexpr int kTileBlock = 1024;
+constexpr int kTileWaves = kTileBlock / 64;
+constexpr int kTilePer = 8;
+constexpr int kTileBits = 13;
+constexpr int kTile = 1 << kTileBits;             // groups of a tile
+constexpr int kBucketBits = 9;
+constexpr int kBuckets = 1 << kBucketBits;
+static_assert(kTile == kTileBlock * kTilePer && kBuckets <= kTileBlock, "a tile is one round of a block");
+
+struct bucket_args {
     const uint16_t *codes;
-    int M, m;
-    unsigned mask;
-    __device__ __forceinline__ unsigned operator()(int64_t e) const
-    {
-        return (unsigned)(codes[e * M + m] & mask);
-    }
+    int64_t N;
+    int M, m0;           // codebooks, the first one of this launch
+    unsigned mask;       // 2^B - 1
+    int low, high;       // bits of a code within its bucket, bits that name the bucket
+    int ntiles;
+    uint32_t *entries;   // [codebook of the launch][N] tile by tile: code within the bucket << 16 | place in the tile
+    uint16_t *first;     // [codebook of the launch][tile][buckets + 1] where a bucket starts in its tile
 };
 
-// start[c] = first position of code c in the sorted order (= position of the next present
-// code when c is absent); start[csize] = N.  Also clears the length of the list of long segments.
-__global__ __launch_bounds__(kBlock) void k_pg_starts(const uint16_t *__restrict__ sorted, int64_t N,
-                                                      int csize, int32_t *__restrict__ start,
-                                                      unsigned *__restrict__ nlong)
+// The lanes of a wave (among `valid`) whose low `bits` bits of d are this lane's.
+__device__ __forceinline__ unsigned long long lanes_alike(unsigned d, int bits, bool valid)
 {
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r == 0) *nlong = 0u;
-    if (r >= N) return;
-    const int cur = sorted[r];
-    const int prev = r == 0 ? -1 : (int)sorted[r - 1];
-    for (int c = prev + 1; c <= cur; ++c) start[c] = (int32_t)r;
-    if (r == N - 1)
-        for (int c = cur + 1; c <= csize; ++c) start[c] = (int32_t)N;
+    unsigned long long same = __ballot(valid);
+#pragma unroll
+    for (int bit = 0; bit < kBucketBits; ++bit) {
+        if (bit < bits) {                          // uniform
+            const unsigned long long has = __ballot((d >> bit) & 1u);
+            same &= ((d >> bit) & 1u) ? has : ~has;
+        }
+    }
+    return same;
 }
 
-// Sum of s_o * G[n, i] over ids[a .. b) in that order, kInFlight gathers issued together.
-constexpr int kInFlight = 8;
-template <bool HAVE_SCALES, class IDS>
-__device__ __forceinline__ double ordered_sum(IDS ids, const float *__restrict__ s_of,
-                                              const float *__restrict__ G,
-                                              const float *__restrict__ scales, int gpr, int g,
-                                              int i, int a, int b, double acc = 0.0)
+// Counts of a block's waves per digit become offsets in wave order; start[d] = keys of smaller digits, for d up
+// to DIGITS.  All threads call this (at least DIGITS); wcnt[WAVES][DIGITS], start[DIGITS + 1], s_w[DIGITS / 64] in LDS.
+template <int WAVES, int DIGITS>
+__device__ __forceinline__ void digit_starts(unsigned (*wcnt)[DIGITS], unsigned *start, unsigned *s_w)
 {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned mine = 0, incl = 0;
+    __syncthreads();
+    if (threadIdx.x < DIGITS) {
+        unsigned c[WAVES];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) c[w] = wcnt[w][threadIdx.x];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            wcnt[w][threadIdx.x] = mine;
+            mine += c[w];
+        }
+        incl = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned o = __shfl_up(incl, off);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) s_w[wave] = incl;
+    }
+    __syncthreads();
+    if (threadIdx.x < DIGITS) {
+        unsigned before = 0;
+        for (int w = 0; w < wave; ++w) before += s_w[w];
+        start[threadIdx.x] = before + incl - mine;
+        if (threadIdx.x == DIGITS - 1) start[DIGITS] = before + incl;
+    }
+    __syncthreads();
+}
+
+// Ranks of `per` rounds of a block's keys (thread's key j: wave * 64 * per + 64 j + lane): a key's place among
+// the wave's keys with its digit.  A round finds the lanes with the same digit by one ballot per bit; the wave's
+// running count of a digit is in LDS (wcnt, zero at the start), written by the last lane of each set.  Keys with
+// equal digits keep their order.
+template <int PER, int DIGITS>
+__device__ __forceinline__ void digit_ranks(const unsigned (&d)[PER], unsigned (&rank)[PER], int per, int n, int bits,
+                                            unsigned (*wcnt)[DIGITS])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j < per) {                             // uniform
+            const bool valid = (wave * per + j) * 64 + lane < n;
+            const unsigned long long same = lanes_alike(d[j], bits, valid);
+            const unsigned before = valid ? wcnt[wave][d[j]] : 0u;
+            rank[j] = before + (unsigned)__popcll(same & below);
+            if (valid && lane == 63 - __clzll(same)) wcnt[wave][d[j]] = before + (unsigned)__popcll(same);
+        }
+    }
+}
+
+struct scale_args {
+    const float *G;
+    const uint16_t *codes;
+    const float *codebooks;
+    int64_t rows;
+    int g, M, nbits, gpr;
+    float *grad_scales;
+};
+
+// d phi / d s of one output row by a team of kBlock threads (thread t of it; tmp: kBlock / 64 doubles of LDS);
+// VEC: g % 4 == 0, a thread takes 16-byte vectors.  All threads of the block call this.
+template <bool VEC, int kAhead>
+__device__ __forceinline__ void row_scale_grad(const scale_args &a, int64_t o, int t, double *tmp)
+{
+    const int g = a.g, M = a.M, gpr = a.gpr;
+    const int64_t csize = (int64_t)1 << a.nbits;
+    const unsigned mask = (unsigned)csize - 1u;
+    const int64_t in_features = (int64_t)gpr * g;
+    double acc = 0.0;
+    if (o < a.rows) {
+        if constexpr (VEC) {
+            const unsigned vpg = (unsigned)g / 4u;                  // vectors per group
+            const double inv_vpg = 1.0 / (double)vpg;
+            const int64_t nv = in_features / 4, part = (int64_t)vpg << 24;   // counted in 32 bits: whole groups, whole steps
+            const pv_f4 *C4 = reinterpret_cast<const pv_f4 *>(a.codebooks);
+            // kAhead vectors of a thread at a time: their codes, then their codewords, are in flight
+            // together (a row is only a few vectors per thread: one at a time the kernel is a chain
+            // of round trips); the terms are still added in index order
+            for (int64_t p0 = 0; p0 < nv; p0 += part) {
+                const int cnt = (int)(nv - p0 < part ? nv - p0 : part);
+                const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(a.G + o * in_features) + p0;
+                const uint16_t *row_codes = a.codes + (o * gpr + p0 / vpg) * M;
+                unsigned code[kAhead];
+                auto load_codes = [&](int e0) {
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u)
+                        code[u] = row_codes[(size_t)pv_row_of((unsigned)min(e0 + u * kBlock, cnt - 1), inv_vpg) * M] & mask;
+                };
+                load_codes(t);
+                for (int e0 = t; e0 < cnt; e0 += kBlock * kAhead) {
+                    pv_f4 gv[kAhead], q[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const unsigned e = (unsigned)min(e0 + u * kBlock, cnt - 1);
+                        gv[u] = G4[e];
+                        q[u] = C4[code[u] * vpg + (e - pv_row_of(e, inv_vpg) * vpg)];
+                    }
+                    load_codes(e0 + kBlock * kAhead);        // the next ones (past the end: the last one again)
+                    for (int m = 1; m < M; ++m) {
+                        pv_f4 c[kAhead];
+#pragma unroll
+                        for (int u = 0; u < kAhead; ++u) {
+                            const unsigned e = (unsigned)min(e0 + u * kBlock, cnt - 1), n = pv_row_of(e, inv_vpg);
+                            c[u] = C4[((size_t)m * csize + (row_codes[(size_t)n * M + m] & mask)) * vpg + (e - n * vpg)];
+                        }
+#pragma unroll
+                        for (int u = 0; u < kAhead; ++u) {
+                            q[u].x = q[u].x + c[u].x;
+                            q[u].y = q[u].y + c[u].y;
+                            q[u].z = q[u].z + c[u].z;
+                            q[u].w = q[u].w + c[u].w;
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (e0 + u * kBlock < cnt) {
+                            acc = acc + (double)gv[u].x * (double)q[u].x;
+                            acc = acc + (double)gv[u].y * (double)q[u].y;
+                            acc = acc + (double)gv[u].z * (double)q[u].z;
+                            acc = acc + (double)gv[u].w * (double)q[u].w;
+                        }
+                    }
+                }
+            }
+        } else {
+            for (int64_t e = t; e < in_features; e += kBlock) {
+                const int64_t n = o * gpr + e / g;
+                const int i = (int)(e % g);
+                float q = a.codebooks[(int64_t)(a.codes[n * M] & mask) * g + i];
+                for (int m = 1; m < M; ++m)
+                    q = q + a.codebooks[(m * csize + (a.codes[n * M + m] & mask)) * g + i];
+                acc = acc + (double)a.G[o * in_features + e] * (double)q;
+            }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc = acc + __shfl_down(acc, off);
+    if ((t & 63) == 0) tmp[t >> 6] = acc;
+    __syncthreads();
+    if (t == 0 && o < a.rows) {
+        double sum = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) sum = sum + tmp[w];
+        a.grad_scales[o] = (float)sum;
+    }
+}
+
+// one block per output row
+template <bool VEC>
+__global__ __launch_bounds__(kBlock) void k_pg_scales(scale_args a)
+{
+    __shared__ double tmp[kBlock / 64];
+    row_scale_grad<VEC, 4>(a, blockIdx.x, threadIdx.x, tmp);
+}
+
+// The first `sort_blocks` blocks put a tile of groups each in bucket order (stable), the rest take four
+// rows of the scale gradient each: the order is a chain of LDS round trips, the gradient a stream.
+template <bool VEC>
+__global__ __launch_bounds__(kTileBlock, 8) void k_pg_tiles(bucket_args b, scale_args sc, int sort_blocks)
+{
+    __shared__ unsigned wcnt[kTileWaves][kBuckets];
+    __shared__ unsigned s_first[kBuckets + 1], s_w[kBuckets / 64];
+    __shared__ unsigned s_out[kTile];
+    if ((int)blockIdx.x >= sort_blocks) {
+        const int team = threadIdx.x / kBlock;
+        row_scale_grad<VEC, 2>(sc, (int64_t)((int)blockIdx.x - sort_blocks) * (kTileBlock / kBlock) + team,
+                               threadIdx.x % kBlock, reinterpret_cast<double *>(s_out) + team * (kBlock / 64));
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int mi = (int)blockIdx.x / b.ntiles, tile = (int)blockIdx.x - mi * b.ntiles;
+    const int64_t base = (int64_t)tile * kTile;
+    const int n = b.N - base < kTile ? (int)(b.N - base) : kTile;
+    const int per = (n + kTileBlock - 1) / kTileBlock;
+    unsigned code[kTilePer], d[kTilePer], rank[kTilePer];
+#pragma unroll
+    for (int j = 0; j < kTilePer; ++j) {                  // all loads in flight before the first is used
+        const int i = (wave * per + j) * 64 + lane;
+        code[j] = b.codes[(base + (i < n ? i : n - 1)) * b.M + b.m0 + mi] & b.mask;
+    }
+    for (int w = threadIdx.x; w < kTileWaves * kBuckets; w += kTileBlock) (&wcnt[0][0])[w] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kTilePer; ++j) d[j] = code[j] >> b.low;
+    digit_ranks<kTilePer, kBuckets>(d, rank, per, n, b.high, wcnt);
+    digit_starts<kTileWaves, kBuckets>(wcnt, s_first, s_w);
+#pragma unroll
+    for (int j = 0; j < kTilePer; ++j) {
+        const int i = (wave * per + j) * 64 + lane;
+        if (j < per && i < n)
+            s_out[s_first[d[j]] + wcnt[wave][d[j]] + rank[j]] = (code[j] & ((1u << b.low) - 1u)) << 16 | (unsigned)i;
+    }
+    __syncthreads();
+    uint32_t *out = b.entries + (int64_t)mi * b.N + base;
+    for (int i = threadIdx.x; i < n; i += kTileBlock) out[i] = s_out[i];
+    uint16_t *first = b.first + ((int64_t)mi * b.ntiles + tile) * ((1 << b.high) + 1);
+    if ((int)threadIdx.x < 1 << b.high) first[threadIdx.x] = (uint16_t)s_first[threadIdx.x];
+    if (threadIdx.x == 0) first[1 << b.high] = (uint16_t)n;
+}
+
+// acc[v] += s_o * G[n, i * VEC + v] over the groups ids[a .. b) in that order, as many gathers together as fit
+// the registers
+template <int VEC>
+__device__ __forceinline__ void ordered_sum(double (&acc)[VEC], const unsigned *ids, int a, int b,
+                                            const float *__restrict__ G, const float *__restrict__ scales,
+                                            double inv_gpr, int g, int i)
+{
+    typedef float vec __attribute__((ext_vector_type(VEC)));
+    constexpr int kInFlight = VEC == 4 ? 8 : 16;
     for (int r0 = a; r0 < b; r0 += kInFlight) {
-        float gv[kInFlight], sv[kInFlight];
+        vec gv[kInFlight];
+        float sv[kInFlight];
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
-            const int r = r0 + u < b ? r0 + u : b - 1;
-            const int n = ids[r];
-            gv[u] = G[(int64_t)n * g + i];
-            sv[u] = HAVE_SCALES ? s_of[r] : scales[n / gpr];
+            const unsigned n = ids[min(r0 + u, b - 1)];
+            gv[u] = *reinterpret_cast<const vec *>(G + (int64_t)n * g + i * VEC);
+            sv[u] = scales[pv_row_of(n, inv_gpr)];
         }
 #pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-            const double next = acc + (double)sv[u] * (double)gv[u];
-            acc = r0 + u < b ? next : acc;
-        }
-    }
-    return acc;
-}
-
-// Segments of up to kLong groups: one team of TEAM lanes per codeword (TEAM = the group size
-// rounded up to a power of two, at least 8).  The team stages the segment's ids and row
-// scales in LDS, then lane i sums dimension i in segment order.  A longer segment is put on
-// the list for k_pg_long.
-template <int TEAM>
-__global__ __launch_bounds__(kBlock) void k_pg_short(const int32_t *__restrict__ start,
-                                                     const int32_t *__restrict__ order,
-                                                     const float *__restrict__ G,
-                                                     const float *__restrict__ scales, int gpr, int g,
-                                                     int csize, int32_t *__restrict__ long_list,
-                                                     unsigned *__restrict__ nlong,
-                                                     float *__restrict__ out)
-{
-    constexpr int kTeams = kBlock / TEAM;
-    __shared__ int s_id[kTeams][kLong];
-    __shared__ float s_s[kTeams][kLong];
-    const int team = threadIdx.x / TEAM, i = threadIdx.x % TEAM;
-    const int c = blockIdx.x * kTeams + team;
-    int lo = 0, len = 0;
-    bool mine = false;
-    if (c < csize) {
-        lo = start[c];
-        len = start[c + 1] - lo;
-        mine = len <= kLong;
-        if (!mine) {
-            len = 0;
-            if (i == 0) long_list[atomicAdd(nlong, 1u)] = c;
-        }
-    }
-    for (int r = i; r < len; r += TEAM) s_id[team][r] = order[lo + r];
-    __syncthreads();
-    // the first kFirst gathers of G and the row scales of the whole segment are requested
-    // together: a typical segment costs one round trip here, not one per few groups
-    constexpr int kFirst = 32;
-    float gv[kFirst];
-    const int ii = i < g ? i : 0;
-    if (len > 0) {
+        for (int u = 0; u < kInFlight; ++u)
+            if (r0 + u < b) {
 #pragma unroll
-        for (int u = 0; u < kFirst; ++u)
-            gv[u] = G[(int64_t)s_id[team][u < len ? u : len - 1] * g + ii];
-    }
-    for (int r = i; r < len; r += TEAM) s_s[team][r] = scales[s_id[team][r] / gpr];
-    __syncthreads();
-    if (mine && i < g) {
-        double acc = 0.0;
-        if (len > 0) {
-#pragma unroll
-            for (int u = 0; u < kFirst; ++u) {
-                const double next = acc + (double)s_s[team][u < len ? u : len - 1] * (double)gv[u];
-                acc = u < len ? next : acc;
+                for (int v = 0; v < VEC; ++v) {
+                    acc[v] = acc[v] + (double)sv[u] * (double)gv[u][v];
+                }
             }
-            if (len > kFirst)
-                acc = ordered_sum<true>(s_id[team], s_s[team], G, scales, gpr, g, i, kFirst, len, acc);
-        }
-        out[(int64_t)c * g + i] = (float)acc;
     }
 }
 
-// Segments longer than kLong: one block per segment.  Its teams sum pieces of kLong ids in
-// order (piece p of the segment that starts at sorted position lo keeps its sum in
-// partial[lo / kLong + p], p >= 1: the ranges of different segments cannot meet; piece 0 stays
-// in LDS), and the first g threads add the piece sums in piece order.
-template <int TEAM>
-__global__ __launch_bounds__(kBlock) void k_pg_long(const int32_t *__restrict__ long_list,
-                                                    const unsigned *__restrict__ nlong,
-                                                    const int32_t *__restrict__ start,
-                                                    const int32_t *__restrict__ order,
-                                                    const float *__restrict__ G,
-                                                    const float *__restrict__ scales, int gpr, int g,
-                                                    double *partial, float *__restrict__ out)
+// One block per bucket.  The tiles' runs of the bucket are laid end to end in LDS (that is group order), put
+// in code order (stable), and every codeword's groups are summed by a team of LANES lanes, VEC elements
+// each, in ascending group order.  A bucket that does not fit is worked through in chunks, the
+// sums going on in device memory (`carry`, written and read by this block alone).  A codeword with more than kLong
+// groups in a chunk is cut into pieces that the teams share and that are added in piece order.
+constexpr int kSumBlock = 512;
+constexpr int kSumWaves = kSumBlock / 64;
+constexpr int kBucketCodes = 1 << (16 - kBucketBits);   // codes of a bucket at most
+// With chunks of 5120 groups 2^21 groups spread over the codewords fit as well (54 us), but a codeword that holds a
+// twentieth of them costs more than the sort did: 801 us a call against 674, 674 with 8192.
+constexpr int kSumPer = 16;
+constexpr int kChunk = kSumBlock * kSumPer;
+constexpr int kWindow = kSumBlock;                // tiles looked at together
+constexpr int kPiece = 32;
+static_assert(kWindow <= 1024 && kBucketCodes <= 256 && kBucketCodes <= kSumBlock, "an entry in LDS: 8 + 10 + 13 bits");
+
+template <int LANES, int VEC>
+__global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, const float *__restrict__ G,
+                                                             const float *__restrict__ scales, double inv_gpr, int g,
+                                                             double *carry, float *__restrict__ out)
 {
-    constexpr int kTeams = kBlock / TEAM;
-    __shared__ double s_first[64];
-    const int team = threadIdx.x / TEAM, i = threadIdx.x % TEAM;
-    const int count = (int)*nlong;
-    for (int li = blockIdx.x; li < count; li += gridDim.x) {
-        const int c = long_list[li];
-        const int lo = start[c], len = start[c + 1] - lo;
-        const int32_t *ids = order + lo;
-        const int pieces = (len + kLong - 1) / kLong;
-        double *mine = partial + (int64_t)(lo / kLong) * g;
-        for (int p = team; p < pieces; p += kTeams) {
-            const int a = p * kLong, b = a + kLong < len ? a + kLong : len;
-            if (i < g) {
-                const double acc = ordered_sum<false>(ids, nullptr, G, scales, gpr, g, i, a, b);
-                if (p == 0) s_first[i] = acc;
-                else mine[(int64_t)p * g + i] = acc;
+    constexpr int kTeams = kSumBlock / LANES;
+    __shared__ unsigned s_ent[kChunk];
+    __shared__ union {                                // where runs go and counts while a chunk is put in order, then sums of pieces
+        struct {
+            unsigned cnt[kSumWaves][kBucketCodes], pre[kWindow + 1];
+            unsigned short lo[kWindow];
+        } order;
+        double part[kSumBlock * VEC];
+    } s_mem;
+    auto &wcnt = s_mem.order.cnt;
+    auto &s_pre = s_mem.order.pre;
+    auto &s_lo = s_mem.order.lo;
+    auto &s_part = s_mem.part;
+    __shared__ unsigned s_start[kBucketCodes + 1], s_item[kBucketCodes + 1], s_w4[kBucketCodes / 64], s_scan[kSumWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int nb = 1 << b.high, nl = 1 << b.low;
+    const int mi = (int)blockIdx.x / nb, bucket = (int)blockIdx.x - mi * nb;
+    const uint32_t *entries = b.entries + (int64_t)mi * b.N;
+    const uint16_t *first = b.first + (int64_t)mi * b.ntiles * (nb + 1) + bucket;
+    const int team = threadIdx.x / LANES, i = threadIdx.x % LANES;
+    const int64_t row0 = ((int64_t)(b.m0 + mi) << (b.low + b.high)) + (int64_t)bucket * nl;   // row of `out`
+    carry += ((int64_t)mi << (b.low + b.high)) * g + (int64_t)bucket * nl * g;
+    out += row0 * g;
+    bool whole = true;                              // the first chunk: sums start at zero
+    unsigned skip = 0;                              // groups of tile w0's run that an earlier chunk took
+    for (int w0 = 0; w0 < b.ntiles;) {
+        // where the runs of the next tiles go, and how many of them fit
+        const int t = w0 + (int)threadIdx.x;
+        unsigned lo = 0, len = 0;
+        if (t < b.ntiles) {
+            lo = first[(int64_t)t * (nb + 1)];
+            len = first[(int64_t)t * (nb + 1) + 1] - lo;
+            if (threadIdx.x == 0) {
+                lo += skip;
+                len -= skip;
+            }
+        }
+        unsigned incl = len;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const unsigned o = __shfl_up(incl, off);
+            if (lane >= off) incl += o;
+        }
+        if (lane == 63) s_scan[wave] = incl;
+        for (int w = threadIdx.x; w < kSumWaves * kBucketCodes; w += kSumBlock) (&wcnt[0][0])[w] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSumWaves; ++w) incl += w < wave ? s_scan[w] : 0u;
+        s_pre[threadIdx.x] = incl - len;
+        s_lo[threadIdx.x] = (unsigned short)lo;
+        if (threadIdx.x == kWindow - 1) s_pre[kWindow] = incl;
+        const int fit = __syncthreads_count(t < b.ntiles && incl <= (unsigned)kChunk);
+        // the runs that fit, and the beginning of the next one (where the window ends first: nothing of it)
+        const bool cut = fit < kWindow && w0 + fit < b.ntiles;
+        const int runs = cut ? fit + 1 : fit;
+        const int n = cut ? kChunk : (int)s_pre[fit];
+        const bool last = w0 + fit >= b.ntiles;
+        const unsigned taken = cut ? (fit == 0 ? skip : 0u) + (unsigned)(n - (int)s_pre[fit]) : 0u;   // (s_pre gives way to sums below)
+        auto put = [&](int at, int r, unsigned e) { s_ent[at] = (e >> 16) << 23 | (unsigned)r << kTileBits | (e & (kTile - 1)); };
+        if (n > runs * 256) {                       // long runs (a popular codeword): the block takes one after the other
+            for (int r = 0; r < runs; ++r) {
+                const int p = (int)s_pre[r], l = min((int)s_pre[r + 1], n) - p;
+                const uint32_t *run = entries + (unsigned)(w0 + r) * kTile + s_lo[r];
+                for (int q = threadIdx.x; q < l; q += kSumBlock) put(p + q, r, run[q]);
+            }
+        } else {                                    // a wave a run, eight of them in flight
+            constexpr int kRuns = 8;
+            for (int r0 = wave; r0 < runs; r0 += kSumWaves * kRuns) {
+                unsigned v[kRuns];
+#pragma unroll
+                for (int u = 0; u < kRuns; ++u) {
+                    const int r = min(r0 + u * kSumWaves, runs - 1);
+                    const int l = min((int)s_pre[r + 1], n) - (int)s_pre[r];
+                    v[u] = entries[(unsigned)(w0 + r) * kTile + s_lo[r] + (lane < l ? lane : 0)];
+                }
+#pragma unroll
+                for (int u = 0; u < kRuns; ++u) {
+                    const int r = r0 + u * kSumWaves;
+                    if (r >= runs) break;
+                    const int p = (int)s_pre[r], l = min((int)s_pre[r + 1], n) - p;
+                    if (lane < l) put(p + lane, r, v[u]);
+                    for (int q = 64 + lane; q < l; q += 64) put(p + q, r, entries[(unsigned)(w0 + r) * kTile + s_lo[r] + q]);
+                }
             }
         }
         __syncthreads();
-        if ((int)threadIdx.x < g) {
-            double acc = s_first[threadIdx.x];
-            int p = 1;
-            for (; p + 4 <= pieces; p += 4) {          // four loads in flight, added in piece order
-                double v[4];
+        // code order
+        const int per = (n + kSumBlock - 1) / kSumBlock;
+        {
+            unsigned e[kSumPer], d[kSumPer], rank[kSumPer];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = mine[(int64_t)(p + u) * g + threadIdx.x];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc = acc + v[u];
+            for (int j = 0; j < kSumPer; ++j) {
+                const int q = (wave * per + j) * 64 + lane;
+                e[j] = j < per && q < n ? s_ent[q] : 0u;
+                d[j] = e[j] >> 23;
             }
-            for (; p < pieces; ++p) acc = acc + mine[(int64_t)p * g + threadIdx.x];
-            out[(int64_t)c * g + threadIdx.x] = (float)acc;
+            digit_ranks<kSumPer, kBucketCodes>(d, rank, per, n, b.low, wcnt);
+            digit_starts<kSumWaves, kBucketCodes>(wcnt, s_start, s_w4);
+#pragma unroll
+            for (int j = 0; j < kSumPer; ++j) {
+                const int q = (wave * per + j) * 64 + lane;
+                if (j < per && q < n)
+                    s_ent[s_start[d[j]] + wcnt[wave][d[j]] + rank[j]] =
+                        (unsigned)(w0 + (int)((e[j] >> kTileBits) & 1023u)) << kTileBits | (e[j] & (kTile - 1));
+            }
         }
-        __syncthreads();
+        // work items: a codeword, or a piece of one
+        unsigned clen = 0;
+        if ((int)threadIdx.x < nl) clen = s_start[threadIdx.x + 1] - s_start[threadIdx.x];
+        const bool pieces = __syncthreads_or(clen > (unsigned)kLong);
+        const int piece = max(kPiece, (n + kTeams - 1) / kTeams);
+        int items = nl;
+        if (pieces) {
+            unsigned cnt = (int)threadIdx.x < nl ? (clen > (unsigned)kLong ? (clen + piece - 1) / piece : 1u) : 0u;
+            unsigned inc = cnt;
+            if (threadIdx.x < kBucketCodes) {
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const unsigned o = __shfl_up(inc, off);
+                    if (lane >= off) inc += o;
+                }
+                if (lane == 63) s_w4[wave] = inc;
+            }
+            __syncthreads();
+            if (threadIdx.x < kBucketCodes) {
+                for (int w = 0; w < wave; ++w) inc += s_w4[w];
+                s_item[threadIdx.x] = inc - cnt;
+                if (threadIdx.x == kBucketCodes - 1) s_item[kBucketCodes] = inc;
+            }
+            __syncthreads();
+            items = (int)s_item[kBucketCodes];
+        }
+        for (int i0 = 0; i0 < items; i0 += kTeams) {
+            const int item = i0 + team;
+            int c = item, p = 0, np = 1;
+            if (pieces && item < items) {
+                int hi = nl;                        // the last codeword whose items start at or before this one
+                c = 0;
+                while (hi - c > 1) {
+                    const int mid = (c + hi) >> 1;
+                    if ((int)s_item[mid] <= item) c = mid;
+                    else hi = mid;
+                }
+                p = item - (int)s_item[c];
+                np = (int)(s_item[c + 1] - s_item[c]);
+            }
+            const bool mine = item < items && i * VEC < g;
+            double acc[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+            auto finish = [&]() {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    if (last) out[(int64_t)c * g + i * VEC + v] = (float)acc[v];
+                    else carry[(int64_t)c * g + i * VEC + v] = acc[v];
+                }
+            };
+            auto go_on = [&]() {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] = carry[(int64_t)c * g + i * VEC + v];
+            };
+            if (mine) {
+                int from = (int)s_start[c], to = (int)s_start[c + 1];
+                if (np == 1 && !whole) go_on();
+                if (np > 1) {
+                    from += p * piece;
+                    to = min(to, from + piece);
+                }
+                ordered_sum<VEC>(acc, s_ent, from, to, G, scales, inv_gpr, g, i);
+                if (np == 1) finish();
+            }
+            if (pieces) {
+                if (mine && np > 1)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) s_part[(team * LANES + i) * VEC + v] = acc[v];
+                __syncthreads();
+                if (mine && np > 1 && (p == 0 || team == 0)) {   // the codeword's first piece of this round adds up
+                    const int more = min(np - p, kTeams - team);
+                    int q = 0;
+                    if (p > 0 || !whole) go_on();
+                    else q = 1;                     // its own is in acc
+                    for (; q < more; q += 8) {      // eight reads in flight, added in order
+                        double x[8][VEC];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v)
+                                x[u][v] = s_part[((team + min(q + u, more - 1)) * LANES + i) * VEC + v];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (q + u < more)
+#pragma unroll
+                                for (int v = 0; v < VEC; ++v) acc[v] = acc[v] + x[u][v];
+                    }
+                    if (p + more == np) {
+                        finish();
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) carry[(int64_t)c * g + i * VEC + v] = acc[v];
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        skip = taken;
+        w0 += fit;
+        whole = false;
+        __syncthreads();                            // ids, counts and sums of this chunk are done with
     }
 }
 
@@ -541,90 +893,6 @@ __global__ __launch_bounds__(kBlock) void k_pg_small_final(small_mem mem, int bl
     }
 }
 
-// one block per output row; VEC: g % 4 == 0, a thread takes 16-byte vectors
-template <bool VEC>
-__global__ __launch_bounds__(kBlock) void k_pg_scales(const float *__restrict__ G,
-                                                      const uint16_t *__restrict__ codes,
-                                                      const float *__restrict__ codebooks, int g,
-                                                      int M, int nbits, int gpr,
-                                                      float *__restrict__ grad_scales)
-{
-    __shared__ double tmp[kBlock / 64];
-    const int64_t o = blockIdx.x;
-    const int64_t csize = (int64_t)1 << nbits;
-    const unsigned mask = (unsigned)csize - 1u;
-    const int64_t in_features = (int64_t)gpr * g;
-    double acc = 0.0;
-    if constexpr (VEC) {
-        const int vpg = g / 4;                                  // vectors per group
-        const int64_t nv = in_features / 4;
-        const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(G + o * in_features);
-        const pv_f4 *C4 = reinterpret_cast<const pv_f4 *>(codebooks);
-        // kAhead vectors of a thread at a time: their codes, then their codewords, are in flight
-        // together (a row is only a few vectors per thread: one at a time the kernel is a chain
-        // of round trips); the terms are still added in index order
-        constexpr int kAhead = 4;
-        for (int64_t e0 = threadIdx.x; e0 < nv; e0 += (int64_t)kBlock * kAhead) {
-            pv_f4 gv[kAhead], q[kAhead];
-            unsigned code[kAhead];
-            int q4[kAhead];
-            int64_t n[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                const int64_t e = e0 + (int64_t)u * kBlock;
-                const int64_t ec = e < nv ? e : nv - 1;
-                n[u] = o * gpr + ec / vpg;
-                q4[u] = (int)(ec % vpg);
-                gv[u] = __builtin_nontemporal_load(&G4[ec]);
-                code[u] = codes[n[u] * M] & mask;
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) q[u] = C4[((int64_t)code[u] * g) / 4 + q4[u]];
-            for (int m = 1; m < M; ++m) {
-                pv_f4 c[kAhead];
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u)
-                    c[u] = C4[((m * csize + (codes[n[u] * M + m] & mask)) * g) / 4 + q4[u]];
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    q[u].x = q[u].x + c[u].x;
-                    q[u].y = q[u].y + c[u].y;
-                    q[u].z = q[u].z + c[u].z;
-                    q[u].w = q[u].w + c[u].w;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                if (e0 + (int64_t)u * kBlock < nv) {
-                    acc = acc + (double)gv[u].x * (double)q[u].x;
-                    acc = acc + (double)gv[u].y * (double)q[u].y;
-                    acc = acc + (double)gv[u].z * (double)q[u].z;
-                    acc = acc + (double)gv[u].w * (double)q[u].w;
-                }
-            }
-        }
-    } else {
-        for (int64_t e = threadIdx.x; e < in_features; e += kBlock) {
-            const int64_t n = o * gpr + e / g;
-            const int i = (int)(e % g);
-            float q = codebooks[(int64_t)(codes[n * M] & mask) * g + i];
-            for (int m = 1; m < M; ++m)
-                q = q + codebooks[(m * csize + (codes[n * M + m] & mask)) * g + i];
-            const float gv = G[o * in_features + e];
-            acc = acc + (double)gv * (double)q;
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc = acc + __shfl_down(acc, off);
-    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) t = t + tmp[w];
-        grad_scales[o] = (float)t;
-    }
-}
-
 inline size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -639,6 +907,7 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
     const int csize = 1 << l->nbits;
     const unsigned mask = (unsigned)csize - 1u;
     hipStream_t sm = ctx->stream;
+    const scale_args sc{G, codes, codebooks, l->out_features, g, M, l->nbits, gpr, grad_scales};
 
     // small codebooks: per-block LDS tables instead of a sort
     const int64_t entries = (int64_t)M * csize * g;
@@ -669,8 +938,7 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
                             reinterpret_cast<double *>(p + o_unit)};
         pv_timed t(ctx, PV_K_PSTEP);
         if (grad_scales && !rows)
-            hipLaunchKernelGGL(k_pg_scales<true>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,
-                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales);
+            hipLaunchKernelGGL(k_pg_scales<true>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm, sc);
 #define PV_SMALL(V_)                                                                             \
     do {                                                                                         \
         if (rows)                                                                                \
@@ -696,91 +964,42 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
         return PV_OK;
     }
 
-    const size_t nn = (size_t)N;
-    const int nblocks = (int)((N + kSortTile - 1) / kSortTile);           // tiles of a sorting pass
-    const int hist_n = 256 * nblocks;
-    size_t o_start = 0;
-    size_t o_long = o_start + align_up((size_t)(csize + 1) * 4);
-    size_t o_nlong = o_long + align_up((size_t)csize * 4);
-    size_t o_total = o_nlong + 256;
-    size_t o_hist = o_total + 1024;
-    size_t o_base = o_hist + align_up((size_t)hist_n * 4);
-    size_t o_keys_a = o_base + align_up((size_t)hist_n * 4);
-    size_t o_keys_b = o_keys_a + align_up(nn * 2);
-    size_t o_vals_a = o_keys_b + align_up(nn * 2);
-    size_t o_order = o_vals_a + align_up(nn * 4);
-    size_t o_part = o_order + align_up(nn * 4);
-    size_t total = o_part + align_up((size_t)(N / kLong + 2) * g * 8);
+    // Two codebooks at a time: 8 bytes a group of scratch whatever M.
+    const int low = l->nbits > kBucketBits ? l->nbits - kBucketBits : 0, high = l->nbits - low;
+    const int nb = 1 << high;
+    const int64_t ntiles = (N + kTile - 1) / kTile;
+    const int at_once = M < 2 ? M : 2;
+    // sums that go on from one chunk, or one round of pieces, to the next (a codeword may hold every group)
+    const bool chunks = N > kLong;
+    const size_t o_first = align_up((size_t)at_once * N * 4);
+    const size_t o_carry = o_first + align_up((size_t)at_once * ntiles * (nb + 1) * 2);
+    const size_t total = o_carry + (chunks ? (size_t)at_once * csize * g * 8 : 0);
     pv_status st = pv_ensure(ctx, ctx->pstep, total);
     if (st != PV_OK) return st;
     char *base = static_cast<char *>(ctx->pstep.ptr);
-    int32_t *start = reinterpret_cast<int32_t *>(base + o_start);
-    int32_t *long_list = reinterpret_cast<int32_t *>(base + o_long);
-    unsigned *nlong = reinterpret_cast<unsigned *>(base + o_nlong);
-    unsigned *dig_totals = reinterpret_cast<unsigned *>(base + o_total);
-    unsigned *hist = reinterpret_cast<unsigned *>(base + o_hist);
-    unsigned *hbase = reinterpret_cast<unsigned *>(base + o_base);
-    uint16_t *keys_a = reinterpret_cast<uint16_t *>(base + o_keys_a);
-    uint16_t *keys_b = reinterpret_cast<uint16_t *>(base + o_keys_b);
-    int32_t *vals_a = reinterpret_cast<int32_t *>(base + o_vals_a);
-    int32_t *order = reinterpret_cast<int32_t *>(base + o_order);
-    double *partial = reinterpret_cast<double *>(base + o_part);
+    double *carry = reinterpret_cast<double *>(base + o_carry);
+    const double inv_gpr = 1.0 / (double)gpr;
 
     pv_timed t(ctx, PV_K_PSTEP);
-    int team = 8;
-    while (team < g) team <<= 1;      // lanes per work item (g <= 64 checked by the caller)
-    const int teams_per_block = kBlock / team;
-    const unsigned sblocks = (unsigned)((csize + teams_per_block - 1) / teams_per_block);
-    int64_t max_long = N / (kLong + 1);           // segments that can be longer than kLong
-    if (max_long > csize) max_long = csize;
-    if (max_long > 2048) max_long = 2048;         // blocks stride over the list
-    const bool two = l->nbits > 8;
-    for (int m = 0; m < M; ++m) {
-        // pass over the low 8 bits of the codes (the only one when B <= 8) ...
-        uint16_t *k1 = two ? keys_a : keys_b;
-        int32_t *v1 = two ? vals_a : order;
-        const code_keys ck{codes, M, m, mask};
-        hipLaunchKernelGGL(k_digit_hist<code_keys>, dim3(nblocks), dim3(kSortBlock), 0, sm, ck, N, 0,
-                           nblocks, hist);
-        hipLaunchKernelGGL(k_row_scan, dim3(256), dim3(kRadixBlock), 0, sm, hist, nblocks, hbase, dig_totals);
-        hipLaunchKernelGGL((k_digit_scatter<code_keys, uint16_t>), dim3(nblocks), dim3(kSortBlock), 0,
-                           sm, ck, (const int32_t *)nullptr, N, 0, nblocks, hbase, dig_totals, k1, v1);
-        if (two) {   // ... and over the high ones
-            const plain_keys<uint16_t> pk{keys_a};
-            hipLaunchKernelGGL(k_digit_hist<plain_keys<uint16_t>>, dim3(nblocks), dim3(kSortBlock), 0,
-                               sm, pk, N, 8, nblocks, hist);
-            hipLaunchKernelGGL(k_row_scan, dim3(256), dim3(kRadixBlock), 0, sm, hist, nblocks, hbase,
-                               dig_totals);
-            hipLaunchKernelGGL((k_digit_scatter<plain_keys<uint16_t>, uint16_t>), dim3(nblocks),
-                               dim3(kSortBlock), 0, sm, pk, (const int32_t *)vals_a, N, 8, nblocks, hbase,
-                               dig_totals, keys_b, order);
-        }
-        hipLaunchKernelGGL(k_pg_starts, dim3((unsigned)((N + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                           sm, keys_b, N, csize, start, nlong);
-        float *out = grad_codebooks + (int64_t)m * csize * g;
-#define PV_ACC(TEAM_)                                                                            \
-    do {                                                                                         \
-        hipLaunchKernelGGL(k_pg_short<TEAM_>, dim3(sblocks), dim3(kBlock), 0, sm, start, order, G, \
-                           scales, gpr, g, csize, long_list, nlong, out);                         \
-        if (max_long > 0)                                                                        \
-            hipLaunchKernelGGL(k_pg_long<TEAM_>, dim3((unsigned)max_long), dim3(kBlock), 0, sm,   \
-                               long_list, nlong, start, order, G, scales, gpr, g, partial, out);  \
-    } while (0)
-        switch (team) {
-        case 8: PV_ACC(8); break;
-        case 16: PV_ACC(16); break;
-        case 32: PV_ACC(32); break;
-        default: PV_ACC(64); break;
-        }
-#undef PV_ACC
-    }
-    if (grad_scales) {
-        if (g % 4 == 0)
-            hipLaunchKernelGGL(k_pg_scales<true>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,
-                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales);
-        else
-            hipLaunchKernelGGL(k_pg_scales<false>, dim3((unsigned)l->out_features), dim3(kBlock), 0, sm,
-                               G, codes, codebooks, g, M, l->nbits, gpr, grad_scales);
+    for (int m0 = 0; m0 < M; m0 += at_once) {
+        const int now = M - m0 < at_once ? M - m0 : at_once;
+        const bucket_args b{codes, N, M, m0, mask, low, high, (int)ntiles, reinterpret_cast<uint32_t *>(base),
+                            reinterpret_cast<uint16_t *>(base + o_first)};
+        const int sort_blocks = (int)(ntiles * now), rows_a_block = kTileBlock / kBlock;
+        const int64_t row_blocks = m0 == 0 && grad_scales ? (l->out_features + rows_a_block - 1) / rows_a_block : 0;
+        const dim3 grid((unsigned)(sort_blocks + row_blocks));
+        if (g % 4 == 0) hipLaunchKernelGGL(k_pg_tiles<true>, grid, dim3(kTileBlock), 0, sm, b, sc, sort_blocks);
+        else hipLaunchKernelGGL(k_pg_tiles<false>, grid, dim3(kTileBlock), 0, sm, b, sc, sort_blocks);
+#define PV_SUMS(LANES_, VEC_)                                                                          \
+    hipLaunchKernelGGL((k_pg_buckets<LANES_, VEC_>), dim3((unsigned)(nb * now)), dim3(kSumBlock), 0, sm, b, G, \
+                       scales, inv_gpr, g, carry, grad_codebooks)
+        // lanes that share a codeword: vectors as wide as the group's rows allow, four lanes at least
+        if (g == 8) PV_SUMS(4, 2);
+        else if (g % 4 == 0 && g <= 16) PV_SUMS(4, 4);
+        else if (g % 4 == 0) PV_SUMS(16, 4);
+        else if (g <= 8) PV_SUMS(8, 1);
+        else PV_SUMS(64, 1);
+#undef PV_SUMS
     }
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;

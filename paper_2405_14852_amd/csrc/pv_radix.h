@@ -1,13 +1,10 @@
 // Stable least-significant-digit radix sort of (key, value) pairs on the device, 8 bits a
-// pass, written for the two places that need one: the 16-bit codes of the P step (Alg. 3)
-// and the 32-bit update norms that rank the candidates of the trust-ratio rule (Sec. 4.3).
+// pass, for the 32-bit update norms that rank the candidates of the trust-ratio rule (Sec. 4.3).
 // A pass is three kernels - digit histogram per tile, prefix sums per digit row, scatter - and
 // no atomic touches device memory: ranks come from wave ballots and per-wave counters in LDS,
 // so keys with equal digits keep the order they came in.  Keys are read through a functor
 // (KEYS: unsigned operator()(int64_t e) const), values are the element's index in the first
-// pass (vals == nullptr) and carried afterwards.  Kernels live in an unnamed namespace: every
-// file that includes this header instantiates its own.
-#pragma once
+// pass (vals == nullptr) and carried afterwards.  #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -113,6 +113,42 @@ def test_codebook_grads_long_buckets_sorted_in_lds_and_in_global_memory():
     assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
 
 
+@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 11, (70, 4104)),        # 35 910 groups: five tiles, the last ragged
+                                         (16, 3, 10, (33, 4000)),       # three codebooks: two launches
+                                         (4, 1, 16, (16, 32768)),       # 131 072 groups, two a codeword
+                                         (12, 1, 9, (96, 3072)), (20, 1, 12, (21, 2000)), (64, 1, 9, (64, 8192)),
+                                         (6, 2, 9, (37, 3000)), (33, 1, 13, (8, 3300)), (1, 1, 9, (5, 4099)),
+                                         (8, 1, 9, (8, 40)),            # fewer groups than a wave
+                                         (1, 1, 9, (1100, 4096))])      # 550 tiles: two windows of them
+@pytest.mark.parametrize("kind", ["spread", "half", "one", "rows"])
+def test_codebook_grads_buckets(g, M, B, shape, kind):
+    """Large codebooks: codes drawn evenly, half the groups on one codeword, all of them, and codes
+    that follow the rows (so that a tile's groups lie in few buckets).  Sums of up to 128 groups have
+    the oracle's bits; a second run repeats the first."""
+    wl = workloads.make(shape[0], shape[1], g, M, B, seed=94, sigma_g=1e-2)
+    rng = np.random.default_rng(94)
+    if kind == "half":
+        wl.codes[rng.random(wl.codes.shape) < 0.5] = (1 << B) - 3
+    elif kind == "one":
+        wl.codes[:] = 5
+    elif kind == "rows":
+        wl.codes[:] = (np.arange(shape[0]) * (1 << B) // shape[0])[:, None, None]
+    gc, gs, gc_ref, gs_ref = run_case(wl)
+    q = oracle.dequantize(wl.codes, wl.codebooks, np.ones_like(wl.scales))
+    assert close_sum(gs, gs_ref, np.abs(wl.G * q).sum(axis=1))
+    size = np.abs(wl.G).reshape(-1, g).astype(np.float64) * np.repeat(np.abs(wl.scales), wl.layout.groups_per_row)[:, None]
+    for m in range(M):
+        codes = wl.codes[..., m].ravel()
+        thin = np.bincount(codes, minlength=1 << B) <= 128
+        assert np.array_equal(gc[m, thin].view(np.uint32), gc_ref[m, thin].view(np.uint32))
+        mag = np.zeros((1 << B, g))
+        np.add.at(mag, codes, size)
+        assert close_sum(gc[m], gc_ref[m], mag)
+    again, gs2, _, _ = run_case(wl)
+    assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
+    assert np.array_equal(gs.view(np.uint32), gs2.view(np.uint32))
+
+
 @pytest.mark.parametrize("g,M,B,shape", [(8, 1, 16, (256, 2048)), (16, 1, 12, (128, 2048)), (8, 2, 8, (512, 4096)),
                                          (8, 1, 8, (64, 512))])
 def test_codebook_grads_repeat_bit_for_bit(g, M, B, shape):
