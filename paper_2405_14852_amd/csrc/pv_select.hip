@@ -10,7 +10,7 @@
 //
 // Launches: [scores + digit-0 histogram] [collect] [last digit] [ordered write]; up to
 // kSmallGroups groups the last three are one block's work, and for k = N the sweep writes the
-// ids itself.
+// ids itself.  Among many single weights the sweep collects and writes no scores (k_targets_lists).
 // - The sweep counts digit 0 (exponent and four mantissa bits) in an LDS histogram; its blocks
 //   are persistent so that clearing and flushing it is paid once per block.
 // - k_collect is the only pass over all scores after the sweep.  It resolves digit 0, counts
@@ -52,7 +52,8 @@ constexpr int kCopies = 8;
 constexpr int kFine = 64;                      // counters per coarse counter, one per lane of a wave
 constexpr int hist_words(int bins) { return kCopies * (bins + bins / kFine); }
 constexpr int kHist0 = 0, kHist1 = kHist0 + hist_words(kFirstBins), kHist2 = kHist1 + hist_words(kMidBins);
-constexpr int kHistTotal = kHist2 + hist_words(kLastBins);
+constexpr int kHistS = kHist2 + hist_words(kLastBins);   // a sample's digit 0
+constexpr int kHistTotal = kHistS + hist_words(kFirstBins);
 
 // The passes after the sweep: region r of kSelWaves * blocks is the contiguous range of groups
 // that wave r works on in every one of them.
@@ -146,24 +147,25 @@ __device__ __forceinline__ int pick_lane(unsigned count, unsigned &kk)
 }
 
 // The digit d of the histogram `h` (in device memory, `bins` counters) with
-// count(> d) < kk <= count(>= d); kk becomes kk - count(> d).  Called by all threads of a block of
-// at least kCopies waves: wave c fetches the 64 counters of copy c, every wave adds up all
-// copies (the result needs no broadcast).  `tmp`: 2 * kCopies * 64 unsigneds of LDS.
+// count(> d) < kk <= count(>= d); kk becomes kk - count(> d).  Called by all threads of a block:
+// its waves fetch the 64 counters of a copy each, every wave adds up all copies (the result needs
+// no broadcast).  `tmp`: 2 * kCopies * 64 unsigneds of LDS.
 // `share`: the count of the digit.
+template <int WAVES>
 __device__ __forceinline__ int pick_digit(const unsigned *__restrict__ h, int bins, unsigned &kk, unsigned *tmp,
                                           unsigned *share = nullptr)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int ncoarse = bins / kFine;
-    if (wave < kCopies)
-        tmp[wave * 64 + lane] = lane < ncoarse ? h[kCopies * bins + wave * ncoarse + (ncoarse - 1 - lane)] : 0u;
+    for (int i = wave; i < kCopies; i += WAVES)
+        tmp[i * 64 + lane] = lane < ncoarse ? h[kCopies * bins + i * ncoarse + (ncoarse - 1 - lane)] : 0u;
     __syncthreads();
     unsigned c = 0;
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) c += tmp[i * 64 + lane];
     const int top = ncoarse - 1 - pick_lane(c, kk);
     unsigned *fine = tmp + kCopies * 64;
-    if (wave < kCopies) fine[wave * 64 + lane] = h[wave * bins + top * kFine + (kFine - 1 - lane)];
+    for (int i = wave; i < kCopies; i += WAVES) fine[i * 64 + lane] = h[i * bins + top * kFine + (kFine - 1 - lane)];
     __syncthreads();
     c = 0;
 #pragma unroll
@@ -565,19 +567,30 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_sub(const float
 
 // What a region holds at or above the range of digit 0: `count` entries of `list`, or, if the
 // count exceeds the list's room, the region's scores themselves.
+// Where no scores were written (one weight a group, see k_targets_lists), `scores` is T, W lies beside it, and the keys kept
+// are in cells of kCell consecutive weights: up to kCellList of them as a list, else all the cell's scores.
+constexpr int kCell = 256 * kAhead;
+constexpr int kCellList = kCell / 2;
+struct cell_args {
+    uint2 *lists;                    // [cells][kCellList] {key, id}, or kCell scores in the same place
+    unsigned *counts;                // [cells] keys kept
+    unsigned *waves;                 // [waves of the sweep] the sum of their cells
+};
 struct region_t {
     const uint2 *list;      // {key, id}
-    const float *scores;
+    const float *scores, *W;
     int64_t base;
     int n;
     bool raw;
 };
 __device__ __forceinline__ region_t region_of(int r, const uint2 *list, const unsigned *counts,
-                                              const float *scores, int64_t N, int span, int cap)
+                                              const float *scores, const float *W, int64_t N, int span, int cap,
+                                              bool all_raw)
 {
     region_t g;
     const unsigned c = counts[r];
-    g.raw = c > (unsigned)cap;
+    g.raw = all_raw || c > (unsigned)cap;
+    g.W = W;
     g.base = (int64_t)r * span;
     const int64_t left = N - g.base;
     g.list = list + (int64_t)r * cap;
@@ -585,10 +598,10 @@ __device__ __forceinline__ region_t region_of(int r, const uint2 *list, const un
     g.n = g.raw ? (int)(left < span ? (left < 0 ? 0 : left) : span) : (int)c;
     return g;
 }
-// entry i of the region's list (i < n); key 0 past its end
-__device__ __forceinline__ uint2 list_at(const region_t &g, int i)
+// entry i of a list of n; key 0 past its end
+__device__ __forceinline__ uint2 list_at(const uint2 *list, int n, int i)
 {
-    return i < g.n ? g.list[i] : make_uint2(0u, 0u);
+    return i < n ? list[i] : make_uint2(0u, 0u);
 }
 // kAhead steps of a wave through scores: four consecutive ones a lane, 256 a step; 0 past the n-th.
 // SKIP: no instructions for steps past the n-th score.
@@ -613,16 +626,59 @@ __device__ __forceinline__ void load_scores(const float *s, int at, int n, pv_f4
 // does not fit.  Sixteen bytes a lane (with four: 45 M single weights 541 us a call against 430).  Short code
 // rather than the next steps' loads ahead: it lies between the instructions of the kernels' usual way,
 // and their registers decide what fits beside them (a 224-matrix sweep on four streams: 1 %).
-template <class F>
-__device__ __forceinline__ void for_scores(const float *s, int n, F f)
+// TW: the scores from T and W.
+template <bool TW, class F>
+__device__ __forceinline__ void for_scores(const region_t &g, F f)
 {
+    const float *s = g.scores + g.base;
+    const int n = g.n;
 #pragma unroll 1
     for (int at = 0; at < n; at += 256 * kAhead) {
         pv_f4 v[kAhead];
         load_scores<true>(s, at, n, v);
+        if constexpr (TW) {
+            pv_f4 w[kAhead];
+            load_scores<true>(g.W + g.base, at, n, w);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float d = v[u][e] - w[u][e];
+                    v[u][e] = d * d;               // (the chain of one element: fma(d, d, 0))
+                }
+        }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
             if (at + u * 256 < n) f(v[u], at + u * 256);      // uniform over the wave
+    }
+}
+// A region's keys one way or another: on_list(list, entries) or on_scores(region of scores in memory or of T and W, see
+// for_scores), in id order.  WAY 0: scores in memory, where the list does not fit; 1: from T and W, every region; 2: from
+// the cells, where it does not fit (a region is a whole number of them).
+template <int WAY, class L, class S>
+__device__ __forceinline__ void for_region(const cell_args &c, const region_t &g, L on_list, S on_scores)
+{
+    if (WAY == 2) {
+        const int cells = g.raw ? (g.n + kCell - 1) / kCell : 1;
+#pragma unroll 1
+        for (int i = 0; i < cells; ++i) {
+            const int64_t cell = g.base / kCell + i;
+            const unsigned cnt = g.raw ? c.counts[cell] : 0u;
+            const uint2 *list = g.raw ? c.lists + cell * kCellList : g.list;
+            if (cnt > (unsigned)kCellList) {
+                region_t d;
+                d.base = g.base + (int64_t)i * kCell;
+                d.n = g.n - i * kCell < kCell ? g.n - i * kCell : kCell;
+                d.scores = reinterpret_cast<const float *>(list) - d.base;
+                on_scores(d);
+            } else {
+                on_list(list, g.raw ? (int)cnt : g.n);
+            }
+        }
+    } else if (WAY == 1 || g.raw) {
+        on_scores(g);
+    } else {
+        on_list(g.list, g.n);
     }
 }
 
@@ -650,11 +706,11 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
     load_scores<false>(mine_scores, 0, n, cur);     // in flight while digit 0 is resolved
     for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
     // the last digit's histogram starts at zero (its reader of the call before has run)
-    for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
+    for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistS; z += gridDim.x * kSelBlock)
         hist_all[z] = 0u;
     unsigned kk = k;
     unsigned share;
-    const int d0 = pick_digit(hist_all + kHist0, kFirstBins, kk, tmp, &share);   // its barriers also order the clearing above
+    const int d0 = pick_digit<kSelWaves>(hist_all + kHist0, kFirstBins, kk, tmp, &share);   // its barriers also order the clearing above
     const int log = mid_log(share, N);                       // the same in every thread
     if (log) {
         for (int b = kMidBins + threadIdx.x; b < kMidBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
@@ -707,27 +763,33 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
 // block, those equal are counted by digit 2: per block as suffix sums (how many have digit 2 >= d,
 // so that the next kernel reads two numbers a block) and over all blocks in the histogram.
 // Publishes digit 1 and the rank left: state[5], state[7].
-__global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restrict__ scores,
-                                                          unsigned *__restrict__ hist_all,
-                                                          unsigned *__restrict__ state, int64_t N,
-                                                          int span, int cap, const uint2 *__restrict__ list,
-                                                          const unsigned *__restrict__ counts,
-                                                          unsigned *__restrict__ above,
-                                                          unsigned *__restrict__ suffix)
+struct sel_args {
+    const float *scores;     // (or T, and)
+    const float *W;
+    unsigned *hist_all, *state;
+    int64_t N;
+    int span, cap;
+    const uint2 *list;
+    const unsigned *counts;
+    unsigned *above, *suffix;
+    cell_args cells;
+};
+// WAY: see for_region
+template <int WAY>
+__device__ __forceinline__ void last_digit(const sel_args &a, unsigned *tmp, unsigned *lh)
 {
-    __shared__ unsigned tmp[2 * kCopies * 64];
-    __shared__ unsigned lh[kLastBins << kSpreadLog];
     __shared__ unsigned s_above;
+    unsigned *hist_all = a.hist_all, *state = a.state;
     const int lane = threadIdx.x & 63;
     for (int b = threadIdx.x; b < kLastBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
     if (threadIdx.x == 0) s_above = 0;
     // digit 0's histogram is done with: zero for the next call
     for (int z = kHist0 + blockIdx.x * kSelBlock + threadIdx.x; z < kHist1; z += gridDim.x * kSelBlock)
         hist_all[z] = 0u;
-    const region_t g = region_of(blockIdx.x * kSelWaves + (threadIdx.x >> 6), list, counts, scores, N, span, cap);
+    const region_t g = region_of(blockIdx.x * kSelWaves + (threadIdx.x >> 6), a.list, a.counts, a.scores, a.W, a.N, a.span, a.cap, WAY == 1);
     unsigned kk = state[6];
     const unsigned d0 = state[4];
-    const unsigned d1 = (unsigned)pick_digit(hist_all + kHist1, kMidBins, kk, tmp);
+    const unsigned d1 = (unsigned)pick_digit<kSelWaves>(hist_all + kHist1, kMidBins, kk, tmp);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         state[5] = d1;
         state[7] = kk;
@@ -739,25 +801,28 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
         gt += p > want;
         if (p == want && in) spread_add(lh, key & (kLastBins - 1), kSpreadLog);
     };
-    if (g.raw) {
-        for_scores(g.scores + g.base, g.n, [&](const pv_f4 &v, int at) {
+    for_region<WAY>(
+        a.cells, g,
+        [&](const uint2 *list, int n) {
+            for (int i0 = 0; i0 < n; i0 += 64 * kAhead) {
+                unsigned key[kAhead];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
+                for (int u = 0; u < kAhead; ++u) key[u] = list_at(list, n, i0 + u * 64 + lane).x;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) count(key[u], i0 + u * 64 + lane < n);
+            }
+        },
+        [&](const region_t &d) {
+            for_scores<WAY == 1>(d, [&](const pv_f4 &v, int at) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < d.n);
+            });
         });
-    } else {
-        for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
-            unsigned key[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) key[u] = list_at(g, i0 + u * 64 + lane).x;
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) count(key[u], i0 + u * 64 + lane < g.n);
-        }
-    }
     gt = wave_sum(gt);
     if (lane == 0 && gt) atomicAdd(&s_above, gt);
     __syncthreads();
     flush_hist(lh, hist_all + kHist2, kLastBins, tmp, kSpreadLog);
-    if (threadIdx.x == 0) above[blockIdx.x] = s_above;
+    if (threadIdx.x == 0) a.above[blockIdx.x] = s_above;
     if (threadIdx.x < 64) {
         // four digits a lane, lane 0 the largest
         unsigned c[kLastBins / 64], sum = 0;
@@ -767,7 +832,7 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
             sum += c[q];
         }
         unsigned run = wave_incl_scan(sum) - sum;
-        unsigned *row = suffix + (int64_t)blockIdx.x * kSuffix;
+        unsigned *row = a.suffix + (int64_t)blockIdx.x * kSuffix;
 #pragma unroll
         for (int q = 0; q < kLastBins / 64; ++q) {
             run += c[q];
@@ -777,35 +842,37 @@ __global__ __launch_bounds__(kSelBlock) void k_last_digit(const float *__restric
     }
 }
 
+__global__ __launch_bounds__(kSelBlock) void k_last_digit(sel_args a)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kLastBins << kSpreadLog];
+    last_digit<0>(a, tmp, lh);
+}
+
 // Digit 2 and with it the threshold and the number of ties to take; then the ids, in order:
 // position of a chosen group = (#greater with a lower id) + min(#equal with a lower id, ties to
 // take).  What the blocks before this one hold comes from their counts.
-__global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict__ scores,
-                                                         unsigned *__restrict__ hist_all,
-                                                         const unsigned *__restrict__ state, int64_t N,
-                                                         int span, int cap, const uint2 *__restrict__ list,
-                                                         const unsigned *__restrict__ counts,
-                                                         const unsigned *__restrict__ above,
-                                                         const unsigned *__restrict__ suffix,
-                                                         int32_t *__restrict__ out_idx)
+template <int WAY>
+__device__ __forceinline__ void write_ids(const sel_args &a, unsigned *tmp, int32_t *__restrict__ out_idx)
 {
-    __shared__ unsigned tmp[2 * kCopies * 64];
+    unsigned *hist_all = a.hist_all;
+    const unsigned *state = a.state;
     __shared__ unsigned s_gt[kSelWaves], s_eq[kSelWaves], s_bg[kSelWaves], s_be[kSelWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // digit 1's histogram is done with: zero for the next call
     for (int z = kHist1 + blockIdx.x * kSelBlock + threadIdx.x; z < kHist2; z += gridDim.x * kSelBlock)
         hist_all[z] = 0u;
-    const region_t g = region_of(blockIdx.x * kSelWaves + wave, list, counts, scores, N, span, cap);
+    const region_t g = region_of(blockIdx.x * kSelWaves + wave, a.list, a.counts, a.scores, a.W, a.N, a.span, a.cap, WAY == 1);
     const unsigned d0 = state[4], d1 = state[5];
     unsigned need = state[7];
-    const unsigned d2 = (unsigned)pick_digit(hist_all + kHist2, kLastBins, need, tmp);
+    const unsigned d2 = (unsigned)pick_digit<kSelWaves>(hist_all + kHist2, kLastBins, need, tmp);
     const unsigned thr = (((d0 << (kRestBits - kLastBits)) | d1) << kLastBits) | d2;
     // the blocks before this one (at most kSelBlocks <= kSelBlock of them, one a thread)
     unsigned bg = 0, be = 0;
     if (threadIdx.x < blockIdx.x) {
-        const unsigned *row = suffix + (int64_t)threadIdx.x * kSuffix;
+        const unsigned *row = a.suffix + (int64_t)threadIdx.x * kSuffix;
         const unsigned more = row[d2 + 1];
-        bg = above[threadIdx.x] + more;
+        bg = a.above[threadIdx.x] + more;
         be = row[d2] - more;
     }
     bg = wave_sum(bg);
@@ -815,20 +882,23 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
         gt += key > thr;
         eq += key == thr && in;
     };
-    if (g.raw) {
-        for_scores(g.scores + g.base, g.n, [&](const pv_f4 &v, int at) {
+    for_region<WAY>(
+        a.cells, g,
+        [&](const uint2 *list, int n) {
+            for (int i0 = 0; i0 < n; i0 += 64 * kAhead) {
+                unsigned key[kAhead];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < g.n);
+                for (int u = 0; u < kAhead; ++u) key[u] = list_at(list, n, i0 + u * 64 + lane).x;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) count(key[u], i0 + u * 64 + lane < n);
+            }
+        },
+        [&](const region_t &d) {
+            for_scores<WAY == 1>(d, [&](const pv_f4 &v, int at) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) count(score_key(v[e]), at + lane * 4 + e < d.n);
+            });
         });
-    } else {
-        for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
-            unsigned key[kAhead];
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) key[u] = list_at(g, i0 + u * 64 + lane).x;
-#pragma unroll
-            for (int u = 0; u < kAhead; ++u) count(key[u], i0 + u * 64 + lane < g.n);
-        }
-    }
     gt = wave_sum(gt);
     eq = wave_sum(eq);
     if (lane == 0) {
@@ -844,50 +914,396 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(const float *__restrict
         rg += s_bg[w] + (w < wave ? s_gt[w] : 0u);
         re += s_be[w] + (w < wave ? s_eq[w] : 0u);
     }
-    if (g.raw) {
-        for_scores(g.scores + g.base, g.n, [&](const pv_f4 &v, int at) {
-            unsigned long long bgt[4], beq[4];
+    for_region<WAY>(
+        a.cells, g,
+        [&](const uint2 *list, int n) {
+            for (int i0 = 0; i0 < n; i0 += 64 * kAhead) {
+                uint2 en[kAhead];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const unsigned key = score_key(v[e]);
-                bgt[e] = __ballot(key > thr);
-                beq[e] = __ballot(key == thr && at + lane * 4 + e < g.n);
-            }
-            if (!(bgt[0] | bgt[1] | bgt[2] | bgt[3] | beq[0] | beq[1] | beq[2] | beq[3])) return;   // uniform over the wave
-            unsigned pg = rg, pe = re;
+                for (int u = 0; u < kAhead; ++u) en[u] = list_at(list, n, i0 + u * 64 + lane);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pg = __builtin_amdgcn_mbcnt_hi((unsigned)(bgt[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bgt[e], pg));
-                pe = __builtin_amdgcn_mbcnt_hi((unsigned)(beq[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)beq[e], pe));
-                rg += (unsigned)__popcll(bgt[e]);
-                re += (unsigned)__popcll(beq[e]);
+                for (int u = 0; u < kAhead; ++u) {
+                    const bool in = i0 + u * 64 + lane < n;
+                    const bool isg = en[u].x > thr, ise = in && en[u].x == thr;
+                    const unsigned long long bgt = __ballot(isg), beq = __ballot(ise);
+                    const unsigned long long below = (1ull << lane) - 1ull;
+                    const unsigned pg = rg + __popcll(bgt & below), pe = re + __popcll(beq & below);
+                    if (isg || (ise && pe < need)) out_idx[pg + (pe < need ? pe : need)] = (int32_t)en[u].y;
+                    rg += __popcll(bgt);
+                    re += __popcll(beq);
+                }
             }
+        },
+        [&](const region_t &d) {
+            for_scores<WAY == 1>(d, [&](const pv_f4 &v, int at) {
+                unsigned long long bgt[4], beq[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool isg = (bgt[e] >> lane) & 1ull, ise = (beq[e] >> lane) & 1ull;
-                if (isg || (ise && pe < need)) out_idx[pg + (pe < need ? pe : need)] = (int32_t)(g.base + at + lane * 4 + e);
-                pg += isg;
-                pe += ise;
-            }
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned key = score_key(v[e]);
+                    bgt[e] = __ballot(key > thr);
+                    beq[e] = __ballot(key == thr && at + lane * 4 + e < d.n);
+                }
+                if (!(bgt[0] | bgt[1] | bgt[2] | bgt[3] | beq[0] | beq[1] | beq[2] | beq[3])) return;   // uniform over the wave
+                unsigned pg = rg, pe = re;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    pg = __builtin_amdgcn_mbcnt_hi((unsigned)(bgt[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bgt[e], pg));
+                    pe = __builtin_amdgcn_mbcnt_hi((unsigned)(beq[e] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)beq[e], pe));
+                    rg += (unsigned)__popcll(bgt[e]);
+                    re += (unsigned)__popcll(beq[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool isg = (bgt[e] >> lane) & 1ull, ise = (beq[e] >> lane) & 1ull;
+                    if (isg || (ise && pe < need)) out_idx[pg + (pe < need ? pe : need)] = (int32_t)(d.base + at + lane * 4 + e);
+                    pg += isg;
+                    pe += ise;
+                }
+            });
         });
-        return;
-    }
-    for (int i0 = 0; i0 < g.n; i0 += 64 * kAhead) {
-        uint2 en[kAhead];
+}
+
+__global__ __launch_bounds__(kSelBlock) void k_write_ids(sel_args a, int32_t *__restrict__ out_idx)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    write_ids<0>(a, tmp, out_idx);
+}
+
+// ---- one weight a group, many of them: the sweep itself collects
+// Scores of single weights are as many bytes as the weights: written and read again they cost a third of
+// the sweep.  A sample of the scores says beforehand which digit 0 the k-th largest will hardly fall below;
+// the sweep keeps the keys from there on, with their ids, in short lists, and writes no scores.  Where a
+// list does not fit, and everywhere if the sample said too much (fewer than k keys were
+// kept: the three kernels then do the steps from the first digit on, and a fourth, which returns at once
+// otherwise, the last), the scores are taken from T and W again.
+constexpr int kSampleBlock = 512;
+constexpr int kSampleBlocks = 32;
+constexpr int kSampleVecs = kSampleBlock * kSampleBlocks;    // four weights each, one in every 1 / kSampleVecs of the matrix
+__global__ __launch_bounds__(kSampleBlock) void k_sample(const float *__restrict__ W, const float *__restrict__ G,
+                                                         float alpha, int64_t nvec, unsigned *__restrict__ hist)
+{
+    __shared__ unsigned lh[kFirstBins];
+    __shared__ unsigned s_coarse[64];
+    for (int b = threadIdx.x; b < kFirstBins; b += kSampleBlock) lh[b] = 0;
+    const int i = blockIdx.x * kSampleBlock + threadIdx.x;
+    // a place in the i-th part: anywhere, so that no pattern of rows or columns is missed
+    unsigned h = (unsigned)i * 0x9E3779B9u;
+    h = (h ^ (h >> 15)) * 0x2C1B3C6Du;
+    h ^= h >> 13;
+    const int64_t width = nvec / kSampleVecs;
+    const int64_t at = (int64_t)i * nvec / kSampleVecs + (int64_t)(((unsigned long long)h * (unsigned long long)width) >> 32);
+    const pv_f4 w = reinterpret_cast<const pv_f4 *>(W)[at], g = reinterpret_cast<const pv_f4 *>(G)[at];
+    __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) en[u] = list_at(g, i0 + u * 64 + lane);
+    for (int e = 0; e < 4; ++e) {
+        const float d = fmaf(-alpha, g[e], w[e]) - w[e];
+        hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(score_key(d * d)), true);
+    }
+    __syncthreads();
+    flush_hist(lh, hist, kFirstBins, s_coarse);
+}
+
+// how many of the sample's keys lie at or above the digit that the sweep collects from: k's share, and ten times
+// its root more (the weights of a vector may go together, and so may vectors)
+static unsigned sample_rank(int64_t N, int64_t k)
+{
+    double m = 4.0 * kSampleVecs * (double)k / (double)N, r = 1.0;
+    for (int i = 0; i < 40; ++i) r = 0.5 * (r + m / r);
+    return (unsigned)(m + 10.0 * r + 32.0);
+}
+
+// T = W - alpha * G, and the keys kept: cell by cell, kCell consecutive weights a wave at a time, all waves side by
+// side (a contiguous range a wave is 120 us for 45 M weights, a range a block 112, this 96: it is
+// bound by the 12 bytes a weight).  Scores that are alike cost no more than writing them
+// would.
+constexpr int kListBlock = 256;
+constexpr int kListBlocks = 1024;
+__global__ __launch_bounds__(kListBlock, 4) void k_targets_lists(const float *W, const float *G, float alpha, float *T,
+                                                              unsigned *__restrict__ hist_all,
+                                                              unsigned *__restrict__ state, int64_t N,
+                                                              unsigned sample_kk, cell_args c)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kFirstBins];
+    const int lane = threadIdx.x & 63;
+    const int wave = blockIdx.x * (kListBlock / 64) + (threadIdx.x >> 6), waves = gridDim.x * (kListBlock / 64);
+    const int ncells = (int)((N + kCell - 1) / kCell);
+    pv_f4 w[kAhead], g[kAhead], wn[kAhead], gn[kAhead];
+    auto load = [&](const float *p, int cell, pv_f4 (&v)[kAhead]) {
+        const int64_t base = (int64_t)cell * kCell;
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            const bool in = i0 + u * 64 + lane < g.n;
-            const bool isg = en[u].x > thr, ise = in && en[u].x == thr;
-            const unsigned long long bgt = __ballot(isg), beq = __ballot(ise);
-            const unsigned long long below = (1ull << lane) - 1ull;
-            const unsigned pg = rg + __popcll(bgt & below), pe = re + __popcll(beq & below);
-            if (isg || (ise && pe < need)) out_idx[pg + (pe < need ? pe : need)] = (int32_t)en[u].y;
-            rg += __popcll(bgt);
-            re += __popcll(beq);
+            const int64_t i = base + u * 256 + lane * 4;
+            v[u] = pv_f4{0.f, 0.f, 0.f, 0.f};
+            if (i + 4 <= N) {
+                v[u] = __builtin_nontemporal_load(reinterpret_cast<const pv_f4 *>(p + i));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < N) v[u][e] = p[i + e];
+            }
+        }
+    };
+    load(W, wave, w);                               // in flight while the digit is looked up
+    load(G, wave, g);
+    for (int b = threadIdx.x; b < kFirstBins; b += kListBlock) lh[b] = 0;
+    unsigned kk = sample_kk;
+    const unsigned lo = (unsigned)pick_digit<kListBlock / 64>(hist_all + kHistS, kFirstBins, kk, tmp) << kRestBits;   // its barriers also order the clearing above
+    if (blockIdx.x == 0 && threadIdx.x == 0) state[2] = lo;
+    unsigned total = 0;
+    for (int cell = wave; cell < ncells; cell += waves) {
+        if (cell + waves < ncells) {
+            load(W, cell + waves, wn);
+            load(G, cell + waves, gn);
+        }
+        const int64_t base = (int64_t)cell * kCell;
+        uint2 *mine = c.lists + (int64_t)cell * kCellList;
+        unsigned cnt = 0;
+        unsigned long long hits[kAhead][4];
+        auto score = [&](int u, int e) {
+            const float d = fmaf(-alpha, g[u][e], w[u][e]) - w[u][e];
+            return d * d;
+        };
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t i = base + u * 256 + lane * 4;
+            pv_f4 t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                t[e] = fmaf(-alpha, g[u][e], w[u][e]);
+                hits[u][e] = __ballot(score_key(score(u, e)) >= lo && i + e < N);
+                cnt += (unsigned)__popcll(hits[u][e]);
+            }
+            if (i + 4 <= N) {
+                __builtin_nontemporal_store(t, reinterpret_cast<pv_f4 *>(T + i));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < N) T[i + e] = t[e];
+            }
+        }
+        if (lane == 0) c.counts[cell] = cnt;
+        total += cnt;
+        if (cnt > (unsigned)kCellList) {            // uniform over the wave
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                pv_f4 sc;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sc[e] = score(u, e);
+                    hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(score_key(sc[e])), (hits[u][e] >> lane) & 1ull);
+                }
+                reinterpret_cast<pv_f4 *>(mine)[u * 64 + lane] = sc;   // (past the matrix' end: nobody reads them)
+            }
+        } else {
+            unsigned at = 0;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (!(hits[u][0] | hits[u][1] | hits[u][2] | hits[u][3])) continue;   // uniform over the wave
+                unsigned pos = at;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    pos = __builtin_amdgcn_mbcnt_hi((unsigned)(hits[u][e] >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((unsigned)hits[u][e], pos));
+                    at += (unsigned)__popcll(hits[u][e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (!hits[u][e]) continue;       // uniform over the wave
+                    const bool hit = (hits[u][e] >> lane) & 1ull;
+                    const unsigned key = score_key(score(u, e));
+                    if (hit) mine[pos++] = make_uint2(key, (unsigned)(base + u * 256 + lane * 4 + e));
+                    hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(key), hit);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            w[u] = wn[u];
+            g[u] = gn[u];
         }
     }
+    if (lane == 0) c.waves[wave] = total;
+    __syncthreads();
+    flush_hist(lh, hist_all + kHist0, kFirstBins, tmp);
+}
+
+// Digit 0 is resolved and published with the rank left (state[4], state[6]); returns it.  lh: zeroed here.
+__device__ __forceinline__ unsigned first_digit(const sel_args &a, unsigned k, unsigned *tmp, unsigned *lh, int *log)
+{
+    for (int b = threadIdx.x; b < kMidBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
+    unsigned kk = k, share;
+    const unsigned d0 = (unsigned)pick_digit<kSelWaves>(a.hist_all + kHist0, kFirstBins, kk, tmp, &share);   // its barriers also order the clearing above
+    *log = mid_log(share, a.N);                              // the same in every thread
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.state[4] = d0;
+        a.state[6] = kk;
+    }
+    return d0;
+}
+
+// Digit 1 of the keys that share digit 0, from T and W.
+__device__ __forceinline__ void mid_digit_raw(const sel_args &a, unsigned k, unsigned *tmp, unsigned *lh)
+{
+    int log;
+    const unsigned d0 = first_digit(a, k, tmp, lh, &log);
+    const region_t g = region_of(blockIdx.x * kSelWaves + (threadIdx.x >> 6), a.list, a.counts, a.scores, a.W, a.N, a.span, a.cap, true);
+    for_scores<true>(g, [&](const pv_f4 &v, int at) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned key = score_key(v[e]);
+            if (at + (int)(threadIdx.x & 63) * 4 + e < g.n && (key >> kRestBits) == d0)
+                spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
+        }
+    });
+    __syncthreads();
+    flush_hist(lh, a.hist_all + kHist1, kMidBins, tmp, log);
+}
+
+// The same from the cells; the keys at or above digit 0's range go to the region's list, as in k_collect.
+__device__ __forceinline__ void mid_digit_cells(const sel_args &a, unsigned k, uint2 *list, unsigned *counts, unsigned *tmp,
+                                                unsigned *lh)
+{
+    constexpr int kCells = 6;                     // cells whose entries are in flight together
+    const int lane = threadIdx.x & 63;
+    const int r = blockIdx.x * kSelWaves + (threadIdx.x >> 6);
+    const int ncells = (int)((a.N + kCell - 1) / kCell), per = a.span / kCell;
+    const int first = r * per, end = first + per < ncells ? first + per : ncells;
+    int log;
+    const unsigned d0 = first_digit(a, k, tmp, lh, &log);
+    const unsigned lo = d0 << kRestBits, hi = (d0 + 1u) << kRestBits;
+    uint2 *mine = list + (int64_t)r * a.cap;
+    unsigned cnt = 0;
+    auto take = [&](unsigned key, unsigned id, bool in) {
+        const bool hit = in && key >= lo;
+        const unsigned long long hits = __ballot(hit);
+        if (!hits) return;                        // uniform over the wave
+        const unsigned pos = __builtin_amdgcn_mbcnt_hi((unsigned)(hits >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hits, cnt));
+        cnt += (unsigned)__popcll(hits);
+        if (hit) {
+            if (pos < (unsigned)a.cap) mine[pos] = make_uint2(key, id);
+            if (key < hi) spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
+        }
+    };
+    unsigned counts64 = 0;                        // of 64 cells, one a lane
+    for (int c0 = first; c0 < end; c0 += kCells) {
+        const int in64 = (c0 - first) % (64 / kCells * kCells);
+        if (in64 == 0) counts64 = c0 + lane < end ? a.cells.counts[c0 + lane] : 0u;
+        unsigned have[kCells];
+        uint2 e[kCells];
+#pragma unroll
+        for (int u = 0; u < kCells; ++u) have[u] = (unsigned)__builtin_amdgcn_readlane((int)counts64, in64 + u);
+#pragma unroll
+        for (int u = 0; u < kCells; ++u)
+            e[u] = lane < (int)have[u] ? a.cells.lists[(int64_t)(c0 + u) * kCellList + lane] : make_uint2(0u, 0u);
+#pragma unroll
+        for (int u = 0; u < kCells; ++u) {
+            const int n = (int)have[u];
+            const uint2 *cell = a.cells.lists + (int64_t)(c0 + u) * kCellList;
+            if (n <= kCellList) {
+                take(e[u].x, e[u].y, lane < n);
+#pragma unroll 1
+                for (int q = 64; q < n; q += 64) {
+                    const uint2 x = list_at(cell, n, q + lane);
+                    take(x.x, x.y, q + lane < n);
+                }
+            } else {
+                const int64_t base = (int64_t)(c0 + u) * kCell + lane * 4;
+                pv_f4 v[kAhead];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) v[q] = reinterpret_cast<const pv_f4 *>(cell)[q * 64 + lane];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    unsigned long long hits[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) hits[x] = __ballot(score_key(v[q][x]) >= lo && base + q * 256 + x < a.N);
+                    if (!(hits[0] | hits[1] | hits[2] | hits[3])) continue;   // uniform over the wave
+                    unsigned pos = cnt;
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        pos = __builtin_amdgcn_mbcnt_hi((unsigned)(hits[x] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hits[x], pos));
+                        cnt += (unsigned)__popcll(hits[x]);
+                    }
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        if ((hits[x] >> lane) & 1ull) {
+                            const unsigned key = score_key(v[q][x]);
+                            if (pos < (unsigned)a.cap) mine[pos] = make_uint2(key, (unsigned)(base + q * 256 + x));
+                            ++pos;
+                            if (key < hi) spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
+                        }
+                }
+            }
+        }
+    }
+    if (lane == 0) counts[r] = cnt;
+    __syncthreads();
+    flush_hist(lh, a.hist_all + kHist1, kMidBins, tmp, log);
+}
+
+// The sweep kept at least k keys: digit 1 of those.  It kept fewer (state[3]): digit 0 of the others is counted
+// first, and everything after it comes a launch later.
+__global__ __launch_bounds__(kSelBlock) void k_mid_or_first(sel_args a, int waves, unsigned k, uint2 *list,
+                                                            unsigned *counts)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kMidBins << kSpreadLog];
+    __shared__ unsigned s_sum[kSelWaves];
+    static_assert(kFirstBins <= kMidBins << kSpreadLog, "either histogram fits");
+    const int lane = threadIdx.x & 63;
+    // the last digit's histogram starts at zero, and the sample's is done with
+    for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
+        a.hist_all[z] = 0u;
+    // from the waves' counts and not from digit 0's histogram, to which blocks of this launch may add
+    unsigned kept = 0;
+    for (int i = threadIdx.x; i < waves; i += kSelBlock) kept += a.cells.waves[i];
+    kept = wave_sum(kept);
+    if (lane == 0) s_sum[threadIdx.x >> 6] = kept;
+    __syncthreads();
+    kept = 0;
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) kept += s_sum[w];
+    const bool few = kept < k;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.state[3] = few;
+    if (!few) {
+        mid_digit_cells(a, k, list, counts, tmp, lh);
+        return;
+    }
+    for (int b = threadIdx.x; b < kFirstBins; b += kSelBlock) lh[b] = 0;
+    __syncthreads();
+    const unsigned lo = a.state[2];
+    const region_t g = region_of(blockIdx.x * kSelWaves + (threadIdx.x >> 6), a.list, a.counts, a.scores, a.W, a.N, a.span, a.cap, true);
+    for_scores<true>(g, [&](const pv_f4 &v, int at) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned key = score_key(v[e]);
+            hist_add<PV_VOTE_ROUNDS>(lh, digit0_of(key), key < lo && at + lane * 4 + e < g.n);
+        }
+    });
+    __syncthreads();
+    flush_hist(lh, a.hist_all + kHist0, kFirstBins, tmp);
+}
+
+__global__ __launch_bounds__(kSelBlock) void k_last_or_mid(sel_args a, unsigned k)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kMidBins << kSpreadLog];
+    if (a.state[3]) mid_digit_raw(a, k, tmp, lh);
+    else last_digit<2>(a, tmp, lh);
+}
+
+__global__ __launch_bounds__(kSelBlock) void k_write_or_last(sel_args a, int32_t *__restrict__ out_idx)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    __shared__ unsigned lh[kLastBins << kSpreadLog];
+    if (a.state[3]) last_digit<1>(a, tmp, lh);
+    else write_ids<2>(a, tmp, out_idx);
+}
+
+__global__ __launch_bounds__(kSelBlock) void k_write_if_few(sel_args a, int32_t *__restrict__ out_idx)
+{
+    __shared__ unsigned tmp[2 * kCopies * 64];
+    if (a.state[3]) write_ids<1>(a, tmp, out_idx);
 }
 
 // Few groups: one block does what the three kernels above do, every key in a register (thread t
@@ -923,7 +1339,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_small(const float *__restr
     for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
     if (threadIdx.x < kLastBins) ll[threadIdx.x] = 0;
     unsigned kk = k, share;
-    const unsigned d0 = (unsigned)pick_digit(hist_all + kHist0, kFirstBins, kk, tmp, &share);
+    const unsigned d0 = (unsigned)pick_digit<kSelWaves>(hist_all + kHist0, kFirstBins, kk, tmp, &share);
     const int log = mid_log(share, N);                       // the same in every thread
     if (log) {
         for (int b = kMidBins + threadIdx.x; b < kMidBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
@@ -1020,6 +1436,7 @@ struct sel_bufs {
     uint2 *list = nullptr;
     sel_plan plan{};
     pv_norm_req *norm = nullptr;
+    cell_args cells{};       // lists: nullptr unless the sweep collects
 };
 
 __global__ void k_sel_clear(unsigned *p, int n)
@@ -1034,10 +1451,14 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
 // A context's scratch, one block: histograms, counts and state | lists | scores.  Lists are
 // left out where the device has no room for them (then, and for that size from then on: a call of
 // a size that was seen before does not allocate).
+constexpr int64_t kCollectMin = 3 << 22;
+static int64_t cells_of(int64_t N) { return (N + kCell - 1) / kCell; }
 static pv_status sel_scratch(pv_ctx *ctx, int64_t N, bool own_scores, sel_bufs *b, bool *lists)
 {
     constexpr size_t head = ((kHistTotal + kSelCountWords + 8) * sizeof(unsigned) + 255) & ~(size_t)255;
-    const size_t list = sel_list_bytes(N), rest = own_scores ? (size_t)N * sizeof(float) + 16 : 0;
+    const size_t list = sel_list_bytes(N);
+    // whatever the group size: the scores, or the cells in their place
+    const size_t rest = own_scores ? (size_t)cells_of(N) * (kCellList * sizeof(uint2) + sizeof(unsigned)) : 0;
     *lists = list == 0 || ctx->select.bytes >= head + list + rest;
     if (!*lists && head + list + rest < ctx->select_refused) {
         *lists = pv_ensure(ctx, ctx->select, head + list + rest, kHistTotal * sizeof(unsigned)) == PV_OK;
@@ -1064,6 +1485,17 @@ pv_status pv_select_scores(pv_ctx *ctx, int64_t N, float **scores)
     return st;
 }
 
+// One weight a group, and so many that the scores' way through memory costs more than the sample (6 us) and a launch that
+// returns at once (4.6).  The call, k = N / 100, scores written / collected: 4 M weights 40.0 / 39.6 us, 8 M 53.6 /
+// 50.3, 16 M 78.8 / 67.8, 45 M 163.8 / 130.0 (k = N / 10: 40.4 / 43.7, 57.9 / 60.0, 86.0 / 82.7, 196.4 / 161.0; rows of
+// their own size, 45 M: 202.6 / 166.6).  What loses is all scores alike, which are written and read all the same:
+// 45 M 273 / 291, 16 M 118 / 131.
+static bool sweep_collects(const pv_layout *l, int64_t k)
+{
+    const int64_t N = pv_num_groups(l);
+    return l->group_size == 1 && N >= kCollectMin && k > 0 && k <= N / 8;
+}
+
 // G != nullptr: T is an OUTPUT, formed here as W - alpha * G in the same pass that scores it.
 pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, const float *W,
                            int64_t k, int32_t *out_idx, float *scores, const float *G, float alpha,
@@ -1078,6 +1510,14 @@ pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, cons
     st = sel_scratch(ctx, N, /*own_scores=*/!scores, &bufs, &lists);
     if (st != PV_OK) return st;
     bufs.plan = make_sel_plan(N, k, lists);
+    if (G && !adam && !scores && lists && sweep_collects(l, k)) {
+        // the cells take the place of the scores
+        bufs.cells.lists = reinterpret_cast<uint2 *>(bufs.scores);
+        bufs.cells.counts = reinterpret_cast<unsigned *>(bufs.cells.lists + cells_of(N) * kCellList);
+        bufs.cells.waves = bufs.counts + (size_t)kSelBlocks * (kSelWaves + 1);   // where the suffix counts come later
+        static_assert(kListBlocks * (kListBlock / 64) <= kSelBlocks * kSuffix, "a count a wave");
+        bufs.plan.span = (bufs.plan.span + kCell - 1) / kCell * kCell;           // (cap stays: a quarter of the span that the lists were sized for)
+    }
     if (scores) bufs.scores = scores;
     bufs.norm = norm;
     return select_run(ctx, l, T, W, k, out_idx, bufs, G, alpha, adam, m, v);
@@ -1164,6 +1604,28 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
     int32_t *all_ids = k == N ? out_idx : nullptr;   // every group is chosen: the sweep writes the ids as it goes
     const int want_hist = k > 0 && k < N ? 1 : 0;
     const bool vec_g = g == 4 || g == 8 || g == 16 || g == 32 || g == 64;
+    if (bufs.cells.lists) {   // (see sweep_collects)
+        const sel_plan p = bufs.plan;
+        unsigned *counts = bufs.counts, *above = counts + (size_t)kSelBlocks * kSelWaves;
+        const sel_args a{T, W, hist, state, (int64_t)N, p.span, p.cap, bufs.list, counts, above, above + kSelBlocks, bufs.cells};
+        int64_t blocks = ((int64_t)N + kCell * (kListBlock / 64) - 1) / (kCell * (kListBlock / 64));
+        if (blocks > kListBlocks) blocks = kListBlocks;
+        {
+            pv_timed t(ctx, PV_K_ENCODE_TARGETS);
+            hipLaunchKernelGGL(k_sample, dim3(kSampleBlocks), dim3(kSampleBlock), 0, ctx->stream, W, G, alpha,
+                               (int64_t)N / 4, hist + kHistS);
+            hipLaunchKernelGGL(k_targets_lists, dim3((unsigned)blocks), dim3(kListBlock), 0, ctx->stream, W, G, alpha,
+                               const_cast<float *>(T), hist, state, (int64_t)N, sample_rank(N, k), bufs.cells);
+        }
+        pv_timed t(ctx, PV_K_SELECT);
+        hipLaunchKernelGGL(k_mid_or_first, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, a,
+                           (int)blocks * (kListBlock / 64), (unsigned)k, bufs.list, counts);
+        hipLaunchKernelGGL(k_last_or_mid, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, a, (unsigned)k);
+        hipLaunchKernelGGL(k_write_or_last, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, a, out_idx);
+        hipLaunchKernelGGL(k_write_if_few, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, a, out_idx);
+        PV_HIP(ctx, hipGetLastError());
+        return PV_OK;
+    }
     if (G && !adam && (g == 1 || g == 2)) {
         pv_timed t(ctx, PV_K_ENCODE_TARGETS);
         const int64_t nelem = (int64_t)N * g;
@@ -1256,10 +1718,9 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
         unsigned *suffix = above + kSelBlocks;
         hipLaunchKernelGGL(k_collect, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, scores, hist, state,
                            (int64_t)N, (unsigned)k, p.span, p.cap, bufs.list, counts);
-        hipLaunchKernelGGL(k_last_digit, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, scores, hist, state,
-                           (int64_t)N, p.span, p.cap, bufs.list, counts, above, suffix);
-        hipLaunchKernelGGL(k_write_ids, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, scores, hist, state,
-                           (int64_t)N, p.span, p.cap, bufs.list, counts, above, suffix, out_idx);
+        const sel_args a{scores, nullptr, hist, state, (int64_t)N, p.span, p.cap, bufs.list, counts, above, suffix, {}};
+        hipLaunchKernelGGL(k_last_digit, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, a);
+        hipLaunchKernelGGL(k_write_ids, dim3(p.blocks), dim3(kSelBlock), 0, ctx->stream, a, out_idx);
     }
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;

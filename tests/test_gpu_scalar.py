@@ -69,3 +69,60 @@ def test_scalar_tie_rule_empty_list_and_errors():
     with pytest.raises(PVError):
         ctx.pv_reencode_scalar(1, 4, 4, 2, T, sc, zp, dev_i32(np.array([0], np.int32)), 5, codes, nch)
     ctx.close()
+
+
+def sampled_vectors(n):
+    """The vectors of four weights that the sweep of many single weights samples its scores from."""
+    i, u32 = np.arange(16384, dtype=np.uint64), np.uint64(0xFFFFFFFF)
+    h = (i * np.uint64(0x9E3779B9)) & u32
+    h = ((h ^ (h >> np.uint64(15))) * np.uint64(0x2C1B3C6D)) & u32
+    h ^= h >> np.uint64(13)
+    nvec = np.uint64(n // 4)
+    return ((i * nvec) // np.uint64(16384) + ((h * (nvec // np.uint64(16384))) >> np.uint64(32))).astype(np.int64)
+
+
+@pytest.mark.parametrize("shape", [(3072, 4096), (4001, 3777)])      # the fewest that the sweep collects from; a ragged end
+@pytest.mark.parametrize("kind", ["normal", "equal", "rows", "columns", "zeros", "not_finite", "sampled", "sampled_few"])
+def test_selection_among_many_single_weights(shape, kind):
+    """The sweep that keeps keys from a sampled digit on, against a partition of all scores: spread scores, all
+    alike, rows and columns of their own size (cells and regions whose lists do not fit), mostly zeros, NaN
+    and infinities; and large updates exactly where the sample looks, so that fewer than k (or just the rest)
+    are kept and every digit is counted from T and W."""
+    rows, cols = shape
+    n = rows * cols
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(96)
+    W = torch.randn(rows, cols, generator=gen, device=DEV) * 0.02
+    G = torch.randn(rows, cols, generator=gen, device=DEV) * 1e-4
+    if kind == "equal":
+        W.zero_()
+        G.fill_(1e-4)
+    elif kind in ("rows", "columns"):
+        size = (rows, 1) if kind == "rows" else (1, cols)
+        G *= torch.exp(2 * torch.randn(*size, generator=gen, device=DEV))
+    elif kind == "zeros":
+        G *= torch.rand(rows, cols, generator=gen, device=DEV) < 0.003
+    elif kind == "not_finite":
+        G[3, 5], G[7, 9], G[rows - 1, cols - 1] = float("nan"), float("inf"), -float("nan")
+    elif kind != "normal":
+        at = torch.from_numpy(sampled_vectors(n)).to(DEV)
+        G.mul_(1e-2).view(-1)[:n // 4 * 4].view(-1, 4)[at] = 1 + torch.rand(len(at), 4, generator=gen, device=DEV)
+        if kind == "sampled_few":
+            G.view(-1)[-1000:] = 3.0
+    lay, ctx, T = Layout(rows, cols, 1, 1, 2), PVContext(0), torch.empty_like(W)
+    for k in (n // 100, 7, n // 8):
+        for call in range(2):           # the second finds what the first left in the scratch
+            idx = torch.full((k,), -7, dtype=torch.int32, device=DEV)
+            T.fill_(5.0)
+            ctx.pv_encode_targets_select(lay, W, G, 0.3, T, k, idx)
+        torch.cuda.synchronize()
+        want_T = torch.empty_like(W)
+        ctx.pv_encode_targets(lay, W, G, 0.3, want_T)
+        assert torch.equal(T.view(torch.int32), want_T.view(torch.int32))
+        key = ((T - W) ** 2).view(-1).view(torch.int32).cpu().numpy()
+        key = np.where(key < 0, 0x7FFFFFFF, key)
+        least = np.partition(key, n - k)[n - k]
+        ties = np.nonzero(key == least)[0][:k - int((key > least).sum())]
+        want = np.sort(np.concatenate([np.nonzero(key > least)[0], ties]))
+        assert np.array_equal(idx.cpu().numpy(), want)
+    ctx.close()
