@@ -128,7 +128,7 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->select, &c->stats, &c->search, &c->fb_list, &c->trust, &c->pstep};
+    pv_buffer *bufs[] = {&c->select, &c->stats, &c->few, &c->search, &c->fb_list, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     for (auto &t : c->timers)
@@ -317,6 +317,8 @@ pv_status pv_reencode_dispatch(pv_ctx *ctx, const pv_layout *l, const float *T,
     int64_t *stats = static_cast<int64_t *>(ctx->stats.ptr);
     ctx->rr_blocks_last = 0;
     const bool filter = M == 1 && k > 0 && ctx->search_mode == 0 && pv_mfma_supported(l);
+    if (filter && pv_search_few(l, k))
+        return pv_launch_search_few(ctx, l, T, codebooks, scales, group_idx, k, codes, num_changed);
     if (filter)   // its first kernel clears the counters
         return pv_launch_mfma_search(ctx, l, T, codebooks, scales, group_idx, k, codes, num_changed);
     st = pv_launch_fill_i64(ctx, stats, 8, 0, num_changed);

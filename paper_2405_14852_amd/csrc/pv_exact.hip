@@ -234,6 +234,166 @@ __global__ __launch_bounds__(kBlock) void k_exact_scan(
     }
 }
 
+// ------------------------------------------------------------------ M = 1, little work
+//
+// Small codebooks and short lists: one launch in place of the matrix-core filter's three or four, each of which
+// is a round trip of its own.  A wave (`split` = 1) or the four waves of a block, each on a part of the
+// codebook (4), take kFew groups at a time: a lane scores codewords 64 apart against all of them, a codeword's element
+// converted once for the four; the four minima are found together, every exchange halving the groups that a
+// lane carries.  Bound by the fp64 vector rate: three operations an element and group.
+constexpr int kFew = 4;
+constexpr int kFewWaves = kBlock / 64;
+
+// What a call counts, without a launch that clears it: a word is left zero by the last block to arrive.
+// arrivals << 40 | groups decided << 20 | codes changed
+constexpr int kFewSlots = 32, kFewStride = 16;
+__device__ __forceinline__ void few_counts(unsigned long long *slots, unsigned done, unsigned changed,
+                                           unsigned long long *num_changed, unsigned long long *stats)
+{
+    constexpr unsigned long long kOne = 1ull << 40;
+    const unsigned slot = blockIdx.x % kFewSlots, nslots = gridDim.x < (unsigned)kFewSlots ? gridDim.x : (unsigned)kFewSlots;
+    const unsigned members = (gridDim.x - slot + kFewSlots - 1) / kFewSlots;
+    unsigned long long *word = slots + slot * kFewStride;
+    unsigned long long sum = kOne | (unsigned long long)done << 20 | changed;
+    sum += atomicAdd(word, sum);
+    if ((unsigned)(sum >> 40) != members) return;
+    atomicExch(word, 0ull);
+    word = slots + kFewSlots * kFewStride;
+    sum = kOne | (sum & (kOne - 1ull));
+    sum += atomicAdd(word, sum);
+    if ((unsigned)(sum >> 40) != nslots) return;
+    atomicExch(word, 0ull);
+    if (num_changed) *num_changed = sum & 0xFFFFFull;
+    for (int i = 0; i < 8; ++i) stats[i] = i == 3 ? (sum >> 20) & 0xFFFFFull : 0ull;
+}
+
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_search_few(const float *__restrict__ T, const float *__restrict__ codebook,
+                                                       const float *__restrict__ scales,
+                                                       const int32_t *__restrict__ list, int k, uint16_t *codes,
+                                                       unsigned long long *num_changed, unsigned long long *stats,
+                                                       unsigned long long *slots, int nbits, double inv_gpr, int N,
+                                                       int split)
+{
+    __shared__ double s_obj[kFewWaves][kFew];
+    __shared__ int s_idx[kFewWaves][kFew];
+    __shared__ unsigned s_cnt[2];
+    constexpr int kAtOnce = G == 8 ? 4 : 2;        // codewords of a lane whose loads are in flight together
+    const int csize = 1 << nbits;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x < 2) s_cnt[threadIdx.x] = 0u;
+    const int part = split > 1 ? wave : 0;
+    const int j0 = __builtin_amdgcn_readfirstlane((split > 1 ? (int)blockIdx.x : (int)blockIdx.x * kFewWaves + wave) * kFew);
+    const int c_begin = part * (csize / split), c_end = c_begin + csize / split;
+    int n[kFew];
+    double sc[kFew], t[kFew][G];
+#pragma unroll
+    for (int q = 0; q < kFew; ++q) {
+        n[q] = j0 + q < k ? list[j0 + q] : -1;
+        if (n[q] < 0 || n[q] >= N) n[q] = -1;
+    }
+    // the lane that decides a group at the end asks for what it needs now
+    const int mine = (lane & 1) << 1 | (lane >> 1 & 1);
+    int my_n = n[0];
+#pragma unroll
+    for (int q = 1; q < kFew; ++q) my_n = mine == q ? n[q] : my_n;
+    const int prev = lane < kFew && my_n >= 0 ? (int)codes[my_n] & (csize - 1) : 0;
+#pragma unroll
+    for (int q = 0; q < kFew; ++q) {
+        const int m = n[q] < 0 ? 0 : n[q];
+        sc[q] = (double)scales[pv_row_of((unsigned)m, inv_gpr)];
+#pragma unroll
+        for (int i = 0; i < G; ++i) t[q][i] = (double)T[(int64_t)m * G + i];
+    }
+    best_t best[kFew];
+#pragma unroll
+    for (int q = 0; q < kFew; ++q) {
+        best[q].obj = kInf;
+        best[q].idx = 0x7fffffff;
+    }
+    for (int c0 = c_begin + lane; c0 < c_end; c0 += 64 * kAtOnce) {
+        pv_f4 cv[kAtOnce][G / 4];
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int c = c0 + u * 64;
+            const pv_f4 *cw4 = reinterpret_cast<const pv_f4 *>(codebook + (int64_t)(c < c_end ? c : c_begin) * G);
+#pragma unroll
+            for (int v4 = 0; v4 < G / 4; ++v4) cv[u][v4] = cw4[v4];
+        }
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int c = c0 + u * 64;
+            double obj[kFew];
+#pragma unroll
+            for (int q = 0; q < kFew; ++q) obj[q] = 0.0;
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const double acc = (double)cv[u][i / 4][i % 4];
+#pragma unroll
+                for (int q = 0; q < kFew; ++q) {
+                    const double r = fma(sc[q], acc, -t[q][i]);   // (s * c is exact in double)
+                    obj[q] = obj[q] + r * r;
+                }
+            }
+            if (c < c_end) {                       // ascending codes: the lowest of equal ones stays
+#pragma unroll
+                for (int q = 0; q < kFew; ++q)
+                    if (obj[q] < best[q].obj) {
+                        best[q].obj = obj[q];
+                        best[q].idx = c;
+                    }
+            }
+        }
+    }
+    auto less = [](best_t x, best_t y) { return better(y.obj, y.idx, x.obj, x.idx) ? y : x; };
+    auto other = [](best_t x, int off) {
+        best_t y;
+        y.obj = __shfl_xor(x.obj, off);
+        y.idx = __shfl_xor(x.idx, off);
+        return y;
+    };
+    // lanes ^ 1 share out the groups, then lanes ^ 2: group `mine` is left, over the lanes with the same lane & 3
+    const bool odd = lane & 1, second = lane & 2;
+    best_t a = less(odd ? best[2] : best[0], other(odd ? best[0] : best[2], 1));
+    best_t b = less(odd ? best[3] : best[1], other(odd ? best[1] : best[3], 1));
+    best_t r = less(second ? b : a, other(second ? a : b, 2));
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1) r = less(r, other(r, off));
+    if (split > 1) {
+        if (lane < kFew) {
+            s_obj[wave][lane] = r.obj;
+            s_idx[wave][lane] = r.idx;
+        }
+        __syncthreads();
+        if (lane < kFew)
+            for (int w = 0; w < kFewWaves; ++w) {
+                best_t o;
+                o.obj = s_obj[w][lane];
+                o.idx = s_idx[w][lane];
+                r = less(r, o);
+            }
+    } else {
+        __syncthreads();
+    }
+    if (lane < kFew && my_n >= 0 && (split == 1 || wave == 0)) {
+        const double s = (double)scales[pv_row_of((unsigned)my_n, inv_gpr)];
+        double o_prev = 0.0;
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const double d = fma(s, (double)codebook[(int64_t)prev * G + i], -(double)T[(int64_t)my_n * G + i]);
+            o_prev = o_prev + d * d;
+        }
+        const int pick = o_prev == r.obj || r.idx == 0x7fffffff ? prev : r.idx;
+        if (pick != prev) {
+            codes[my_n] = (uint16_t)pick;
+            atomicAdd(&s_cnt[1], 1u);
+        }
+        atomicAdd(&s_cnt[0], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) few_counts(slots, s_cnt[0], s_cnt[1], num_changed, stats);
+}
+
 // ------------------------------------------------------------------ beam search
 //
 // One block per listed group.  The beam (tuples + objectives) and the pool of
@@ -956,6 +1116,42 @@ __global__ __launch_bounds__(kBeamBlock, 4) void k_beam_2x8_mfma(
 }
 
 }  // namespace
+
+// Where one launch beats the filter.  The search, filter / one launch: g = 8, 256 codewords, 64 groups 13.4 / 7.1 us,
+// 8192 14.8 / 7.3, 16384 16.2 / 10.8; 1024 codewords, 8192 groups (2^26 operations) 17.4 / 13.2, 16384
+// 18.9 / 22.0.  g = 16, where the filter also sorts norms: 256 codewords, 8192 groups 21.2 / 10.3; 1024, 8192
+// (2^27) 26.3 / 21.7, 16384 29.6 / 38.4.
+bool pv_search_few(const pv_layout *l, int64_t k)
+{
+    const int g = l->group_size;
+    return l->num_codebooks == 1 && (g == 8 || g == 16) && l->nbits >= 6 && l->nbits <= 10 && k <= 16384 &&
+           (k * g << l->nbits) <= (g == 8 ? 1ll << 26 : 1ll << 27);
+}
+
+pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, const float *codebook,
+                               const float *scales, const int32_t *group_idx, int64_t k, uint16_t *codes,
+                               int64_t *num_changed)
+{
+    constexpr size_t bytes = (size_t)(kFewSlots + 1) * kFewStride * 8;
+    pv_status st = pv_ensure(ctx, ctx->few, bytes, bytes);
+    if (st != PV_OK) return st;
+    pv_timed t(ctx, PV_K_EXACT_SCAN);
+    const int g = l->group_size, gpr = (int)(l->in_features / g), N = (int)pv_num_groups(l);
+    // enough waves with one for kFew groups, or nothing to share
+    const int split = l->nbits > 8 && k < 4096 ? kFewWaves : 1;
+    const int64_t per = split > 1 ? kFew : kFew * kFewWaves;
+    const dim3 grid((unsigned)((k + per - 1) / per));
+    auto stats = static_cast<unsigned long long *>(ctx->stats.ptr), slots = static_cast<unsigned long long *>(ctx->few.ptr);
+    auto nc = reinterpret_cast<unsigned long long *>(num_changed);
+    if (g == 8)
+        hipLaunchKernelGGL(k_search_few<8>, grid, dim3(kBlock), 0, ctx->stream, T, codebook, scales, group_idx, (int)k,
+                           codes, nc, stats, slots, l->nbits, 1.0 / (double)gpr, N, split);
+    else
+        hipLaunchKernelGGL(k_search_few<16>, grid, dim3(kBlock), 0, ctx->stream, T, codebook, scales, group_idx, (int)k,
+                           codes, nc, stats, slots, l->nbits, 1.0 / (double)gpr, N, split);
+    PV_HIP(ctx, hipGetLastError());
+    return PV_OK;
+}
 
 pv_status pv_launch_exact_scan(pv_ctx *ctx, const pv_layout *l, const float *T,
                                const float *codebooks, const float *scales, const int32_t *list,

@@ -413,6 +413,47 @@ def test_reencode_m1_list_lengths_around_the_launch_plan(g, k):
     assert st["filtered"] + st["fallback"] == k
 
 
+@pytest.mark.parametrize("g,B,k", [(8, 6, 1), (8, 6, 16384), (8, 7, 13), (8, 8, 8191), (8, 8, 16385), (8, 9, 4095),
+                                   (8, 9, 4096), (8, 9, 16384), (8, 10, 3), (8, 10, 8192), (8, 10, 8193), (16, 6, 5),
+                                   (16, 8, 4097), (16, 9, 16384), (16, 9, 4094), (16, 10, 8192), (16, 10, 8193)])
+@pytest.mark.parametrize("case", ["plain", "ties", "odd"])
+def test_reencode_m1_in_one_launch(g, B, k, case):
+    """Little work is one launch: lists that end inside a wave's and a block's groups, both sides of the
+    line and of the split of the codebook over a block's waves; exact ties (equal codewords, targets on them);
+    codewords and targets that are not finite, scales of zero and below, ids outside the matrix, stored codes
+    above 2^B.  Codes and count equal the exact scan's, twice in a row (the counters are left zero)."""
+    wl = workloads.make(160, 128 * g, g, 1, B, seed=97, sigma_g=2e-3, tau=1.0)
+    rng = np.random.default_rng(k)
+    if case == "ties":
+        wl.codebooks[0, 1::2] = wl.codebooks[0, ::2]
+        wl.codebooks[0, -3:] = 0.0
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    if case == "ties":
+        T_np[::3] = 0.0
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    if case == "odd":
+        wl.scales[::5] = 0.0
+        wl.scales[1::5] *= np.float32(-1.0)
+        wl.codebooks[0, 3, 1], wl.codebooks[0, 5, 0] = np.nan, np.inf
+        T_np[2, 7], T_np[9] = np.inf, np.nan
+        wl.codes[::7] |= np.uint16(1 << B)
+        idx = np.sort(np.where(rng.random(k) < 0.1, idx + wl.layout.num_groups, idx)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx)
+    run.ctx.pv_set_search_mode(0)
+    for _ in range(2):
+        got, n_got = run.reencode(T, idx)
+        assert np.array_equal(got, want) and n_got == n_want
+    st = run.ctx.pv_reencode_stats()
+    valid = int((idx < wl.layout.num_groups).sum())
+    if k <= 16384 and k * g << B <= (1 << 26 if g == 8 else 1 << 27):
+        assert st["exact"] == valid and st["filtered"] == st["fallback"] == 0
+    if case != "odd":
+        ref, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, idx, wl.codes)
+        check_codes_on(wl, T_np, idx, got, ref, info)
+
+
 @pytest.mark.parametrize("B,k", [(16, 32768), (16, 34001), (15, 65536), (14, 131072)])
 @pytest.mark.parametrize("regime", ["near", "far", "lumps", "degenerate"])
 def test_reencode_m1_cells_of_the_codebook(B, k, regime):
