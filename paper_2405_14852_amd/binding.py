@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 from dataclasses import dataclass
+from functools import cached_property
 from pathlib import Path
 
 import torch
@@ -43,9 +44,13 @@ class Layout:
     num_codebooks: int
     nbits: int
 
-    def c(self) -> _CLayout:
+    @cached_property
+    def _c(self) -> _CLayout:
         return _CLayout(self.out_features, self.in_features, self.group_size,
                         self.num_codebooks, self.nbits)
+
+    def c(self) -> _CLayout:
+        return self._c          # the library only reads it
 
     @property
     def num_groups(self) -> int:
@@ -119,7 +124,7 @@ def _dev_ptr(t, dtype, what: str, allow_none: bool = False):
         raise TypeError(f"{what} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise TypeError(f"{what} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 class PVContext:
