@@ -387,9 +387,6 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_vec(const float
 {
     __shared__ unsigned lh[kFirstBins];
     __shared__ unsigned s_coarse[64];
-    if (want_hist)
-        for (int b = threadIdx.x; b < kFirstBins; b += kBlock) lh[b] = 0;
-    __syncthreads();
     const pv_f4 *W4 = reinterpret_cast<const pv_f4 *>(W);
     const pv_f4 *G4 = reinterpret_cast<const pv_f4 *>(G);
     pv_f4 *T4 = reinterpret_cast<pv_f4 *>(T);
@@ -413,6 +410,9 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_vec(const float
     };
     int64_t cbase = (int64_t)blockIdx.x * (kBlock * kVecUnroll);
     if (cbase < nvec) load(cbase, w, gr);
+    if (want_hist)
+        for (int b = threadIdx.x; b < kFirstBins; b += kBlock) lh[b] = 0;
+    __syncthreads();
     for (; cbase < nvec; cbase += step) {
         // the loads of the next chunk are in flight while this one is scored
         if (cbase + step < nvec) load(cbase + step, wn, gn);
@@ -435,8 +435,8 @@ __global__ __launch_bounds__(kBlock) void k_targets_scores_hist0_vec(const float
                     vv[e] = vi;
                 }
                 if (i < nvec) {
-                    M4[i] = mm;
-                    V4[i] = vv;
+                    __builtin_nontemporal_store(mm, &M4[i]);
+                    __builtin_nontemporal_store(vv, &V4[i]);
                 }
             } else {
                 t.x = fmaf(-alpha, gr[u].x, w[u].x);
