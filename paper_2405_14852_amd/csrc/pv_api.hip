@@ -128,7 +128,7 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->select, &c->stats, &c->few, &c->search, &c->fb_list, &c->trust, &c->pstep};
+    pv_buffer *bufs[] = {&c->select, &c->stats, &c->counts, &c->search, &c->fb_list, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     for (auto &t : c->timers)
@@ -321,8 +321,10 @@ pv_status pv_reencode_dispatch(pv_ctx *ctx, const pv_layout *l, const float *T,
         return pv_launch_search_few(ctx, l, T, codebooks, scales, group_idx, k, codes, num_changed);
     if (filter)   // its first kernel clears the counters
         return pv_launch_mfma_search(ctx, l, T, codebooks, scales, group_idx, k, codes, num_changed);
-    st = pv_launch_fill_i64(ctx, stats, 8, 0, num_changed);
-    if (st != PV_OK) return st;
+    if (k == 0 || M == 1 || !pv_beam_clears_itself(ctx, l, beam_width)) {
+        st = pv_launch_fill_i64(ctx, stats, 8, 0, num_changed);
+        if (st != PV_OK) return st;
+    }
     if (k == 0) return PV_OK;
     if (M > 1) return pv_launch_beam(ctx, l, T, codebooks, scales, group_idx, k, beam_width, codes,
                                      num_changed);

@@ -10,6 +10,7 @@
 // The two-codebook beam search has the same pair: a filter on the fp64 matrix
 // instruction (k_beam_2x8_mfma) whose results are accepted only under
 // double-precision certificates, and the exact kernel behind it.
+#include "pv_counts.h"
 #include "pv_internal.h"
 
 #include <type_traits>
@@ -244,35 +245,12 @@ __global__ __launch_bounds__(kBlock) void k_exact_scan(
 constexpr int kFew = 4;
 constexpr int kFewWaves = kBlock / 64;
 
-// What a call counts, without a launch that clears it: a word is left zero by the last block to arrive.
-// arrivals << 40 | groups decided << 20 | codes changed
-constexpr int kFewSlots = 32, kFewStride = 16;
-__device__ __forceinline__ void few_counts(unsigned long long *slots, unsigned done, unsigned changed,
-                                           unsigned long long *num_changed, unsigned long long *stats)
-{
-    constexpr unsigned long long kOne = 1ull << 40;
-    const unsigned slot = blockIdx.x % kFewSlots, nslots = gridDim.x < (unsigned)kFewSlots ? gridDim.x : (unsigned)kFewSlots;
-    const unsigned members = (gridDim.x - slot + kFewSlots - 1) / kFewSlots;
-    unsigned long long *word = slots + slot * kFewStride;
-    unsigned long long sum = kOne | (unsigned long long)done << 20 | changed;
-    sum += atomicAdd(word, sum);
-    if ((unsigned)(sum >> 40) != members) return;
-    atomicExch(word, 0ull);
-    word = slots + kFewSlots * kFewStride;
-    sum = kOne | (sum & (kOne - 1ull));
-    sum += atomicAdd(word, sum);
-    if ((unsigned)(sum >> 40) != nslots) return;
-    atomicExch(word, 0ull);
-    if (num_changed) *num_changed = sum & 0xFFFFFull;
-    for (int i = 0; i < 8; ++i) stats[i] = i == 3 ? (sum >> 20) & 0xFFFFFull : 0ull;
-}
-
 template <int G>
 __global__ __launch_bounds__(kBlock) void k_search_few(const float *__restrict__ T, const float *__restrict__ codebook,
                                                        const float *__restrict__ scales,
                                                        const int32_t *__restrict__ list, int k, uint16_t *codes,
                                                        unsigned long long *num_changed, unsigned long long *stats,
-                                                       unsigned long long *slots, int nbits, double inv_gpr, int N,
+                                                       unsigned long long *counts, int nbits, double inv_gpr, int N,
                                                        int split)
 {
     __shared__ double s_obj[kFewWaves][kFew];
@@ -391,7 +369,13 @@ __global__ __launch_bounds__(kBlock) void k_search_few(const float *__restrict__
         atomicAdd(&s_cnt[0], 1u);
     }
     __syncthreads();
-    if (threadIdx.x == 0) few_counts(slots, s_cnt[0], s_cnt[1], num_changed, stats);
+    if (threadIdx.x == 0) {
+        unsigned long long both;                   // (k < 2^20)
+        if (pv_counts_arrive(counts, gridDim.x, (unsigned long long)s_cnt[0] << 20 | s_cnt[1], &both)) {
+            if (num_changed) *num_changed = both & 0xFFFFFull;
+            for (int i = 0; i < 8; ++i) stats[i] = i == 3 ? both >> 20 : 0ull;
+        }
+    }
 }
 
 // ------------------------------------------------------------------ beam search
@@ -684,15 +668,30 @@ __global__ __launch_bounds__(kBlock) void k_beam_2x8(
     const float *__restrict__ T, const float *__restrict__ codebooks,
     const float *__restrict__ scales, const int32_t *__restrict__ group_idx, int64_t k,
     int beam_width, uint16_t *__restrict__ codes, unsigned long long *__restrict__ num_changed,
-    unsigned long long *__restrict__ stat_counter, int gpr, int N,
-    const unsigned long long *__restrict__ d_count)
+    unsigned long long *__restrict__ stat_counter, int gpr, int N, unsigned long long *counts,
+    unsigned long long *stats)
 {
-    // d_count: the list length when an earlier kernel of the stream wrote the list
-    if (d_count) {
-        const int64_t c = (int64_t)*d_count;
+    // counts: an earlier kernel of the stream wrote the list; its length and what that kernel counted are
+    // there, and the last block with work publishes all of it and leaves zeros (`stats`: the call's counters)
+    unsigned working = 1;
+    if (counts) {
+        const int64_t c = (int64_t)counts[kCountList];
         if (c < k) k = c;
+        working = (unsigned)min((int64_t)gridDim.x, max((int64_t)1, (k + kBlock / 64 - 1) / (kBlock / 64)));
     }
-    if ((int64_t)blockIdx.x * (kBlock / 64) >= k) return;   // before the tables are loaded
+    auto arrive = [&](unsigned changed) {
+        unsigned long long all;
+        if (!pv_counts_arrive(counts, working, changed, &all)) return;
+        const unsigned long long early = atomicExch(&counts[kCountChanged], 0ull);
+        const unsigned long long fast = atomicExch(&counts[kCountFast], 0ull);
+        const unsigned long long listed = atomicExch(&counts[kCountList], 0ull);
+        if (num_changed) *num_changed = all + early;
+        for (int i = 0; i < 8; ++i) stats[i] = i == 0 ? fast : i == 1 || i == 4 ? listed : 0ull;
+    };
+    if ((int64_t)blockIdx.x * (kBlock / 64) >= k) {   // before the tables are loaded
+        if (counts && blockIdx.x == 0 && threadIdx.x == 0) arrive(0u);
+        return;
+    }
     __shared__ float s_cb[2 * 256 * G];
     for (int i = threadIdx.x; i < 2 * 256 * G / 4; i += kBlock)
         reinterpret_cast<pv_f4 *>(s_cb)[i] = reinterpret_cast<const pv_f4 *>(codebooks)[i];
@@ -720,8 +719,12 @@ __global__ __launch_bounds__(kBlock) void k_beam_2x8(
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (s_changed && num_changed) atomicAdd(num_changed, (unsigned long long)s_changed);
-        if (s_done && stat_counter) atomicAdd(stat_counter, (unsigned long long)s_done);
+        if (counts) {
+            arrive(s_changed);
+        } else {
+            if (s_changed && num_changed) atomicAdd(num_changed, (unsigned long long)s_changed);
+            if (s_done && stat_counter) atomicAdd(stat_counter, (unsigned long long)s_done);
+        }
     }
 }
 
@@ -1132,8 +1135,7 @@ pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, 
                                const float *scales, const int32_t *group_idx, int64_t k, uint16_t *codes,
                                int64_t *num_changed)
 {
-    constexpr size_t bytes = (size_t)(kFewSlots + 1) * kFewStride * 8;
-    pv_status st = pv_ensure(ctx, ctx->few, bytes, bytes);
+    pv_status st = pv_ensure(ctx, ctx->counts, kCountBytes, kCountBytes);
     if (st != PV_OK) return st;
     pv_timed t(ctx, PV_K_EXACT_SCAN);
     const int g = l->group_size, gpr = (int)(l->in_features / g), N = (int)pv_num_groups(l);
@@ -1141,14 +1143,14 @@ pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, 
     const int split = l->nbits > 8 && k < 4096 ? kFewWaves : 1;
     const int64_t per = split > 1 ? kFew : kFew * kFewWaves;
     const dim3 grid((unsigned)((k + per - 1) / per));
-    auto stats = static_cast<unsigned long long *>(ctx->stats.ptr), slots = static_cast<unsigned long long *>(ctx->few.ptr);
+    auto stats = static_cast<unsigned long long *>(ctx->stats.ptr), counts = static_cast<unsigned long long *>(ctx->counts.ptr);
     auto nc = reinterpret_cast<unsigned long long *>(num_changed);
     if (g == 8)
         hipLaunchKernelGGL(k_search_few<8>, grid, dim3(kBlock), 0, ctx->stream, T, codebook, scales, group_idx, (int)k,
-                           codes, nc, stats, slots, l->nbits, 1.0 / (double)gpr, N, split);
+                           codes, nc, stats, counts, l->nbits, 1.0 / (double)gpr, N, split);
     else
         hipLaunchKernelGGL(k_search_few<16>, grid, dim3(kBlock), 0, ctx->stream, T, codebook, scales, group_idx, (int)k,
-                           codes, nc, stats, slots, l->nbits, 1.0 / (double)gpr, N, split);
+                           codes, nc, stats, counts, l->nbits, 1.0 / (double)gpr, N, split);
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;
 }
@@ -1179,6 +1181,18 @@ pv_status pv_launch_exact_scan(pv_ctx *ctx, const pv_layout *l, const float *T,
     return PV_OK;
 }
 
+static bool beam_2x8(const pv_layout *l, int32_t beam_width)
+{
+    return l->num_codebooks == 2 && l->nbits == 8 && beam_width <= kBeam2Max &&
+           (l->group_size == 8 || l->group_size == 16);
+}
+
+// the filter's counters need no clearing before the call
+bool pv_beam_clears_itself(const pv_ctx *ctx, const pv_layout *l, int32_t beam_width)
+{
+    return ctx->search_mode == 0 && beam_2x8(l, beam_width);
+}
+
 pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const float *codebooks,
                          const float *scales, const int32_t *group_idx, int64_t k,
                          int32_t beam_width, uint16_t *codes, int64_t *num_changed)
@@ -1188,34 +1202,36 @@ pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const 
     const int gpr = (int)(l->in_features / g);
     const int N = (int)pv_num_groups(l);
     int64_t *stat = static_cast<int64_t *>(ctx->stats.ptr) + 3;
-    if (l->num_codebooks == 2 && l->nbits == 8 && beam_width <= kBeam2Max && (g == 8 || g == 16)) {
+    if (beam_2x8(l, beam_width)) {
         int64_t wblocks = (k + kBlock / 64 - 1) / (kBlock / 64);
         if (wblocks > 2048) wblocks = 2048;
         auto nc = reinterpret_cast<unsigned long long *>(num_changed);
         auto sc = reinterpret_cast<unsigned long long *>(stat);
         if (ctx->search_mode == 0) {
             // matrix-core filter; stats[0] = groups it decided, stats[1] = groups redone exactly,
-            // stats[4] = length of the redo list (all cleared by the caller's fill)
+            // stats[4] = length of the redo list
             pv_status est = pv_ensure(ctx, ctx->fb_list, (size_t)k * sizeof(int32_t) + 16);
+            if (est == PV_OK) est = pv_ensure(ctx, ctx->counts, kCountBytes, kCountBytes);
             if (est != PV_OK) return est;
             int32_t *redo = reinterpret_cast<int32_t *>(static_cast<char *>(ctx->fb_list.ptr) + 16);
             auto st0 = reinterpret_cast<unsigned long long *>(stat - 3);
+            auto counts = static_cast<unsigned long long *>(ctx->counts.ptr);
             int64_t pblocks = ((k + 1) / 2 + kBeamBlock / 64 - 1) / (kBeamBlock / 64);
             if (pblocks > 512) pblocks = 512;
             int64_t rblocks = wblocks < 1024 ? wblocks : 1024;
 #define PV_BEAM2(G_)                                                                             \
     hipLaunchKernelGGL(k_beam_2x8_mfma<G_>, dim3((unsigned)pblocks), dim3(kBeamBlock), 0, ctx->stream, \
-                       T, codebooks, scales, group_idx, k, beam_width, codes, nc, st0, redo,       \
-                       st0 + 4, gpr, N);                                                           \
+                       T, codebooks, scales, group_idx, k, beam_width, codes, counts + kCountChanged, \
+                       counts + kCountFast, redo, counts + kCountList, gpr, N);                    \
     hipLaunchKernelGGL(k_beam_2x8<G_>, dim3((unsigned)rblocks), dim3(kBlock), 0, ctx->stream, T,   \
-                       codebooks, scales, redo, k, beam_width, codes, nc, st0 + 1, gpr, N, st0 + 4)
+                       codebooks, scales, redo, k, beam_width, codes, nc, nullptr, gpr, N, counts, st0)
             if (g == 8) {
                 // fp32 / fp16 filter (pv_beam.hip), then the exact kernel on what it leaves
                 pv_launch_beam_2x8_f16(ctx, T, codebooks, scales, group_idx, k, beam_width, codes,
-                                       num_changed, st0, redo, st0 + 4, gpr, N);
+                                       reinterpret_cast<int64_t *>(counts + kCountChanged), counts + kCountFast, redo,
+                                       counts + kCountList, gpr, N);
                 hipLaunchKernelGGL(k_beam_2x8<8>, dim3((unsigned)rblocks), dim3(kBlock), 0, ctx->stream,
-                                   T, codebooks, scales, redo, k, beam_width, codes, nc, st0 + 1, gpr, N,
-                                   st0 + 4);
+                                   T, codebooks, scales, redo, k, beam_width, codes, nc, nullptr, gpr, N, counts, st0);
             } else {
                 PV_BEAM2(16);
             }
@@ -1226,11 +1242,11 @@ pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const 
         if (g == 8)
             hipLaunchKernelGGL(k_beam_2x8<8>, dim3((unsigned)wblocks), dim3(kBlock), 0, ctx->stream, T,
                                codebooks, scales, group_idx, k, beam_width, codes, nc, sc, gpr, N,
-                               (const unsigned long long *)nullptr);
+                               nullptr, nullptr);
         else
             hipLaunchKernelGGL(k_beam_2x8<16>, dim3((unsigned)wblocks), dim3(kBlock), 0, ctx->stream, T,
                                codebooks, scales, group_idx, k, beam_width, codes, nc, sc, gpr, N,
-                               (const unsigned long long *)nullptr);
+                               nullptr, nullptr);
         PV_HIP(ctx, hipGetLastError());
         return PV_OK;
     }

@@ -39,7 +39,7 @@ struct pv_ctx {
                             // when the caller passes none (see sel_scratch)
     size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
     pv_buffer stats;        // i64 [8]            counters of the last re-encode
-    pv_buffer few;          // counters of the search in one launch, zero between calls
+    pv_buffer counts;       // what a call's blocks count, zero between calls (pv_counts.h)
     pv_buffer search;       // the matrix-core filter's: statistics, operands, records, counters (see pv_launch_mfma_search)
     const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel
     pv_buffer fb_list;      // beam path: the groups left to the exact kernel
@@ -156,6 +156,7 @@ bool pv_search_few(const pv_layout *l, int64_t k);
 pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, const float *codebook,
                                const float *scales, const int32_t *group_idx, int64_t k, uint16_t *codes,
                                int64_t *num_changed);
+bool pv_beam_clears_itself(const pv_ctx *ctx, const pv_layout *l, int32_t beam_width);
 pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const float *codebooks,
                          const float *scales, const int32_t *group_idx, int64_t k,
                          int32_t beam_width, uint16_t *codes, int64_t *num_changed);

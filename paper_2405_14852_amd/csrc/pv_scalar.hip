@@ -5,6 +5,7 @@
 // grid value (App. K), done as the definition states it - every value tried, objective in
 // double on the fp32 dequantised value, previous code kept on a tie - so the result is the
 // oracle's bit for bit.  At most 256 candidates per weight: no search structure is needed.
+#include "pv_counts.h"
 #include "pv_internal.h"
 
 namespace {
@@ -46,7 +47,8 @@ __global__ __launch_bounds__(kBlock) void k_reencode_scalar(const float *__restr
                                                             const float *__restrict__ zeros,
                                                             const int32_t *__restrict__ weight_idx,
                                                             int64_t k, uint8_t *__restrict__ codes,
-                                                            unsigned long long *__restrict__ num_changed,
+                                                            unsigned long long *num_changed,
+                                                            unsigned long long *counts,
                                                             int64_t n, int64_t in_features, int blk,
                                                             int nvals)
 {
@@ -85,7 +87,10 @@ __global__ __launch_bounds__(kBlock) void k_reencode_scalar(const float *__restr
     const unsigned long long b = __ballot(moved);
     if ((threadIdx.x & 63) == 0 && b) atomicAdd(&s_changed, (unsigned)__popcll(b));
     __syncthreads();
-    if (threadIdx.x == 0 && s_changed && num_changed) atomicAdd(num_changed, (unsigned long long)s_changed);
+    if (threadIdx.x == 0 && num_changed) {
+        unsigned long long changed;
+        if (pv_counts_arrive(counts, gridDim.x, s_changed, &changed)) *num_changed = changed;
+    }
 }
 
 }  // namespace
@@ -115,7 +120,8 @@ pv_status pv_launch_reencode_scalar(pv_ctx *ctx, int64_t out_features, int64_t i
                                     uint8_t *codes, int64_t *num_changed)
 {
     if (num_changed) {
-        pv_status st = pv_launch_fill_i64(ctx, num_changed, 1, 0);
+        pv_status st = k == 0 ? pv_launch_fill_i64(ctx, num_changed, 1, 0)
+                              : pv_ensure(ctx, ctx->counts, kCountBytes, kCountBytes);
         if (st != PV_OK) return st;
     }
     if (k == 0) return PV_OK;
@@ -123,6 +129,7 @@ pv_status pv_launch_reencode_scalar(pv_ctx *ctx, int64_t out_features, int64_t i
     const int64_t blocks = (k + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_reencode_scalar, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, T, scales,
                        zeros, weight_idx, k, codes, reinterpret_cast<unsigned long long *>(num_changed),
+                       static_cast<unsigned long long *>(ctx->counts.ptr),
                        out_features * in_features, in_features, blk, 1 << nbits);
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;
