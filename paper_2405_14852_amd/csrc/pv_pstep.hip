@@ -576,12 +576,12 @@ struct small_mem {
     double *unit;        // [blocks] what one in `partial` stands for; NaN: some input was not finite
 };
 
-// x + 1.5 * 2^52 holds the integer nearest to x (ties to even) in its low mantissa bits for
-// |x| < 2^51; the terms stay below 2^50
-__device__ __forceinline__ unsigned long long fixed_point_term(double x)
+// s * g + 1.5 * 2^52 holds the integer nearest to s * g (ties to even) in its low mantissa bits for
+// |s * g| < 2^51; the terms stay below 2^51.  (s: a scale times a power of two, so the product is exact.)
+__device__ __forceinline__ unsigned long long fixed_point_term(double s, float g)
 {
     constexpr double kMagic = 6755399441055744.0;
-    return (unsigned long long)(__double_as_longlong(x + kMagic) - __double_as_longlong(kMagic));
+    return (unsigned long long)(__double_as_longlong(fma(s, (double)g, kMagic)) - __double_as_longlong(kMagic));
 }
 
 // sums and maxima over a wave through the lane-permute paths of the vector unit; uniform results
@@ -681,7 +681,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
         unsigned long long term[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            term[e] = fixed_point_term(ss * (double)x[e]);
+            term[e] = fixed_point_term(ss, x[e]);
             if (negate) term[e] = 0ull - term[e];
         }
         for (int m = 0; m < M; ++m) {
@@ -708,6 +708,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
         int row_end = row_vecs(gpr - (int)rem0);           // in vectors from the wave's first
         double acc = 0.0;
         gb = sb = 0u;
+        float gbf = 0.0f;
         for (int v0 = 0; v0 < len; v0 += 64 * kSmallAhead) {
             pv_f4 gv[kSmallAhead];
             unsigned nl[kSmallAhead], q4[kSmallAhead], c01[kSmallAhead][2];
@@ -734,8 +735,9 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
                 } else {
                     sf = scales[row0 + pv_row_of(rem0 + nl[u], inv_gpr)];
                 }
-                gb = max(max(gb, __float_as_uint(fabsf(gv[u].x))), __float_as_uint(fabsf(gv[u].y)));
-                gb = max(max(gb, __float_as_uint(fabsf(gv[u].z))), __float_as_uint(fabsf(gv[u].w)));
+                // (maxima that keep a NaN: half an instruction an element)
+                gbf = __builtin_elementwise_maximum(__builtin_elementwise_maximum(gbf, fabsf(gv[u].x)), fabsf(gv[u].y));
+                gbf = __builtin_elementwise_maximum(__builtin_elementwise_maximum(gbf, fabsf(gv[u].z)), fabsf(gv[u].w));
                 sb = max(sb, in ? __float_as_uint(fabsf(sf)) : 0u);
                 if (in) add_terms(gv[u], (double)sf * up, q4[u], c01[u], codes0 + (size_t)nl[u] * M);
                 if constexpr (ROWS) {
@@ -775,6 +777,7 @@ __global__ __launch_bounds__(kSmallBlock, 8) void k_pg_small(
             const double total = wave_sum_f64(acc);
             if (lane == 0) mem.rows[(size_t)cur + wave] = total;
         }
+        gb = __float_as_uint(gbf) & 0x7FFFFFFFu;
         X = block_bound(gb, sb, s_max);                    // what the block did meet
         if (!(X < __builtin_huge_val())) unit = __builtin_nan("");
         // terms up to the limit stay below 2^51 and their sums below 2^63
