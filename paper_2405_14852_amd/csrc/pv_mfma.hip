@@ -381,6 +381,14 @@ __device__ __forceinline__ operand_row operand_row_of(int pos)
     return {(pos / (32 * kU)) * kU + uu, 8 * (q >> 2) + 4 * hw + (q & 3)};
 }
 
+// Place of the smallest norm behind the key of a position: the keys of a residue cycle lie next to
+// each other for each half wave, so that one 16-byte read brings a lane all it closes in a cycle.
+__device__ __forceinline__ int key_norm_at(int pos)
+{
+    const int key = pos / (16 * kU), su = key >> 1, hw = key & 1;
+    return (su / kResidues * 2 + hw) * kResidues + su % kResidues;
+}
+
 // What the preparation of the selected groups reads and writes.
 struct group_args {
     const float *T, *scales, *codebook;
@@ -528,7 +536,7 @@ __device__ __forceinline__ void prep_group(const group_args &ga, int j, float P,
 // U pieces of 16, one per tile: position pos = ((su * 2 + hw) * U + uu) * 16 + q sits in tile
 // su * U + uu at row 8*(q/4) + 4*hw + q%4, so that accumulator q of half wave hw is that
 // position, and the 16 U positions behind one key of a lane are consecutive (for g = 16: in
-// norm order, none of their norms is below nmin[su * 2 + hw]).  Operand A of tile t, k-half h, row r
+// norm order, none of their norms is below nmin[key_norm_at(pos)]).  Operand A of tile t, k-half h, row r
 // is the 16-byte chunk A[(t * 2 + h) * 32 + r]:
 //   g = 8:  k-half 0 = 2 c_hi, k-half 1 = { three pieces of ||c_hi||^2, 1, 1, 1, 0, 0 }
 //   g = 16: k-half 0 = 2 c_hi[0..8), k-half 1 = 2 c_hi[8..16)
@@ -681,7 +689,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(const float *__restrict__ cb, i
         }
         // keys with nothing but padding behind them
         if (blockIdx.x == 0)
-            for (int h = (csize + 16 * kU - 1) / (16 * kU) + tid; h < cpad / (16 * kU); h += kBlock) nmin[place_of(h * (16 * kU)) / (16 * kU)] = 3.0e38f;
+            for (int h = (csize + 16 * kU - 1) / (16 * kU) + tid; h < cpad / (16 * kU); h += kBlock) nmin[key_norm_at(place_of(h * (16 * kU)))] = 3.0e38f;
         __syncthreads();
     }
 
@@ -722,7 +730,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(const float *__restrict__ cb, i
                 pos = place_of((int)rank);
                 cnorm[pos] = n2;           // for the re-rank kernel's cheap distances
                 // the ranks of a key's positions lie in the bucket of the first of them, or above it
-                if (rank % (16 * kU) == 0) nmin[pos / (16 * kU)] = norm_bucket_floor(b, anchor, P);
+                if (rank % (16 * kU) == 0) nmin[key_norm_at(pos)] = norm_bucket_floor(b, anchor, P);
             }
             perm[pos] = (uint16_t)c;
         } else if (G == 16) {
@@ -833,9 +841,11 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     // for the fill before every read
     __shared__ h8 lds0[kStageChunks + 64];
     __shared__ h8 lds1[kStageChunks + 64];
-    __shared__ float ldn0[64], ldn1[64];     // smallest norm behind each key of the stage (g = 16)
+    __shared__ __align__(16) float ldn0[64], ldn1[64];     // smallest norm behind each key of the stage (g = 16)
     __shared__ unsigned s_item;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // the wave's number in a scalar register: what follows from it is uniform (g = 16 reloaded
+    // spilled registers inside the loop over the tiles without it)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     unsigned vmask = ~kKeyMask;
     asm volatile("" : "+v"(vmask));   // keep the mask in a vector register
     // Work items = (group block, codeword split).  A block starts with item blockIdx.x; when
@@ -894,6 +904,8 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     static_assert(kUnitsCycle % kSets == 0 && kD >= 1 && kD < kSets, "accumulator sets must line up");
     f16v acc[kSets];
     h8 a_cur, a_nxt;
+    pv_f4 norm = {0.0f, 0.0f, 0.0f, 0.0f};              // g = 16: of the keys of a residue cycle
+    static_assert(kResidues == 4, "a cycle's norms are one vector");
     auto issue = [&](int nb, int set) {
         const f16v z = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         acc[set] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_cur, b[nb], z, 0, 0, 0);
@@ -901,7 +913,7 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     // rel: the tile's place in its residue cycle (a constant after unrolling: it picks the
     // registers); su_stage: its super-unit within the stage.  The key is closed at the last
     // tile of a super-unit.
-    auto reduce = [&](const float *bufn, int t0, int su_stage, int rel, int nb, int set) {
+    auto reduce = [&](int t0, int su_stage, int rel, int nb, int set) {
         const int uu = rel % kU;
         // g = 16: the chain starts at zero (the products can be negative, and a negative
         // maximum would not come out of the integer comparison: zero bounds it from above)
@@ -910,7 +922,7 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
         if (uu == kU - 1) {
             const int r = rel / kU;
             int kv = run[nb];
-            if (G == 16) kv = __float_as_int((__int_as_float(kv) - bufn[su_stage * 2 + (lane >> 5)]) + shift[nb]);
+            if (G == 16) kv = __float_as_int((__int_as_float(kv) - norm[r]) + shift[nb]);
             const int key = and_or(kv, vmask, (unsigned)(t0 / kU + su_stage));
             second[nb][r] = imed3(best[nb][r], second[nb][r], key);
             best[nb][r] = max(best[nb][r], key);
@@ -924,17 +936,33 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
 #pragma unroll
             for (int vr = 0; vr < kUnitsCycle; ++vr) {
                 const int u = vr / NB, nb = vr % NB, ts = q4 + u;
-                if (nb == 0) a_nxt = buf[(ts + 1) * 64 + lane];   // one spare tile pads the LDS array
+                if (G == 8 && nb == 0) a_nxt = buf[(ts + 1) * 64 + lane];   // one spare tile pads the LDS array
                 // g = 16: the wave asks for priority while it hands its matrix instruction over
-                // (measured: 408 -> 399 us on 183 500 groups; at g = 8 it costs 2 %)
+                // (measured: 384.0 -> 382.0 us on 183 500 groups; at g = 8 it costs 2 %)
                 if (G == 16) __builtin_amdgcn_s_setprio(3);
                 issue(nb, vr % kSets);
-                if (G == 16) __builtin_amdgcn_s_setprio(0);
+                if (G == 16) {
+                    __builtin_amdgcn_s_setprio(0);
+                    // Reads of LDS behind the matrix instruction that waits for the ones before: the wait counts
+                    // all reads, and one issued just before it would be waited for in full.  The cycle's norms
+                    // once the last key of the cycle before is closed, a tile ahead of the first use (183 500
+                    // groups x 65536 codewords: 402 -> 382 us with this and scalar wave numbers; the two norms of
+                    // a key read where it is closed held the wave up for a round trip twice a super-unit).
+                    // Matrix instruction and maxima alone, nothing read, take 27 ns a unit on random operands
+                    // (18 on zeros: the clock gives way to the power); this loop takes 33.
+                    if (nb == 0) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        a_nxt = buf[(ts + 1) * 64 + lane];
+                        if (u == (kD + NB - 1) / NB)
+                            norm = *reinterpret_cast<const pv_f4 *>(bufn + q4 / kCycle * 2 * kResidues + (lane >> 5) * kResidues);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
                 // the unit kD back: tile q4 + dq (dq may point into the cycle before), group tile wnb
                 const int dq = (vr - kD >= 0) ? (vr - kD) / NB : -((kD - vr + NB - 1) / NB);
                 const int wnb = ((vr - kD) % NB + NB) % NB;
                 if (q4 > 0 || vr >= kD)
-                    reduce(bufn, t0, (q4 + dq) / kU, (dq + kCycle) % kCycle, wnb,
+                    reduce(t0, (q4 + dq) / kU, (dq + kCycle) % kCycle, wnb,
                            ((vr - kD) % kSets + kSets) % kSets);
                 // keep this order: left to itself the scheduler moves a unit's reduction up
                 // behind its own matrix instruction, and the wave then waits out that
@@ -946,7 +974,7 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
         // the last kD units of the stage (its last residue cycle)
 #pragma unroll
         for (int w = kUnitsCycle - kD; w < kUnitsCycle; ++w)
-            reduce(bufn, t0, (cnt - kCycle + w / NB) / kU, w / NB, w % NB, w % kSets);
+            reduce(t0, (cnt - kCycle + w / NB) / kU, w / NB, w % NB, w % kSets);
     };
 
     if (t_begin < t_end) fetch(t_begin, lds0, ldn0);
