@@ -6,6 +6,7 @@
 
 #include <new>
 
+#include "pv_counts.h"
 #include "pv_internal.h"
 
 // ---------------------------------------------------------------- helpers
@@ -43,6 +44,17 @@ pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head)
     buf.ptr = p;
     buf.bytes = want;
     if (zero_head) PV_HIP(ctx, hipMemsetAsync(p, 0, zero_head, ctx->stream));
+    return PV_OK;
+}
+
+pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, unsigned long long **counts)
+{
+    constexpr size_t bytes = 8 * sizeof(int64_t) + kCountBytes;
+    const pv_status st = pv_ensure(ctx, ctx->stats, bytes, bytes);
+    if (st != PV_OK) return st;
+    auto p = static_cast<unsigned long long *>(ctx->stats.ptr);
+    if (stats) *stats = p;
+    if (counts) *counts = p + 8;
     return PV_OK;
 }
 
@@ -128,7 +140,7 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->select, &c->stats, &c->counts, &c->search, &c->fb_list, &c->trust, &c->pstep};
+    pv_buffer *bufs[] = {&c->select, &c->stats, &c->search, &c->fb_list, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     for (auto &t : c->timers)
@@ -312,7 +324,7 @@ pv_status pv_reencode_dispatch(pv_ctx *ctx, const pv_layout *l, const float *T,
                                uint16_t *codes, int64_t *num_changed)
 {
     const int M = l->num_codebooks;
-    pv_status st = pv_ensure(ctx, ctx->stats, 8 * sizeof(int64_t));
+    pv_status st = pv_counters(ctx, nullptr, nullptr);
     if (st != PV_OK) return st;
     int64_t *stats = static_cast<int64_t *>(ctx->stats.ptr);
     ctx->rr_blocks_last = 0;
@@ -368,7 +380,7 @@ extern "C" pv_status pv_reencode_groups_stochastic(pv_ctx *ctx, const pv_layout 
     if (k > 0 && ctx->search_mode == 0 && pv_mfma_supported(l)) {
         // the matrix-core filter with the certificate taken from the second nearest; its first
         // kernel clears the counters
-        st = pv_ensure(ctx, ctx->stats, 8 * sizeof(int64_t));
+        st = pv_counters(ctx, nullptr, nullptr);
         if (st != PV_OK) return st;
         return pv_launch_mfma_search(ctx, l, T, codebooks, scales, group_idx, k, codes, num_changed,
                                      power, seed);

@@ -1135,7 +1135,8 @@ pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, 
                                const float *scales, const int32_t *group_idx, int64_t k, uint16_t *codes,
                                int64_t *num_changed)
 {
-    pv_status st = pv_ensure(ctx, ctx->counts, kCountBytes, kCountBytes);
+    unsigned long long *stats, *counts;
+    pv_status st = pv_counters(ctx, &stats, &counts);
     if (st != PV_OK) return st;
     pv_timed t(ctx, PV_K_EXACT_SCAN);
     const int g = l->group_size, gpr = (int)(l->in_features / g), N = (int)pv_num_groups(l);
@@ -1143,7 +1144,6 @@ pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, 
     const int split = l->nbits > 8 && k < 4096 ? kFewWaves : 1;
     const int64_t per = split > 1 ? kFew : kFew * kFewWaves;
     const dim3 grid((unsigned)((k + per - 1) / per));
-    auto stats = static_cast<unsigned long long *>(ctx->stats.ptr), counts = static_cast<unsigned long long *>(ctx->counts.ptr);
     auto nc = reinterpret_cast<unsigned long long *>(num_changed);
     if (g == 8)
         hipLaunchKernelGGL(k_search_few<8>, grid, dim3(kBlock), 0, ctx->stream, T, codebook, scales, group_idx, (int)k,
@@ -1211,11 +1211,10 @@ pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const 
             // matrix-core filter; stats[0] = groups it decided, stats[1] = groups redone exactly,
             // stats[4] = length of the redo list
             pv_status est = pv_ensure(ctx, ctx->fb_list, (size_t)k * sizeof(int32_t) + 16);
-            if (est == PV_OK) est = pv_ensure(ctx, ctx->counts, kCountBytes, kCountBytes);
+            unsigned long long *st0 = nullptr, *counts = nullptr;
+            if (est == PV_OK) est = pv_counters(ctx, &st0, &counts);
             if (est != PV_OK) return est;
             int32_t *redo = reinterpret_cast<int32_t *>(static_cast<char *>(ctx->fb_list.ptr) + 16);
-            auto st0 = reinterpret_cast<unsigned long long *>(stat - 3);
-            auto counts = static_cast<unsigned long long *>(ctx->counts.ptr);
             int64_t pblocks = ((k + 1) / 2 + kBeamBlock / 64 - 1) / (kBeamBlock / 64);
             if (pblocks > 512) pblocks = 512;
             int64_t rblocks = wblocks < 1024 ? wblocks : 1024;

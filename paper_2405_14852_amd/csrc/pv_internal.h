@@ -38,8 +38,7 @@ struct pv_ctx {
     pv_buffer select;       // the selection's: histograms (kept zero between calls), counts, lists, group scores
                             // when the caller passes none (see sel_scratch)
     size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
-    pv_buffer stats;        // i64 [8]            counters of the last re-encode
-    pv_buffer counts;       // what a call's blocks count, zero between calls (pv_counts.h)
+    pv_buffer stats;        // i64 [8] counters of the last re-encode | what a call's blocks count (pv_counters)
     pv_buffer search;       // the matrix-core filter's: statistics, operands, records, counters (see pv_launch_mfma_search)
     const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel
     pv_buffer fb_list;      // beam path: the groups left to the exact kernel
@@ -59,6 +58,9 @@ struct pv_timed {
 pv_status pv_fail(pv_ctx *ctx, pv_status st, const char *fmt, ...);
 // A buffer of at least `bytes`; the first `zero_head` bytes of a new block are cleared on the stream.
 pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head = 0);
+// Both kinds of counters, in one block whatever the route: a smaller k of a shape that was seen before may take
+// another route, and allocates nothing.
+pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, unsigned long long **counts);
 
 #define PV_HIP(ctx, call)                                                              \
     do {                                                                               \

@@ -89,7 +89,8 @@ __global__ __launch_bounds__(kBlock) void k_reencode_scalar(const float *__restr
     __syncthreads();
     if (threadIdx.x == 0 && num_changed) {
         unsigned long long changed;
-        if (pv_counts_arrive(counts, gridDim.x, s_changed, &changed)) *num_changed = changed;
+        if (!counts) atomicAdd(num_changed, (unsigned long long)s_changed);
+        else if (pv_counts_arrive(counts, gridDim.x, s_changed, &changed)) *num_changed = changed;
     }
 }
 
@@ -119,9 +120,13 @@ pv_status pv_launch_reencode_scalar(pv_ctx *ctx, int64_t out_features, int64_t i
                                     const float *zeros, const int32_t *weight_idx, int64_t k,
                                     uint8_t *codes, int64_t *num_changed)
 {
+    unsigned long long *counts = nullptr;
     if (num_changed) {
-        pv_status st = k == 0 ? pv_launch_fill_i64(ctx, num_changed, 1, 0)
-                              : pv_ensure(ctx, ctx->counts, kCountBytes, kCountBytes);
+        // a context's first call, into a graph: it cannot allocate, a launch clears the caller's word
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (k > 0 && !ctx->stats.ptr) PV_HIP(ctx, hipStreamIsCapturing(ctx->stream, &capture));
+        pv_status st = k == 0 || capture != hipStreamCaptureStatusNone ? pv_launch_fill_i64(ctx, num_changed, 1, 0)
+                                                                       : pv_counters(ctx, nullptr, &counts);
         if (st != PV_OK) return st;
     }
     if (k == 0) return PV_OK;
@@ -129,8 +134,7 @@ pv_status pv_launch_reencode_scalar(pv_ctx *ctx, int64_t out_features, int64_t i
     const int64_t blocks = (k + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_reencode_scalar, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, T, scales,
                        zeros, weight_idx, k, codes, reinterpret_cast<unsigned long long *>(num_changed),
-                       static_cast<unsigned long long *>(ctx->counts.ptr),
-                       out_features * in_features, in_features, blk, 1 << nbits);
+                       counts, out_features * in_features, in_features, blk, 1 << nbits);
     PV_HIP(ctx, hipGetLastError());
     return PV_OK;
 }

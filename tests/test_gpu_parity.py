@@ -12,6 +12,7 @@ import torch
 
 import oracle
 import workloads
+from paper_2405_14852_amd import PVContext
 from gpu_util import DEV, GpuRun, check_codes_on, dev_f32, dev_i32, dev_u16, host_u16
 
 pytestmark = pytest.mark.gpu
@@ -452,6 +453,37 @@ def test_reencode_m1_in_one_launch(g, B, k, case):
     if case != "odd":
         ref, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, idx, wl.codes)
         check_codes_on(wl, T_np, idx, got, ref, info)
+
+
+def test_reencode_m1_of_a_smaller_k_can_be_captured():
+    """The shape was seen with a list that the filter takes; a short list goes another way, and a captured
+    call cannot allocate.  The replay also after the context counted something else."""
+    wl = workloads.make(160, 1024, 8, 1, 8, seed=98, tau=1.0, sigma_g=2e-3)
+    N, k = wl.layout.num_groups, 8192
+    side = torch.cuda.Stream(device=DEV)
+    run = GpuRun(wl, PVContext(0, stream=side))
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    T, idx = dev_f32(T_np), dev_i32(np.arange(N, dtype=np.int32))
+    count = torch.zeros(1, dtype=torch.int64, device=DEV)
+    first, codes = run.codes.clone(), run.codes.clone()
+    torch.cuda.synchronize()
+    run.ctx.pv_reencode_groups(run.lay, T, run.cb, run.sc, idx, N, 1, first, count)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        run.ctx.pv_reencode_groups(run.lay, T, run.cb, run.sc, idx, k, 1, codes, count)
+    ids = np.arange(k, dtype=np.int32)
+    want, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, ids, wl.codes)
+    for rep in range(3):
+        codes.view(torch.int16).copy_(run.codes.view(torch.int16))
+        count.fill_(-5)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        check_codes(wl, T_np, ids, host_u16(codes), want, info)
+        assert int(count.item()) == info["num_changed"] or info["near_tie"].any()
+        run.ctx.pv_reencode_groups(run.lay, T, run.cb, run.sc, idx, 77 + rep, 1, first, count)
+        side.synchronize()
 
 
 @pytest.mark.parametrize("B,k", [(16, 32768), (16, 34001), (15, 65536), (14, 131072)])

@@ -71,6 +71,35 @@ def test_scalar_tie_rule_empty_list_and_errors():
     ctx.close()
 
 
+def test_scalar_first_call_of_a_context_can_be_captured():
+    """The search needs no scratch memory of a context for the caller's count: a first call may be captured,
+    and calls outside the graph that count otherwise leave its replays as they are."""
+    o, i, block, nbits = 64, 512, 128, 2
+    W0, G, codes, sc, zp = workloads.make_scalar(o, i, block, nbits, seed=96)
+    side = torch.cuda.Stream(device=DEV)
+    ctx = PVContext(0, stream=side)
+    T_np = oracle.encode_targets(oracle.dequantize_scalar(codes, sc, zp, block, nbits), G * 20, 1.0)
+    ids = np.arange(0, o * i, 3, dtype=np.int32)
+    T, sd, zd, cd, idx = dev_f32(T_np), dev_f32(sc), dev_f32(zp), dev_u8(codes), dev_i32(ids)
+    before, nch = cd.clone(), torch.zeros(1, dtype=torch.int64, device=DEV)
+    want, changed = oracle.reencode_scalar(T_np, sc, zp, ids, codes, block, nbits)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.pv_reencode_scalar(o, i, block, nbits, T, sd, zd, idx, len(ids), cd, nch)
+    for replay in (True, True, False, True):
+        cd.copy_(before)
+        nch.fill_(-3)
+        torch.cuda.synchronize()
+        if replay:
+            graph.replay()
+        else:
+            ctx.pv_reencode_scalar(o, i, block, nbits, T, sd, zd, idx, len(ids), cd, nch)
+        torch.cuda.synchronize()
+        assert np.array_equal(cd.cpu().numpy(), want) and int(nch.item()) == changed > 0
+    ctx.close()
+
+
 def sampled_vectors(n):
     """The vectors of four weights that the sweep of many single weights samples its scores from."""
     i, u32 = np.arange(16384, dtype=np.uint64), np.uint64(0xFFFFFFFF)
