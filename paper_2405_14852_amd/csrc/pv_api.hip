@@ -140,7 +140,7 @@ extern "C" void pv_destroy(pv_ctx *c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    pv_buffer *bufs[] = {&c->select, &c->stats, &c->search, &c->fb_list, &c->trust, &c->pstep};
+    pv_buffer *bufs[] = {&c->select, &c->sample, &c->stats, &c->search, &c->fb_list, &c->trust, &c->pstep};
     for (pv_buffer *b : bufs)
         if (b->ptr) (void)hipFree(b->ptr);
     for (auto &t : c->timers)

@@ -38,6 +38,8 @@ struct pv_ctx {
     pv_buffer select;       // the selection's: histograms (kept zero between calls), counts, lists, group scores
                             // when the caller passes none (see sel_scratch)
     size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
+    pv_buffer sample;       // and its sample of many single weights: a histogram, zero between calls
+    bool sample_refused = false;          // there was no memory for it: scores are written instead
     pv_buffer stats;        // i64 [8] counters of the last re-encode | what a call's blocks count (pv_counters)
     pv_buffer search;       // the matrix-core filter's: statistics, operands, records, counters (see pv_launch_mfma_search)
     const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel

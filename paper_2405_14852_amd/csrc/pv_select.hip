@@ -52,8 +52,7 @@ constexpr int kCopies = 8;
 constexpr int kFine = 64;                      // counters per coarse counter, one per lane of a wave
 constexpr int hist_words(int bins) { return kCopies * (bins + bins / kFine); }
 constexpr int kHist0 = 0, kHist1 = kHist0 + hist_words(kFirstBins), kHist2 = kHist1 + hist_words(kMidBins);
-constexpr int kHistS = kHist2 + hist_words(kLastBins);   // a sample's digit 0
-constexpr int kHistTotal = kHistS + hist_words(kFirstBins);
+constexpr int kHistTotal = kHist2 + hist_words(kLastBins);
 
 // The passes after the sweep: region r of kSelWaves * blocks is the contiguous range of groups
 // that wave r works on in every one of them.
@@ -575,6 +574,7 @@ struct cell_args {
     uint2 *lists;                    // [cells][kCellList] {key, id}, or kCell scores in the same place
     unsigned *counts;                // [cells] keys kept
     unsigned *waves;                 // [waves of the sweep] the sum of their cells
+    unsigned *sample;                // digit 0 of the sample, zero between calls
 };
 struct region_t {
     const uint2 *list;      // {key, id}
@@ -706,7 +706,7 @@ __global__ __launch_bounds__(kSelBlock) void k_collect(const float *__restrict__
     load_scores<false>(mine_scores, 0, n, cur);     // in flight while digit 0 is resolved
     for (int b = threadIdx.x; b < kMidBins; b += kSelBlock) lh[b] = 0;
     // the last digit's histogram starts at zero (its reader of the call before has run)
-    for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistS; z += gridDim.x * kSelBlock)
+    for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
         hist_all[z] = 0u;
     unsigned kk = k;
     unsigned share;
@@ -978,6 +978,7 @@ __global__ __launch_bounds__(kSelBlock) void k_write_ids(sel_args a, int32_t *__
 // otherwise, the last), the scores are taken from T and W again.
 constexpr int kSampleBlock = 512;
 constexpr int kSampleBlocks = 32;
+constexpr int kSampleWords = hist_words(kFirstBins);
 constexpr int kSampleVecs = kSampleBlock * kSampleBlocks;    // four weights each, one in every 1 / kSampleVecs of the matrix
 __global__ __launch_bounds__(kSampleBlock) void k_sample(const float *__restrict__ W, const float *__restrict__ G,
                                                          float alpha, int64_t nvec, unsigned *__restrict__ hist)
@@ -1048,7 +1049,7 @@ __global__ __launch_bounds__(kListBlock, 4) void k_targets_lists(const float *W,
     load(G, wave, g);
     for (int b = threadIdx.x; b < kFirstBins; b += kListBlock) lh[b] = 0;
     unsigned kk = sample_kk;
-    const unsigned lo = (unsigned)pick_digit<kListBlock / 64>(hist_all + kHistS, kFirstBins, kk, tmp) << kRestBits;   // its barriers also order the clearing above
+    const unsigned lo = (unsigned)pick_digit<kListBlock / 64>(c.sample, kFirstBins, kk, tmp) << kRestBits;   // its barriers also order the clearing above
     if (blockIdx.x == 0 && threadIdx.x == 0) state[2] = lo;
     unsigned total = 0;
     for (int cell = wave; cell < ncells; cell += waves) {
@@ -1254,6 +1255,7 @@ __global__ __launch_bounds__(kSelBlock) void k_mid_or_first(sel_args a, int wave
     // the last digit's histogram starts at zero, and the sample's is done with
     for (int z = kHist2 + blockIdx.x * kSelBlock + threadIdx.x; z < kHistTotal; z += gridDim.x * kSelBlock)
         a.hist_all[z] = 0u;
+    for (int z = blockIdx.x * kSelBlock + threadIdx.x; z < kSampleWords; z += gridDim.x * kSelBlock) a.cells.sample[z] = 0u;
     // from the waves' counts and not from digit 0's histogram, to which blocks of this launch may add
     unsigned kept = 0;
     for (int i = threadIdx.x; i < waves; i += kSelBlock) kept += a.cells.waves[i];
@@ -1510,7 +1512,15 @@ pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, cons
     st = sel_scratch(ctx, N, /*own_scores=*/!scores, &bufs, &lists);
     if (st != PV_OK) return st;
     bufs.plan = make_sel_plan(N, k, lists);
-    if (G && !adam && !scores && lists && sweep_collects(l, k)) {
+    // whatever k and the direction: a later call of the shape does not allocate.  A block of its own: in the one
+    // above it took smaller matrices past sizes from which an allocation costs more (2 MiB for 1003 x 2072 in groups of 8)
+    bool sample = !scores && l->group_size == 1 && N >= kCollectMin && !ctx->sample_refused;
+    if (sample) {
+        sample = pv_ensure(ctx, ctx->sample, kSampleWords * sizeof(unsigned), kSampleWords * sizeof(unsigned)) == PV_OK;
+        ctx->sample_refused = !sample;
+    }
+    if (G && !adam && sample && lists && sweep_collects(l, k)) {
+        bufs.cells.sample = static_cast<unsigned *>(ctx->sample.ptr);
         // the cells take the place of the scores
         bufs.cells.lists = reinterpret_cast<uint2 *>(bufs.scores);
         bufs.cells.counts = reinterpret_cast<unsigned *>(bufs.cells.lists + cells_of(N) * kCellList);
@@ -1613,7 +1623,7 @@ static pv_status select_run(pv_ctx *ctx, const pv_layout *l, const float *T, con
         {
             pv_timed t(ctx, PV_K_ENCODE_TARGETS);
             hipLaunchKernelGGL(k_sample, dim3(kSampleBlocks), dim3(kSampleBlock), 0, ctx->stream, W, G, alpha,
-                               (int64_t)N / 4, hist + kHistS);
+                               (int64_t)N / 4, bufs.cells.sample);
             hipLaunchKernelGGL(k_targets_lists, dim3((unsigned)blocks), dim3(kListBlock), 0, ctx->stream, W, G, alpha,
                                const_cast<float *>(T), hist, state, (int64_t)N, sample_rank(N, k), bufs.cells);
         }
