@@ -4,7 +4,8 @@
 // no atomic touches device memory: ranks come from wave ballots and per-wave counters in LDS,
 // so keys with equal digits keep the order they came in.  Keys are read through a functor
 // (KEYS: unsigned operator()(int64_t e) const), values are the element's index in the first
-// pass (vals == nullptr) and carried afterwards.  #pragma once
+// pass (vals == nullptr) and carried afterwards.
+#pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
