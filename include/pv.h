@@ -242,11 +242,12 @@ pv_status pv_dequantize_groups(pv_ctx *ctx, const pv_layout *layout, const uint1
  *                                                                        f32 [out_features], optional
  * Products are exact in double and every result is rounded to fp32 once.  Two routes, both a
  * function of the inputs only (a second call returns the same bits):
- *   - the table of M * 2^B * g sums does not fit one block's LDS as 8-byte entries (64 KiB), or
- *     fewer than 64 groups share a codeword on average: the groups are sorted by code and a
- *     codeword's sum runs over its groups in ascending order, in double - equal to a
- *     sequential loop - unless more than 128 groups share the codeword, in which case pieces
- *     of 128 are summed that way and added in order;
+ *   - the table of M * 2^B * g sums does not fit one block's LDS as 8-byte entries (64 KiB),
+ *     fewer than 64 groups share a codeword on average, or g is no multiple of 4: a codeword's
+ *     sum runs over its groups in ascending order, in double - equal to a sequential loop -
+ *     unless more than 128 groups share the codeword.  Then pieces of its groups are summed
+ *     that way and added in order; where the pieces begin depends on the codes of the whole
+ *     matrix (so the double sum may round differently when other groups' codes change);
  *   - else (small codebooks): the terms are added in 64-bit fixed point scaled by a power of
  *     two taken from max|scales| * max|G|, exact up to 2^-39 of that product per term, in
  *     any order; if a gradient or a scale is not finite every entry of grad_codebooks is NaN.

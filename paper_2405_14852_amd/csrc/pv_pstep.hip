@@ -9,8 +9,8 @@
 // atomics would serialise on popular codewords and give run-dependent roundings (and atomics
 // on device memory are slow on a part whose L2 is split over several dies); instead the
 // groups are put in code order by two launches that exchange 4 bytes a group and no atomics:
-// - k_pg_tiles puts every tile of 8192 groups in the order of up to 512 buckets of consecutive
-//   codes and writes the tile where it was read, with the places where its buckets start; no
+// - k_pg_tiles puts every tile of 8192 groups in the order of up to 512 buckets of codes and writes
+//   the tile where it was read, with the places where its buckets start; no
 //   counts over the whole matrix are needed.  Blocks of the same launch take the scale gradient,
 //   a tree sum per row.
 // - k_pg_buckets gives a block to a bucket: it lays the tiles' runs end to end in LDS, puts them in
@@ -19,12 +19,20 @@
 //   groups.  Codewords with more than kLong groups in a chunk of the bucket are summed in pieces that are
 //   added in order (a different association from the plain loop: reproducible from run to run,
 //   but no longer the sequential rounding).
+// - A bucket with far more groups than the others (a codeword that holds many, or several that meet
+//   in a bucket) would be one block's work for long: a chunk of 8192 groups takes it 36 us (21 the sums, whose
+//   gathers are bound by what one compute unit has in flight).  Its chunks go to blocks of their own, and the last of
+//   those to be done adds up.
 // Bound by the gathers: 32 bytes of G (g = 8) bring a line of 128, and 2^21 of them in random order
 // take 41 us of k_pg_buckets' 54 whatever the kind of load (plain, nontemporal, device scope) and
-// whether G was read shortly before.  4096 x 4096, 1 x 16: 107 -> 83 us a call against a radix sort of
-// (code, group) in two passes of three kernels, segment starts, sums and scales (nine launches);
-// 354 x 384, 1 x 12 40 -> 20; 4096 x 4096, 1 x 12 118 -> 90.  Scales as a launch of their own: 84; beside the
+// whether G was read shortly before.  4096 x 4096, 1 x 16, codes drawn evenly: 107 -> 82 us a call against a radix
+// sort of (code, group) in two passes of three kernels, segment starts, sums and scales (nine launches);
+// 354 x 384, 1 x 12 40 -> 21; 4096 x 4096, 1 x 12 118 -> 87.  Scales as a launch of their own: 84; beside the
 // sums instead of the order: 82.  Buckets of 256 or tiles of 4096 groups: 1 to 8 us more.
+// Codes used unevenly, 4096 x 4096, 1 x 16 (the radix sort / buckets of consecutive codes, a block each / this):
+// 64 neighbouring codewords hold everything 1370 / 5640 / 131 us, 512 of them 1250 / 1900 / 110; uses that fall
+// like 1 / code 704 / 4280 / 174, the same in random order 720 / 727 / 177; one codeword with a third 3370 / 3160 /
+// 150; 64 at random places 384 / 388 / 131, 512 150 / 131 / 138; 128 codewords 512 apart 194 / 171 / 175.
 // Small codebooks take another route (k_pg_small below), which takes the scale gradient along.
 #include "pv_internal.h"
 #include "pv_dpp.h"
@@ -36,7 +44,11 @@ constexpr int kLong = 128;       // groups of a codeword in a chunk that one tea
 
 // ---- large codebooks: tiles put in bucket order, then a block for every bucket
 
-// A bucket is a range of 2^low consecutive codes, at most 512 buckets a codebook.
+// A bucket is 2^low codes, at most 512 buckets a codebook: those whose product with the golden section of 2^B (an odd
+// number, so every code has a product of its own) agrees in its high bits.  Neighbouring codes, and codes a power of two
+// apart, are spread evenly over the buckets that way, and where few codewords hold most groups they are often
+// such (a codebook in order of norm or of use, a part of it in use).  With high bits folded into low ones by
+// exclusive or, every 64th code used: 160 us a call, 85 this way.
 constexpr int kTileBlock = 1024;
 constexpr int kTileWaves = kTileBlock / 64;
 constexpr int kTilePer = 8;
@@ -51,10 +63,20 @@ struct bucket_args {
     int64_t N;
     int M, m0;           // codebooks, the first one of this launch
     unsigned mask;       // 2^B - 1
-    int low, high;       // bits of a code within its bucket, bits that name the bucket
+    unsigned mul, inv;   // product of one another: 1 modulo 2^B
+    int low, high;       // bits of code * mul within its bucket, bits that name the bucket
     int ntiles;
     uint32_t *entries;   // [codebook of the launch][N] tile by tile: code within the bucket << 16 | place in the tile
-    uint16_t *first;     // [codebook of the launch][tile][buckets + 1] where a bucket starts in its tile
+    uint16_t *first;     // [codebook of the launch][tile][stride] where a bucket starts in its tile, for buckets + 1
+    int stride;          // a multiple of 8
+    // buckets with more groups than `overfull`: `spare` chunks in a codebook at most
+    unsigned overfull, long_run;         // such a bucket has a tile with more than long_run of its groups
+    int mains, spare;                    // blocks with a bucket of their own; then `spare` for each codebook
+    unsigned *uneven;                    // [codebook][tile] some bucket has more than long_run groups there
+    unsigned *arrived;                   // [codebook][bucket] chunks done
+    double *part;                        // [codebook][spare][codes of a bucket][g] their sums
+    uint32_t *ids;                       // [codebook][spare][kChunk] their groups in code order
+    uint16_t *starts;                    // [codebook][spare][codes of a bucket + 1] where a code's begin
 };
 
 // The lanes of a wave (among `valid`) whose low `bits` bits of d are this lane's.
@@ -239,7 +261,7 @@ __global__ __launch_bounds__(kTileBlock, 8) void k_pg_tiles(bucket_args b, scale
 {
     __shared__ unsigned wcnt[kTileWaves][kBuckets];
     __shared__ unsigned s_first[kBuckets + 1], s_w[kBuckets / 64];
-    __shared__ unsigned s_out[kTile];
+    __shared__ unsigned s_out[kTile], s_uneven;
     if ((int)blockIdx.x >= sort_blocks) {
         const int team = threadIdx.x / kBlock;
         row_scale_grad<VEC, 2>(sc, (int64_t)((int)blockIdx.x - sort_blocks) * (kTileBlock / kBlock) + team,
@@ -258,9 +280,13 @@ __global__ __launch_bounds__(kTileBlock, 8) void k_pg_tiles(bucket_args b, scale
         code[j] = b.codes[(base + (i < n ? i : n - 1)) * b.M + b.m0 + mi] & b.mask;
     }
     for (int w = threadIdx.x; w < kTileWaves * kBuckets; w += kTileBlock) (&wcnt[0][0])[w] = 0u;
+    if (threadIdx.x == 0) s_uneven = 0u;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kTilePer; ++j) d[j] = code[j] >> b.low;
+    for (int j = 0; j < kTilePer; ++j) {
+        code[j] = (code[j] * b.mul) & b.mask;
+        d[j] = code[j] >> b.low;
+    }
     digit_ranks<kTilePer, kBuckets>(d, rank, per, n, b.high, wcnt);
     digit_starts<kTileWaves, kBuckets>(wcnt, s_first, s_w);
 #pragma unroll
@@ -269,23 +295,28 @@ __global__ __launch_bounds__(kTileBlock, 8) void k_pg_tiles(bucket_args b, scale
         if (j < per && i < n)
             s_out[s_first[d[j]] + wcnt[wave][d[j]] + rank[j]] = (code[j] & ((1u << b.low) - 1u)) << 16 | (unsigned)i;
     }
+    if ((int)threadIdx.x < 1 << b.high && s_first[threadIdx.x + 1] - s_first[threadIdx.x] > b.long_run) s_uneven = 1u;
     __syncthreads();
+    if (b.spare) {
+        if (threadIdx.x == 0) b.uneven[mi * b.ntiles + tile] = s_uneven;
+        for (int i = tile * kTileBlock + (int)threadIdx.x; i < 1 << b.high; i += b.ntiles * kTileBlock)
+            b.arrived[(mi << b.high) + i] = 0u;
+    }
     uint32_t *out = b.entries + (int64_t)mi * b.N + base;
     for (int i = threadIdx.x; i < n; i += kTileBlock) out[i] = s_out[i];
-    uint16_t *first = b.first + ((int64_t)mi * b.ntiles + tile) * ((1 << b.high) + 1);
+    uint16_t *first = b.first + ((int64_t)mi * b.ntiles + tile) * b.stride;
     if ((int)threadIdx.x < 1 << b.high) first[threadIdx.x] = (uint16_t)s_first[threadIdx.x];
     if (threadIdx.x == 0) first[1 << b.high] = (uint16_t)n;
 }
 
 // acc[v] += s_o * G[n, i * VEC + v] over the groups ids[a .. b) in that order, as many gathers together as fit
 // the registers
-template <int VEC>
+template <int VEC, int kInFlight>
 __device__ __forceinline__ void ordered_sum(double (&acc)[VEC], const unsigned *ids, int a, int b,
                                             const float *__restrict__ G, const float *__restrict__ scales,
                                             double inv_gpr, int g, int i)
 {
     typedef float vec __attribute__((ext_vector_type(VEC)));
-    constexpr int kInFlight = VEC == 4 ? 8 : 16;
     for (int r0 = a; r0 < b; r0 += kInFlight) {
         vec gv[kInFlight];
         float sv[kInFlight];
@@ -306,11 +337,15 @@ __device__ __forceinline__ void ordered_sum(double (&acc)[VEC], const unsigned *
     }
 }
 
-// One block per bucket.  The tiles' runs of the bucket are laid end to end in LDS (that is group order), put
+// The tiles' runs of a bucket are laid end to end in LDS (that is group order), put
 // in code order (stable), and every codeword's groups are summed by a team of LANES lanes, VEC elements
 // each, in ascending group order.  A bucket that does not fit is worked through in chunks, the
 // sums going on in device memory (`carry`, written and read by this block alone).  A codeword with more than kLong
 // groups in a chunk is cut into pieces that the teams share and that are added in piece order.
+// An overfull bucket's chunks are summed by blocks of their own, each of which leaves its sums and the
+// groups in code order in device memory.  The block that is done last adds the chunks' sums up, in order, for codewords
+// with more than kLong groups altogether, and sums the others from their groups: one after the other, as where
+// the bucket is one block's work.
 constexpr int kSumBlock = 512;
 constexpr int kSumWaves = kSumBlock / 64;
 constexpr int kBucketCodes = 1 << (16 - kBucketBits);   // codes of a bucket at most
@@ -320,9 +355,32 @@ constexpr int kSumPer = 16;
 constexpr int kChunk = kSumBlock * kSumPer;
 constexpr int kWindow = kSumBlock;                // tiles looked at together
 constexpr int kPiece = 32;
-static_assert(kWindow <= 1024 && kBucketCodes <= 256 && kBucketCodes <= kSumBlock, "an entry in LDS: 8 + 10 + 13 bits");
+constexpr int kRead = 8;                          // groups of a thread that are read together
+constexpr int kTilesRel = 4096;                   // tiles that a chunk may span
+static_assert(kBucketCodes <= 128 && kTilesRel * kTile <= 1 << 25 && kWindow <= kTilesRel, "an entry in LDS: 7 + 12 + 13 bits");
+static_assert(kBuckets == kSumBlock && kBuckets == 64 * 8 && (kSumWaves + 1) * kBuckets < kChunk, "totals of the buckets");
+static_assert(kSumBlock % kBucketCodes == 0 && kChunk / kLong <= kBucketCodes, "see the ends of k_pg_buckets");
 
-template <int LANES, int VEC>
+// inclusive, over the block; a barrier before the next call
+__device__ __forceinline__ unsigned block_scan(unsigned v, unsigned *s_scan)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const unsigned o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) s_scan[wave] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kSumWaves; ++w) incl += w < wave ? s_scan[w] : 0u;
+    return incl;
+}
+
+// The first blocks have a bucket each.  SPLIT: `spare` more for each codebook have a chunk each of the overfull buckets,
+// and return at once where no tile has a run long enough for such a bucket.
+template <int LANES, int VEC, bool SPLIT>
 __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, const float *__restrict__ G,
                                                              const float *__restrict__ scales, double inv_gpr, int g,
                                                              double *carry, float *__restrict__ out)
@@ -340,79 +398,178 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
     auto &s_pre = s_mem.order.pre;
     auto &s_lo = s_mem.order.lo;
     auto &s_part = s_mem.part;
-    __shared__ unsigned s_start[kBucketCodes + 1], s_item[kBucketCodes + 1], s_w4[kBucketCodes / 64], s_scan[kSumWaves];
+    __shared__ unsigned s_start[kBucketCodes + 1], s_item[kBucketCodes + 1], s_w4[kBucketCodes / 64], s_scan[kSumWaves], s_fit[kSumWaves], s_pieces;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nb = 1 << b.high, nl = 1 << b.low;
-    const int mi = (int)blockIdx.x / nb, bucket = (int)blockIdx.x - mi * nb;
-    const uint32_t *entries = b.entries + (int64_t)mi * b.N;
-    const uint16_t *first = b.first + (int64_t)mi * b.ntiles * (nb + 1) + bucket;
     const int team = threadIdx.x / LANES, i = threadIdx.x % LANES;
-    const int64_t row0 = ((int64_t)(b.m0 + mi) << (b.low + b.high)) + (int64_t)bucket * nl;   // row of `out`
-    carry += ((int64_t)mi << (b.low + b.high)) * g + (int64_t)bucket * nl * g;
-    out += row0 * g;
+    const bool main = !SPLIT || (int)blockIdx.x < b.mains;
+    const int mi = main ? (int)blockIdx.x / nb : ((int)blockIdx.x - b.mains) / b.spare;
+    int bucket = main ? (int)blockIdx.x - mi * nb : 0;
+    int slot = 0, seg = 0, segs = 0;                // chunk `seg` of `segs` of an overfull bucket
+    unsigned before = 0, total = 0;                 // groups of the bucket before this block's, and all of them
+    const uint16_t *first = b.first + (int64_t)mi * b.ntiles * b.stride;
+    if (!main) {
+        slot = (int)blockIdx.x - b.mains - mi * b.spare;
+        int uneven = 0;
+        for (int t = threadIdx.x; t < b.ntiles; t += kSumBlock) uneven |= (int)b.uneven[mi * b.ntiles + t];
+        if (!__syncthreads_or(uneven)) return;
+        // Every bucket's groups; the chunk that this block's number stands for.  A wave adds up an eighth of the
+        // tiles, a lane eight buckets: the sum of where a bucket starts, of which neighbours' difference is the
+        // groups.  (Buckets of more than one code are kBuckets.)
+        {
+            typedef unsigned short us8 __attribute__((ext_vector_type(8)));
+            unsigned sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+            const us8 *row = reinterpret_cast<const us8 *>(first) + lane;
+#pragma unroll 8
+            for (int t = wave; t < b.ntiles; t += kSumWaves) {
+                const us8 v = row[(int64_t)t * (b.stride / 8)];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) sum[q] += v[q];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s_ent[wave * kBuckets + lane * 8 + q] = sum[q];
+            __syncthreads();
+            unsigned at = 0;
+#pragma unroll
+            for (int w = 0; w < kSumWaves; ++w) at += s_ent[w * kBuckets + threadIdx.x];
+            s_ent[kSumWaves * kBuckets + threadIdx.x] = at;
+            if (threadIdx.x == 0) s_ent[kSumWaves * kBuckets + kBuckets] = (unsigned)b.N;
+            __syncthreads();
+            total = s_ent[kSumWaves * kBuckets + threadIdx.x + 1] - at;
+        }
+        const unsigned chunks = total > b.overfull ? (total + kChunk - 1) / kChunk : 0u;
+        const unsigned upto = block_scan(chunks, s_scan);
+        const bool mine = (unsigned)slot < upto && (unsigned)slot >= upto - chunks;
+        if (mine) {
+            s_item[0] = threadIdx.x;
+            s_item[1] = (unsigned)slot - (upto - chunks);
+            s_item[2] = total;
+        }
+        if (!__syncthreads_or(mine)) return;
+        bucket = __builtin_amdgcn_readfirstlane((int)s_item[0]);
+        seg = __builtin_amdgcn_readfirstlane((int)s_item[1]);
+        total = (unsigned)__builtin_amdgcn_readfirstlane((int)s_item[2]);
+        segs = (int)((total + kChunk - 1) / kChunk);
+        before = (unsigned)seg * kChunk;
+        carry = b.part + ((int64_t)mi * b.spare + slot) * nl * g;
+    } else {
+        carry += ((int64_t)mi << (b.low + b.high)) * g + (int64_t)bucket * nl * g;
+    }
+    const uint32_t *entries = b.entries + (int64_t)mi * b.N;
+    first += bucket;
+    out += ((int64_t)(b.m0 + mi) << (b.low + b.high)) * g;
+    if (SPLIT && main && b.ntiles > kWindow) {    // (else the first window has all of it)
+        for (int t = threadIdx.x; t < b.ntiles; t += kSumBlock)
+            total += (unsigned)first[(int64_t)t * b.stride + 1] - first[(int64_t)t * b.stride];
+        block_scan(total, s_scan);
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < kSumWaves; ++w) total += s_scan[w];
+        if (total > b.overfull) return;
+        __syncthreads();
+    }
     bool whole = true;                              // the first chunk: sums start at zero
-    unsigned skip = 0;                              // groups of tile w0's run that an earlier chunk took
-    for (int w0 = 0; w0 < b.ntiles;) {
-        // where the runs of the next tiles go, and how many of them fit
+    int w0 = 0;                                     // the first tile that is not done,
+    unsigned skip = 0;                              // and its groups that an earlier chunk took
+    // Where the runs of the tiles from w0 on go, and how many of them make `room` groups: n groups in `runs` runs,
+    // the last of them perhaps in part (where the window ends first: nothing of the next).  Tiles w .. w + runs;
+    // w0 and skip are moved past what was found.
+    int runs, n, w;
+    auto window = [&](int room) {
         const int t = w0 + (int)threadIdx.x;
         unsigned lo = 0, len = 0;
         if (t < b.ntiles) {
-            lo = first[(int64_t)t * (nb + 1)];
-            len = first[(int64_t)t * (nb + 1) + 1] - lo;
+            lo = first[(int64_t)t * b.stride];
+            len = first[(int64_t)t * b.stride + 1] - lo;
             if (threadIdx.x == 0) {
                 lo += skip;
                 len -= skip;
             }
         }
-        unsigned incl = len;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const unsigned o = __shfl_up(incl, off);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) s_scan[wave] = incl;
-        for (int w = threadIdx.x; w < kSumWaves * kBucketCodes; w += kSumBlock) (&wcnt[0][0])[w] = 0u;
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < kSumWaves; ++w) incl += w < wave ? s_scan[w] : 0u;
+        const unsigned incl = block_scan(len, s_scan);
         s_pre[threadIdx.x] = incl - len;
         s_lo[threadIdx.x] = (unsigned short)lo;
         if (threadIdx.x == kWindow - 1) s_pre[kWindow] = incl;
-        const int fit = __syncthreads_count(t < b.ntiles && incl <= (unsigned)kChunk);
-        // the runs that fit, and the beginning of the next one (where the window ends first: nothing of it)
-        const bool cut = fit < kWindow && w0 + fit < b.ntiles;
-        const int runs = cut ? fit + 1 : fit;
-        const int n = cut ? kChunk : (int)s_pre[fit];
-        const bool last = w0 + fit >= b.ntiles;
-        const unsigned taken = cut ? (fit == 0 ? skip : 0u) + (unsigned)(n - (int)s_pre[fit]) : 0u;   // (s_pre gives way to sums below)
-        auto put = [&](int at, int r, unsigned e) { s_ent[at] = (e >> 16) << 23 | (unsigned)r << kTileBits | (e & (kTile - 1)); };
-        if (n > runs * 256) {                       // long runs (a popular codeword): the block takes one after the other
-            for (int r = 0; r < runs; ++r) {
-                const int p = (int)s_pre[r], l = min((int)s_pre[r + 1], n) - p;
-                const uint32_t *run = entries + (unsigned)(w0 + r) * kTile + s_lo[r];
-                for (int q = threadIdx.x; q < l; q += kSumBlock) put(p + q, r, run[q]);
-            }
-        } else {                                    // a wave a run, eight of them in flight
-            constexpr int kRuns = 8;
-            for (int r0 = wave; r0 < runs; r0 += kSumWaves * kRuns) {
-                unsigned v[kRuns];
-#pragma unroll
-                for (int u = 0; u < kRuns; ++u) {
-                    const int r = min(r0 + u * kSumWaves, runs - 1);
-                    const int l = min((int)s_pre[r + 1], n) - (int)s_pre[r];
-                    v[u] = entries[(unsigned)(w0 + r) * kTile + s_lo[r] + (lane < l ? lane : 0)];
-                }
-#pragma unroll
-                for (int u = 0; u < kRuns; ++u) {
-                    const int r = r0 + u * kSumWaves;
-                    if (r >= runs) break;
-                    const int p = (int)s_pre[r], l = min((int)s_pre[r + 1], n) - p;
-                    if (lane < l) put(p + lane, r, v[u]);
-                    for (int q = 64 + lane; q < l; q += 64) put(p + q, r, entries[(unsigned)(w0 + r) * kTile + s_lo[r] + q]);
-                }
-            }
-        }
+        const unsigned long long in = __ballot(t < b.ntiles && incl <= (unsigned)room);
+        if (lane == 0) s_fit[wave] = (unsigned)__popcll(in);
         __syncthreads();
+        int fit = 0;
+#pragma unroll
+        for (int v = 0; v < kSumWaves; ++v) fit += (int)s_fit[v];
+        const bool cut = fit < kWindow && w0 + fit < b.ntiles;
+        const int whole_runs = (int)s_pre[fit];
+        runs = cut ? fit + 1 : fit;
+        n = cut ? room : whole_runs;
+        skip = cut ? (fit == 0 ? skip : 0u) + (unsigned)(n - whole_runs) : 0u;
+        w = w0;
+        w0 += fit;
+    };
+    while (SPLIT && before > 0) {                            // groups of other blocks
+        window((int)before);
+        before -= (unsigned)n;
+        __syncthreads();
+    }
+    auto row = [&](int c) { return out + (int64_t)((((unsigned)bucket << b.low | (unsigned)c) * b.inv) & b.mask) * g + i * VEC; };
+    while (w0 < b.ntiles) {
+        const int most = SPLIT && segs && seg == segs - 1 ? (int)(total - (unsigned)seg * kChunk) : kChunk;
+        const int from = w0;
+        int have = 0;
+        for (int q = threadIdx.x; q < kSumWaves * kBucketCodes; q += kSumBlock) (&wcnt[0][0])[q] = 0u;
+        if (threadIdx.x == 0) s_pieces = 0u;
+        for (;;) {
+            const bool fresh = w0 == 0 && skip == 0u;
+            window(most - have);
+            if (SPLIT && main && b.ntiles <= kWindow && fresh && s_pre[kWindow] > b.overfull) return;
+            // in LDS: code within the bucket, tile counted from `from`, place in the tile
+            auto put = [&](int at, int r, unsigned e) {
+                s_ent[have + at] = (e >> 16) << 25 | (unsigned)(w - from + r) << kTileBits | (e & (kTile - 1));
+            };
+            if (n > runs * 64) {                    // long runs: a thread takes kRead groups at once, wherever they lie
+#pragma unroll 1
+                for (int q0 = (int)threadIdx.x; q0 - (int)threadIdx.x < n; q0 += kSumBlock * kRead) {
+                    unsigned v[kRead];
+                    int r[kRead];
+#pragma unroll
+                    for (int j = 0; j < kRead; ++j) r[j] = 0;
+                    for (int step = 1 << (31 - __clz(runs)); step > 0; step >>= 1) {   // the last run that starts at or before it
+#pragma unroll
+                        for (int j = 0; j < kRead; ++j)
+                            if (r[j] + step < runs && (int)s_pre[r[j] + step] <= min(q0 + j * kSumBlock, n - 1)) r[j] += step;
+                    }
+#pragma unroll
+                    for (int j = 0; j < kRead; ++j)
+                        v[j] = entries[(unsigned)(w + r[j]) * kTile + s_lo[r[j]] +
+                                       (unsigned)(min(q0 + j * kSumBlock, n - 1) - (int)s_pre[r[j]])];
+#pragma unroll
+                    for (int j = 0; j < kRead; ++j)
+                        if (q0 + j * kSumBlock < n) put(q0 + j * kSumBlock, r[j], v[j]);
+                }
+            } else {                                // a wave a run, eight of them in flight
+                constexpr int kRuns = 8;
+                for (int r0 = wave; r0 < runs; r0 += kSumWaves * kRuns) {
+                    unsigned v[kRuns];
+#pragma unroll
+                    for (int u = 0; u < kRuns; ++u) {
+                        const int r = min(r0 + u * kSumWaves, runs - 1);
+                        const int l = min((int)s_pre[r + 1], n) - (int)s_pre[r];
+                        v[u] = entries[(unsigned)(w + r) * kTile + s_lo[r] + (lane < l ? lane : 0)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < kRuns; ++u) {
+                        const int r = r0 + u * kSumWaves;
+                        if (r >= runs) break;
+                        const int p = (int)s_pre[r], l = min((int)s_pre[r + 1], n) - p;
+                        if (lane < l) put(p + lane, r, v[u]);
+                        for (int q = 64 + lane; q < l; q += 64) put(p + q, r, entries[(unsigned)(w + r) * kTile + s_lo[r] + q]);
+                    }
+                }
+            }
+            have += n;
+            __syncthreads();
+            if (have >= most || w0 >= b.ntiles || w0 - from > kTilesRel - kWindow) break;
+        }
+        n = have;
+        const bool last = !(SPLIT && segs) && w0 >= b.ntiles;
         // code order
         const int per = (n + kSumBlock - 1) / kSumBlock;
         {
@@ -421,7 +578,7 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
             for (int j = 0; j < kSumPer; ++j) {
                 const int q = (wave * per + j) * 64 + lane;
                 e[j] = j < per && q < n ? s_ent[q] : 0u;
-                d[j] = e[j] >> 23;
+                d[j] = e[j] >> 25;
             }
             digit_ranks<kSumPer, kBucketCodes>(d, rank, per, n, b.low, wcnt);
             digit_starts<kSumWaves, kBucketCodes>(wcnt, s_start, s_w4);
@@ -430,13 +587,15 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
                 const int q = (wave * per + j) * 64 + lane;
                 if (j < per && q < n)
                     s_ent[s_start[d[j]] + wcnt[wave][d[j]] + rank[j]] =
-                        (unsigned)(w0 + (int)((e[j] >> kTileBits) & 1023u)) << kTileBits | (e[j] & (kTile - 1));
+                        (unsigned)(from + (int)((e[j] >> kTileBits) & (kTilesRel - 1u))) << kTileBits | (e[j] & (kTile - 1));
             }
         }
         // work items: a codeword, or a piece of one
         unsigned clen = 0;
         if ((int)threadIdx.x < nl) clen = s_start[threadIdx.x + 1] - s_start[threadIdx.x];
-        const bool pieces = __syncthreads_or(clen > (unsigned)kLong);
+        if (clen > (unsigned)kLong) s_pieces = 1u;
+        __syncthreads();
+        const bool pieces = s_pieces != 0u;
         const int piece = max(kPiece, (n + kTeams - 1) / kTeams);
         int items = nl;
         if (pieces) {
@@ -480,7 +639,7 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
             auto finish = [&]() {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
-                    if (last) out[(int64_t)c * g + i * VEC + v] = (float)acc[v];
+                    if (last) row(c)[v] = (float)acc[v];
                     else carry[(int64_t)c * g + i * VEC + v] = acc[v];
                 }
             };
@@ -495,7 +654,7 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
                     from += p * piece;
                     to = min(to, from + piece);
                 }
-                ordered_sum<VEC>(acc, s_ent, from, to, G, scales, inv_gpr, g, i);
+                ordered_sum<VEC, VEC == 4 ? 8 : 16>(acc, s_ent, from, to, G, scales, inv_gpr, g, i);
                 if (np == 1) finish();
             }
             if (pieces) {
@@ -531,10 +690,96 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
                 __syncthreads();
             }
         }
-        skip = taken;
-        w0 += fit;
+        if (SPLIT && segs) break;
         whole = false;
         __syncthreads();                            // ids, counts and sums of this chunk are done with
+    }
+    if (!SPLIT || !segs) return;
+
+    // ---- a chunk of an overfull bucket is done: the block that is the last adds up
+    const int64_t at = (int64_t)mi * b.spare + slot;
+    for (int q = threadIdx.x; q < n; q += kSumBlock) b.ids[at * kChunk + q] = s_ent[q];
+    if ((int)threadIdx.x <= nl) b.starts[at * (nl + 1) + threadIdx.x] = (uint16_t)s_start[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x == 0) {                         // one wave's fence writes the die's cache back, for all of the block
+        __threadfence();
+        s_item[0] = atomicAdd(b.arrived + (mi << b.high) + bucket, 1u) + 1u;
+        __threadfence();
+    }
+    __syncthreads();
+    if (s_item[0] != (unsigned)segs) return;
+    __syncthreads();
+    const uint16_t *starts = b.starts + (at - seg) * (nl + 1);
+    const double *part = b.part + (at - seg) * nl * g;
+    const uint32_t *ids = b.ids + (at - seg) * kChunk;
+    constexpr int kShare = kSumBlock / kBucketCodes;
+    {                                               // a codeword's groups, by kShare threads
+        const int c = (int)threadIdx.x / kShare, p = (int)threadIdx.x % kShare;
+        unsigned have = 0;
+        if (c < nl)
+#pragma unroll 4
+            for (int j = p; j < segs; j += kShare)
+                have += (unsigned)starts[(int64_t)j * (nl + 1) + c + 1] - starts[(int64_t)j * (nl + 1) + c];
+#pragma unroll
+        for (int off = 1; off < kShare; off <<= 1) have += __shfl_xor(have, off);
+        if (p == 0) s_item[c] = have;
+    }
+    __syncthreads();
+    constexpr int kTogether = 8;
+#pragma unroll 1
+    for (int c = team; c < nl; c += kTeams)         // more than kLong groups: the chunks' sums in order
+        if (s_item[c] > (unsigned)kLong && i * VEC < g) {
+            double acc[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+#pragma unroll 1
+            for (int j0 = 0; j0 < segs; j0 += kTogether) {
+                double x[kTogether][VEC];
+#pragma unroll
+                for (int u = 0; u < kTogether; ++u)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) x[u][v] = part[((int64_t)min(j0 + u, segs - 1) * nl + c) * g + i * VEC + v];
+#pragma unroll
+                for (int u = 0; u < kTogether; ++u)
+                    if (j0 + u < segs)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) acc[v] = acc[v] + x[u][v];
+            }
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) row(c)[v] = (float)acc[v];
+        }
+    // up to kLong groups: one after the other, from the chunks' lists
+    constexpr int kCodes = kChunk / kLong;          // codewords whose groups fit the list
+    constexpr int kLister = kSumBlock / kCodes;     // threads of a codeword, each with some of the chunks
+#pragma unroll 1
+    for (int c0 = 0; c0 < nl; c0 += kCodes) {
+        const int c = c0 + (int)threadIdx.x / kLister, p = (int)threadIdx.x % kLister;
+        const int j0 = (int)((int64_t)segs * p / kLister), j1 = (int)((int64_t)segs * (p + 1) / kLister);
+        unsigned have = 0;
+        if (c < nl && s_item[c] <= (unsigned)kLong)
+#pragma unroll 4
+            for (int j = j0; j < j1; ++j)
+                have += (unsigned)starts[(int64_t)j * (nl + 1) + c + 1] - starts[(int64_t)j * (nl + 1) + c];
+        __syncthreads();                            // the lists of the codewords before are done with
+        unsigned to = block_scan(have, s_scan) - have;
+        if (p == 0) s_start[threadIdx.x / kLister] = to;
+        if (threadIdx.x == kSumBlock - 1) s_start[kCodes] = to + have;
+        if (have)
+            for (int j = j0; j < j1; ++j) {
+                const unsigned f = starts[(int64_t)j * (nl + 1) + c], l = starts[(int64_t)j * (nl + 1) + c + 1];
+                for (unsigned q = f; q < l; ++q) s_ent[to++] = ids[(int64_t)j * kChunk + q];
+            }
+        __syncthreads();
+#pragma unroll 1
+        for (int q = team; q < kCodes && c0 + q < nl; q += kTeams)
+            if (s_item[c0 + q] <= (unsigned)kLong && i * VEC < g) {
+                double acc[VEC];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+                ordered_sum<VEC, kTogether>(acc, s_ent, (int)s_start[q], (int)s_start[q + 1], G, scales, inv_gpr, g, i);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) row(c0 + q)[v] = (float)acc[v];
+            }
     }
 }
 
@@ -967,16 +1212,33 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
         return PV_OK;
     }
 
-    // Two codebooks at a time: 8 bytes a group of scratch whatever M.
+    // Two codebooks at a time: 8 bytes a group of scratch whatever M, and up to 16 for the chunks of overfull buckets.
     const int low = l->nbits > kBucketBits ? l->nbits - kBucketBits : 0, high = l->nbits - low;
-    const int nb = 1 << high;
+    const int nb = 1 << high, stride = (nb + 8) & ~7;
+    // the golden section of 2^B, odd: neighbouring codes, and codes a power of two apart, fall far from one another
+    const unsigned mul = low ? (0x9E3779B9u >> (32 - l->nbits)) | 1u : 1u;
+    unsigned inv = mul;
+    for (int i = 0; i < 4; ++i) inv *= 2u - mul * inv;      // Newton: 3 bits are right to begin with, then 6, 12, 24, 48
     const int64_t ntiles = (N + kTile - 1) / kTile;
     const int at_once = M < 2 ? M : 2;
     // sums that go on from one chunk, or one round of pieces, to the next (a codeword may hold every group)
     const bool chunks = N > kLong;
-    const size_t o_first = align_up((size_t)at_once * N * 4);
-    const size_t o_carry = o_first + align_up((size_t)at_once * ntiles * (nb + 1) * 2);
-    const size_t total = o_carry + (chunks ? (size_t)at_once * csize * g * 8 : 0);
+    // A bucket of more than `overfull` groups is worked through chunk by chunk, by a block each: at least two and a
+    // half chunks (128 codewords of 16384 groups, a bucket each: 175 us in two or three chunks one after the other, 210
+    // side by side and added up), and three times the average, so that codes drawn evenly have no such bucket.
+    const int64_t overfull = 5 * kChunk / 2 > 3 * (N >> high) ? 5 * kChunk / 2 : 3 * (N >> high);
+    const int64_t spare = low && N > overfull && ntiles <= kTilesRel ? N / kChunk + N / overfull : 0;
+    size_t total = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = total;
+        total += align_up(bytes);
+        return at;
+    };
+    const size_t o_entries = take((size_t)at_once * N * 4), o_first = take((size_t)at_once * ntiles * stride * 2);
+    const size_t o_carry = take(chunks ? (size_t)at_once * csize * g * 8 : 0);
+    const size_t o_part = take((size_t)(at_once * spare) * (csize / nb) * g * 8);
+    const size_t o_ids = take((size_t)(at_once * spare) * kChunk * 4), o_starts = take((size_t)(at_once * spare) * (csize / nb + 1) * 2);
+    const size_t o_uneven = take((size_t)(at_once * ntiles) * 4), o_arrived = take((size_t)at_once * nb * 4);
     pv_status st = pv_ensure(ctx, ctx->pstep, total);
     if (st != PV_OK) return st;
     char *base = static_cast<char *>(ctx->pstep.ptr);
@@ -986,16 +1248,26 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
     pv_timed t(ctx, PV_K_PSTEP);
     for (int m0 = 0; m0 < M; m0 += at_once) {
         const int now = M - m0 < at_once ? M - m0 : at_once;
-        const bucket_args b{codes, N, M, m0, mask, low, high, (int)ntiles, reinterpret_cast<uint32_t *>(base),
-                            reinterpret_cast<uint16_t *>(base + o_first)};
+        const bucket_args b{codes, N, M, m0, mask, mul, inv, low, high, (int)ntiles,
+                            reinterpret_cast<uint32_t *>(base + o_entries), reinterpret_cast<uint16_t *>(base + o_first), stride,
+                            (unsigned)overfull, (unsigned)(overfull / ntiles), nb * now, (int)spare,
+                            reinterpret_cast<unsigned *>(base + o_uneven), reinterpret_cast<unsigned *>(base + o_arrived),
+                            reinterpret_cast<double *>(base + o_part), reinterpret_cast<uint32_t *>(base + o_ids),
+                            reinterpret_cast<uint16_t *>(base + o_starts)};
         const int sort_blocks = (int)(ntiles * now), rows_a_block = kTileBlock / kBlock;
         const int64_t row_blocks = m0 == 0 && grad_scales ? (l->out_features + rows_a_block - 1) / rows_a_block : 0;
         const dim3 grid((unsigned)(sort_blocks + row_blocks));
         if (g % 4 == 0) hipLaunchKernelGGL(k_pg_tiles<true>, grid, dim3(kTileBlock), 0, sm, b, sc, sort_blocks);
         else hipLaunchKernelGGL(k_pg_tiles<false>, grid, dim3(kTileBlock), 0, sm, b, sc, sort_blocks);
-#define PV_SUMS(LANES_, VEC_)                                                                          \
-    hipLaunchKernelGGL((k_pg_buckets<LANES_, VEC_>), dim3((unsigned)(nb * now)), dim3(kSumBlock), 0, sm, b, G, \
-                       scales, inv_gpr, g, carry, grad_codebooks)
+#define PV_SUMS(LANES_, VEC_)                                                                                \
+    do {                                                                                                     \
+        if (spare)                                                                                           \
+            hipLaunchKernelGGL((k_pg_buckets<LANES_, VEC_, true>), dim3((unsigned)((nb + spare) * now)),     \
+                               dim3(kSumBlock), 0, sm, b, G, scales, inv_gpr, g, carry, grad_codebooks);     \
+        else                                                                                                 \
+            hipLaunchKernelGGL((k_pg_buckets<LANES_, VEC_, false>), dim3((unsigned)(nb * now)),              \
+                               dim3(kSumBlock), 0, sm, b, G, scales, inv_gpr, g, carry, grad_codebooks);     \
+    } while (0)
         // lanes that share a codeword: vectors as wide as the group's rows allow, four lanes at least
         if (g == 8) PV_SUMS(4, 2);
         else if (g % 4 == 0 && g <= 16) PV_SUMS(4, 4);

@@ -12,6 +12,7 @@ import torch
 import oracle
 import workloads
 from gpu_util import DEV, GpuRun, dev_f32, dev_u16
+from paper_2405_14852_amd import Layout, PVContext
 
 pytestmark = pytest.mark.gpu
 
@@ -147,6 +148,76 @@ def test_codebook_grads_buckets(g, M, B, shape, kind):
     again, gs2, _, _ = run_case(wl)
     assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
     assert np.array_equal(gs.view(np.uint32), gs2.view(np.uint32))
+
+
+def alike_bits(B, n, rng):
+    """n codes that the P step sums in one bucket (512 of them, by the high bits of code * golden section)."""
+    mul = (0x9E3779B9 >> (32 - B)) | 1
+    codes = np.arange(1 << B)
+    buckets = (codes * mul % (1 << B)) >> (B - 9)
+    return rng.permutation(codes[buckets == 77])[:n]
+
+
+@pytest.mark.parametrize("g,M,B,shape", [(8, 1, 16, (256, 2056)),     # 65 792 groups: nine tiles, the last ragged
+                                         (16, 3, 10, (520, 4096)),    # three codebooks: two launches
+                                         (4, 1, 13, (130, 4000)), (33, 2, 12, (700, 1320)), (64, 1, 16, (400, 4096)),
+                                         (1, 1, 11, (1100, 4096))])   # 550 tiles: two windows of them
+@pytest.mark.parametrize("kind", ["neighbours", "meet", "front", "tail"])
+def test_codebook_grads_overfull_buckets(g, M, B, shape, kind):
+    """Codewords that hold most groups and share buckets, whose chunks several blocks sum: 64 neighbours hold all;
+    a few of one bucket do, beside rarely used ones of it; one that only the first rows use (a window of
+    tiles and then nothing) or only the last.  Sums of up to 128 groups have the oracle's bits."""
+    wl = workloads.make(shape[0], shape[1], g, M, B, seed=95, sigma_g=1e-2)
+    rng = np.random.default_rng(95)
+    draw = rng.random(wl.codes.shape)
+    if kind == "neighbours":
+        wl.codes[:] = (1 << B) // 3 + wl.codes % 64
+    elif kind == "meet":
+        few = alike_bits(B, 128, rng)
+        wl.codes[draw < 0.9] = rng.choice(few[:3], size=int((draw < 0.9).sum()))
+        wl.codes[draw < 0.001] = rng.choice(few, size=int((draw < 0.001).sum()))
+    else:
+        rows = slice(None, shape[0] // 2) if kind == "front" else slice(shape[0] // 2, None)
+        wl.codes[rows][draw[rows] < 0.95] = (1 << B) - 2
+    gc, gs, gc_ref, gs_ref = run_case(wl)
+    q = oracle.dequantize(wl.codes, wl.codebooks, np.ones_like(wl.scales))
+    assert close_sum(gs, gs_ref, np.abs(wl.G * q).sum(axis=1))
+    size = np.abs(wl.G).reshape(-1, g).astype(np.float64) * np.repeat(np.abs(wl.scales), wl.layout.groups_per_row)[:, None]
+    for m in range(M):
+        codes = wl.codes[..., m].ravel()
+        thin = np.bincount(codes, minlength=1 << B) <= 128
+        assert np.array_equal(gc[m, thin].view(np.uint32), gc_ref[m, thin].view(np.uint32))
+        mag = np.stack([np.bincount(codes, size[:, i], minlength=1 << B) for i in range(g)], axis=1)
+        assert close_sum(gc[m], gc_ref[m], mag)
+    again, _, _, _ = run_case(wl)
+    assert np.array_equal(gc.view(np.uint32), again.view(np.uint32))
+
+
+def test_codebook_grads_time_does_not_follow_the_use_of_codewords():
+    """64 neighbouring codewords that hold all groups: a few times an even use at most (one block for a range of
+    codes took 68 times as long)."""
+    rows, cols, g, B = 4096, 4096, 8, 16
+    lay, ctx = Layout(rows, cols, g, 1, B), PVContext(0)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(95)
+    G = torch.randn(rows, cols, generator=gen, device=DEV)
+    even = torch.randint(-(1 << 15), 1 << 15, (rows, cols // g, 1), generator=gen, device=DEV, dtype=torch.int16)
+    cb, sc = torch.randn(1, 1 << B, g, generator=gen, device=DEV), torch.ones(rows, device=DEV)
+    gc, gs = torch.empty_like(cb), torch.empty_like(sc)
+
+    def microseconds(codes):
+        best = float("inf")
+        for _ in range(5):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            ctx.pv_codebook_grads(lay, G, codes.view(torch.uint16), cb, sc, gc, gs)
+            end.record()
+            end.synchronize()
+            best = min(best, start.elapsed_time(end) * 1e3)
+        return best
+
+    assert microseconds((even & 63) + 12345) < 6 * microseconds(even)
+    ctx.close()
 
 
 @pytest.mark.parametrize("g,M,B,shape", [(8, 1, 16, (256, 2048)), (16, 1, 12, (128, 2048)), (8, 2, 8, (512, 4096)),
