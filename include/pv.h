@@ -36,8 +36,10 @@
  *     a step (dequantize, targets, selection, re-encode and their variants) only launch
  *     kernels on the context's stream, so a caller may capture them into a HIP graph and
  *     replay it; the inputs may change in place between replays (a codebook rewritten by
- *     the P step).  pv_reencode_stats, pv_timing_read and pv_destroy synchronise and do
- *     not belong into a capture.
+ *     the P step).  Replays use the context's scratch, as its calls do: order them like calls
+ *     of the context, not beside its other calls or replays on another stream.  (pv_reencode_scalar
+ *     and the dequantisations use none of it.)  pv_reencode_stats, pv_timing_read and pv_destroy
+ *     synchronise and do not belong into a capture.
  *   - Errors are reported by the return code only; on an error nothing has been
  *     enqueued or written.  pv_last_error gives a short text for the last error
  *     of a context.

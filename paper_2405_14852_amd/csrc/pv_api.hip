@@ -47,15 +47,37 @@ pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head)
     return PV_OK;
 }
 
-pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, unsigned long long **counts)
+pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, pv_counts *counts)
 {
-    constexpr size_t bytes = 8 * sizeof(int64_t) + kCountBytes;
+    constexpr size_t bytes = 8 * sizeof(int64_t) + 3 * kCountBytes;
     const pv_status st = pv_ensure(ctx, ctx->stats, bytes, bytes);
     if (st != PV_OK) return st;
     auto p = static_cast<unsigned long long *>(ctx->stats.ptr);
     if (stats) *stats = p;
-    if (counts) *counts = p + 8;
+    if (!counts) return PV_OK;
+    if (pv_capturing(ctx)) {
+        counts->mine = p + 8 + 2 * kCountWords;
+        counts->next = nullptr;
+        return pv_launch_fill_i64(ctx, reinterpret_cast<int64_t *>(counts->mine), kCountWords, 0);
+    }
+    counts->mine = p + 8 + ctx->count_set * kCountWords;
+    counts->next = p + 8 + (ctx->count_set ^ 1) * kCountWords;
     return PV_OK;
+}
+
+void pv_counters_cleared(pv_ctx *ctx, const pv_counts &counts)
+{
+    if (counts.next) ctx->count_set ^= 1;
+}
+
+bool pv_capturing(const pv_ctx *ctx)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &status) != hipSuccess) {
+        (void)hipGetLastError();      // the launches will say
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
 }
 
 static hipEvent_t take_event(pv_ctx *c)

@@ -34,6 +34,7 @@
 // every best key at or above that cut is evaluated as well, and a second key at or above it
 // sends the group to the list.  The winner among the evaluated pairs (objective, then pair)
 // replaces the current pair if it is strictly better, as everywhere else.
+#include "pv_counts.h"
 #include "pv_internal.h"
 #include "pv_dpp.h"
 
@@ -208,9 +209,7 @@ struct wave_t {
 __global__ __launch_bounds__(kBlock, 2) void k_beam_2x8_f16(
     const float *__restrict__ T, const float *__restrict__ codebooks,
     const float *__restrict__ scales, const int32_t *__restrict__ group_idx, int64_t k,
-    int beam_width, uint16_t *__restrict__ codes, unsigned long long *__restrict__ num_changed,
-    unsigned long long *__restrict__ stat_fast, int32_t *__restrict__ redo_list,
-    unsigned long long *__restrict__ redo_count, int gpr, int N)
+    int beam_width, uint16_t *__restrict__ codes, pv_counts counts, int32_t *__restrict__ redo_list, int gpr, int N)
 {
     __shared__ tables_t tb;
     __shared__ wave_t ws[kWaves];
@@ -638,7 +637,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_beam_2x8_f16(
             const bool gok = w.ok[gl] != 0;
             const bool head = e == 0 && hw == 0 && w.n[gl] >= 0;   // the lane that speaks for the group
             if (!__any(gok)) {                           // nothing of this tile is with the filter
-                if (head) redo_list[atomicAdd(redo_count, 1ull)] = w.n[gl];
+                if (head) pv_list_redo(counts, redo_list, k, w.n[gl]);
                 continue;
             }
             const bool live = gok && e < keep;
@@ -813,8 +812,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_beam_2x8_f16(
             if (head) {
                 const int n = w.n[gl];
                 if (!gok || open) {
-                    const unsigned long long slot = atomicAdd(redo_count, 1ull);
-                    redo_list[slot] = n;
+                    pv_list_redo(counts, redo_list, k, n);
                 } else {
                     if (gidx != 0x7fffffff && gobj < o_prev) {
                         codes[(int64_t)n * 2] = (uint16_t)(gidx >> 8);
@@ -827,6 +825,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_beam_2x8_f16(
         }
         __builtin_amdgcn_wave_barrier();
     }
+    pv_counts_clear(counts);
     for (int off = 32; off > 0; off >>= 1) {
         changed += __shfl_xor(changed, off);
         fast += __shfl_xor(fast, off);
@@ -842,8 +841,8 @@ __global__ __launch_bounds__(kBlock, 2) void k_beam_2x8_f16(
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (s_changed && num_changed) atomicAdd(num_changed, (unsigned long long)s_changed);
-        if (s_fast && stat_fast) atomicAdd(stat_fast, (unsigned long long)s_fast);
+        if (s_changed) atomicAdd(counts.mine + kCountChanged, (unsigned long long)s_changed);
+        if (s_fast) atomicAdd(counts.mine + kCountFast, (unsigned long long)s_fast);
     }
 }
 
@@ -851,16 +850,14 @@ __global__ __launch_bounds__(kBlock, 2) void k_beam_2x8_f16(
 
 pv_status pv_launch_beam_2x8_f16(pv_ctx *ctx, const float *T, const float *codebooks,
                                  const float *scales, const int32_t *group_idx, int64_t k,
-                                 int32_t beam_width, uint16_t *codes, int64_t *num_changed,
-                                 unsigned long long *stat_fast, int32_t *redo_list,
-                                 unsigned long long *redo_count, int gpr, int N)
+                                 int32_t beam_width, uint16_t *codes, const pv_counts &counts,
+                                 int32_t *redo_list, int gpr, int N)
 {
     int64_t blocks = (k + kBatch * kWaves - 1) / (kBatch * kWaves);
     if (blocks > 768) blocks = 768;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(k_beam_2x8_f16, dim3((unsigned)blocks), dim3(kBlock), 0, ctx->stream, T,
-                       codebooks, scales, group_idx, k, beam_width, codes,
-                       reinterpret_cast<unsigned long long *>(num_changed), stat_fast, redo_list,
-                       redo_count, gpr, N);
+                       codebooks, scales, group_idx, k, beam_width, codes, counts, redo_list, gpr, N);
+    PV_HIP(ctx, hipGetLastError());
     return PV_OK;
 }

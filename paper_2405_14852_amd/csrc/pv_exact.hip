@@ -250,9 +250,10 @@ __global__ __launch_bounds__(kBlock) void k_search_few(const float *__restrict__
                                                        const float *__restrict__ scales,
                                                        const int32_t *__restrict__ list, int k, uint16_t *codes,
                                                        unsigned long long *num_changed, unsigned long long *stats,
-                                                       unsigned long long *counts, int nbits, double inv_gpr, int N,
+                                                       pv_counts counts, int nbits, double inv_gpr, int N,
                                                        int split)
 {
+    pv_counts_clear(counts);
     __shared__ double s_obj[kFewWaves][kFew];
     __shared__ int s_idx[kFewWaves][kFew];
     __shared__ unsigned s_cnt[2];
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_search_few(const float *__restrict__
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long both;                   // (k < 2^20)
-        if (pv_counts_arrive(counts, gridDim.x, (unsigned long long)s_cnt[0] << 20 | s_cnt[1], &both)) {
+        if (pv_counts_arrive(counts.mine, gridDim.x, (unsigned long long)s_cnt[0] << 20 | s_cnt[1], &both)) {
             if (num_changed) *num_changed = both & 0xFFFFFull;
             for (int i = 0; i < 8; ++i) stats[i] = i == 3 ? both >> 20 : 0ull;
         }
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(kBlock) void k_beam_2x8(
     unsigned long long *stats)
 {
     // counts: an earlier kernel of the stream wrote the list; its length and what that kernel counted are
-    // there, and the last block with work publishes all of it and leaves zeros (`stats`: the call's counters)
+    // there, and the last block with work publishes all of it (`stats`: the call's counters)
     unsigned working = 1;
     if (counts) {
         const int64_t c = (int64_t)counts[kCountList];
@@ -682,11 +683,9 @@ __global__ __launch_bounds__(kBlock) void k_beam_2x8(
     auto arrive = [&](unsigned changed) {
         unsigned long long all;
         if (!pv_counts_arrive(counts, working, changed, &all)) return;
-        const unsigned long long early = atomicExch(&counts[kCountChanged], 0ull);
-        const unsigned long long fast = atomicExch(&counts[kCountFast], 0ull);
-        const unsigned long long listed = atomicExch(&counts[kCountList], 0ull);
-        if (num_changed) *num_changed = all + early;
-        for (int i = 0; i < 8; ++i) stats[i] = i == 0 ? fast : i == 1 || i == 4 ? listed : 0ull;
+        if (num_changed) *num_changed = all + counts[kCountChanged];
+        for (int i = 0; i < 8; ++i)
+            stats[i] = i == 0 ? counts[kCountFast] : i == 1 || i == 4 ? counts[kCountList] : 0ull;
     };
     if ((int64_t)blockIdx.x * (kBlock / 64) >= k) {   // before the tables are loaded
         if (counts && blockIdx.x == 0 && threadIdx.x == 0) arrive(0u);
@@ -806,9 +805,7 @@ template <int G>
 __global__ __launch_bounds__(kBeamBlock, 4) void k_beam_2x8_mfma(
     const float *__restrict__ T, const float *__restrict__ codebooks,
     const float *__restrict__ scales, const int32_t *__restrict__ group_idx, int64_t k,
-    int beam_width, uint16_t *__restrict__ codes, unsigned long long *__restrict__ num_changed,
-    unsigned long long *__restrict__ stat_fast, int32_t *__restrict__ redo_list,
-    unsigned long long *__restrict__ redo_count, int gpr, int N)
+    int beam_width, uint16_t *__restrict__ codes, pv_counts counts, int32_t *__restrict__ redo_list, int gpr, int N)
 {
     constexpr int KS = G / 4;        // matrix steps that carry coordinates
     constexpr int KP = G + 4;        // operand row: G coordinates, the squared norm, 3 zeros
@@ -1099,10 +1096,11 @@ __global__ __launch_bounds__(kBeamBlock, 4) void k_beam_2x8_mfma(
             }
         }
         // groups the filter could not decide go to the list of the exact kernel
-        if (valid && !fast_h && hl == 0) redo_list[atomicAdd(redo_count, 1ull)] = n;
+        if (valid && !fast_h && hl == 0) pv_list_redo(counts, redo_list, k, n);
         // the next pair overwrites the per-wave staging: every lane is done reading it
         __builtin_amdgcn_wave_barrier();
     }
+    pv_counts_clear(counts);
     // lanes 0 and 32 hold the counters of their halves; one atomic per block and counter
     __shared__ unsigned s_changed, s_fast;
     if (threadIdx.x == 0) s_changed = s_fast = 0u;
@@ -1113,8 +1111,8 @@ __global__ __launch_bounds__(kBeamBlock, 4) void k_beam_2x8_mfma(
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (s_changed && num_changed) atomicAdd(num_changed, (unsigned long long)s_changed);
-        if (s_fast && stat_fast) atomicAdd(stat_fast, (unsigned long long)s_fast);
+        if (s_changed) atomicAdd(counts.mine + kCountChanged, (unsigned long long)s_changed);
+        if (s_fast) atomicAdd(counts.mine + kCountFast, (unsigned long long)s_fast);
     }
 }
 
@@ -1135,7 +1133,8 @@ pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, 
                                const float *scales, const int32_t *group_idx, int64_t k, uint16_t *codes,
                                int64_t *num_changed)
 {
-    unsigned long long *stats, *counts;
+    unsigned long long *stats;
+    pv_counts counts;
     pv_status st = pv_counters(ctx, &stats, &counts);
     if (st != PV_OK) return st;
     pv_timed t(ctx, PV_K_EXACT_SCAN);
@@ -1152,6 +1151,7 @@ pv_status pv_launch_search_few(pv_ctx *ctx, const pv_layout *l, const float *T, 
         hipLaunchKernelGGL(k_search_few<16>, grid, dim3(kBlock), 0, ctx->stream, T, codebook, scales, group_idx, (int)k,
                            codes, nc, stats, counts, l->nbits, 1.0 / (double)gpr, N, split);
     PV_HIP(ctx, hipGetLastError());
+    pv_counters_cleared(ctx, counts);
     return PV_OK;
 }
 
@@ -1211,30 +1211,30 @@ pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const 
             // matrix-core filter; stats[0] = groups it decided, stats[1] = groups redone exactly,
             // stats[4] = length of the redo list
             pv_status est = pv_ensure(ctx, ctx->fb_list, (size_t)k * sizeof(int32_t) + 16);
-            unsigned long long *st0 = nullptr, *counts = nullptr;
+            unsigned long long *st0 = nullptr;
+            pv_counts counts;
             if (est == PV_OK) est = pv_counters(ctx, &st0, &counts);
             if (est != PV_OK) return est;
             int32_t *redo = reinterpret_cast<int32_t *>(static_cast<char *>(ctx->fb_list.ptr) + 16);
             int64_t pblocks = ((k + 1) / 2 + kBeamBlock / 64 - 1) / (kBeamBlock / 64);
             if (pblocks > 512) pblocks = 512;
             int64_t rblocks = wblocks < 1024 ? wblocks : 1024;
-#define PV_BEAM2(G_)                                                                             \
-    hipLaunchKernelGGL(k_beam_2x8_mfma<G_>, dim3((unsigned)pblocks), dim3(kBeamBlock), 0, ctx->stream, \
-                       T, codebooks, scales, group_idx, k, beam_width, codes, counts + kCountChanged, \
-                       counts + kCountFast, redo, counts + kCountList, gpr, N);                    \
-    hipLaunchKernelGGL(k_beam_2x8<G_>, dim3((unsigned)rblocks), dim3(kBlock), 0, ctx->stream, T,   \
-                       codebooks, scales, redo, k, beam_width, codes, nc, nullptr, gpr, N, counts, st0)
             if (g == 8) {
                 // fp32 / fp16 filter (pv_beam.hip), then the exact kernel on what it leaves
-                pv_launch_beam_2x8_f16(ctx, T, codebooks, scales, group_idx, k, beam_width, codes,
-                                       reinterpret_cast<int64_t *>(counts + kCountChanged), counts + kCountFast, redo,
-                                       counts + kCountList, gpr, N);
+                est = pv_launch_beam_2x8_f16(ctx, T, codebooks, scales, group_idx, k, beam_width, codes, counts, redo,
+                                             gpr, N);
+                if (est != PV_OK) return est;
+                pv_counters_cleared(ctx, counts);
                 hipLaunchKernelGGL(k_beam_2x8<8>, dim3((unsigned)rblocks), dim3(kBlock), 0, ctx->stream,
-                                   T, codebooks, scales, redo, k, beam_width, codes, nc, nullptr, gpr, N, counts, st0);
+                                   T, codebooks, scales, redo, k, beam_width, codes, nc, nullptr, gpr, N, counts.mine, st0);
             } else {
-                PV_BEAM2(16);
+                hipLaunchKernelGGL(k_beam_2x8_mfma<16>, dim3((unsigned)pblocks), dim3(kBeamBlock), 0, ctx->stream, T,
+                                   codebooks, scales, group_idx, k, beam_width, codes, counts, redo, gpr, N);
+                PV_HIP(ctx, hipGetLastError());
+                pv_counters_cleared(ctx, counts);
+                hipLaunchKernelGGL(k_beam_2x8<16>, dim3((unsigned)rblocks), dim3(kBlock), 0, ctx->stream, T,
+                                   codebooks, scales, redo, k, beam_width, codes, nc, nullptr, gpr, N, counts.mine, st0);
             }
-#undef PV_BEAM2
             PV_HIP(ctx, hipGetLastError());
             return PV_OK;
         }

@@ -40,7 +40,8 @@ struct pv_ctx {
     size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
     pv_buffer sample;       // and its sample of many single weights: a histogram, zero between calls
     bool sample_refused = false;          // there was no memory for it: scores are written instead
-    pv_buffer stats;        // i64 [8] counters of the last re-encode | what a call's blocks count (pv_counters)
+    pv_buffer stats;        // i64 [8] counters of the last re-encode | three sets of what a call's blocks count (pv_counts.h)
+    int count_set = 0;      // the one of the first two that is clear
     pv_buffer search;       // the matrix-core filter's: statistics, operands, records, counters (see pv_launch_mfma_search)
     const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel
     pv_buffer fb_list;      // beam path: the groups left to the exact kernel
@@ -61,8 +62,12 @@ pv_status pv_fail(pv_ctx *ctx, pv_status st, const char *fmt, ...);
 // A buffer of at least `bytes`; the first `zero_head` bytes of a new block are cleared on the stream.
 pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head = 0);
 // Both kinds of counters, in one block whatever the route: a smaller k of a shape that was seen before may take
-// another route, and allocates nothing.
-pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, unsigned long long **counts);
+// another route, and allocates nothing.  counts: the words of this call and those that its first kernel clears
+// (see pv_counts.h); pv_counters_cleared once that kernel is launched.
+struct pv_counts;
+pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, pv_counts *counts);
+void pv_counters_cleared(pv_ctx *ctx, const pv_counts &counts);
+bool pv_capturing(const pv_ctx *ctx);
 
 #define PV_HIP(ctx, call)                                                              \
     do {                                                                               \
@@ -165,12 +170,11 @@ pv_status pv_launch_beam(pv_ctx *ctx, const pv_layout *l, const float *T, const 
                          const float *scales, const int32_t *group_idx, int64_t k,
                          int32_t beam_width, uint16_t *codes, int64_t *num_changed);
 // two 8-bit codebooks, g = 8, beam <= 8: fp32 / fp16 matrix-core filter; groups it cannot
-// certify are appended to redo_list (count in *redo_count) for the exact kernel
+// certify are appended to redo_list [k] (their number in the counts) for the exact kernel
 pv_status pv_launch_beam_2x8_f16(pv_ctx *ctx, const float *T, const float *codebooks,
                                  const float *scales, const int32_t *group_idx, int64_t k,
-                                 int32_t beam_width, uint16_t *codes, int64_t *num_changed,
-                                 unsigned long long *stat_fast, int32_t *redo_list,
-                                 unsigned long long *redo_count, int gpr, int N);
+                                 int32_t beam_width, uint16_t *codes, const pv_counts &counts,
+                                 int32_t *redo_list, int gpr, int N);
 bool pv_mfma_supported(const pv_layout *l);
 // power == 0: the nearest codeword (deterministic V step); power >= 1: stochastic rounding over
 // the two nearest with that power and seed

@@ -48,10 +48,11 @@ __global__ __launch_bounds__(kBlock) void k_reencode_scalar(const float *__restr
                                                             const int32_t *__restrict__ weight_idx,
                                                             int64_t k, uint8_t *__restrict__ codes,
                                                             unsigned long long *num_changed,
-                                                            unsigned long long *counts,
+                                                            pv_counts counts,
                                                             int64_t n, int64_t in_features, int blk,
                                                             int nvals)
 {
+    pv_counts_clear(counts);
     __shared__ unsigned s_changed;
     if (threadIdx.x == 0) s_changed = 0;
     __syncthreads();
@@ -89,8 +90,8 @@ __global__ __launch_bounds__(kBlock) void k_reencode_scalar(const float *__restr
     __syncthreads();
     if (threadIdx.x == 0 && num_changed) {
         unsigned long long changed;
-        if (!counts) atomicAdd(num_changed, (unsigned long long)s_changed);
-        else if (pv_counts_arrive(counts, gridDim.x, s_changed, &changed)) *num_changed = changed;
+        if (!counts.mine) atomicAdd(num_changed, (unsigned long long)s_changed);
+        else if (pv_counts_arrive(counts.mine, gridDim.x, s_changed, &changed)) *num_changed = changed;
     }
 }
 
@@ -120,13 +121,12 @@ pv_status pv_launch_reencode_scalar(pv_ctx *ctx, int64_t out_features, int64_t i
                                     const float *zeros, const int32_t *weight_idx, int64_t k,
                                     uint8_t *codes, int64_t *num_changed)
 {
-    unsigned long long *counts = nullptr;
+    pv_counts counts;
     if (num_changed) {
-        // a context's first call, into a graph: it cannot allocate, a launch clears the caller's word
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (k > 0 && !ctx->stats.ptr) PV_HIP(ctx, hipStreamIsCapturing(ctx->stream, &capture));
-        pv_status st = k == 0 || capture != hipStreamCaptureStatusNone ? pv_launch_fill_i64(ctx, num_changed, 1, 0)
-                                                                       : pv_counters(ctx, nullptr, &counts);
+        // Into a graph: replays, several of them side by side perhaps, share nothing but what the caller gives them,
+        // and a first call cannot allocate.  A launch clears the caller's word.
+        pv_status st = k == 0 || pv_capturing(ctx) ? pv_launch_fill_i64(ctx, num_changed, 1, 0)
+                                                   : pv_counters(ctx, nullptr, &counts);
         if (st != PV_OK) return st;
     }
     if (k == 0) return PV_OK;
@@ -136,5 +136,6 @@ pv_status pv_launch_reencode_scalar(pv_ctx *ctx, int64_t out_features, int64_t i
                        zeros, weight_idx, k, codes, reinterpret_cast<unsigned long long *>(num_changed),
                        counts, out_features * in_features, in_features, blk, 1 << nbits);
     PV_HIP(ctx, hipGetLastError());
+    pv_counters_cleared(ctx, counts);
     return PV_OK;
 }

@@ -486,6 +486,34 @@ def test_reencode_m1_of_a_smaller_k_can_be_captured():
         side.synchronize()
 
 
+@pytest.mark.parametrize("g,k", [(8, 1), (8, 127), (8, 128), (8, 129), (8, 98304), (8, 98305), (8, 131072),
+                                 (16, 1), (16, 15), (16, 17), (16, 8192), (16, 8193), (16, 65536)])
+@pytest.mark.parametrize("left", ["all", "some", "none"])
+def test_reencode_m2_lists_for_the_exact_kernel(g, k, left):
+    """What the filter of the two-codebook search leaves goes into a list a block: nothing, every group of
+    every block (a codeword that is not finite), some; list lengths around a block's groups, a launch's blocks and a
+    second round of them.  Codes and count equal the exact kernel's, whatever call came before."""
+    wl = workloads.make(1024, 1024, g, 2, 8, seed=99, sigma_g=2e-3, tau=1.0)
+    rng = np.random.default_rng(k)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    if left == "all":
+        wl.codebooks[1, 9, 2] = np.inf
+    elif left == "some":
+        T_np[::3, 5::g] = np.nan
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx, beam_width=8)
+    run.ctx.pv_set_search_mode(0)
+    for _ in range(2):
+        got, n_got = run.reencode(T, idx, beam_width=8)
+        assert np.array_equal(got, want) and n_got == n_want
+        st = run.ctx.pv_reencode_stats()
+        assert st["filtered"] + st["fallback"] == k and st["exact"] == 0
+        assert left != "all" or st["filtered"] == 0
+        run.reencode(T, idx[: (k + 1) // 2], beam_width=4)
+
+
 @pytest.mark.parametrize("B,k", [(16, 32768), (16, 34001), (15, 65536), (14, 131072)])
 @pytest.mark.parametrize("regime", ["near", "far", "lumps", "degenerate"])
 def test_reencode_m1_cells_of_the_codebook(B, k, regime):

@@ -100,6 +100,47 @@ def test_scalar_first_call_of_a_context_can_be_captured():
     ctx.close()
 
 
+def test_scalar_replays_beside_one_another_and_beside_a_call():
+    """Graphs of one context's scalar searches share nothing but what the caller gives them: two of them replayed side
+    by side, and one beside a call, all count right, as does every call after them."""
+    o, i, block, nbits = 8192, 4096, 128, 2
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(97)
+    T = torch.randn(o, i, generator=gen, device=DEV)
+    sc, zp = (torch.rand(o, i // block, generator=gen, device=DEV) + 0.2 for _ in range(2))
+    before = torch.randint(0, 4, (o, i), generator=gen, device=DEV, dtype=torch.uint8)
+    idx = torch.arange(o * i, dtype=torch.int32, device=DEV)
+    streams = [torch.cuda.Stream(device=DEV) for _ in range(3)]
+    ctx = PVContext(0, stream=streams[0])
+    codes = [before.clone() for _ in range(3)]
+    nch = [torch.zeros(1, dtype=torch.int64, device=DEV) for _ in range(3)]
+    torch.cuda.synchronize()
+
+    def call(n):
+        ctx.pv_reencode_scalar(o, i, block, nbits, T, sc, zp, idx, o * i, codes[n], nch[n])
+
+    call(0)                             # the context has counted before
+    torch.cuda.synchronize()
+    want, changed = codes[0].clone(), int((codes[0] != before).sum())
+    graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+    for n, graph in enumerate(graphs):
+        with torch.cuda.graph(graph, stream=streams[0]):
+            call(n + 1)
+    for _ in range(4):
+        for n in range(3):
+            codes[n].copy_(before)
+            nch[n].fill_(-3)
+        torch.cuda.synchronize()
+        for n, graph in enumerate(graphs):
+            with torch.cuda.stream(streams[n + 1]):
+                graph.replay()
+        call(0)
+        torch.cuda.synchronize()
+        for n in range(3):
+            assert int(nch[n].item()) == changed > 0 and torch.equal(codes[n], want)
+    ctx.close()
+
+
 def sampled_vectors(n):
     """The vectors of four weights that the sweep of many single weights samples its scores from."""
     i, u32 = np.arange(16384, dtype=np.uint64), np.uint64(0xFFFFFFFF)
