@@ -1130,10 +1130,11 @@ __global__ __launch_bounds__(kListBlock, 4) void k_targets_lists(const float *W,
 }
 
 // Digit 0 is resolved and published with the rank left (state[4], state[6]); returns it.  lh: zeroed here.
-__device__ __forceinline__ unsigned first_digit(const sel_args &a, unsigned k, unsigned *tmp, unsigned *lh, int *log)
+__device__ __forceinline__ unsigned first_digit(const sel_args &a, unsigned k, unsigned *tmp, unsigned *lh, int *log,
+                                                unsigned &share)
 {
     for (int b = threadIdx.x; b < kMidBins << kSpreadLog; b += kSelBlock) lh[b] = 0;
-    unsigned kk = k, share;
+    unsigned kk = k;
     const unsigned d0 = (unsigned)pick_digit<kSelWaves>(a.hist_all + kHist0, kFirstBins, kk, tmp, &share);   // its barriers also order the clearing above
     *log = mid_log(share, a.N);                              // the same in every thread
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1147,7 +1148,8 @@ __device__ __forceinline__ unsigned first_digit(const sel_args &a, unsigned k, u
 __device__ __forceinline__ void mid_digit_raw(const sel_args &a, unsigned k, unsigned *tmp, unsigned *lh)
 {
     int log;
-    const unsigned d0 = first_digit(a, k, tmp, lh, &log);
+    unsigned share;
+    const unsigned d0 = first_digit(a, k, tmp, lh, &log, share);
     const region_t g = region_of(blockIdx.x * kSelWaves + (threadIdx.x >> 6), a.list, a.counts, a.scores, a.W, a.N, a.span, a.cap, true);
     for_scores<true>(g, [&](const pv_f4 &v, int at) {
 #pragma unroll
@@ -1171,9 +1173,13 @@ __device__ __forceinline__ void mid_digit_cells(const sel_args &a, unsigned k, u
     const int ncells = (int)((a.N + kCell - 1) / kCell), per = a.span / kCell;
     const int first = r * per, end = first + per < ncells ? first + per : ncells;
     int log;
-    const unsigned d0 = first_digit(a, k, tmp, lh, &log);
+    unsigned share;
+    const unsigned d0 = first_digit(a, k, tmp, lh, &log, share);
     const unsigned lo = d0 << kRestBits, hi = (d0 + 1u) << kRestBits;
     uint2 *mine = list + (int64_t)r * a.cap;
+    // Where most of all weights share digit 0, a region's list (a quarter of its weights) will hardly hold its share: it
+    // is not begun, 8 bytes a key that would be written in vain (45 M scores alike: 71.7 us, 41.6 this way).
+    const unsigned cap = (int64_t)share * 2 > a.N ? 0u : (unsigned)a.cap;
     unsigned cnt = 0;
     auto take = [&](unsigned key, unsigned id, bool in) {
         const bool hit = in && key >= lo;
@@ -1182,7 +1188,7 @@ __device__ __forceinline__ void mid_digit_cells(const sel_args &a, unsigned k, u
         const unsigned pos = __builtin_amdgcn_mbcnt_hi((unsigned)(hits >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hits, cnt));
         cnt += (unsigned)__popcll(hits);
         if (hit) {
-            if (pos < (unsigned)a.cap) mine[pos] = make_uint2(key, id);
+            if (pos < cap) mine[pos] = make_uint2(key, id);
             if (key < hi) spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
         }
     };
@@ -1229,7 +1235,7 @@ __device__ __forceinline__ void mid_digit_cells(const sel_args &a, unsigned k, u
                     for (int x = 0; x < 4; ++x)
                         if ((hits[x] >> lane) & 1ull) {
                             const unsigned key = score_key(v[q][x]);
-                            if (pos < (unsigned)a.cap) mine[pos] = make_uint2(key, (unsigned)(base + q * 256 + x));
+                            if (pos < cap) mine[pos] = make_uint2(key, (unsigned)(base + q * 256 + x));
                             ++pos;
                             if (key < hi) spread_add(lh, (key >> kLastBits) & (kMidBins - 1), log);
                         }
@@ -1237,7 +1243,7 @@ __device__ __forceinline__ void mid_digit_cells(const sel_args &a, unsigned k, u
             }
         }
     }
-    if (lane == 0) counts[r] = cnt;
+    if (lane == 0) counts[r] = cap ? cnt : max(cnt, (unsigned)a.cap + 1u);
     __syncthreads();
     flush_hist(lh, a.hist_all + kHist1, kMidBins, tmp, log);
 }
@@ -1488,14 +1494,17 @@ pv_status pv_select_scores(pv_ctx *ctx, int64_t N, float **scores)
 }
 
 // One weight a group, and so many that the scores' way through memory costs more than the sample (6 us) and a launch that
-// returns at once (4.6).  The call, k = N / 100, scores written / collected: 4 M weights 40.0 / 39.6 us, 8 M 53.6 /
-// 50.3, 16 M 78.8 / 67.8, 45 M 163.8 / 130.0 (k = N / 10: 40.4 / 43.7, 57.9 / 60.0, 86.0 / 82.7, 196.4 / 161.0; rows of
-// their own size, 45 M: 202.6 / 166.6).  What loses is all scores alike, which are written and read all the same:
-// 45 M 273 / 291, 16 M 118 / 131.
+// returns at once (4.6).  The call, scores written / collected: k = N / 100, 4 M weights 40.0 / 39.6 us, 8 M 53.6 /
+// 50.3, 12.6 M 65.4 / 59.8, 16.8 M 79.6 / 69.0, 25 M 105 / 85.6, 45 M 164 / 130; rows of their own size 78.2 / 76.1,
+// 96.9 / 92.6, 129 / 112, 202 / 169 from 12.6 M on.  The keys kept are 8 bytes each, so fewer of fewer weights pay:
+// k = N / 16, 12.6 M 69.4 / 67.4 (rows 85.1 / 85.0); N / 10, 12.6 M 70.9 / 71.6, 16.8 M 85.7 / 82.6 (102.2 / 103.8); N / 8,
+// 16.8 M 88.1 / 86.2 (103.6 / 106.9), 25 M 119 / 111 (146 / 141).  Scores all alike are written and read all the same:
+// 12.6 M 98.4 / 105.2, 16.8 M 125.3 / 128.5, 25 M 172.4 / 171.6, 45 M 295 / 277.
 static bool sweep_collects(const pv_layout *l, int64_t k)
 {
     const int64_t N = pv_num_groups(l);
-    return l->group_size == 1 && N >= kCollectMin && k > 0 && k <= N / 8;
+    const int64_t most = N / (N >= 3 << 23 ? 8 : N >= 1 << 24 ? 10 : 16);
+    return l->group_size == 1 && N >= kCollectMin && k > 0 && k <= most;
 }
 
 // G != nullptr: T is an OUTPUT, formed here as W - alpha * G in the same pass that scores it.

@@ -152,7 +152,8 @@ def sampled_vectors(n):
 
 
 @pytest.mark.parametrize("shape", [(3072, 4096), (4001, 3777)])      # the fewest that the sweep collects from; a ragged end
-@pytest.mark.parametrize("kind", ["normal", "equal", "rows", "columns", "zeros", "not_finite", "sampled", "sampled_few"])
+@pytest.mark.parametrize("kind", ["normal", "equal", "rows", "columns", "zeros", "not_finite", "sampled", "sampled_few",
+                                  "half_alike"])
 def test_selection_among_many_single_weights(shape, kind):
     """The sweep that keeps keys from a sampled digit on, against a partition of all scores: spread scores, all
     alike, rows and columns of their own size (cells and regions whose lists do not fit), mostly zeros, NaN
@@ -172,6 +173,9 @@ def test_selection_among_many_single_weights(shape, kind):
         G *= torch.exp(2 * torch.randn(*size, generator=gen, device=DEV))
     elif kind == "zeros":
         G *= torch.rand(rows, cols, generator=gen, device=DEV) < 0.003
+    elif kind == "half_alike":          # the lower rows alike, more than half of all; few in a region of the upper ones
+        W[rows // 3:], G[rows // 3:] = 0.0, 1e-4
+        G[:rows // 3] *= torch.rand(rows // 3, cols, generator=gen, device=DEV) < 0.02
     elif kind == "not_finite":
         G[3, 5], G[7, 9], G[rows - 1, cols - 1] = float("nan"), float("inf"), -float("nan")
     elif kind != "normal":
@@ -180,7 +184,7 @@ def test_selection_among_many_single_weights(shape, kind):
         if kind == "sampled_few":
             G.view(-1)[-1000:] = 3.0
     lay, ctx, T = Layout(rows, cols, 1, 1, 2), PVContext(0), torch.empty_like(W)
-    for k in (n // 100, 7, n // 8):
+    for k in (n // 100, 7, n // 16, n // 8):
         for call in range(2):           # the second finds what the first left in the scratch
             idx = torch.full((k,), -7, dtype=torch.int32, device=DEV)
             T.fill_(5.0)
