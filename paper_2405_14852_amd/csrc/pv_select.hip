@@ -1524,6 +1524,8 @@ pv_status pv_launch_select(pv_ctx *ctx, const pv_layout *l, const float *T, cons
     // whatever k and the direction: a later call of the shape does not allocate.  A block of its own: in the one
     // above it took smaller matrices past sizes from which an allocation costs more (2 MiB for 1003 x 2072 in groups of 8)
     bool sample = !scores && l->group_size == 1 && N >= kCollectMin && !ctx->sample_refused;
+    // a first call of such a shape into a graph, its other scratch large enough from a call of another shape: scores are written
+    if (sample && !ctx->sample.ptr && pv_capturing(ctx)) sample = false;
     if (sample) {
         sample = pv_ensure(ctx, ctx->sample, kSampleWords * sizeof(unsigned), kSampleWords * sizeof(unsigned)) == PV_OK;
         ctx->sample_refused = !sample;

@@ -200,3 +200,40 @@ def test_selection_among_many_single_weights(shape, kind):
         want = np.sort(np.concatenate([np.nonzero(key > least)[0], ties]))
         assert np.array_equal(idx.cpu().numpy(), want)
     ctx.close()
+
+
+def test_selection_among_many_single_weights_first_called_into_a_graph():
+    """A context whose scratch is large enough from a larger shape: the first call among many single weights may be
+    captured (the sample's memory is not there, and cannot be allocated), and calls after it sample."""
+    rows, cols = 3072, 4096
+    n, k = rows * cols, rows * cols // 100
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(98)
+    W, G = (torch.randn(rows, 2 * cols, generator=gen, device=DEV) for _ in range(2))
+    side = torch.cuda.Stream(device=DEV)
+    ctx, T = PVContext(0, stream=side), torch.empty_like(W)
+    idx = torch.empty(k, dtype=torch.int32, device=DEV)
+    torch.cuda.synchronize()
+    ctx.pv_encode_targets_select(Layout(rows, 2 * cols, 2, 1, 2), W, G, 0.3, T, k, idx)
+    side.synchronize()
+    W1, G1 = W[:, :cols].contiguous(), G[:, :cols].contiguous()
+    T1, lay = torch.empty_like(W1), Layout(rows, cols, 1, 1, 2)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        ctx.pv_encode_targets_select(lay, W1, G1, 0.3, T1, k, idx)
+    for call in ("replay", "eager", "replay", "replay"):
+        idx.fill_(-7)
+        T1.fill_(5.0)
+        torch.cuda.synchronize()
+        if call == "replay":
+            graph.replay()
+        else:
+            ctx.pv_encode_targets_select(lay, W1, G1, 0.3, T1, k, idx)
+        torch.cuda.synchronize()
+        score = ((T1 - W1) ** 2).view(-1)
+        least = torch.topk(score, k).values[-1]
+        above = torch.nonzero(score > least).view(-1)
+        ties = torch.nonzero(score == least).view(-1)[:k - len(above)]
+        assert torch.equal(idx.long(), torch.sort(torch.cat([above, ties])).values)
+    ctx.close()
