@@ -906,6 +906,10 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     h8 a_cur, a_nxt;
     pv_f4 norm = {0.0f, 0.0f, 0.0f, 0.0f};              // g = 16: of the keys of a residue cycle
     static_assert(kResidues == 4, "a cycle's norms are one vector");
+    // they are read with the kNormTile-th tile: after the last key of the cycle before is closed (kD units into this one),
+    // and not after the first of this one
+    constexpr int kNormTile = (kD + NB - 1) / NB;
+    static_assert(G != 16 || (kNormTile * NB <= kD + (kU - 1) * NB && kNormTile < kCycle), "norms come before they are used");
     auto issue = [&](int nb, int set) {
         const f16v z = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         acc[set] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a_cur, b[nb], z, 0, 0, 0);
@@ -953,7 +957,7 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
                     if (nb == 0) {
                         __builtin_amdgcn_sched_barrier(0);
                         a_nxt = buf[(ts + 1) * 64 + lane];
-                        if (u == (kD + NB - 1) / NB)
+                        if (u == kNormTile)
                             norm = *reinterpret_cast<const pv_f4 *>(bufn + q4 / kCycle * 2 * kResidues + (lane >> 5) * kResidues);
                         __builtin_amdgcn_sched_barrier(0);
                     }
