@@ -380,6 +380,12 @@ def reencode_case(wl, mode, idx=None, T_np=None):
     return run, got, want, info
 
 
+def check_route(run, k, filtered):
+    """The last search (mode 0, one codebook, k listed groups): the matrix-core filter took it, or one launch did."""
+    st = run.ctx.pv_reencode_stats()
+    assert (st["filtered"] + st["fallback"], st["exact"]) == ((k, 0) if filtered else (0, k))
+
+
 @pytest.mark.parametrize("mode", [1, 0])
 @pytest.mark.parametrize("g,B,shape,tau", [
     (8, 8, (256, 256), 1.0),        # config 1 as stated
@@ -481,7 +487,7 @@ def test_reencode_m1_of_a_smaller_k_can_be_captured():
         graph.replay()
         torch.cuda.synchronize()
         check_codes(wl, T_np, ids, host_u16(codes), want, info)
-        assert int(count.item()) == info["num_changed"] or info["near_tie"].any()
+        assert int(count.item()) == int((host_u16(codes) != wl.codes).sum()) > 0
         run.ctx.pv_reencode_groups(run.lay, T, run.cb, run.sc, idx, 77 + rep, 1, first, count)
         side.synchronize()
 
@@ -614,7 +620,8 @@ def test_reencode_m1_on_one_context_equals_fresh_contexts():
 def test_reencode_m1_codebook_preparation(g, B, norms):
     """Both ways of taking the codebook's statistics (1024 codewords, and more), and norms on which
     the norm ordering is put to the test: all alike, far beyond a sample's, at the bottom of float32."""
-    wl = workloads.make(64, 64 * g, g, 1, B, seed=71, sigma_g=4e-3, tau=0.5)
+    # (1024 codewords: more groups than one launch takes, which prepares nothing)
+    wl = workloads.make(256 if B == 10 else 64, 64 * g, g, 1, B, seed=71, sigma_g=4e-3, tau=0.55)
     if norms == "one":
         wl.codebooks[:] = np.float32(0.02) * np.sign(wl.codebooks)
     if norms == "spread":
@@ -624,15 +631,18 @@ def test_reencode_m1_codebook_preparation(g, B, norms):
     if norms == "tiny":
         wl.codebooks *= np.float32(1e-14)
         wl.scales *= np.float32(1e14)
-    reencode_case(wl, 0)
+    run, *_ = reencode_case(wl, 0)
+    check_route(run, wl.k, filtered=True)
 
 
-@pytest.mark.parametrize("B", [5, 6, 9, 13, 16])
-def test_reencode_m1_codebook_sizes_with_long_lists(B):
-    """More than 4096 listed groups (two group tiles per wave) at every codebook size class."""
-    wl = workloads.make(64, 1024, 8, 1, B, seed=51, sigma_g=2e-3, tau=0.6)
+@pytest.mark.parametrize("B,rows", [(5, 64), (6, 64), (9, 64), (13, 64), (16, 64), (6, 256), (9, 256)])
+def test_reencode_m1_codebook_sizes_with_long_lists(B, rows):
+    """More than 4096 listed groups (two group tiles per wave) at every codebook size class; up to 16384 of
+    small ones are one launch."""
+    wl = workloads.make(rows, 1024, 8, 1, B, seed=51, sigma_g=2e-3, tau=0.6)
     assert wl.k > 4096
-    reencode_case(wl, 0)
+    run, *_ = reencode_case(wl, 0)
+    check_route(run, wl.k, filtered=rows == 256 or B not in (6, 9))
 
 
 @pytest.mark.parametrize("seed", range(8))
@@ -665,30 +675,38 @@ def test_reencode_m1_filter_agrees_with_the_exact_scan_on_large_lists(seed):
 
 
 @pytest.mark.parametrize("mode", [1, 0])
-def test_reencode_m1_scale_edge_cases(mode):
-    wl = workloads.make(32, 512, 8, 1, 10, seed=8, sigma_g=2e-3, tau=1.0)
+@pytest.mark.parametrize("g,B", [(8, 10), (8, 11), (16, 11)])     # one launch, the filter twice
+def test_reencode_m1_scale_edge_cases(mode, g, B):
+    wl = workloads.make(32, 64 * g, g, 1, B, seed=8, sigma_g=2e-3, tau=1.0)
     wl.scales[3] = 0.0          # every code ties: previous code kept
     wl.scales[5] = -0.9         # negative scale
     wl.scales[7] = 1e-6         # targets far outside the codebook's range after normalisation
     wl.scales[9] = 300.0
-    _, got, want, _ = reencode_case(wl, mode)
+    run, got, want, _ = reencode_case(wl, mode)
+    if mode == 0:
+        check_route(run, wl.k, filtered=B == 11)
     gpr = wl.layout.groups_per_row
     assert np.array_equal(got.reshape(-1)[3 * gpr:4 * gpr], wl.codes.reshape(-1)[3 * gpr:4 * gpr])
 
 
 @pytest.mark.parametrize("mode", [1, 0])
-def test_reencode_m1_duplicate_codewords_tie_rule(mode):
-    wl = workloads.make(16, 256, 8, 1, 8, seed=9, sigma_g=2e-3, tau=1.0)
-    wl.codebooks[0, 128:] = wl.codebooks[0, :128]       # every codeword exists twice
-    _, got, want, info = reencode_case(wl, mode)
+@pytest.mark.parametrize("g,B", [(8, 8), (8, 11), (16, 11)])      # one launch, the filter twice
+def test_reencode_m1_duplicate_codewords_tie_rule(mode, g, B):
+    wl = workloads.make(16, 32 * g, g, 1, B, seed=9, sigma_g=2e-3, tau=1.0)
+    half = 1 << (B - 1)
+    wl.codebooks[0, half:] = wl.codebooks[0, :half]     # every codeword exists twice
+    run, got, want, info = reencode_case(wl, mode)
+    if mode == 0:
+        check_route(run, wl.k, filtered=B == 11)
     assert np.array_equal(got, want)                     # exact ties resolve identically
 
 
-@pytest.mark.parametrize("g,B", [(8, 10), (16, 9)])
+@pytest.mark.parametrize("g,B", [(8, 10), (16, 9), (8, 11), (16, 11), (16, 13)])   # one launch, then the filter
 @pytest.mark.parametrize("case", ["targets_on_codewords", "mixed_magnitudes", "tiny_values", "huge_values",
                                   "clustered_codebook", "one_dimension_dominates"])
 def test_reencode_m1_inputs_that_stress_the_filter(g, B, case):
-    """Inputs chosen against the fp16 filter and its bounds; the decision must stay the oracle's."""
+    """Inputs chosen against the fp16 filter and its bounds; the decision must stay the oracle's (and, below
+    2048 codewords, that of the one launch that takes so little work)."""
     wl = workloads.make(24, 64 * g, g, 1, B, seed=12, sigma_g=2e-3, tau=1.0)
     rng = np.random.default_rng(12)
     T_np = None
@@ -712,7 +730,8 @@ def test_reencode_m1_inputs_that_stress_the_filter(g, B, case):
     elif case == "one_dimension_dominates":
         wl.codebooks[0, :, 0] *= np.float32(1000.0)
         wl.W[:, ::g] *= np.float32(1000.0)
-    _, got, want, info = reencode_case(wl, 0, T_np=T_np)
+    run, got, want, info = reencode_case(wl, 0, T_np=T_np)
+    check_route(run, wl.k, filtered=B >= 11)
     if case == "targets_on_codewords":
         assert (info["obj_new"] <= 1e-12).all()
 
@@ -754,7 +773,8 @@ def test_reencode_empty_selection_and_errors():
 
 
 @pytest.mark.parametrize("mode", [1, 0])
-@pytest.mark.parametrize("g,M,B,beam", [(8, 1, 10, 1), (16, 1, 9, 1), (8, 2, 8, 8), (8, 3, 4, 4), (4, 1, 3, 1)])
+@pytest.mark.parametrize("g,M,B,beam", [(8, 1, 10, 1), (16, 1, 9, 1), (8, 1, 11, 1), (16, 1, 11, 1), (8, 2, 8, 8), (8, 3, 4, 4),
+                                        (4, 1, 3, 1)])
 def test_reencode_reads_stored_codes_modulo_the_codebook_size(mode, g, M, B, beam):
     """Stray bits above B in the stored codes: the library reads the low B bits (the oracle
     refuses such input, so it is given the clean codes); a group that keeps its code keeps its
@@ -775,6 +795,8 @@ def test_reencode_reads_stored_codes_modulo_the_codebook_size(mode, g, M, B, bea
     run = GpuRun(wl)
     run.ctx.pv_set_search_mode(mode)
     got, nch = run.reencode(dev_f32(T_np), idx, codes=dev_u16(dirty))
+    if mode == 0 and M == 1 and g >= 8:
+        check_route(run, len(idx), filtered=B == 11)
     want, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, idx, wl.codes, beam_width=beam)
     mask = np.uint16((1 << B) - 1)
     ndiff = check_codes_on(wl, T_np, idx, got & mask, want, info)
