@@ -843,8 +843,8 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
     __shared__ h8 lds1[kStageChunks + 64];
     __shared__ __align__(16) float ldn0[64], ldn1[64];     // smallest norm behind each key of the stage (g = 16)
     __shared__ unsigned s_item;
-    // the wave's number in a scalar register: what follows from it is uniform (g = 16 reloaded
-    // spilled registers inside the loop over the tiles without it)
+    // the wave's number in a scalar register: what follows from it is uniform (g = 16: 18 spilled registers without
+    // it, some reloaded inside the loop over the tiles, 7 with it)
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     unsigned vmask = ~kKeyMask;
     asm volatile("" : "+v"(vmask));   // keep the mask in a vector register
@@ -950,8 +950,9 @@ __global__ __launch_bounds__(PV_WAVES * 64, (PV_OCC * PV_WAVES) / 4) void k_scor
                     // Reads of LDS behind the matrix instruction that waits for the ones before: the wait counts
                     // all reads, and one issued just before it would be waited for in full.  The cycle's norms
                     // once the last key of the cycle before is closed, a tile ahead of the first use (183 500
-                    // groups x 65536 codewords: 402 -> 382 us with this and scalar wave numbers; the two norms of
-                    // a key read where it is closed held the wave up for a round trip twice a super-unit).
+                    // groups x 65536 codewords: 413 -> 390 us in the mean, 397 -> 376 at best, with this and scalar
+                    // wave numbers; the two norms of a key read where it is closed held the wave up for a round trip
+                    // twice a super-unit).  Seven vector registers are still spilled (18 before).
                     // Matrix instruction and maxima alone, nothing read, take 27 ns a unit on random operands
                     // (18 on zeros: the clock gives way to the power); this loop takes 33.
                     if (nb == 0) {

@@ -25,14 +25,14 @@
 //   those to be done adds up.
 // Bound by the gathers: 32 bytes of G (g = 8) bring a line of 128, and 2^21 of them in random order
 // take 41 us of k_pg_buckets' 54 whatever the kind of load (plain, nontemporal, device scope) and
-// whether G was read shortly before.  4096 x 4096, 1 x 16, codes drawn evenly: 107 -> 82 us a call against a radix
+// whether G was read shortly before.  4096 x 4096, 1 x 16, codes drawn evenly: 107 -> 80 us a call against a radix
 // sort of (code, group) in two passes of three kernels, segment starts, sums and scales (nine launches);
-// 354 x 384, 1 x 12 40 -> 21; 4096 x 4096, 1 x 12 118 -> 87.  Scales as a launch of their own: 84; beside the
+// 354 x 384, 1 x 12 41 -> 19; 4096 x 4096, 1 x 12 118 -> 85.  Scales as a launch of their own: 84; beside the
 // sums instead of the order: 82.  Buckets of 256 or tiles of 4096 groups: 1 to 8 us more.
 // Codes used unevenly, 4096 x 4096, 1 x 16 (the radix sort / buckets of consecutive codes, a block each / this):
 // 64 neighbouring codewords hold everything 1370 / 5640 / 131 us, 512 of them 1250 / 1900 / 110; uses that fall
-// like 1 / code 704 / 4280 / 174, the same in random order 720 / 727 / 177; one codeword with a third 3370 / 3160 /
-// 150; 64 at random places 384 / 388 / 131, 512 150 / 131 / 138; 128 codewords 512 apart 194 / 171 / 175.
+// like 1 / code 705 / 4310 / 172, the same in random order 720 / 730 / 171; one codeword with a third 3370 / 3170 /
+// 146; 64 at random places 382 / 389 / 128, 512 151 / 132 / 136; 128 codewords 512 apart 194 / 171 / 170.
 // Small codebooks take another route (k_pg_small below), which takes the scale gradient along.
 #include "pv_internal.h"
 #include "pv_dpp.h"
@@ -48,7 +48,8 @@ constexpr int kLong = 128;       // groups of a codeword in a chunk that one tea
 // number, so every code has a product of its own) agrees in its high bits.  Neighbouring codes, and codes a power of two
 // apart, are spread evenly over the buckets that way, and where few codewords hold most groups they are often
 // such (a codebook in order of norm or of use, a part of it in use).  With high bits folded into low ones by
-// exclusive or, every 64th code used: 160 us a call, 85 this way.
+// exclusive or, every 64th code used: 160 us a call, 85 this way; with runs of four codes kept together, whose rows of the
+// result share a cache line, 512 neighbours that hold all groups 138, 109 this way, and even use the same.
 constexpr int kTileBlock = 1024;
 constexpr int kTileWaves = kTileBlock / 64;
 constexpr int kTilePer = 8;
@@ -79,18 +80,29 @@ struct bucket_args {
     uint16_t *starts;                    // [codebook][spare][codes of a bucket + 1] where a code's begin
 };
 
-// The lanes of a wave (among `valid`) whose low `bits` bits of d are this lane's.
+// With mul: bucket of a code << low | its number there; with inv: back again.  (16 bits by 16.)
+__device__ __forceinline__ unsigned spread_code(unsigned code, unsigned mul, const bucket_args &b)
+{
+    return (unsigned)__umul24(code, mul) & b.mask;
+}
+
+// The lanes of a wave (among `valid`) whose low `bits` bits of d are this lane's: of the lanes with a bit set, those if
+// it is set here, else the others.  (The bit spread over a word, and halves of 32: 1 to 3 us a call less than a 64-bit
+// choice between the ballot and its complement.)
 __device__ __forceinline__ unsigned long long lanes_alike(unsigned d, int bits, bool valid)
 {
-    unsigned long long same = __ballot(valid);
+    const unsigned long long in = __ballot(valid);
+    unsigned lo = (unsigned)in, hi = (unsigned)(in >> 32);
 #pragma unroll
     for (int bit = 0; bit < kBucketBits; ++bit) {
         if (bit < bits) {                          // uniform
-            const unsigned long long has = __ballot((d >> bit) & 1u);
-            same &= ((d >> bit) & 1u) ? has : ~has;
+            const unsigned here = (unsigned)((int)(d << (31 - bit)) >> 31);     // all ones if the bit is set
+            const unsigned long long has = __ballot(here != 0u);
+            lo &= ~((unsigned)has ^ here);
+            hi &= ~((unsigned)(has >> 32) ^ here);
         }
     }
-    return same;
+    return (unsigned long long)hi << 32 | lo;
 }
 
 // Counts of a block's waves per digit become offsets in wave order; start[d] = keys of smaller digits, for d up
@@ -284,7 +296,7 @@ __global__ __launch_bounds__(kTileBlock, 8) void k_pg_tiles(bucket_args b, scale
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kTilePer; ++j) {
-        code[j] = (code[j] * b.mul) & b.mask;
+        code[j] = spread_code(code[j], b.mul, b);
         d[j] = code[j] >> b.low;
     }
     digit_ranks<kTilePer, kBuckets>(d, rank, per, n, b.high, wcnt);
@@ -509,7 +521,7 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
         before -= (unsigned)n;
         __syncthreads();
     }
-    auto row = [&](int c) { return out + (int64_t)((((unsigned)bucket << b.low | (unsigned)c) * b.inv) & b.mask) * g + i * VEC; };
+    auto row = [&](int c) { return out + (int64_t)spread_code((unsigned)bucket << b.low | (unsigned)c, b.inv, b) * g + i * VEC; };
     while (w0 < b.ntiles) {
         const int most = SPLIT && segs && seg == segs - 1 ? (int)(total - (unsigned)seg * kChunk) : kChunk;
         const int from = w0;
@@ -803,8 +815,8 @@ __global__ __launch_bounds__(kSumBlock, 4) void k_pg_buckets(bucket_args b, cons
 // added with the rounding errors carried along, and the total is rounded to fp32.  Gradients or
 // scales that are not finite make every entry NaN.  A row's products are summed by the waves that
 // meet it, lanes first, and added in order of the waves.
-// 11008 x 4096, 2 x 8: vector-ALU issue fills 91 of the kernel's 141 thousand cycles (23.4 M instructions,
-// much of it the conversion to integers), the LDS 60 (sixteen 64-bit atomics a group and codebook; 35 of
+// 11008 x 4096, 2 x 8: vector-ALU issue fills 84 of the kernel's 138 thousand cycles (21.6 M instructions,
+// much of it the conversion to integers), the LDS 60 (sixteen 64-bit atomics a group and codebook; 36 of
 // them bank conflicts), reading G takes 75; none alone is the bound, their overlap is.  There, with the
 // scale gradient (and the maxima) as a kernel of its own that read G first: 98.7 us a step, in one
 // pass 73.  Gradients with heavy tails (cubed normal, Student's t): 82 and 86.  Ordering tiles of
@@ -1215,10 +1227,10 @@ pv_status pv_launch_codebook_grads(pv_ctx *ctx, const pv_layout *l, const float 
     // Two codebooks at a time: 8 bytes a group of scratch whatever M, and up to 16 for the chunks of overfull buckets.
     const int low = l->nbits > kBucketBits ? l->nbits - kBucketBits : 0, high = l->nbits - low;
     const int nb = 1 << high, stride = (nb + 8) & ~7;
-    // the golden section of 2^B, odd: neighbouring codes, and codes a power of two apart, fall far from one another
-    const unsigned mul = low ? (0x9E3779B9u >> (32 - l->nbits)) | 1u : 1u;
+    const unsigned mul = low ? (0x9E3779B9u >> (32 - l->nbits)) | 1u : 1u;     // the golden section of 2^B
     unsigned inv = mul;
     for (int i = 0; i < 4; ++i) inv *= 2u - mul * inv;      // Newton: 3 bits are right to begin with, then 6, 12, 24, 48
+    inv &= mask;
     const int64_t ntiles = (N + kTile - 1) / kTile;
     const int at_once = M < 2 ? M : 2;
     // sums that go on from one chunk, or one round of pieces, to the next (a codeword may hold every group)
