@@ -8,7 +8,8 @@
 // The codebook gradient is a scatter-add of N * g values into 2^B * g sums.  Floating-point
 // atomics would serialise on popular codewords and give run-dependent roundings (and atomics
 // on device memory are slow on a part whose L2 is split over several dies); instead the
-// groups are put in code order by two launches that exchange 4 bytes a group and no atomics:
+// groups are put in code order by two launches that exchange 4 bytes a group and, where no bucket is
+// overfull, no atomics:
 // - k_pg_tiles puts every tile of 8192 groups in the order of up to 512 buckets of codes and writes
 //   the tile where it was read, with the places where its buckets start; no
 //   counts over the whole matrix are needed.  Blocks of the same launch take the scale gradient,
@@ -30,8 +31,8 @@
 // 354 x 384, 1 x 12 41 -> 19; 4096 x 4096, 1 x 12 118 -> 85.  Scales as a launch of their own: 84; beside the
 // sums instead of the order: 82.  Buckets of 256 or tiles of 4096 groups: 1 to 8 us more.
 // Codes used unevenly, 4096 x 4096, 1 x 16 (the radix sort / buckets of consecutive codes, a block each / this):
-// 64 neighbouring codewords hold everything 1370 / 5640 / 131 us, 512 of them 1250 / 1900 / 110; uses that fall
-// like 1 / code 705 / 4310 / 172, the same in random order 720 / 730 / 171; one codeword with a third 3370 / 3170 /
+// 64 neighbouring codewords hold everything 1390 / 5640 / 131 us, 512 of them 1225 / 1895 / 106; uses that fall
+// like 1 / code 705 / 4310 / 172, the same in random order 719 / 730 / 171; one codeword with a third 3370 / 3170 /
 // 146; 64 at random places 382 / 389 / 128, 512 151 / 132 / 136; 128 codewords 512 apart 194 / 171 / 170.
 // Small codebooks take another route (k_pg_small below), which takes the scale gradient along.
 #include "pv_internal.h"
@@ -49,7 +50,7 @@ constexpr int kLong = 128;       // groups of a codeword in a chunk that one tea
 // apart, are spread evenly over the buckets that way, and where few codewords hold most groups they are often
 // such (a codebook in order of norm or of use, a part of it in use).  With high bits folded into low ones by
 // exclusive or, every 64th code used: 160 us a call, 85 this way; with runs of four codes kept together, whose rows of the
-// result share a cache line, 512 neighbours that hold all groups 138, 109 this way, and even use the same.
+// result share a cache line, 512 neighbours that hold all groups 138, 106 this way, and even use the same.
 constexpr int kTileBlock = 1024;
 constexpr int kTileWaves = kTileBlock / 64;
 constexpr int kTilePer = 8;
