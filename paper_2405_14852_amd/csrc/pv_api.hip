@@ -47,13 +47,14 @@ pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head)
     return PV_OK;
 }
 
-pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, pv_counts *counts)
+pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, pv_counts *counts, uint32_t **block_counts)
 {
-    constexpr size_t bytes = 8 * sizeof(int64_t) + 3 * kCountBytes;
+    constexpr size_t head = 8 * sizeof(int64_t) + 3 * kCountBytes, bytes = head + kCountedBlocks * 4 * sizeof(uint32_t);
     const pv_status st = pv_ensure(ctx, ctx->stats, bytes, bytes);
     if (st != PV_OK) return st;
     auto p = static_cast<unsigned long long *>(ctx->stats.ptr);
     if (stats) *stats = p;
+    if (block_counts) *block_counts = reinterpret_cast<uint32_t *>(static_cast<char *>(ctx->stats.ptr) + head);
     if (!counts) return PV_OK;
     if (pv_capturing(ctx)) {
         counts->mine = p + 8 + 2 * kCountWords;

@@ -40,7 +40,7 @@ struct pv_ctx {
     size_t select_refused = ~(size_t)0;   // smallest size of that block, with lists, that could not be allocated
     pv_buffer sample;       // and its sample of many single weights: a histogram, zero between calls
     bool sample_refused = false;          // there was no memory for it: scores are written instead
-    pv_buffer stats;        // i64 [8] counters of the last re-encode | three sets of what a call's blocks count (pv_counts.h)
+    pv_buffer stats;        // i64 [8] counters of the last re-encode | three sets of what a call's blocks count (pv_counts.h) | counters per block
     int count_set = 0;      // the one of the first two that is clear
     pv_buffer search;       // the matrix-core filter's: statistics, operands, records, counters (see pv_launch_mfma_search)
     const uint32_t *rr_counts = nullptr;  // in there: [blocks][4] counters of the last call's re-rank kernel
@@ -65,7 +65,9 @@ pv_status pv_ensure(pv_ctx *ctx, pv_buffer &buf, size_t bytes, size_t zero_head 
 // another route, and allocates nothing.  counts: the words of this call and those that its first kernel clears
 // (see pv_counts.h); pv_counters_cleared once that kernel is launched.
 struct pv_counts;
-pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, pv_counts *counts);
+// block_counts: u32 [kCountedBlocks][4], what each block of a search in one launch leaves for pv_reencode_stats.
+constexpr int kCountedBlocks = 1024;
+pv_status pv_counters(pv_ctx *ctx, unsigned long long **stats, pv_counts *counts, uint32_t **block_counts = nullptr);
 void pv_counters_cleared(pv_ctx *ctx, const pv_counts &counts);
 bool pv_capturing(const pv_ctx *ctx);
 

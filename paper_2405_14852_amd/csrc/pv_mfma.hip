@@ -39,6 +39,7 @@
 // chosen code is the double-precision argmin with the tie rule of the definition, whatever the
 // fp16 rounding did.
 #include "pv_internal.h"
+#include "pv_counts.h"
 #include "pv_dpp.h"
 
 // Launch shape of the contraction kernel (tunable at build time).
@@ -1563,6 +1564,10 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
     }
 }
 
+}  // namespace
+#include "pv_smallcb.h"
+namespace {
+
 // ------------------------------------------------ stochastic rounding over the two nearest
 //
 // The same filter serves App. F's rounding over the TWO nearest codewords: the certificate is
@@ -2034,6 +2039,8 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
                                 const int32_t *group_idx, int64_t k, uint16_t *codes,
                                 int64_t *num_changed, int32_t power, uint64_t seed)
 {
+    if (power == 0 && small_codebook(l, k))
+        return pv_launch_search_small(ctx, l, T, codebooks, scales, group_idx, k, codes, num_changed);
     plan_t p = make_plan(l, k, power > 0);
     const plan_t dense = p;      // with cells: the plan of the dense contraction, should it be needed
     // Cells (pv_cells.h): g = 8, the nearest codeword, work enough to pay for cutting the codebook.

@@ -461,6 +461,49 @@ def test_reencode_m1_in_one_launch(g, B, k, case):
         check_codes_on(wl, T_np, idx, got, ref, info)
 
 
+@pytest.mark.parametrize("g,B,k", [(8, 8, 16385), (8, 8, 131077), (8, 9, 16385), (8, 10, 8193), (8, 11, 1), (8, 11, 33),
+                                   (8, 11, 32769), (8, 12, 31), (8, 12, 16449), (16, 8, 16385), (16, 9, 16385),
+                                   (16, 10, 8193), (16, 11, 65), (16, 11, 16449)])
+@pytest.mark.parametrize("case", ["plain", "ties", "odd"])
+def test_reencode_m1_small_codebook(g, B, k, case):
+    """Codebooks that fit the LDS: the filter in one launch.  Lists that end inside a tile of groups, a block's groups
+    and a second round of the blocks; exact ties, several equal codewords behind one key and in one partition; codewords
+    and targets that are not finite, scales of zero and below, targets far outside, ids outside the matrix, stored codes above
+    2^B.  Codes and count equal the exact scan's, twice in a row (the counters are left zero)."""
+    wl = workloads.make(160 if k < 20000 else 1040, 128 * g, g, 1, B, seed=101, sigma_g=2e-3, tau=1.0)
+    rng = np.random.default_rng(k)
+    if case == "ties":
+        wl.codebooks[0, 1::2] = wl.codebooks[0, ::2]
+        wl.codebooks[0, -40:] = 0.0
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    if case == "ties":
+        T_np[::3] = 0.0
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    if case == "odd":
+        wl.scales[::5] = 0.0
+        wl.scales[1::5] *= np.float32(-1.0)
+        wl.scales[2::5] *= np.float32(1e-3)
+        if k % 2:
+            wl.codebooks[0, 3, 1], wl.codebooks[0, 5, 0] = np.nan, np.inf
+        T_np[2, 7], T_np[9] = np.inf, np.nan
+        wl.codes[::7] |= np.uint16(1 << B)
+        idx = np.sort(np.where(rng.random(k) < 0.1, idx + wl.layout.num_groups, idx)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx)
+    run.ctx.pv_set_search_mode(0)
+    for _ in range(2):
+        got, n_got = run.reencode(T, idx)
+        assert np.array_equal(got, want) and n_got == n_want
+    st = run.ctx.pv_reencode_stats()
+    valid = int((idx < wl.layout.num_groups).sum())
+    assert st["filtered"] + st["fallback"] == valid and st["exact"] == 0
+    assert case != "plain" or st["fallback"] < 0.02 * k + 2      # the certificate holds for nearly every group
+    if case != "odd" and k < 20000:
+        ref, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, idx, wl.codes)
+        check_codes_on(wl, T_np, idx, got, ref, info)
+
+
 def test_reencode_m1_of_a_smaller_k_can_be_captured():
     """The shape was seen with a list that the filter takes; a short list goes another way, and a captured
     call cannot allocate.  The replay also after the context counted something else."""
