@@ -11,8 +11,8 @@
 //   ranked candidates (radix select, then a stable descending sort of the k_max
 //   selected keys: inside one block's LDS when they fit, else the four-pass
 //   device-wide radix sort) -> all candidates re-encoded in place (previous codes saved) ->
-//   squared change per candidate -> prefix sums in rank order -> first prefix
-//   that breaks the bound -> codes of the candidates behind it restored.
+//   squared change per candidate, summed over tiles of ranks -> first prefix in rank order
+//   that breaks the bound, codes of the candidates behind it restored.
 // Everything stays on the device; the kept count is written to device memory.
 //
 // Arithmetic: a group's change is the sum over its weights of
@@ -26,16 +26,13 @@
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kPer = 8;                       // ranks per thread in the scan kernels
-constexpr int kTile = kBlock * kPer;          // ranks per block there
+constexpr int kTilesMax = 2048;               // tiles of ranks at the end, at most
 constexpr unsigned kNone = 0xFFFFFFFFu;
 
-struct tr_state {
-    unsigned first_violation;   // lowest rank r whose prefix of r + 1 groups breaks the bound
-    unsigned first_moved;       // lowest rank whose code tuple moved
-    unsigned kept;              // result
-    unsigned pad;
-    double normsq;
+// A tile of ranks: the sum of its changes, the lowest rank whose code tuple moved.
+struct tr_tile {
+    double sum;
+    unsigned moved, pad;
 };
 
 // fixed-order sum over the block; result valid in thread 0
@@ -60,7 +57,7 @@ __global__ __launch_bounds__(kBlock) void k_tr_gather(const int32_t *__restrict_
                                                       unsigned *__restrict__ keys,
                                                       int32_t *__restrict__ pos,
                                                       const double *__restrict__ norm_partial,
-                                                      int norm_parts, tr_state *__restrict__ state)
+                                                      int norm_parts, double *__restrict__ normsq)
 {
     __shared__ double tmp[kBlock / 64];
     const int j = blockIdx.x * kBlock + threadIdx.x;
@@ -74,12 +71,7 @@ __global__ __launch_bounds__(kBlock) void k_tr_gather(const int32_t *__restrict_
         double acc = 0.0;
         for (int i = threadIdx.x; i < norm_parts; i += kBlock) acc = acc + norm_partial[i];
         acc = block_sum(acc, tmp);
-        if (threadIdx.x == 0) {
-            state->normsq = acc;
-            state->first_violation = kNone;
-            state->first_moved = kNone;
-            state->kept = 0;
-        }
+        if (threadIdx.x == 0) *normsq = acc;
     }
 }
 
@@ -97,11 +89,11 @@ constexpr int kRankTilesMax = 32;
 constexpr int kSmallMax = kRankTile * kRankTilesMax;     // 32768
 // The kernel also does what k_tr_gather does for the device-wide route: the keys are read
 // straight from the scores of the selected groups, the candidates' codes are saved, and block 0
-// adds up the partial norms and resets the state.
+// adds up the partial norms.
 __global__ __launch_bounds__(kSortBlock) void k_tr_sort_tiles(
     const int32_t *__restrict__ idx, const float *__restrict__ scores, int k,
     const uint16_t *__restrict__ codes, int M, uint16_t *__restrict__ old_codes,
-    const double *__restrict__ norm_partial, int norm_parts, tr_state *__restrict__ state,
+    const double *__restrict__ norm_partial, int norm_parts, double *__restrict__ normsq,
     unsigned *__restrict__ tile_keys, int32_t *__restrict__ tile_pos)
 {
     __shared__ unsigned s_key[kRankTile];
@@ -136,10 +128,7 @@ __global__ __launch_bounds__(kSortBlock) void k_tr_sort_tiles(
         if (threadIdx.x == 0) {
             double t = 0.0;
             for (int w = 0; w < kBlock / 64; ++w) t = t + s_norm[w];
-            state->normsq = t;
-            state->first_violation = kNone;
-            state->first_moved = kNone;
-            state->kept = 0;
+            *normsq = t;
         }
     }
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -423,35 +412,29 @@ __global__ __launch_bounds__(kBlock) void k_tr_normsq(const uint16_t *__restrict
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// change of every candidate, stored in rank order (one thread per rank)
-__global__ __launch_bounds__(kBlock) void k_tr_delta(
-    const int32_t *__restrict__ idx, const int32_t *__restrict__ order, int k,
-    const uint16_t *__restrict__ old_codes, const uint16_t *__restrict__ codes,
-    const float *__restrict__ codebooks, const float *__restrict__ scales, int g, int M, int nbits,
-    int gpr, double *__restrict__ delta, uint8_t *__restrict__ moved)
+// The value of another lane (a DPP control); 0 where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v)
 {
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= k) return;
-    const int j = order[r];
-    bool mv;
-    delta[r] = candidate_change(idx[j], j, old_codes, codes, codebooks, scales, g, M, nbits, gpr, &mv);
-    moved[r] = mv ? 1 : 0;
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// Position of a thread's kPer values inside its tile: wave-wide inclusive scan with a fixed
-// association, wave totals added in wave order.  Returns the sum of everything before the
-// thread; *total = sum of the tile.  s_wave: kBlock / 64 doubles of LDS.
-__device__ __forceinline__ double tile_exclusive(double mine, double *s_wave, double *total)
+// Sum of everything before a thread of its block: wave-wide inclusive scan with a fixed
+// association, wave totals added in wave order; *total = sum of the block.  s_wave: kBlock / 64 doubles of LDS.
+__device__ __forceinline__ double block_exclusive(double mine, double *s_wave, double *total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double inc = mine;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        double u = __shfl_up(inc, off);
-        if (lane >= off) inc = u + inc;
-    }
-    double excl = __shfl_up(inc, 1);
-    if (lane == 0) excl = 0.0;
+    inc = inc + dpp_or_zero<0x111, 0xf>(inc);    // one lane below within 16, then 2, 4, 8
+    inc = inc + dpp_or_zero<0x112, 0xf>(inc);
+    inc = inc + dpp_or_zero<0x114, 0xf>(inc);
+    inc = inc + dpp_or_zero<0x118, 0xf>(inc);
+    inc = inc + dpp_or_zero<0x142, 0xa>(inc);    // lane 15 of 32 to its upper 16
+    inc = inc + dpp_or_zero<0x143, 0xc>(inc);    // lane 31 to the upper 32
+    const double excl = dpp_or_zero<0x138, 0xf>(inc);      // one lane below in the wave
     __syncthreads();
     if (lane == 63) s_wave[wave] = inc;
     __syncthreads();
@@ -465,131 +448,156 @@ __device__ __forceinline__ double tile_exclusive(double mine, double *s_wave, do
     return before + excl;
 }
 
-// sum over the ranks [b * kTile, (b + 1) * kTile)
-__global__ __launch_bounds__(kBlock) void k_tr_tile_sums(const double *__restrict__ delta, int k,
-                                                         double *__restrict__ tile_sum)
+// Change of every candidate, stored in rank order; a tile of `rounds` x kBlock ranks a block, whose sum and whose lowest
+// rank with a moved code tuple go to `tiles`.
+__global__ __launch_bounds__(kBlock) void k_tr_delta(
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ order, int k, int rounds,
+    const uint16_t *__restrict__ old_codes, const uint16_t *__restrict__ codes,
+    const float *__restrict__ codebooks, const float *__restrict__ scales, int g, int M, int nbits,
+    int gpr, double *__restrict__ delta, tr_tile *__restrict__ tiles)
 {
-    __shared__ double s_wave[kBlock / 64];
-    const int64_t r0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kPer;
-    double acc = 0.0;
-#pragma unroll
-    for (int e = 0; e < kPer; ++e)
-        if (r0 + e < k) acc = acc + delta[r0 + e];
-    double total;
-    (void)tile_exclusive(acc, s_wave, &total);
-    if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
-}
-
-// one block: exclusive prefix of the tile sums, in place, tile order
-__global__ __launch_bounds__(kBlock) void k_tr_tile_offsets(double *__restrict__ tile_sum, int tiles)
-{
-    __shared__ double s_in[kBlock];
-    __shared__ double s_carry;
-    if (threadIdx.x == 0) s_carry = 0.0;
-    __syncthreads();
-    for (int base = 0; base < tiles; base += kBlock) {
-        const int i = base + threadIdx.x;
-        s_in[threadIdx.x] = i < tiles ? tile_sum[i] : 0.0;
-        __syncthreads();
-        if (threadIdx.x == 0) {               // short and exactly ordered
-            double run = s_carry;
-            for (int t = 0; t < kBlock; ++t) {
-                double v = s_in[t];
-                s_in[t] = run;
-                run = run + v;
-            }
-            s_carry = run;
-        }
-        __syncthreads();
-        if (i < tiles) tile_sum[i] = s_in[threadIdx.x];
-        __syncthreads();
-    }
-}
-
-// prefix sums in rank order; the first prefix that breaks the bound and the first moved
-// group are recorded with atomic minima
-__global__ __launch_bounds__(kBlock) void k_tr_prefix(const double *__restrict__ delta,
-                                                      const uint8_t *__restrict__ moved, int k,
-                                                      const double *__restrict__ tile_off,
-                                                      bool offsets_ready /* else: tile sums */,
-                                                      double ratio, double *__restrict__ prefix,
-                                                      tr_state *__restrict__ state)
-{
-    __shared__ double s_wave[kBlock / 64];
-    const int64_t r0 = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kPer;
-    double d[kPer];
-    unsigned mv = 0;
+    __shared__ tr_tile s_wave[kBlock / 64];
+    const int64_t r0 = (int64_t)blockIdx.x * rounds * kBlock + threadIdx.x;
     double mine = 0.0;
-#pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        d[e] = 0.0;
-        if (r0 + e < k) {
-            d[e] = delta[r0 + e];
-            mv |= (unsigned)(moved[r0 + e] != 0) << e;
+    unsigned first = kNone;                                  // of the wave
+    for (int e = 0; e < rounds; ++e) {
+        const int64_t r = r0 + (int64_t)e * kBlock;
+        bool mv = false;
+        if (r < k) {
+            const int j = order[r];
+            const double d = candidate_change(idx[j], j, old_codes, codes, codebooks, scales, g, M, nbits, gpr, &mv);
+            delta[r] = d;
+            mine = mine + d;
         }
-        mine = mine + d[e];
+        const unsigned long long b = __ballot(mv);
+        if (first == kNone && b) first = (unsigned)(r - (threadIdx.x & 63)) + (unsigned)__ffsll(b) - 1u;
     }
-    double total;
-    double before_tile = 0.0;
-    if (offsets_ready) {
-        before_tile = tile_off[blockIdx.x];
-    } else {              // few tiles: the sums of the tiles before this one, added in tile order
-        for (int t = 0; t < (int)blockIdx.x; ++t) before_tile = before_tile + tile_off[t];
-    }
-    const double off = before_tile + tile_exclusive(mine, s_wave, &total);
-    const double bound = ratio * ratio * state->normsq;
-    unsigned viol = kNone, first_mv = kNone;
-    double run = off;
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) {
-        if (r0 + e < k) {
-            run = run + d[e];
-            prefix[r0 + e + 1] = run;
-            if (!(run < bound) && viol == kNone) viol = (unsigned)(r0 + e);
-            if (((mv >> e) & 1u) && first_mv == kNone) first_mv = (unsigned)(r0 + e);
+    for (int off = 32; off > 0; off >>= 1) mine = mine + __shfl_down(mine, off);
+    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = tr_tile{mine, first, 0u};
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        tr_tile t = s_wave[0];
+        for (int w = 1; w < kBlock / 64; ++w) {
+            t.sum = t.sum + s_wave[w].sum;
+            t.moved = t.moved < s_wave[w].moved ? t.moved : s_wave[w].moved;
         }
+        tiles[blockIdx.x] = t;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) prefix[0] = 0.0;
-    if (viol != kNone) atomicMin(&state->first_violation, viol);
-    if (first_mv != kNone) atomicMin(&state->first_moved, first_mv);
 }
 
-// the kept count with the rule that one moved group always stays
-__device__ __forceinline__ int64_t kept_count(const tr_state *state, int k, int64_t chunk)
+// The result, and the previous codes back into the candidates behind the kept prefix.  Every block adds up all tiles'
+// sums and finds the tile, then the rank, at which the bound breaks, all alike; then it writes the ranks of its own tile.
+// The work is a few dependent loads deep, so launches are what it costs: changes, tile sums, prefix sums with the first
+// violation, and the roll-back as four kernels took 21.9 us on 20 971 candidates, as these two 16.1 (5.9 + 10.3).
+__global__ __launch_bounds__(kBlock) void k_tr_finish(
+    const int32_t *__restrict__ idx, const int32_t *__restrict__ order, int k, int rounds,
+    const uint16_t *__restrict__ old_codes, uint16_t *__restrict__ codes, int M,
+    const double *__restrict__ normsq, const double *__restrict__ delta, const tr_tile *__restrict__ tiles, int ntiles,
+    double ratio, int64_t chunk, int32_t *__restrict__ rank_idx, int64_t *__restrict__ num_applied, double *__restrict__ stats)
 {
-    int64_t kept = state->first_violation == kNone ? k : (int64_t)state->first_violation;
-    if (kept < k && state->first_moved != kNone) {
-        // the chunk that was being applied when the bound broke ends here
+    __shared__ double s_wave[kBlock / 64], s_before, s_sum;
+    __shared__ unsigned s_tile, s_viol, s_moved;
+    const int tid = threadIdx.x;
+    const int64_t span = (int64_t)rounds * kBlock;
+    // (a block's own first ranks are under way while the bound is looked for)
+    const int64_t r_own = (int64_t)blockIdx.x * span + tid;
+    const int own_j = k > 0 ? order[r_own < k ? r_own : 0] : 0;
+    const double nsq = *normsq, bound = ratio * ratio * nsq;
+    if (tid == 0) {
+        s_tile = s_viol = s_moved = kNone;
+        s_before = 0.0;
+    }
+    __syncthreads();
+    // `share` consecutive tiles a thread
+    const int share = (ntiles + kBlock - 1) / kBlock, t0 = tid * share;
+    const tr_tile tile0 = t0 < ntiles ? tiles[t0] : tr_tile{0.0, kNone, 0u};
+    double mine = tile0.sum, total;
+    unsigned moved = tile0.moved;
+    for (int t = t0 + 1; t < t0 + share && t < ntiles; ++t) {
+        const tr_tile v = tiles[t];
+        mine = mine + v.sum;
+        moved = moved < v.moved ? moved : v.moved;
+    }
+    if (moved != kNone) atomicMin(&s_moved, moved);
+    const double off = block_exclusive(mine, s_wave, &total);
+    const int own_n = k > 0 ? idx[own_j] : 0;
+    const uint16_t own_old = k > 0 ? old_codes[(int64_t)own_j * M] : 0;
+    double run = off;
+    for (int t = t0; t < t0 + share && t < ntiles; ++t) {
+        run = run + (t == t0 ? tile0.sum : tiles[t].sum);
+        if (!(run < bound)) {
+            atomicMin(&s_tile, (unsigned)t);
+            break;
+        }
+    }
+    __syncthreads();
+    // the sum of the tiles before t, the same t in every thread
+    auto before_tile = [&](int t) {
+        __syncthreads();
+        if (t < ntiles && t0 <= t && t < t0 + share) {
+            double b = off;
+            for (int u = t0; u < t; ++u) b = b + tiles[u].sum;
+            s_before = b;
+        }
+        if (t >= ntiles && tid == 0) s_before = total;
+        __syncthreads();
+        return s_before;
+    };
+    int64_t kept = k;
+    const unsigned at = s_tile;
+    if (at != kNone) {
+        double before = before_tile((int)at);
+        for (int e = 0; e < rounds && s_viol == kNone; ++e) {
+            const int64_t r = (int64_t)at * span + (int64_t)e * kBlock + tid;
+            const double d = r < k ? delta[r] : 0.0;
+            double part;
+            const double ahead = before + block_exclusive(d, s_wave, &part);
+            const bool breaks = r < k && !(ahead + d < bound);
+            if (breaks) atomicMin(&s_viol, (unsigned)r);
+            before = before + part;
+            __syncthreads();
+            if (breaks && s_viol == (unsigned)r) s_sum = ahead;
+        }
+        // (the tile's sum is rounded in another order: if no prefix in it breaks the bound, the one behind it does)
+        kept = s_viol != kNone ? (int64_t)s_viol : ((int64_t)at + 1) * span;
+        if (kept > k) kept = k;
+    }
+    if (kept < k && s_moved != kNone) {
+        // one moved group always stays, if the chunk that was being applied when the bound broke holds one
         int64_t chunk_end = (kept / chunk + 1) * chunk;
         if (chunk_end > k) chunk_end = k;
-        const int64_t fm = (int64_t)state->first_moved;
+        const int64_t fm = (int64_t)s_moved;
         if (fm >= kept && fm < chunk_end) kept = fm + 1;
     }
-    return kept;
-}
-
-// previous codes back into the candidates behind the kept prefix; ranked ids and results out
-__global__ __launch_bounds__(kBlock) void k_tr_rollback(
-    const int32_t *__restrict__ idx, const int32_t *__restrict__ order, int k,
-    const uint16_t *__restrict__ old_codes, uint16_t *__restrict__ codes, int M,
-    const tr_state *__restrict__ state, const double *__restrict__ prefix, int64_t chunk,
-    int32_t *__restrict__ rank_idx, int64_t *__restrict__ num_applied, double *__restrict__ stats)
-{
-    const int64_t kept = kept_count(state, k, chunk);   // the same in every thread
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r == 0) {
-        if (num_applied) *num_applied = kept;
-        if (stats) {
-            stats[0] = k > 0 ? prefix[kept] : 0.0;
-            stats[1] = state->normsq;
+    if (blockIdx.x == 0) {
+        __syncthreads();
+        double sum = at == kNone ? total : s_sum;
+        if (at != kNone && kept != (int64_t)s_viol) {        // one more group stays, or none in the tile
+            const int64_t tile = kept / span;
+            double mine_in = 0.0, inside;
+            for (int64_t r = tile * span + tid; r < kept; r += kBlock) mine_in = mine_in + delta[r];
+            sum = before_tile((int)tile);
+            (void)block_exclusive(mine_in, s_wave, &inside);
+            sum = sum + inside;
+        }
+        if (tid == 0) {
+            if (num_applied) *num_applied = kept;
+            if (stats) {
+                stats[0] = sum;
+                stats[1] = nsq;
+            }
         }
     }
-    if (r >= k) return;
-    const int j = order[r];
-    const int64_t n = idx[j];
-    if (rank_idx) rank_idx[r] = (int32_t)n;
-    if (r >= kept)
-        for (int m = 0; m < M; ++m) codes[n * M + m] = old_codes[(int64_t)j * M + m];
+    for (int e = 0; e < rounds; ++e) {
+        const int64_t r = r_own + (int64_t)e * kBlock;
+        if (r >= k) break;
+        const int j = e ? order[r] : own_j;
+        const int64_t n = e ? idx[j] : own_n;
+        if (rank_idx) rank_idx[r] = (int32_t)n;
+        if (r >= kept)
+            for (int m = 0; m < M; ++m) codes[n * M + m] = e || m ? old_codes[(int64_t)j * M + m] : own_old;
+    }
 }
 
 inline size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -605,7 +613,9 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     const int g = l->group_size, M = l->num_codebooks;
     const int gpr = (int)(l->in_features / g);
     const int k = (int)k_max;
-    const int tiles = (k + kTile - 1) / kTile;
+    // tiles of ranks for the decision: a block each, `rounds` x kBlock ranks
+    const int rounds = k > 0 ? (int)(((int64_t)k + (int64_t)kTilesMax * kBlock - 1) / ((int64_t)kTilesMax * kBlock)) : 1;
+    const int ntiles = k > 0 ? (int)(((int64_t)k + (int64_t)rounds * kBlock - 1) / ((int64_t)rounds * kBlock)) : 0;
     int norm_blocks = (int)((N + 1023) / 1024);       // a round of gathers per thread: latency, not volume, sets the time
     if (norm_blocks > 4096) norm_blocks = 4096;
     if (norm_blocks < 1) norm_blocks = 1;
@@ -615,18 +625,16 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     const bool small_sort = k <= kSmallMax;
     // one scratch block, carved up
     const size_t kk = (size_t)(k > 0 ? k : 1);
-    size_t o_state = 0;
-    size_t o_idx = o_state + align_up(sizeof(tr_state));
+    size_t o_normsq = 0;
+    size_t o_idx = o_normsq + align_up(sizeof(double));
     size_t o_keys = o_idx + align_up(kk * 4);
     size_t o_keys2 = o_keys + align_up(kk * 4);
     size_t o_pos = o_keys2 + align_up(kk * 4);
     size_t o_order = o_pos + align_up(kk * 4);
     size_t o_old = o_order + align_up(kk * 4);
     size_t o_delta = o_old + align_up(kk * M * 2);
-    size_t o_prefix = o_delta + align_up(kk * 8);
-    size_t o_moved = o_prefix + align_up((kk + 1) * 8);
-    size_t o_tiles = o_moved + align_up(kk);
-    size_t o_norm = o_tiles + align_up((size_t)(tiles > 0 ? tiles : 1) * 8);
+    size_t o_tiles = o_delta + align_up(kk * 8);
+    size_t o_norm = o_tiles + align_up((size_t)(ntiles > 0 ? ntiles : 1) * sizeof(tr_tile));
     size_t o_keys3 = o_norm + align_up((size_t)(norm_blocks > pv_select_norm_parts() ? norm_blocks : pv_select_norm_parts()) * 8);
     size_t o_vals2 = o_keys3 + align_up(small_sort ? 0 : kk * 4);
     size_t o_hist = o_vals2 + align_up(small_sort ? 0 : kk * 4);
@@ -639,7 +647,7 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     st = pv_select_scores(ctx, N, &scores);
     if (st != PV_OK) return st;
     char *base = static_cast<char *>(ctx->trust.ptr);
-    tr_state *state = reinterpret_cast<tr_state *>(base + o_state);
+    double *normsq = reinterpret_cast<double *>(base + o_normsq);
     int32_t *idx = reinterpret_cast<int32_t *>(base + o_idx);
     unsigned *keys = reinterpret_cast<unsigned *>(base + o_keys);
     unsigned *keys2 = reinterpret_cast<unsigned *>(base + o_keys2);
@@ -647,9 +655,7 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     int32_t *order = reinterpret_cast<int32_t *>(base + o_order);
     uint16_t *old_codes = reinterpret_cast<uint16_t *>(base + o_old);
     double *delta = reinterpret_cast<double *>(base + o_delta);
-    double *prefix = reinterpret_cast<double *>(base + o_prefix);
-    uint8_t *moved = reinterpret_cast<uint8_t *>(base + o_moved);
-    double *tile_sum = reinterpret_cast<double *>(base + o_tiles);
+    tr_tile *tiles = reinterpret_cast<tr_tile *>(base + o_tiles);
     double *norm_partial = reinterpret_cast<double *>(base + o_norm);
     unsigned *keys3 = reinterpret_cast<unsigned *>(base + o_keys3);
     int32_t *vals2 = reinterpret_cast<int32_t *>(base + o_vals2);
@@ -688,12 +694,12 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
         pv_timed t(ctx, PV_K_TRUST_RATIO);
         if (!(k > 0 && small_sort))
             hipLaunchKernelGGL(k_tr_gather, dim3(kblocks > 0 ? kblocks : 1), dim3(kBlock), 0, sm, idx, k,
-                               scores, codes, M, old_codes, keys, pos, norm_partial, norm_blocks, state);
+                               scores, codes, M, old_codes, keys, pos, norm_partial, norm_blocks, normsq);
         // descending keys; equal keys keep their order (ascending ids): the sort is stable
         if (k > 0 && small_sort) {
             const unsigned rtiles = (unsigned)((k + kRankTile - 1) / kRankTile);
             hipLaunchKernelGGL(k_tr_sort_tiles, dim3(rtiles), dim3(kSortBlock), 0, sm, idx, scores, k, codes,
-                               M, old_codes, norm_partial, norm_blocks, state, keys2, pos);
+                               M, old_codes, norm_partial, norm_blocks, normsq, keys2, pos);
             hipLaunchKernelGGL(k_tr_merge_ranks, dim3((unsigned)((k + kMergeCands - 1) / kMergeCands)),
                                dim3(kSortBlock), 0, sm, keys2, pos, k, order);
         } else if (k > 0) {
@@ -731,18 +737,11 @@ pv_status pv_launch_trust_ratio(pv_ctx *ctx, const pv_layout *l, const float *T,
     }
     {
         pv_timed t(ctx, PV_K_TRUST_RATIO);
-        if (k > 0) {
-            hipLaunchKernelGGL(k_tr_delta, dim3(kblocks), dim3(kBlock), 0, sm, idx, order, k, old_codes,
-                               codes, codebooks, scales, g, M, l->nbits, gpr, delta, moved);
-            hipLaunchKernelGGL(k_tr_tile_sums, dim3(tiles), dim3(kBlock), 0, sm, delta, k, tile_sum);
-            const bool few = tiles <= 256;   // then every block adds the earlier tile sums itself
-            if (!few)
-                hipLaunchKernelGGL(k_tr_tile_offsets, dim3(1), dim3(kBlock), 0, sm, tile_sum, tiles);
-            hipLaunchKernelGGL(k_tr_prefix, dim3(tiles), dim3(kBlock), 0, sm, delta, moved, k,
-                               (const double *)tile_sum, !few, ratio, prefix, state);
-        }
-        hipLaunchKernelGGL(k_tr_rollback, dim3(kblocks > 0 ? kblocks : 1), dim3(kBlock), 0, sm, idx,
-                           order, k, old_codes, codes, M, state, prefix, chunk, rank_idx, num_applied,
+        if (k > 0)
+            hipLaunchKernelGGL(k_tr_delta, dim3(ntiles), dim3(kBlock), 0, sm, idx, order, k, rounds, old_codes,
+                               codes, codebooks, scales, g, M, l->nbits, gpr, delta, tiles);
+        hipLaunchKernelGGL(k_tr_finish, dim3(ntiles > 0 ? ntiles : 1), dim3(kBlock), 0, sm, idx, order, k, rounds,
+                           old_codes, codes, M, normsq, delta, tiles, ntiles, ratio, chunk, rank_idx, num_applied,
                            stats);
     }
     PV_HIP(ctx, hipGetLastError());

@@ -116,3 +116,15 @@ def test_trust_ratio_ranks_more_candidates_than_one_block_sorts(k_max):
     wl.G[rng.random(wl.G.shape) < 0.3] = 0.0
     L, info = run_case(wl, k_max=k_max, chunk=997, ratio=0.02)
     assert 0 < L <= k_max
+
+
+@pytest.mark.parametrize("ratio", [1e-7, 0.05, 0.25, 1e30])
+@pytest.mark.parametrize("shape,k_max", [
+    ((64, 256), 255), ((64, 256), 257),                          # around one tile of 256 ranks
+    ((1024, 520), 65536), ((1024, 520), 65537),                  # one and two tiles a thread of the deciding blocks
+    ((2048, 2056), 524288), ((2048, 2056), 524289),              # 2048 tiles of one round of ranks, then of two
+])
+def test_trust_ratio_decides_over_tiles_of_ranks(shape, k_max, ratio):
+    wl = workloads.make(shape[0], shape[1], 8, 1, 6, seed=46, sigma_g=1e-2)
+    L, info = run_case(wl, k_max=k_max, chunk=997, ratio=ratio)
+    assert 0 < L <= k_max
