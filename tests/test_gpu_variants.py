@@ -231,6 +231,29 @@ def test_stochastic_rounding_on_inputs_that_strain_the_filter(g, B):
         ctx.close()
 
 
+@pytest.mark.parametrize("shape,g,B", [((64, 1024), 8, 13), ((256, 2048), 8, 16), ((1024, 2048), 8, 16),
+                                       ((64, 2048), 16, 14), ((512, 4096), 16, 13)])
+def test_stochastic_rounding_filtered_like_the_scan(shape, g, B):
+    """Few and many groups (the codebook in many parts and in few, so that a part has up to hundreds of
+    positions a lane), rows without a usable scale (every position of every part), twins; the scan in
+    double precision is the reference, code by code."""
+    wl = workloads.make(shape[0], shape[1], g, 1, B, sigma_g=5e-3, seed=900 + B)
+    cb = wl.codebooks
+    cb[0, 5::97] = cb[0, 4:-1:97][:len(cb[0, 5::97])]
+    wl.scales[3] = 0.0
+    wl.scales[5] = 1e-20
+    T = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    T[9] *= 1e6
+    idx = np.arange(wl.layout.num_groups, dtype=np.int32)
+    out = []
+    for mode in (0, 1):
+        ctx = PVContext(0)
+        ctx.pv_set_search_mode(mode)
+        out.append(stochastic_on_gpu(ctx, wl, T, idx, 5, 77))
+        ctx.close()
+    assert out[0][1] == out[1][1] and np.array_equal(out[0][0], out[1][0])
+
+
 @pytest.mark.parametrize("g,M,B,beam,stochastic", [(8, 1, 12, 1, False), (16, 1, 11, 1, False), (8, 2, 8, 8, False),
                                                    (8, 1, 12, 1, True), (16, 1, 10, 1, True),
                                                    (16, 1, 10, 1, False), (8, 1, 8, 1, False),
