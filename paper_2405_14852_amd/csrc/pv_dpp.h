@@ -10,6 +10,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <type_traits>
+#include <utility>
 
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141, kDppMirror16 = 0x140;
 
@@ -31,6 +32,22 @@ template <int CTRL>
 __device__ __forceinline__ double pv_dpp_f64(double v)
 {
     return __hiloint2double(pv_dpp<CTRL>(__double2hiint(v)), pv_dpp<CTRL>(__double2loint(v)));
+}
+
+// lane LANE of every row of 16, to the whole row
+template <int LANE>
+__device__ __forceinline__ double pv_dpp_f64_row(double v)
+{
+    return __longlong_as_double(__builtin_amdgcn_update_dpp((long long)0, __double_as_longlong(v), 0x150 + LANE, 0xf, 0xf, false));
+}
+
+// the sum over a row of 16 lanes, from 0 on, in the order of the lanes; the whole row gets it
+template <int... LANE>
+__device__ __forceinline__ double pv_row_sum_in_order(double v, std::integer_sequence<int, LANE...>)
+{
+    double sum = 0.0;
+    ((sum = sum + pv_dpp_f64_row<LANE>(v)), ...);
+    return sum;
 }
 
 // f(integral_constant<int, control word>) once per stage of a TEAM of 8 or 16 lanes

@@ -1079,6 +1079,17 @@ __device__ __forceinline__ double exact_obj(const float *__restrict__ cw, float 
     return obj;
 }
 
+// The same for 16 dimensions, one a lane of a row of 16 that works on one codeword together: the lane's square, then
+// the sum in the order of the dimensions, every lane adding the same numbers.  A lane that takes all dimensions
+// alone keeps its team waiting for 80 instructions a codeword, this is 35 and a load of 64 bytes; and the best needs no search
+// over the team.  The re-rank at g = 16 is bound by instructions issued (60 % of its cycles, at the clock that the matrix
+// product before it leaves): 31.7 -> 25.7 M, 119 -> 111 us on 183 500 groups of 16, 65 536 codewords.
+__device__ __forceinline__ double exact_obj_row(const float *__restrict__ cw, float s, float t, int q)
+{
+    const double r = fma((double)s, (double)cw[q], -(double)t);
+    return pv_row_sum_in_order(r * r, std::make_integer_sequence<int, 16>{});
+}
+
 // largest value a key can stand for: the super-unit bits replaced by ones; a negative key
 // (every value behind it negative) is bounded by zero
 __device__ __forceinline__ float key_upper(int key)
@@ -1156,7 +1167,7 @@ struct open_rec_t {
 // block waits for another and none publishes plain stores to another (a device-wide release
 // costs a write-back of the whole L2 of the block's die).
 #ifndef PV_RR_OCC
-#define PV_RR_OCC 4   // blocks of the re-rank kernel per compute unit the register budget must allow (g = 16: 149 -> 128 registers, four waves per SIMD instead of three; five would spill)
+#define PV_RR_OCC 4   // waves per SIMD that the register budget of the re-rank kernel must allow; g = 16: five without a spill since a lane holds one dimension (six spill: 12-bit codebook 148.8 us a search against 146.9, four 154.9)
 #endif
 // v_sqrt_f32 and v_rcp_f32 as they are (1 ulp each; the library's sqrtf and the division add a
 // dozen instructions apiece to round correctly and to scale denormal arguments).  Every use
@@ -1170,7 +1181,7 @@ __device__ __forceinline__ float fast_rcp(float v) { return __builtin_amdgcn_rcp
 __device__ __forceinline__ float float_above(double v) { return (float)v * 1.0000002f; }
 
 template <int G, bool CELLS>
-__global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
+__global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
     const float *__restrict__ x_stage, const float *__restrict__ codebook, int k, int k_pad,
     const int2 *__restrict__ partials, int P, int per_half, int ncyc, int nsplit,
     const int *__restrict__ su_bounds, const float *__restrict__ dense, int dense_P, int dense_per_half,
@@ -1183,6 +1194,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
     constexpr int kTeam = rerank_team(G);          // lanes per group
     constexpr int kTeams = kBlock / kTeam;         // groups per block
     constexpr int kPer = 16 / kTeam;               // positions of a half tile per lane
+    constexpr bool kWide = G == 16 && kTeam == 16; // a lane a dimension, the team takes one objective together
     static_assert(kTeam == 8 || kTeam == 16, "a team is 8 or 16 consecutive lanes");
     __shared__ unsigned s_cnt[4];   // groups decided by the teams, codes changed, candidates evaluated, groups scanned
     __shared__ open_rec_t s_open[kTeams];
@@ -1220,15 +1232,24 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
     }
     if (live) {
         const float s = tail.x;
-        float t[G];
+        float t[kWide ? 1 : G];
+        if constexpr (kWide) {
+            t[0] = reinterpret_cast<const float *>(stage)[q];
+        } else {
 #pragma unroll
-        for (int v4 = 0; v4 < G / 4; ++v4) {
-            pv_f4 v = stage[v4];
-            t[v4 * 4 + 0] = v.x;
-            t[v4 * 4 + 1] = v.y;
-            t[v4 * 4 + 2] = v.z;
-            t[v4 * 4 + 3] = v.w;
+            for (int v4 = 0; v4 < G / 4; ++v4) {
+                pv_f4 v = stage[v4];
+                t[v4 * 4 + 0] = v.x;
+                t[v4 * 4 + 1] = v.y;
+                t[v4 * 4 + 2] = v.z;
+                t[v4 * 4 + 3] = v.w;
+            }
         }
+        // of one codeword for the whole team (kWide), else of each lane's own
+        auto objective = [&](int cw) {
+            if constexpr (kWide) return exact_obj_row(codebook + (int64_t)cw * G, s, t[0], q);
+            else return exact_obj<G>(codebook + (int64_t)cw * G, s, t);
+        };
         const int prev = __float_as_int(tail.y);
         constexpr int kMaxRec = 64 / kTeam;  // P <= 64
         int2 rec[kMaxRec];
@@ -1237,7 +1258,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
             int p = q + kTeam * u;
             rec[u] = p < P ? partials[rec_at(p, j, P, k_pad)] : make_int2(kNoKey, kNoKey);
         }
-        const double o_prev = exact_obj<G>(codebook + (int64_t)prev * G, s, t);
+        const double o_prev = objective(prev);
         // best key over all partitions, with its partition
         long long bk = (long long)0x8000000000000000ull;
 #pragma unroll
@@ -1292,10 +1313,35 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                 if (!CELLS && pos[i] >= csize) dd[i] = __builtin_huge_valf();
         };
         auto exact_at = [&](int cw, cand_t &c) {
-            const double o = exact_obj<G>(codebook + (int64_t)cw * G, s, t);
+            const double o = objective(cw);
             if (cand_better(o, cw, c.obj, c.idx)) {
                 c.obj = o;
                 c.idx = cw;
+            }
+        };
+        // exact objectives of every lane's positions in `todo`; kWide: one after the other for the team
+        unsigned exact_evals = 1;                      // the previous code
+        const int team_shift = (threadIdx.x & 63) & ~(kTeam - 1);
+        auto exact_of = [&](unsigned todo, const int (&cwd)[kMine], cand_t &c) {
+            if constexpr (kWide) {
+                for (;;) {
+                    const unsigned team = (unsigned)((__ballot(todo != 0) >> team_shift) & ((1ull << kTeam) - 1ull));
+                    if (!team) break;
+                    int cw = cwd[kMine - 1];
+#pragma unroll
+                    for (int uu = kMine - 1; uu-- > 0;) cw = (todo >> uu) & 1u ? cwd[uu] : cw;
+                    const int src = __ffs((int)team) - 1;
+                    exact_at(__shfl(cw, src, kTeam), c);
+                    if (q == src) todo &= todo - 1u;
+                    ++exact_evals;
+                }
+            } else {
+#pragma unroll
+                for (int uu = 0; uu < kMine; ++uu)
+                    if ((todo >> uu) & 1u) {
+                        exact_at(cwd[uu], c);
+                        ++exact_evals;
+                    }
             }
         };
         // upper bound, in fp32 with every rounding covered, of (P sqrt(E) / |s| + dC + dx)^2
@@ -1322,7 +1368,6 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
         cand_t mine;
         mine.obj = __builtin_huge_val();
         mine.idx = 0x7fffffff;
-        unsigned exact_evals = 1;                      // the previous code
         double e_star = o_prev;
         if (best_key != kNoKey) {
             float dd[kMine];
@@ -1337,28 +1382,37 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                     dmin = dd[uu];
                     wu = uu;
                 }
-            unsigned long long pick = ((unsigned long long)__float_as_uint(dmin) << 32) | (unsigned)q;
+            int pw = cwd[0];                       // cwd[wu] without dynamic register indexing
+#pragma unroll
+            for (int uu = 1; uu < kMine; ++uu)
+                if (uu == wu) pw = cwd[uu];
+            unsigned long long pick = ((unsigned long long)__float_as_uint(dmin) << 32) | (kWide ? ((unsigned)pw << 4) | q : (unsigned)q);
             pick = pv_team_min_u64<kTeam>(pick);
             const bool chosen = (int)(pick & 15u) == q && dmin < 3.0e38f;
-            if (chosen) {
-                int pw = cwd[0];                   // cwd[wu] without dynamic register indexing
-#pragma unroll
-                for (int uu = 1; uu < kMine; ++uu)
-                    if (uu == wu) pw = cwd[uu];
-                exact_at(pw, mine);
-            }
-            const double o0 = __shfl(mine.obj, (int)(pick & 15u), kTeam);
-            if (o0 < e_star) e_star = o0;
-            const float r2f = reach2_of(e_star);
-#pragma unroll
-            for (int uu = 0; uu < kMine; ++uu)
-                if (!(chosen && uu == wu) && dd[uu] - dabs <= r2f && dd[uu] < 3.0e38f) {
-                    exact_at(cwd[uu], mine);
+            double o0;
+            if constexpr (kWide) {
+                const bool any = __uint_as_float((unsigned)(pick >> 32)) < 3.0e38f;      // the same in the whole team
+                if (any) {
+                    exact_at((int)((unsigned)pick >> 4), mine);
                     ++exact_evals;
                 }
-            if (chosen) ++exact_evals;
+                o0 = mine.obj;
+            } else {
+                if (chosen) {
+                    exact_at(pw, mine);
+                    ++exact_evals;
+                }
+                o0 = __shfl(mine.obj, (int)(pick & 15u), kTeam);
+            }
+            if (o0 < e_star) e_star = o0;
+            const float r2f = reach2_of(e_star);
+            unsigned todo = 0;
+#pragma unroll
+            for (int uu = 0; uu < kMine; ++uu)
+                if (!(chosen && uu == wu) && dd[uu] - dabs <= r2f && dd[uu] < 3.0e38f) todo |= 1u << uu;
+            exact_of(todo, cwd, mine);
         }
-        cand_t first = team_min(mine);
+        cand_t first = kWide ? mine : team_min(mine);
         if (first.obj < e_star) e_star = first.obj;
 
         // every codeword that was not evaluated and could still reach E* sits behind a key
@@ -1380,9 +1434,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
             }
         }
         open = pv_team_or_u64<kTeam>(open);
-        const int team_shift = (threadIdx.x & 63) & ~(kTeam - 1);
         // the best key of every other partition at or above kcut: its positions are evaluated here
-        unsigned extra = 0;
         for (;;) {
             const unsigned long long pb = __ballot(pending != 0);
             const unsigned team = (unsigned)((pb >> team_shift) & ((1ull << kTeam) - 1ull));
@@ -1399,19 +1451,16 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                 float dd[kMine];
                 int pos[kMine], cwd[kMine];
                 level1(key, src + kTeam * u, dd, pos, cwd);
+                unsigned todo = 0;
 #pragma unroll
                 for (int uu = 0; uu < kMine; ++uu)
-                    if (dd[uu] - dabs <= reach2f && dd[uu] < 3.0e38f) {
-                        exact_at(cwd[uu], mine);
-                        ++exact_evals;
-                    }
+                    if (dd[uu] - dabs <= reach2f && dd[uu] < 3.0e38f) todo |= 1u << uu;
+                exact_of(todo, cwd, mine);
             }
             if (q == src) pending &= ~(1u << u);
-            ++extra;
         }
-        (void)extra;
-        exact_evals = pv_team_sum_u32<kTeam>(exact_evals);
-        const cand_t win = team_min(mine);
+        if (!kWide) exact_evals = pv_team_sum_u32<kTeam>(exact_evals);
+        const cand_t win = kWide ? mine : team_min(mine);
         if (q == 0) {
             if (open) {
                 // a partition may hide further codewords at or above kcut: all of its
@@ -1433,7 +1482,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                 }
                 atomicAdd(&s_cnt[0], 1u);
             }
-            atomicAdd(&s_cnt[2], exact_evals - (unsigned)(kTeam - 1));   // the previous code was counted by every lane
+            atomicAdd(&s_cnt[2], exact_evals - (kWide ? 0u : (unsigned)(kTeam - 1)));   // the previous code was counted by every lane
         }
     }
     __syncthreads();
@@ -1450,18 +1499,22 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
         const pv_f4 *stage2 = reinterpret_cast<const pv_f4 *>(x_stage + (int64_t)rec.j * (G + 4));
         const pv_f4 tail2 = stage2[G / 4];
         const float s = tail2.x;
-        float t[G];
-#pragma unroll
-        for (int v4 = 0; v4 < G / 4; ++v4) {
-            pv_f4 v = stage2[v4];
-            t[v4 * 4 + 0] = v.x;
-            t[v4 * 4 + 1] = v.y;
-            t[v4 * 4 + 2] = v.z;
-            t[v4 * 4 + 3] = v.w;
-        }
         const int prev = __float_as_int(tail2.y);
         const int lane = threadIdx.x & 63;
         const int qq = threadIdx.x & 15, slot = threadIdx.x >> 4;
+        float t[kWide ? 1 : G];
+        if constexpr (kWide) {
+            t[0] = reinterpret_cast<const float *>(stage2)[qq];
+        } else {
+#pragma unroll
+            for (int v4 = 0; v4 < G / 4; ++v4) {
+                pv_f4 v = stage2[v4];
+                t[v4 * 4 + 0] = v.x;
+                t[v4 * 4 + 1] = v.y;
+                t[v4 * 4 + 2] = v.z;
+                t[v4 * 4 + 3] = v.w;
+            }
+        }
         constexpr int kSlots = kBlock / 16;
         // the group's fp16 operand as the matrix cores saw it
         h8 xq[G / 8];
@@ -1511,14 +1564,27 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
 #pragma unroll
                     for (int uu = 0; uu < kU; ++uu) {
                         const int pos = ((su * 2 + hw) * kU + uu) * 16 + qq;
-                        if (su < su_end && (CELLS ? dd[bb][uu] < 3.0e38f : pos < csize) &&
-                            (!test || dd[bb][uu] - dabs <= r2f)) {
-                            const int cw = G == 8 && !CELLS ? pos : (int)perm[pos];
-                            const double obj = exact_obj<G>(codebook + (int64_t)cw * G, s, t);
-                            if (cand_better(obj, cw, mine.obj, mine.idx)) {
+                        bool in = su < su_end && (CELLS ? dd[bb][uu] < 3.0e38f : pos < csize) &&
+                                  (!test || dd[bb][uu] - dabs <= r2f);
+                        int cw = 0;
+                        if (in) cw = G == 8 && !CELLS ? pos : (int)perm[pos];
+                        auto take = [&](int c, double obj) {
+                            if (cand_better(obj, c, mine.obj, mine.idx)) {
                                 mine.obj = obj;
-                                mine.idx = cw;
+                                mine.idx = c;
                             }
+                        };
+                        if constexpr (kWide) {           // one codeword after the other, by the row of lanes
+                            for (;;) {
+                                const unsigned row_in = (unsigned)(__ballot(in) >> (lane & 48)) & 0xFFFFu;
+                                if (!row_in) break;
+                                const int src = __ffs((int)row_in) - 1;
+                                const int c = __shfl(cw, src, 16);
+                                take(c, exact_obj_row(codebook + (int64_t)c * G, s, t[0], qq));
+                                in = in && qq != src;
+                            }
+                        } else if (in) {
+                            take(cw, exact_obj<G>(codebook + (int64_t)cw * G, s, t));
                         }
                     }
                 }
@@ -1540,6 +1606,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
             s_idx[threadIdx.x >> 6] = mine.idx;
         }
         __syncthreads();
+        const double o_prev2 = kWide ? exact_obj_row(codebook + (int64_t)prev * G, s, t[0], qq) : 0.0;
         if (threadIdx.x == 0) {
             cand_t win;
             win.obj = rec.obj;
@@ -1549,7 +1616,8 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_rerank(
                     win.obj = s_obj[w];
                     win.idx = s_idx[w];
                 }
-            const double o_prev = exact_obj<G>(codebook + (int64_t)prev * G, s, t);
+            double o_prev = o_prev2;
+            if constexpr (!kWide) o_prev = exact_obj<G>(codebook + (int64_t)prev * G, s, t);
             int pick = win.idx;
             if (o_prev <= win.obj || pick == 0x7fffffff) pick = prev;
             if (pick != prev) {

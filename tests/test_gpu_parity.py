@@ -504,6 +504,41 @@ def test_reencode_m1_small_codebook(g, B, k, case):
         check_codes_on(wl, T_np, idx, got, ref, info)
 
 
+@pytest.mark.parametrize("B,k", [(12, 2051), (12, 16400), (13, 16385), (14, 4099), (16, 1037)])
+@pytest.mark.parametrize("case", ["plain", "ties", "odd"])
+def test_reencode_m1_g16_row_of_lanes_a_codeword(B, k, case):
+    """Groups of 16 behind the filter: a row of lanes takes one codeword at a time.  Several codewords of a lane and of a
+    row within reach (ties), partitions left open, values that are not finite, scales of zero and below, ids outside the
+    matrix.  Codes and count equal the exact scan's."""
+    wl = workloads.make(160, 2048, 16, 1, B, seed=103, sigma_g=2e-3, tau=1.0)
+    rng = np.random.default_rng(k)
+    if case == "ties":
+        wl.codebooks[0, 1::2] = wl.codebooks[0, ::2]
+        wl.codebooks[0, -40:] = 0.0
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    if case == "ties":
+        T_np[::3] = 0.0
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    if case == "odd":
+        wl.scales[::5] = 0.0
+        wl.scales[1::5] *= np.float32(-1.0)
+        wl.scales[2::5] *= np.float32(1e-3)
+        if k % 2:
+            wl.codebooks[0, 3, 1], wl.codebooks[0, 5, 0] = np.nan, np.inf
+        T_np[2, 7], T_np[9] = np.inf, np.nan
+        idx = np.sort(np.where(rng.random(k) < 0.1, idx + wl.layout.num_groups, idx)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx)
+    run.ctx.pv_set_search_mode(0)
+    got, n_got = run.reencode(T, idx)
+    assert np.array_equal(got, want) and n_got == n_want
+    st = run.ctx.pv_reencode_stats()
+    valid = int((idx < wl.layout.num_groups).sum())
+    assert st["filtered"] + st["fallback"] == valid and st["exact"] == 0
+    assert st["reranked_candidates"] <= 64 * valid       # what the team looks at beside the open partitions
+
+
 def test_reencode_m1_of_a_smaller_k_can_be_captured():
     """The shape was seen with a list that the filter takes; a short list goes another way, and a captured
     call cannot allocate.  The replay also after the context counted something else."""
