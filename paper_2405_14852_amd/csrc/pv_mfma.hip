@@ -1082,8 +1082,8 @@ __device__ __forceinline__ double exact_obj(const float *__restrict__ cw, float 
 // The same for 16 dimensions, one a lane of a row of 16 that works on one codeword together: the lane's square, then
 // the sum in the order of the dimensions, every lane adding the same numbers.  A lane that takes all dimensions
 // alone keeps its team waiting for 80 instructions a codeword, this is 35 and a load of 64 bytes; and the best needs no search
-// over the team.  The re-rank at g = 16 is bound by instructions issued (60 % of its cycles, at the clock that the matrix
-// product before it leaves): 31.7 -> 25.7 M, 119 -> 111 us on 183 500 groups of 16, 65 536 codewords.
+// over the team.  Many groups of 16 are bound by instructions issued (60 % of the re-rank's cycles, at the clock that the
+// matrix product before it leaves): 31.7 -> 25.7 M, 119 -> 109 us on 183 500 groups, 65 536 codewords.
 __device__ __forceinline__ double exact_obj_row(const float *__restrict__ cw, float s, float t, int q)
 {
     const double r = fma((double)s, (double)cw[q], -(double)t);
@@ -1167,7 +1167,7 @@ struct open_rec_t {
 // block waits for another and none publishes plain stores to another (a device-wide release
 // costs a write-back of the whole L2 of the block's die).
 #ifndef PV_RR_OCC
-#define PV_RR_OCC 4   // waves per SIMD that the register budget of the re-rank kernel must allow; g = 16: five without a spill since a lane holds one dimension (six spill: 12-bit codebook 148.8 us a search against 146.9, four 154.9)
+#define PV_RR_OCC 4   // waves per SIMD that the register budget of the re-rank kernel must allow (g = 16: 149 -> 128 registers, four waves instead of three; five would spill, but where a lane holds one dimension)
 #endif
 // v_sqrt_f32 and v_rcp_f32 as they are (1 ulp each; the library's sqrtf and the division add a
 // dozen instructions apiece to round correctly and to scale denormal arguments).  Every use
@@ -1180,8 +1180,12 @@ __device__ __forceinline__ float fast_rcp(float v) { return __builtin_amdgcn_rcp
 // applied before the root takes over
 __device__ __forceinline__ float float_above(double v) { return (float)v * 1.0000002f; }
 
-template <int G, bool CELLS>
-__global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
+// WIDE from two rounds of blocks on, where the instructions issued count; below, the chain of one block does, which the
+// sums over a row make longer.  Whole searches, 14 bits: 7 864 groups 64.6 us (a lane a codeword: 62.2), 16 252 71.4 (70.7),
+// 32 505 96.0 (96.2), 65 536 115.9 (118.8); 16 bits: 32 505 133.8 (135.7), 183 500 508.7 (520.2); 12 bits: 183 500 143 (157).
+constexpr int64_t kWideFrom = 32768;
+template <int G, bool CELLS, bool WIDE = false>
+__global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
     const float *__restrict__ x_stage, const float *__restrict__ codebook, int k, int k_pad,
     const int2 *__restrict__ partials, int P, int per_half, int ncyc, int nsplit,
     const int *__restrict__ su_bounds, const float *__restrict__ dense, int dense_P, int dense_per_half,
@@ -1194,7 +1198,7 @@ __global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
     constexpr int kTeam = rerank_team(G);          // lanes per group
     constexpr int kTeams = kBlock / kTeam;         // groups per block
     constexpr int kPer = 16 / kTeam;               // positions of a half tile per lane
-    constexpr bool kWide = G == 16 && kTeam == 16; // a lane a dimension, the team takes one objective together
+    constexpr bool kWide = WIDE && G == 16 && kTeam == 16; // a lane a dimension, the team takes one objective together
     static_assert(kTeam == 8 || kTeam == 16, "a team is 8 or 16 consecutive lanes");
     __shared__ unsigned s_cnt[4];   // groups decided by the teams, codes changed, candidates evaluated, groups scanned
     __shared__ open_rec_t s_open[kTeams];
@@ -1502,19 +1506,19 @@ __global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
         const int prev = __float_as_int(tail2.y);
         const int lane = threadIdx.x & 63;
         const int qq = threadIdx.x & 15, slot = threadIdx.x >> 4;
-        float t[kWide ? 1 : G];
-        if constexpr (kWide) {
-            t[0] = reinterpret_cast<const float *>(stage2)[qq];
-        } else {
+        // kWide: the targets are read again for each exact objective (from a cache), they are registers that spill
+        float own[kWide ? 1 : G];
+        if constexpr (!kWide) {
 #pragma unroll
             for (int v4 = 0; v4 < G / 4; ++v4) {
                 pv_f4 v = stage2[v4];
-                t[v4 * 4 + 0] = v.x;
-                t[v4 * 4 + 1] = v.y;
-                t[v4 * 4 + 2] = v.z;
-                t[v4 * 4 + 3] = v.w;
+                own[v4 * 4 + 0] = v.x;
+                own[v4 * 4 + 1] = v.y;
+                own[v4 * 4 + 2] = v.z;
+                own[v4 * 4 + 3] = v.w;
             }
         }
+        const float *t = kWide ? reinterpret_cast<const float *>(stage2) : own;
         constexpr int kSlots = kBlock / 16;
         // the group's fp16 operand as the matrix cores saw it
         h8 xq[G / 8];
@@ -1564,27 +1568,14 @@ __global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
 #pragma unroll
                     for (int uu = 0; uu < kU; ++uu) {
                         const int pos = ((su * 2 + hw) * kU + uu) * 16 + qq;
-                        bool in = su < su_end && (CELLS ? dd[bb][uu] < 3.0e38f : pos < csize) &&
-                                  (!test || dd[bb][uu] - dabs <= r2f);
-                        int cw = 0;
-                        if (in) cw = G == 8 && !CELLS ? pos : (int)perm[pos];
-                        auto take = [&](int c, double obj) {
-                            if (cand_better(obj, c, mine.obj, mine.idx)) {
+                        if (su < su_end && (CELLS ? dd[bb][uu] < 3.0e38f : pos < csize) &&
+                            (!test || dd[bb][uu] - dabs <= r2f)) {
+                            const int cw = G == 8 && !CELLS ? pos : (int)perm[pos];
+                            const double obj = exact_obj<G>(codebook + (int64_t)cw * G, s, t);
+                            if (cand_better(obj, cw, mine.obj, mine.idx)) {
                                 mine.obj = obj;
-                                mine.idx = c;
+                                mine.idx = cw;
                             }
-                        };
-                        if constexpr (kWide) {           // one codeword after the other, by the row of lanes
-                            for (;;) {
-                                const unsigned row_in = (unsigned)(__ballot(in) >> (lane & 48)) & 0xFFFFu;
-                                if (!row_in) break;
-                                const int src = __ffs((int)row_in) - 1;
-                                const int c = __shfl(cw, src, 16);
-                                take(c, exact_obj_row(codebook + (int64_t)c * G, s, t[0], qq));
-                                in = in && qq != src;
-                            }
-                        } else if (in) {
-                            take(cw, exact_obj<G>(codebook + (int64_t)cw * G, s, t));
                         }
                     }
                 }
@@ -1606,7 +1597,6 @@ __global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
             s_idx[threadIdx.x >> 6] = mine.idx;
         }
         __syncthreads();
-        const double o_prev2 = kWide ? exact_obj_row(codebook + (int64_t)prev * G, s, t[0], qq) : 0.0;
         if (threadIdx.x == 0) {
             cand_t win;
             win.obj = rec.obj;
@@ -1616,8 +1606,7 @@ __global__ __launch_bounds__(kBlock, G == 16 ? 5 : PV_RR_OCC) void k_rerank(
                     win.obj = s_obj[w];
                     win.idx = s_idx[w];
                 }
-            double o_prev = o_prev2;
-            if constexpr (!kWide) o_prev = exact_obj<G>(codebook + (int64_t)prev * G, s, t);
+            const double o_prev = exact_obj<G>(codebook + (int64_t)prev * G, s, t);
             int pick = win.idx;
             if (o_prev <= win.obj || pick == 0x7fffffff) pick = prev;
             if (pick != prev) {
@@ -1972,19 +1961,33 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
     }
     __syncthreads();
 
-    // ---- groups left open: every position of their open partitions, a wave a group.  One group in 45 is left open, in
-    // half of the blocks none, in the fullest five: one after the other by the whole block, which read
-    // the group again for each, the kernel took 29.3 us; so, with the group handed over in LDS, 23.3.
+    // ---- groups left open: every position of their open partitions, a wave a group, one or two groups all the waves.
+    // One group in 45 is left open, in half of the blocks none, in the fullest five: one after the other by the whole
+    // block, which read the group again for each, the kernel took 29.3 us; so, with the group handed over in LDS,
+    // 23.3.  (One wave for the only group too: a short list of groups of 16, 65 536 codewords, 5 us slower.)
     const unsigned nopen = s_nopen;
-    for (unsigned item = threadIdx.x >> 6; item < nopen; item += kBlock / 64) {
+    __shared__ two_t s_two[kBlock / 64];
+    const unsigned wave = threadIdx.x >> 6;
+    const unsigned share = nopen == 1u ? kBlock / 64 : nopen == 2u ? kBlock / 128 : 1u;      // waves a group
+    auto finish = [&](const open2_t<G> &rec, two_t win, const two_t *o, unsigned parts) {
+        // a codeword of an open partition may already sit in the team's pair (it was behind an
+        // evaluated key): the same index is not taken twice
+        const int t1 = win.i1, t2 = win.i2;
+        for (unsigned w = 0; w < parts; ++w) {
+            if (o[w].i1 != kPvNoCode && o[w].i1 != t1 && o[w].i1 != t2) two_insert(win, o[w].o1, o[w].i1);
+            if (o[w].i2 != kPvNoCode && o[w].i2 != t1 && o[w].i2 != t2) two_insert(win, o[w].o2, o[w].i2);
+        }
+        decide(win, rec.n, rec.prev);
+        atomicAdd(&s_cnt[3], 1u);
+    };
+    for (unsigned item = wave / share; item < nopen; item += (kBlock / 64) / share) {
         const open2_t<G> &rec = s_open[item];
         const float xx = rec.xx, cut = rec.dabs, r2f = rec.reach2;
         h8 xo[G / 8];
 #pragma unroll
         for (int h = 0; h < G / 8; ++h) xo[h] = rec.xq[h];
         const int lane = threadIdx.x & 63;
-        const int qq = lane & 15, slot = lane >> 4;
-        constexpr int kSlots = 64 / 16;
+        const int qq = lane & 15, slot = (int)(wave % share) * 4 + (lane >> 4);
         const bool test = r2f < 3.0e38f;
         two_t mine;
         two_clear(mine);
@@ -1997,7 +2000,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
             const int row = 8 * (qq >> 2) + 4 * hw + (qq & 3);
             constexpr int kBatch = G == 8 ? 4 : 2;
             // a lane's super-units: su0, su0 + step, ..; up to 64 / kU of them are looked at before the exact objectives
-            const int step = kSlots * per_half;
+            const int step = 4 * (int)share * per_half;
             for (int su0 = su_begin + (p % per_half) + slot * per_half; su0 < su_end; su0 += (64 / kU) * step) {
                 unsigned long long todo = 0;
                 for (int c = 0; c < 64 / kU && su0 + c * step < su_end; c += kBatch) {
@@ -2047,14 +2050,14 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
             o = two_merge(o, other);
         }
         if (lane == 0) {
-            // a codeword of an open partition may already sit in the team's pair (it was behind an
-            // evaluated key): the same index is not taken twice
-            two_t win = rec.best;
-            if (o.i1 != kPvNoCode && o.i1 != win.i1 && o.i1 != win.i2) two_insert(win, o.o1, o.i1);
-            if (o.i2 != kPvNoCode && o.i2 != win.i1 && o.i2 != win.i2) two_insert(win, o.o2, o.i2);
-            decide(win, rec.n, rec.prev);
-            atomicAdd(&s_cnt[3], 1u);
+            s_two[wave] = o;
+            if (share == 1u) finish(rec, rec.best, s_two + wave, 1u);
         }
+    }
+    if (share > 1u) {                        // the same in the whole block: every group had its waves at once
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0 && wave % share == 0u && wave / share < nopen)
+            finish(s_open[wave / share], s_open[wave / share].best, s_two + wave, share);
     }
     __syncthreads();
     if (threadIdx.x < 4) block_counts[4 * blockIdx.x + threadIdx.x] = s_cnt[threadIdx.x];
@@ -2382,8 +2385,12 @@ pv_status pv_launch_mfma_search(pv_ctx *ctx, const pv_layout *l, const float *T,
             hipLaunchKernelGGL((k_rerank<8, false>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
                                p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, (const float *)nullptr, 0, 0, x_meta,
                                cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
-        else
+        else if (k < kWideFrom)
             hipLaunchKernelGGL((k_rerank<16, false>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
+                               p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, (const float *)nullptr, 0, 0, x_meta,
+                               cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
+        else
+            hipLaunchKernelGGL((k_rerank<16, false, true>), rgrid, dim3(kBlock), 0, sm, x_stage, codebooks, (int)k,
                                p.k_pad, partials, p.P, p.per_half, p.ncyc, p.nsplit, (const int *)nullptr, (const float *)nullptr, 0, 0, x_meta,
                                cb_meta, A, cnorm, X, perm, codes, rr_counts, change_slots, nc, l->nbits);
     }

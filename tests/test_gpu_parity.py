@@ -504,13 +504,13 @@ def test_reencode_m1_small_codebook(g, B, k, case):
         check_codes_on(wl, T_np, idx, got, ref, info)
 
 
-@pytest.mark.parametrize("B,k", [(12, 2051), (12, 16400), (13, 16385), (14, 4099), (16, 1037)])
+@pytest.mark.parametrize("B,k", [(12, 2051), (14, 32767), (12, 32768), (13, 32785), (16, 33001)])
 @pytest.mark.parametrize("case", ["plain", "ties", "odd"])
 def test_reencode_m1_g16_row_of_lanes_a_codeword(B, k, case):
-    """Groups of 16 behind the filter: a row of lanes takes one codeword at a time.  Several codewords of a lane and of a
+    """Groups of 16 behind the filter, up to 32767 a lane a codeword, above a row of lanes.  Several codewords of a lane and of a
     row within reach (ties), partitions left open, values that are not finite, scales of zero and below, ids outside the
     matrix.  Codes and count equal the exact scan's."""
-    wl = workloads.make(160, 2048, 16, 1, B, seed=103, sigma_g=2e-3, tau=1.0)
+    wl = workloads.make(320, 2048, 16, 1, B, seed=103, sigma_g=2e-3, tau=1.0)
     rng = np.random.default_rng(k)
     if case == "ties":
         wl.codebooks[0, 1::2] = wl.codebooks[0, ::2]
