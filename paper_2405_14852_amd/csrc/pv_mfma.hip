@@ -1184,6 +1184,12 @@ __device__ __forceinline__ float float_above(double v) { return (float)v * 1.000
 // sums over a row make longer.  Whole searches, 14 bits: 7 864 groups 64.6 us (a lane a codeword: 62.2), 16 252 71.4 (70.7),
 // 32 505 96.0 (96.2), 65 536 115.9 (118.8); 16 bits: 32 505 133.8 (135.7), 183 500 508.7 (520.2); 12 bits: 183 500 143 (157).
 constexpr int64_t kWideFrom = 32768;
+// A row of lanes a codeword pays only where few codewords need their exact objective: with more than kRowMost lanes of a
+// team in need, each takes its own.  Whole searches with a lane a codeword throughout / the row throughout / the row up to
+// one lane / up to two.  12 bits, 52 428 groups: 30 % of the codewords zero 406 / 1737 / 412 / 416 us, one codeword 100
+// times the others 168 / 252 / 172 / 177, targets far from every codeword 137 / 187 / 134 / 135, ordinary ones 77.6 / 73.3 /
+// 74.6 / 75.4; 16 bits, 183 500 ordinary ones 518.9 / 507.2 / 512.2 / 512.6.
+constexpr int kRowMost = 1;
 template <int G, bool CELLS, bool WIDE = false>
 __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
     const float *__restrict__ x_stage, const float *__restrict__ codebook, int k, int k_pad,
@@ -1202,6 +1208,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
     static_assert(kTeam == 8 || kTeam == 16, "a team is 8 or 16 consecutive lanes");
     __shared__ unsigned s_cnt[4];   // groups decided by the teams, codes changed, candidates evaluated, groups scanned
     __shared__ open_rec_t s_open[kTeams];
+    __shared__ float s_tgt[kWide ? kTeams : 1][G];  // the block's targets, for a lane that takes a codeword alone
     __shared__ unsigned s_nopen;
     if (threadIdx.x < 4) s_cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) s_nopen = 0;
@@ -1221,6 +1228,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
     const int n = inlist ? __float_as_int(tail.z) : -1;
     bool live = n >= 0;                      // whole teams agree on every branch below
     if (!live) meta.w = -1.0f;
+    if constexpr (kWide) s_tgt[threadIdx.x / kTeam][q] = reinterpret_cast<const float *>(stage)[q];
     if (live && meta.w < 0.0f) {             // the filter was skipped for this group: every partition
         if (q == 0) {
             open_rec_t r;
@@ -1323,14 +1331,41 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                 c.idx = cw;
             }
         };
-        // exact objectives of every lane's positions in `todo`; kWide: one after the other for the team
+        auto team_min = [&](cand_t c) {
+            pv_team_stages<kTeam>([&](auto ctrl) {
+                constexpr int C = decltype(ctrl)::value;
+                const double o = pv_dpp_f64<C>(c.obj);
+                const int i = pv_dpp<C>(c.idx);
+                if (cand_better(o, i, c.obj, c.idx)) {
+                    c.obj = o;
+                    c.idx = i;
+                }
+            });
+            return c;
+        };
+        // Exact objectives of every lane's positions in `todo`.  kWide: those of up to kRowMost lanes one after the other for
+        // the team, those of more by each lane alone, which then has a best of its own.
         unsigned exact_evals = 1;                      // the previous code
+        bool alike = kWide;                            // the lanes of the team hold the same best
         const int team_shift = (threadIdx.x & 63) & ~(kTeam - 1);
         auto exact_of = [&](unsigned todo, const int (&cwd)[kMine], cand_t &c) {
             if constexpr (kWide) {
-                for (;;) {
-                    const unsigned team = (unsigned)((__ballot(todo != 0) >> team_shift) & ((1ull << kTeam) - 1ull));
-                    if (!team) break;
+                unsigned team = (unsigned)((__ballot(todo != 0) >> team_shift) & ((1ull << kTeam) - 1ull));
+                if (__builtin_expect(__popc(team) > kRowMost, 0)) {
+                    exact_evals += pv_team_sum_u32<kTeam>((unsigned)__popc(todo));
+#pragma unroll
+                    for (int uu = 0; uu < kMine; ++uu)
+                        if ((todo >> uu) & 1u) {
+                            const double o = exact_obj<G>(codebook + (int64_t)cwd[uu] * G, s, s_tgt[threadIdx.x / kTeam]);
+                            if (cand_better(o, cwd[uu], c.obj, c.idx)) {
+                                c.obj = o;
+                                c.idx = cwd[uu];
+                            }
+                        }
+                    alike = false;
+                    return;
+                }
+                while (team) {
                     int cw = cwd[kMine - 1];
 #pragma unroll
                     for (int uu = kMine - 1; uu-- > 0;) cw = (todo >> uu) & 1u ? cwd[uu] : cw;
@@ -1338,6 +1373,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                     exact_at(__shfl(cw, src, kTeam), c);
                     if (q == src) todo &= todo - 1u;
                     ++exact_evals;
+                    team = (unsigned)((__ballot(todo != 0) >> team_shift) & ((1ull << kTeam) - 1ull));
                 }
             } else {
 #pragma unroll
@@ -1355,18 +1391,6 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
             const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + dC + meta.w;
             const float r2 = rr * rr * 1.000002f;
             return r2 == r2 ? r2 : __builtin_huge_valf();   // NaN: nothing can be excluded
-        };
-        auto team_min = [&](cand_t c) {
-            pv_team_stages<kTeam>([&](auto ctrl) {
-                constexpr int C = decltype(ctrl)::value;
-                const double o = pv_dpp_f64<C>(c.obj);
-                const int i = pv_dpp<C>(c.idx);
-                if (cand_better(o, i, c.obj, c.idx)) {
-                    c.obj = o;
-                    c.idx = i;
-                }
-            });
-            return c;
         };
 
         cand_t mine;
@@ -1416,7 +1440,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                 if (!(chosen && uu == wu) && dd[uu] - dabs <= r2f && dd[uu] < 3.0e38f) todo |= 1u << uu;
             exact_of(todo, cwd, mine);
         }
-        cand_t first = kWide ? mine : team_min(mine);
+        cand_t first = alike ? mine : team_min(mine);
         if (first.obj < e_star) e_star = first.obj;
 
         // every codeword that was not evaluated and could still reach E* sits behind a key
@@ -1464,7 +1488,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
             if (q == src) pending &= ~(1u << u);
         }
         if (!kWide) exact_evals = pv_team_sum_u32<kTeam>(exact_evals);
-        const cand_t win = kWide ? mine : team_min(mine);
+        const cand_t win = alike ? mine : team_min(mine);
         if (q == 0) {
             if (open) {
                 // a partition may hide further codewords at or above kcut: all of its
@@ -1498,15 +1522,14 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
     __shared__ double s_obj[kBlock / 64];
     __shared__ int s_idx[kBlock / 64];
     for (unsigned item = 0; item < nopen; ++item) {
-        const open_rec_t rec = s_open[item];
-        const int n2 = rec.n;
+        const open_rec_t &rec = s_open[item];
         const pv_f4 *stage2 = reinterpret_cast<const pv_f4 *>(x_stage + (int64_t)rec.j * (G + 4));
         const pv_f4 tail2 = stage2[G / 4];
         const float s = tail2.x;
         const int prev = __float_as_int(tail2.y);
         const int lane = threadIdx.x & 63;
         const int qq = threadIdx.x & 15, slot = threadIdx.x >> 4;
-        // kWide: the targets are read again for each exact objective (from a cache), they are registers that spill
+        // kWide: the targets are read from LDS for each exact objective, they are registers that spill
         float own[kWide ? 1 : G];
         if constexpr (!kWide) {
 #pragma unroll
@@ -1518,7 +1541,9 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                 own[v4 * 4 + 3] = v.w;
             }
         }
-        const float *t = kWide ? reinterpret_cast<const float *>(stage2) : own;
+        const float *t;
+        if constexpr (kWide) t = s_tgt[rec.j - (int)blockIdx.x * kTeams];
+        else t = own;
         constexpr int kSlots = kBlock / 16;
         // the group's fp16 operand as the matrix cores saw it
         h8 xq[G / 8];
@@ -1610,7 +1635,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
             int pick = win.idx;
             if (o_prev <= win.obj || pick == 0x7fffffff) pick = prev;
             if (pick != prev) {
-                codes[n2] = (uint16_t)pick;
+                codes[rec.n] = (uint16_t)pick;
                 atomicAdd(&s_cnt[1], 1u);
             }
             atomicAdd(&s_cnt[3], 1u);

@@ -539,6 +539,39 @@ def test_reencode_m1_g16_row_of_lanes_a_codeword(B, k, case):
     assert st["reranked_candidates"] <= 64 * valid       # what the team looks at beside the open partitions
 
 
+@pytest.mark.parametrize("case", ["zeros", "clusters"])
+def test_reencode_m1_g16_many_codewords_within_reach(case):
+    """Many codewords of a row of lanes need their exact objective (a third of the codebook unused and zero; codewords in
+    tight clusters): the row takes them a lane each.  Codes equal the exact scan's, and a list of the length from which on rows
+    of lanes share a codeword costs what one group less does (one after the other by the row: 3 to 4 times as much)."""
+    wl = workloads.make(320, 2048, 16, 1, 12, seed=104, sigma_g=1e-2, tau=1.0)
+    rng = np.random.default_rng(104)
+    cb = wl.codebooks[0]
+    if case == "zeros":
+        cb[rng.permutation(4096)[:1229]] = 0.0
+    else:
+        cb[:] = cb[rng.integers(0, 64, size=4096)] + (2e-5 * rng.standard_normal(cb.shape)).astype(np.float32)
+    wl.W[:] = oracle.dequantize(wl.codes, wl.codebooks, wl.scales)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=32768, replace=False)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx)
+    run.ctx.pv_set_search_mode(0)
+    got, n_got = run.reencode(T, idx)
+    assert np.array_equal(got, want) and n_got == n_want
+    ids, codes, took = dev_i32(idx), run.codes.clone(), {32767: [], 32768: []}
+    for k in (32767, 32768) * 8:
+        codes.copy_(run.codes)
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        run.ctx.pv_reencode_groups(run.lay, T, run.cb, run.sc, ids, k, 1, codes)
+        stop.record()
+        torch.cuda.synchronize()
+        took[k].append(start.elapsed_time(stop))
+    assert np.median(took[32768]) < 1.5 * np.median(took[32767])
+
+
 def test_reencode_m1_of_a_smaller_k_can_be_captured():
     """The shape was seen with a list that the filter takes; a short list goes another way, and a captured
     call cannot allocate.  The replay also after the context counted something else."""
