@@ -3,10 +3,12 @@
 // The filter of pv_mfma.hip is three or four dependent launches (the codebook's statistics and operand, the groups' operands,
 // the contraction, the decisions), of which each lasts about 5 us for a list of some thousand groups.  A codebook of up
 // to 128 KiB fits the LDS, so a block can do all of it for its groups: every wave holds a share of the codewords as
-// operand rows in registers, contracts them with the block's groups, and teams of 8 lanes decide
+// operand rows in registers, contracts them with the block's groups, and teams of lanes decide
 // the groups from the keys, with exact objectives from the codebook in LDS.  Bounds and certificate are those of pv_mfma.hip:
-// a team evaluates the 16 U codewords behind the best key, then those behind every other key that can still reach the best
-// objective found, and all codewords of a partition (wave, half wave) whose runner-up key can.
+// a team evaluates the 16 U codewords behind the best key, then looks (the objective in single precision, the exact one where
+// that is within reach) at those behind every other key that can still reach the best
+// objective found, and at all codewords of a partition (wave, half wave) whose runner-up key can; where that is much, a wave
+// does it.
 // Latency up to a block a compute unit: load, statistics, operands, contraction, decisions are a chain of five barriers; beyond,
 // a block goes from one batch of groups to the next, whose targets are requested while this one is decided, and the
 // decisions (32 exact objectives a group, double) and the contraction share the vector ALU.  Whole calls, three or four launches / this:
@@ -23,6 +25,14 @@ struct small_shape {
     static constexpr int kMinBits = 8, kMaxBits = G == 8 ? 12 : 11;     // 128 KiB of codewords at most
 };
 
+// Super-units (32 codewords) beside the best key's that a team looks at by itself.  A group with more of them would keep the
+// block waiting, and goes to a wave; unless three quarters of a wave's groups have more and none more than twice that, up to
+// kAlikeUnits: then no team waits for another.  Whole searches, teams alone with every codeword in double / waves from 4 on /
+// from 16 on / as it is.  104 857 groups of 8, 4096 codewords, one of them 100 times the others 437 / 124 / 128 / 122 us,
+// lengths over three decades 859 / 422 / 432 / 412; 1024 codewords in 64 tight clusters 138 / 162 / 102 / 117; 52 428 groups of
+// 16, 2048 codewords over three decades 501 / 164 / 185 / 155, in clusters 252 / 163 / 164 / 161.
+constexpr unsigned kTeamUnits = 4, kAlikeUnits = 16;
+
 // SHIFT makes kv non-negative for every codeword that is no farther than D, the smaller of the current codeword's distance and
 // of a bound for the smallest one's, so a negative key marks codewords that cannot win.
 template <int G, int NBITS>
@@ -35,17 +45,22 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
     constexpr int kTiles = kCsize / 32 / kWaves;          // codeword tiles of a wave
     constexpr int kSu = kTiles / kU, kParts = 2 * kWaves;
     constexpr int kGroups = kCsize * G >= 1 << 15 ? 64 : 128;
-    constexpr int kTeam = 8, kRecs = (kParts + kTeam - 1) / kTeam;
-    static_assert(kTiles % kU == 0 && kGroups <= kThreads, "whole super-units; a thread a group");
+    constexpr int kTeam = kThreads >= 16 * kGroups ? 16 : 8, kRecs = (kParts + kTeam - 1) / kTeam;
+    static_assert(kTiles % kU == 0 && kU == 2 && kGroups <= kThreads, "whole super-units, half a wave each; a thread a group");
     __shared__ pv_f4 s_cb[kCsize * (G / 4)];
     __shared__ h8 s_x[kGroups * (G == 8 ? 2 : 3)];        // operand B: x_hi, {-1, -1, -1, pieces of SHIFT}
     __shared__ pv_f4 s_meta[kGroups], s_t[kGroups * (G / 4)], s_tmp[kWaves];
-    __shared__ float s_s[kGroups];
+    __shared__ float s_s[kGroups], s_err[kWaves];
     __shared__ double s_oprev[kGroups];
     __shared__ int s_prev[kGroups], s_n[kGroups];
     __shared__ int s_rec[2][kParts][kGroups];
-    __shared__ unsigned s_cnt[4];
+    __shared__ double s_best[kGroups];                    // of a group left open: the best objective so far, its codeword
+    __shared__ int s_best_idx[kGroups], s_open[kGroups];
+    __shared__ unsigned s_nopen, s_cnt[4];
     pv_counts_clear(counts);
+    // A codeword's parts of 16 bytes: eight lanes that read the same part of the rows that the matrix instruction gives them
+    // (0 to 3 and 8 to 11) or of eight rows in turn meet in no bank.
+    auto row_at = [](int c, int v) { return (c * (G / 4) + (G == 8 ? (c >> 3) & 1 : (c >> 2) & 3)) ^ v; };
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < 4) s_cnt[tid] = 0u;
@@ -80,7 +95,7 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
         for (int i = 0; i < kTiles / 2; ++i) {
             stat_add<G>(st, own[i]);
 #pragma unroll
-            for (int v = 0; v < G / 4; ++v) s_cb[(row0 + 64 * i) * (G / 4) + v] = own[i][v];
+            for (int v = 0; v < G / 4; ++v) s_cb[row_at(row0 + 64 * i, v)] = own[i][v];
         }
         all = pv_f4{wave_max_f(st.m), wave_min_f(st.nmin), wave_max_f(st.nmax), __any(st.bad) ? 1.0f : 0.0f};
         if (lane == 0) s_tmp[wave] = all;
@@ -117,16 +132,24 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
         first = __builtin_bit_cast(h8, f);
         second = __builtin_bit_cast(h8, g);
     };
+    float err = 0.0f;                                     // largest ||P c - c_hi||^2
 #pragma unroll
     for (int i = 0; i < kTiles / 2; ++i) {
         h8 c[G / 8], nrm, zero;
-        float n2 = 0.0f;
+        float n2 = 0.0f, e2 = 0.0f;
 #pragma unroll
         for (int v = 0; v < G / 4; ++v) {
-            const pv_f4 cw = s_cb[(row0 + 64 * i) * (G / 4) + v];
+            const pv_f4 cw = s_cb[row_at(row0 + 64 * i, v)];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) c[v / 2][v % 2 * 4 + e] = (_Float16)(ok ? 2.0f * P * cw[e] : 0.0f);
+            for (int e = 0; e < 4; ++e) {
+                const float pc = ok ? P * cw[e] : 0.0f;
+                const _Float16 hv = (_Float16)(2.0f * pc);
+                const float d = fmaf(-0.5f, (float)hv, pc);
+                c[v / 2][v % 2 * 4 + e] = hv;
+                e2 = fmaf(d, d, e2);
+            }
         }
+        err = fmaxf(err, e2);
 #pragma unroll
         for (int h = 0; h < G / 8; ++h)
 #pragma unroll
@@ -148,6 +171,9 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
             exchange(nrm, zero, an[2 * i], an[2 * i + 1]);
         }
     }
+    err = wave_max_f(err);
+    if (lane == 0) s_err[wave] = err;
+    float dC = 0.0f;                                      // >= every ||P c - c_hi||
     for (int batch = blockIdx.x; batch < nbatch; batch += gridDim.x) {
     const int have = min(per_block, k - batch * per_block);
     if (tid < kGroups) {
@@ -166,7 +192,7 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
             const float div = fits ? s : 1.0f;
 #pragma unroll
             for (int i = 0; i < G; ++i) {
-                const float t = tgt[i >> 2][i & 3], c = s_cb[code * (G / 4) + (i >> 2)][i & 3];
+                const float t = tgt[i >> 2][i & 3], c = s_cb[row_at(code, i >> 2)][i & 3];
                 const double r = fma((double)s, (double)c, -(double)t);     // (s * c is exact in double)
                 obj = obj + r * r;
                 const float u = P * (t / div);
@@ -219,8 +245,12 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
         s_oprev[tid] = obj;
         load_id(batch + gridDim.x);                       // of the next batch (none: -1)
     }
+    if (tid == 0) s_nopen = 0u;
     __syncthreads();
 
+    if (batch == (int)blockIdx.x)                         // (elements that the matrix core flushes: below 2^-15 each)
+        dC = __int_as_float(__builtin_amdgcn_readfirstlane(
+            __float_as_int(fast_sqrt(wave_max_f(s_err[lane % kWaves])) * 1.0001f + 1.3e-4f)));
     // ---- contraction: the wave's codewords with 32 groups at a time
     unsigned vmask = ~kKeyMask;
     asm volatile("" : "+v"(vmask));   // keep the mask in a vector register
@@ -254,66 +284,84 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
     __syncthreads();
 
     // ---- decisions
-    const int q = tid % kTeam, team_shift = lane & ~(kTeam - 1);
-    for (int g = tid / kTeam; g < have; g += kThreads / kTeam) {
-        const int ng = s_n[g];
-        if (ng < 0) continue;                             // whole teams
+    // (places worked out here again: kept over the loop they are registers that spill)
+    int tid_d = tid;
+    asm volatile("" : "+v"(tid_d));
+    const int lane_d = tid_d & 63, half_d = lane_d >> 5;
+    // The exact objective of codeword c for group g, as everywhere.
+    auto exact_at = [&](int g, float sg, int c, cand_t &mine) {
+        double obj = 0.0;
+#pragma unroll
+        for (int v = 0; v < G / 4; ++v) {
+            const pv_f4 cw = s_cb[row_at(c, v)], tv = s_t[g * (G / 4) + v];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double r = fma((double)sg, (double)cw[e], -(double)tv[e]);
+                obj = obj + r * r;
+            }
+        }
+        if (cand_better(obj, c, mine.obj, mine.idx)) {
+            mine.obj = obj;
+            mine.idx = c;
+        }
+    };
+    // What an objective in single precision must not exceed, if the exact one is to reach e: its sum has a relative error of at
+    // most (G + 2) 2^-24 (product and difference in one rounding), what underflows is below 2e-37.  (NaN, infinity: none does.)
+    auto limit_of = [](double e) { return float_above(e) * 1.000002f + 2.0e-37f; };
+    auto load_t = [&](int g, pv_f4 (&t)[G / 4]) {
+#pragma unroll
+        for (int v = 0; v < G / 4; ++v) t[v] = s_t[g * (G / 4) + v];
+    };
+    auto reaches = [&](const pv_f4 (&t)[G / 4], float sg, int c, float limit) {
+        float dd = 0.0f;
+#pragma unroll
+        for (int v = 0; v < G / 4; ++v) {
+            const pv_f4 cw = s_cb[row_at(c, v)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float r = fmaf(sg, cw[e], -t[v][e]);
+                dd = fmaf(r, r, dd);
+            }
+        }
+        return !(dd > limit);
+    };
+    auto team_min = [](auto team, cand_t c) {
+        pv_team_stages<decltype(team)::value>([&](auto ctrl) {
+            constexpr int C = decltype(ctrl)::value;
+            const double o = pv_dpp_f64<C>(c.obj);
+            const int i = pv_dpp<C>(c.idx);
+            if (cand_better(o, i, c.obj, c.idx)) {
+                c.obj = o;
+                c.idx = i;
+            }
+        });
+        return c;
+    };
+    auto decide = [&](int g, const cand_t &win, unsigned evals, bool scanned) {
+        const int prev = s_prev[g];
+        int pick = win.idx;
+        if (s_oprev[g] <= win.obj || pick == 0x7fffffff) pick = prev;
+        if (pick != prev) {
+            codes[s_n[g]] = (uint16_t)pick;
+            atomicAdd(&s_cnt[1], 1u);
+        }
+        atomicAdd(&s_cnt[scanned ? 3 : 0], 1u);
+        atomicAdd(&s_cnt[2], evals + 1u);
+    };
+    // A team a group (8 lanes, 16 where there are enough) evaluates what is behind the best key, and looks at what else can
+    // reach the objective found, if that is not too much (kTeamUnits).
+    const int q = tid_d % kTeam, team_shift = lane_d & ~(kTeam - 1);
+    for (int g = tid_d / kTeam; g < have; g += kThreads / kTeam) {
+        if (s_n[g] < 0) continue;                         // whole teams
         const pv_f4 m = s_meta[g];
         const float sg = s_s[g];
         const double o_prev = s_oprev[g];
-        const int prev = s_prev[g];
-        pv_f4 t[G / 4];                                   // (g = 16: from LDS as they are needed, the registers are short)
-#pragma unroll
-        for (int v = 0; v < G / 4; ++v) t[v] = G == 8 ? s_t[g * (G / 4) + v] : pv_f4{0.0f, 0.0f, 0.0f, 0.0f};
         cand_t mine;
         mine.obj = __builtin_huge_val();
         mine.idx = 0x7fffffff;
         unsigned evals = 0;
-        auto exact_at = [&](int c) {
-            double obj = 0.0;
-#pragma unroll
-            for (int v = 0; v < G / 4; ++v) {
-                const pv_f4 cw = s_cb[c * (G / 4) + v], tv = G == 8 ? t[v] : s_t[g * (G / 4) + v];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double r = fma((double)sg, (double)cw[e], -(double)tv[e]);
-                    obj = obj + r * r;
-                }
-            }
-            if (cand_better(obj, c, mine.obj, mine.idx)) {
-                mine.obj = obj;
-                mine.idx = c;
-            }
-            ++evals;
-        };
-        auto team_min = [&](cand_t c) {
-            pv_team_stages<kTeam>([&](auto ctrl) {
-                constexpr int C = decltype(ctrl)::value;
-                const double o = pv_dpp_f64<C>(c.obj);
-                const int i = pv_dpp<C>(c.idx);
-                if (cand_better(o, i, c.obj, c.idx)) {
-                    c.obj = o;
-                    c.idx = i;
-                }
-            });
-            return c;
-        };
-        // the codewords of super-unit su of partition p
-        constexpr int kEvalUnroll = G == 8 ? kU : 1;
-        auto eval_su = [&](int p, int su) {
-#pragma unroll kEvalUnroll
-            for (int uu = 0; uu < kU; ++uu)
-#pragma unroll
-                for (int e = 0; e < 16 / kTeam; ++e) {
-                    const int qq = q + kTeam * e;
-                    exact_at(((p >> 1) * kTiles + su * kU + uu) * 32 + 8 * (qq >> 2) + 4 * (p & 1) + (qq & 3));
-                }
-        };
-        bool scanned = false;
-        if (m.w < 0.0f) {                                 // not for the filter
-            for (int c = q; c < kCsize; c += kTeam) exact_at(c);
-            scanned = true;
-        } else {
+        bool open = m.w < 0.0f, scanned = false;          // (not for the filter)
+        if (!open) {
             int2 rec[kRecs];
 #pragma unroll
             for (int u = 0; u < kRecs; ++u) {
@@ -330,58 +378,150 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
             const int best_key = (int)(bk >> 32), best_p = 63 - (int)(bk & 0xFFFFFFFFll);
             double e_star = o_prev;
             if (best_key >= 0) {
-                eval_su(best_p, best_key & (int)kKeyMask);
-                const double o = team_min(mine).obj;
-                if (o < e_star) e_star = o;
+                constexpr int kEvalUnroll = G == 8 ? kU : 1;
+#pragma unroll kEvalUnroll
+                for (int uu = 0; uu < kU; ++uu)
+#pragma unroll
+                    for (int e = 0; e < 16 / kTeam; ++e) {
+                        const int qq = q + kTeam * e;
+                        exact_at(g, sg, ((best_p >> 1) * kTiles + (best_key & (int)kKeyMask) * kU + uu) * 32 +
+                                            8 * (qq >> 2) + 4 * (best_p & 1) + (qq & 3), mine);
+                    }
+                evals = 16 * kU / kTeam;                  // a lane
+                mine = team_min(std::integral_constant<int, kTeam>{}, mine);
+                if (mine.obj < e_star) e_star = mine.obj;
             }
             // every codeword that was not evaluated and could still reach E* sits behind a key whose upper bound is at
             // least kcut (see rerank), and not behind a negative one
             const float p_over_s = P * fast_rcp(fabsf(sg));
             const float ef = float_above(e_star);
-            const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + kNormMargin + m.w;
+            const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + dC + m.w;
             float r2 = rr * rr * 1.000002f;
             if (!(r2 == r2)) r2 = __builtin_huge_valf();
             const float base = m.x + m.y;
             const float kcut = (base * 0.999999f - r2 * 1.000001f) - m.z - 1.0e-6f * (base + r2);
             const bool no_bound = !(kcut > -3.0e38f);
-            unsigned pending = 0;                         // bit u: the key of rec[u]; bit 16 + u: all of its partition
+            unsigned pending = 0, units = 0;              // bit u: the key of rec[u]; bit 16 + u: all of its partition
 #pragma unroll
             for (int u = 0; u < kRecs; ++u) {
+                const int p = q + kTeam * u;
                 if (rec[u].y >= 0 && (no_bound || key_upper(rec[u].y) >= kcut)) pending |= 1u << (16 + u);
-                else if (rec[u].x >= 0 && q + kTeam * u != best_p && (no_bound || key_upper(rec[u].x) >= kcut)) pending |= 1u << u;
+                else if (rec[u].x >= 0 && p != best_p && (no_bound || key_upper(rec[u].x) >= kcut)) pending |= 1u << u;
             }
-            for (;;) {
-                const unsigned long long pb = __ballot(pending != 0u);
-                const unsigned team = (unsigned)((pb >> team_shift) & ((1ull << kTeam) - 1ull));
-                if (!team) break;
-                const int src = __ffs(team) - 1;          // lane of the team with work
-                const int bit = __ffs(__shfl((int)pending, src, kTeam)) - 1, u = bit & 15;
-                int key = 0;
+            if (__ballot(pending != 0u))
+                units = pv_team_sum_u32<kTeam>((unsigned)(__popc(pending & 0xFFFFu) + kSu * __popc(pending >> 16)));
+            unsigned most = kTeamUnits;
+            while (most < kAlikeUnits && __popcll(__ballot(units > most)) >= 48) most *= 2u;
+            if (__ballot(units > most)) most = kTeamUnits;
+            open = units > most;
+            if (open) {                                   // per partition, in place of its second key: 1: its best key, 2: all of it
 #pragma unroll
-                for (int uu = 0; uu < kRecs; ++uu)
-                    if (uu == u) key = rec[uu].x;
-                key = __shfl(key, src, kTeam);
-                if (bit >= 16) {
-                    for (int su = 0; su < kSu; ++su) eval_su(src + kTeam * u, su);
-                    scanned = true;
-                } else {
-                    eval_su(src + kTeam * u, key & (int)kKeyMask);
+                for (int u = 0; u < kRecs; ++u) {
+                    const int p = q + kTeam * u;
+                    if (p < kParts) s_rec[1][p][g] = (pending >> (16 + u)) & 1u ? 2 : (int)((pending >> u) & 1u);
                 }
-                if (q == src) pending &= ~(1u << bit);
+            } else if (units) {
+                float limit = limit_of(e_star);
+                // a lane's rows of a super-unit: of each tile, half of it the partition's, rows q, q + kTeam, ..
+                constexpr int kMine = kU * 16 / kTeam;
+                auto step_of = [](int i) { return kTeam == 16 ? 32 * i : 32 * (i >> 1) + 16 * (i & 1); };
+                pv_f4 t[G / 4];
+                load_t(g, t);
+                for (;;) {
+                    const unsigned team = (unsigned)(__ballot(pending != 0u) >> team_shift) & ((1u << kTeam) - 1u);
+                    if (!team) break;
+                    const int src = __ffs((int)team) - 1;         // lane of the team with work
+                    const int bit = __ffs(__shfl((int)pending, src, kTeam)) - 1, u = bit & 15;
+                    int key = 0;
+#pragma unroll
+                    for (int uu = 0; uu < kRecs; ++uu)
+                        if (uu == u) key = rec[uu].x;
+                    key = __shfl(key, src, kTeam);
+                    const int p = src + kTeam * u;
+                    const int su0 = bit >= 16 ? 0 : key & (int)kKeyMask, su1 = bit >= 16 ? kSu : su0 + 1;
+                    scanned |= bit >= 16;
+                    for (int su = su0; su < su1; ++su) {
+                        const int c0 = ((p >> 1) * kTiles + su * kU) * 32 + 4 * (p & 1) + 8 * (q >> 2) + (q & 3);
+                        unsigned todo = 0;
+#pragma unroll
+                        for (int i = 0; i < kMine; ++i) todo |= (unsigned)reaches(t, sg, c0 + step_of(i), limit) << i;
+                        if (todo) {
+                            evals += (unsigned)__popc(todo);
+                            do {
+                                const int i = __ffs((int)todo) - 1;
+                                exact_at(g, sg, c0 + step_of(i), mine);
+                                todo &= todo - 1u;
+                            } while (todo);
+                            limit = fminf(limit, limit_of(mine.obj));
+                        }
+                    }
+                    if (q == src) pending &= ~(1u << bit);
+                }
+                mine = team_min(std::integral_constant<int, kTeam>{}, mine);
             }
         }
-        const cand_t win = team_min(mine);
         evals = pv_team_sum_u32<kTeam>(evals);
         if (q == 0) {
-            int pick = win.idx;
-            if (o_prev <= win.obj || pick == 0x7fffffff) pick = prev;
-            if (pick != prev) {
-                codes[ng] = (uint16_t)pick;
-                atomicAdd(&s_cnt[1], 1u);
+            if (open) {
+                s_best[g] = mine.obj;
+                s_best_idx[g] = mine.idx;
+                s_open[atomicAdd(&s_nopen, 1u)] = g;
+                atomicAdd(&s_cnt[2], evals);
+            } else {
+                decide(g, mine, evals, scanned);
             }
-            atomicAdd(&s_cnt[scanned ? 3 : 0], 1u);
-            atomicAdd(&s_cnt[2], evals + 1u);
         }
+    }
+    __syncthreads();
+    // The groups left open, a wave each, two partitions at a time.
+    const int nopen = __builtin_amdgcn_readfirstlane((int)s_nopen);
+    if (nopen == 0) continue;                             // (nothing in LDS is read any more)
+    for (int item = wave; item < nopen; item += kWaves) {
+        const int g = s_open[item];
+        const float sg = s_s[g];
+        const bool all_of = s_meta[g].w < 0.0f;
+        const double o_prev = s_oprev[g];
+        cand_t mine;
+        mine.obj = s_best[g];
+        mine.idx = s_best_idx[g];
+        float limit = limit_of(mine.obj < o_prev ? mine.obj : o_prev);
+        pv_f4 t[G / 4];
+        load_t(g, t);
+        const int what_lane = lane_d >= kParts ? 0 : all_of ? 2 : s_rec[1][lane_d][g];
+        const bool scanned = __ballot(what_lane == 2) != 0;
+        unsigned evals = 0;
+        for (unsigned left = (unsigned)__ballot(what_lane != 0); left;) {
+            const int p0 = __ffs((int)left) - 1;
+            left &= left - 1u;
+            const int p1 = __ffs((int)left) - 1;          // -1: none
+            left &= left - 1u;
+            const int p = half_d && p1 >= 0 ? p1 : p0;
+            const int what = half_d && p1 < 0 ? 0 : all_of ? 2 : s_rec[1][p][g];
+            const int su0 = what == 1 ? s_rec[0][p][g] & (int)kKeyMask : 0, su1 = what == 1 ? su0 + 1 : what ? kSu : 0;
+            const int c0 = (p >> 1) * kTiles * 32 + 32 * ((lane_d >> 4) & 1) + 4 * (p & 1) + 8 * ((lane_d >> 2) & 3) + (lane_d & 3);
+            for (int su = su0; su < su1; ++su) {
+                const int c = c0 + su * kU * 32;
+                if (reaches(t, sg, c, limit)) {
+                    exact_at(g, sg, c, mine);
+                    limit = fminf(limit, limit_of(mine.obj));
+                    ++evals;
+                }
+            }
+        }
+        evals = pv_team_sum_u32<16>(evals);
+        evals += (unsigned)__shfl_xor((int)evals, 16);
+        evals += (unsigned)__shfl_xor((int)evals, 32);
+        cand_t win = team_min(std::integral_constant<int, 16>{}, mine);
+#pragma unroll
+        for (int mask = 16; mask < 64; mask <<= 1) {
+            const double o = __shfl_xor(win.obj, mask);
+            const int i = __shfl_xor(win.idx, mask);
+            if (cand_better(o, i, win.obj, win.idx)) {
+                win.obj = o;
+                win.idx = i;
+            }
+        }
+        if (lane_d == 0) decide(g, win, evals, scanned);
     }
     __syncthreads();
     }

@@ -504,6 +504,40 @@ def test_reencode_m1_small_codebook(g, B, k, case):
         check_codes_on(wl, T_np, idx, got, ref, info)
 
 
+@pytest.mark.parametrize("g,B", [(8, 8), (8, 9), (8, 10), (8, 11), (8, 12), (16, 8), (16, 9), (16, 10), (16, 11)])
+@pytest.mark.parametrize("case", ["one_large", "decades", "clusters", "far"])
+def test_reencode_m1_small_codebook_much_within_reach(g, B, case):
+    """Codebooks whose largest codeword leaves the others little of the fp16 range, tight clusters, targets far outside: many
+    keys and partitions can hold the nearest.  Codes and count equal the exact scan's, and what is evaluated in double stays the
+    32 codewords behind the best key and little else (beyond the fp16 range: everything)."""
+    k = 16449
+    wl = workloads.make(160, 128 * g, g, 1, B, seed=105, sigma_g=0.016 * 2.0 ** (-B / g), tau=1.0)
+    rng = np.random.default_rng(B)
+    cb = wl.codebooks[0]
+    if case == "one_large":
+        cb[7] *= np.float32(100.0)
+    elif case == "decades":
+        cb /= (rng.random((len(cb), 1)) ** 0.7 + 1e-3).astype(np.float32)
+    elif case == "clusters":
+        cb[:] = cb[np.arange(len(cb)) % 64] + (2e-5 * rng.standard_normal(cb.shape)).astype(np.float32)
+    else:
+        wl.scales[::3] *= np.float32(1e-4)
+    wl.W[:] = oracle.dequantize(wl.codes, wl.codebooks, wl.scales)
+    if case == "far":
+        wl.W[::6] += np.float32(0.02)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx)
+    run.ctx.pv_set_search_mode(0)
+    got, n_got = run.reencode(T, idx)
+    assert np.array_equal(got, want) and n_got == n_want
+    st = run.ctx.pv_reencode_stats()
+    assert st["filtered"] + st["fallback"] == k and st["exact"] == 0
+    assert case == "far" or st["reranked_candidates"] <= 48 * k
+
+
 @pytest.mark.parametrize("B,k", [(12, 2051), (14, 32767), (12, 32768), (13, 32785), (16, 33001)])
 @pytest.mark.parametrize("case", ["plain", "ties", "odd"])
 def test_reencode_m1_g16_row_of_lanes_a_codeword(B, k, case):
