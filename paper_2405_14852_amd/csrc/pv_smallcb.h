@@ -25,6 +25,13 @@ struct small_shape {
     static constexpr int kMinBits = 8, kMaxBits = G == 8 ? 12 : 11;     // 128 KiB of codewords at most
 };
 
+// Waves of a block (2^bits threads, at most 1024), waves a SIMD that the registers allow (160 of them with g = 16, 8 bits,
+// where 128 spill), and so the blocks that are on the chip's 256 compute units at once.
+constexpr int small_waves(int nbits) { return nbits >= 10 ? 16 : 1 << (nbits - 6); }
+constexpr int small_occupancy(int g, int nbits) { return g == 16 && nbits == 8 ? 3 : 4; }
+constexpr int small_blocks(int g, int nbits) { return 256 * (4 * small_occupancy(g, nbits) / small_waves(nbits)); }
+static_assert(small_blocks(8, 8) <= kCountedBlocks, "a block's counters have a place");
+
 // Super-units (32 codewords) beside the best key's that a team looks at by itself.  A group with more of them would keep the
 // block waiting, and goes to a wave; unless three quarters of a wave's groups have more and none more than twice that, up to
 // kAlikeUnits: then no team waits for another.  Whole searches, teams alone with every codeword in double / waves from 4 on /
@@ -36,12 +43,12 @@ constexpr unsigned kTeamUnits = 4, kAlikeUnits = 16;
 // SHIFT makes kv non-negative for every codeword that is no farther than D, the smaller of the current codeword's distance and
 // of a bound for the smallest one's, so a negative key marks codewords that cannot win.
 template <int G, int NBITS>
-__global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS == 8 ? 3 : 4) void k_search_small(
+__global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS)) void k_search_small(
     const float *__restrict__ T, const float *__restrict__ cb, const float *__restrict__ scales,
     const int32_t *__restrict__ list, int k, int per_block, int nbatch, uint16_t *__restrict__ codes, unsigned long long *num_changed,
     unsigned long long *stats, pv_counts counts, unsigned *__restrict__ block_counts, int gpr, int N)
 {
-    constexpr int kCsize = 1 << NBITS, kWaves = NBITS >= 10 ? 16 : 1 << (NBITS - 6), kThreads = kWaves * 64;
+    constexpr int kCsize = 1 << NBITS, kWaves = small_waves(NBITS), kThreads = kWaves * 64;
     constexpr int kTiles = kCsize / 32 / kWaves;          // codeword tiles of a wave
     constexpr int kSu = kTiles / kU, kParts = 2 * kWaves;
     constexpr int kGroups = kCsize * G >= 1 << 15 ? 64 : 128;
@@ -57,6 +64,9 @@ __global__ __launch_bounds__(NBITS >= 10 ? 1024 : 1 << NBITS, G == 16 && NBITS =
     __shared__ double s_best[kGroups];                    // of a group left open: the best objective so far, its codeword
     __shared__ int s_best_idx[kGroups], s_open[kGroups];
     __shared__ unsigned s_nopen, s_cnt[4];
+    static_assert((sizeof(s_cb) + sizeof(s_x) + sizeof(s_meta) + sizeof(s_t) + sizeof(s_tmp) + sizeof(s_s) + sizeof(s_err) +
+                   sizeof(s_oprev) + sizeof(s_prev) + sizeof(s_n) + sizeof(s_rec) + sizeof(s_best) + sizeof(s_best_idx) +
+                   sizeof(s_open) + 64) * (small_blocks(G, NBITS) / 256) <= 160 * 1024, "the LDS holds small_blocks");
     pv_counts_clear(counts);
     // A codeword's parts of 16 bytes: eight lanes that read the same part of the rows that the matrix instruction gives them
     // (0 to 3 and 8 to 11) or of eight rows in turn meet in no bank.
@@ -551,13 +561,13 @@ pv_status pv_launch_search_small(pv_ctx *ctx, const pv_layout *l, const float *T
     if (st != PV_OK) return st;
     const int g = l->group_size;
     // Groups of a batch: whole tiles of 32, as few as give every compute unit a block, as many as the LDS holds besides the
-    // codebook.  Blocks: what fits the chip at once (four waves a SIMD).
+    // codebook.  Blocks: what is on the chip at once, a batch each or several.  (Four waves a SIMD taken for g = 16, 8 bits too:
+    // the last quarter of the blocks began when the others had ended, 183 500 groups 55.2 us, so 49.1; 367 001 93.3, 87.7.)
     const int most = (g << l->nbits) >= 1 << 15 ? 64 : 128;
     int per_block = (int)(((k + 255) / 256 + 31) & ~(int64_t)31);
     if (k > 256 * most) per_block = most;
     const int nbatch = (int)((k + per_block - 1) / per_block);
-    const int slots = 256 * (l->nbits == 8 ? 4 : l->nbits == 9 ? 2 : 1);       // four waves a SIMD
-    static_assert(4 * 256 <= kCountedBlocks, "a block's counters have a place");
+    const int slots = small_blocks(g, l->nbits);
     const int blocks = nbatch < slots ? nbatch : slots;
     ctx->rr_blocks_last = blocks;
     ctx->rr_counts = rr_counts;
@@ -565,7 +575,7 @@ pv_status pv_launch_search_small(pv_ctx *ctx, const pv_layout *l, const float *T
     auto nc = reinterpret_cast<unsigned long long *>(num_changed);
 #define PV_SMALL_CB(G_, B_)                                                                                          \
     case B_:                                                                                                      \
-        hipLaunchKernelGGL((k_search_small<G_, B_>), dim3(blocks), dim3(B_ >= 10 ? 1024 : 1 << B_), 0, ctx->stream, T, codebook, scales, \
+        hipLaunchKernelGGL((k_search_small<G_, B_>), dim3(blocks), dim3(64 * small_waves(B_)), 0, ctx->stream, T, codebook, scales, \
                            group_idx, (int)k, per_block, nbatch, codes, nc, stats, counts, rr_counts, (int)(l->in_features / g),    \
                            (int)pv_num_groups(l));                                                                \
         break

@@ -463,7 +463,9 @@ def test_reencode_m1_in_one_launch(g, B, k, case):
 
 @pytest.mark.parametrize("g,B,k", [(8, 8, 16385), (8, 8, 131077), (8, 9, 16385), (8, 10, 8193), (8, 11, 1), (8, 11, 33),
                                    (8, 11, 32769), (8, 12, 31), (8, 12, 16449), (16, 8, 16385), (16, 9, 16385),
-                                   (16, 10, 8193), (16, 11, 65), (16, 11, 16449)])
+                                   (16, 10, 8193), (16, 11, 65), (16, 11, 16449),
+                                   # a batch more than there are blocks, in every form
+                                   (8, 9, 65569), (8, 10, 32801), (16, 8, 98337), (16, 9, 65569), (16, 10, 32801)])
 @pytest.mark.parametrize("case", ["plain", "ties", "odd"])
 def test_reencode_m1_small_codebook(g, B, k, case):
     """Codebooks that fit the LDS: the filter in one launch.  Lists that end inside a tile of groups, a block's groups
