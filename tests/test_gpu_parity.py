@@ -381,9 +381,22 @@ def reencode_case(wl, mode, idx=None, T_np=None):
 
 
 def check_route(run, k, filtered):
-    """The last search (mode 0, one codebook, k listed groups): the matrix-core filter took it, or one launch did."""
+    """The last search (mode 0, one codebook, k listed groups): a matrix-core filter took it (as several launches or as one,
+    see check_launches), or the one launch that evaluates everything did."""
     st = run.ctx.pv_reencode_stats()
     assert (st["filtered"] + st["fallback"], st["exact"]) == ((k, 0) if filtered else (0, k))
+
+
+def check_launches(run, T_np, idx, several):
+    """The search of this list in mode 0, once more and timed: the filter that prepares, contracts and re-ranks in launches of
+    their own, or one launch that does it all for a codebook that fits the LDS (the counters tell the same of both)."""
+    run.ctx.pv_set_search_mode(0)
+    run.ctx.pv_timing_enable(True)
+    run.ctx.pv_timing_reset()
+    run.reencode(dev_f32(T_np), idx)
+    n = {name: run.ctx.pv_timing_read(name)[1] for name in ("prep", "score_mfma", "rerank", "exact_scan")}
+    run.ctx.pv_timing_enable(False)
+    assert n == {"prep": int(several), "score_mfma": 1, "rerank": int(several), "exact_scan": 0}
 
 
 @pytest.mark.parametrize("mode", [1, 0])
@@ -410,14 +423,37 @@ def test_reencode_m1_matches_oracle(mode, g, B, shape, tau):
 @pytest.mark.parametrize("g", [8, 16])
 @pytest.mark.parametrize("k", [1, 31, 32, 33, 511, 512, 513, 4095, 4096, 4097, 4609, 8200])
 def test_reencode_m1_list_lengths_around_the_launch_plan(g, k):
-    """The filter's launch plan changes with the list length (group tiles per wave, codeword
-    splits, merged partitions, padded tail): lengths on both sides of every switch."""
+    """2048 codewords fit the LDS: one launch, whose batches and blocks change with the list length."""
     wl = workloads.make(96, 96 * g, g, 1, 11, seed=50, sigma_g=2e-3, tau=1.0)
     T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
     idx = np.sort(np.random.default_rng(k).choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
     run, got, want, info = reencode_case(wl, 0, idx=idx, T_np=T_np)
     st = run.ctx.pv_reencode_stats()
     assert st["filtered"] + st["fallback"] == k
+    check_launches(run, T_np, idx, several=False)
+
+
+@pytest.mark.parametrize("g,B", [(8, 13), (16, 12)])
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 511, 512, 513, 4095, 4096, 4097, 4609, 8200, 32768, 43521, 65536, 65537, 131073])
+def test_reencode_m1_list_lengths_around_the_filters_launch_plan(g, B, k):
+    """The plan of the filter in several launches changes with the list length (group tiles per wave, codeword
+    splits, merged partitions, padded tail): lengths on both sides of every switch.  Codes and count equal the exact scan's,
+    a sample the oracle's."""
+    wl = workloads.make(96 if k < 9000 else 1366, 96 * g, g, 1, B, seed=50, sigma_g=2e-3, tau=1.0)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    rng = np.random.default_rng(k)
+    idx = np.sort(rng.choice(wl.layout.num_groups, size=k, replace=False)).astype(np.int32)
+    run, T = GpuRun(wl), dev_f32(T_np)
+    run.ctx.pv_set_search_mode(1)
+    want, n_want = run.reencode(T, idx)
+    run.ctx.pv_set_search_mode(0)
+    got, n_got = run.reencode(T, idx)
+    assert np.array_equal(got, want) and n_got == n_want
+    check_route(run, k, filtered=True)
+    check_launches(run, T_np, idx, several=True)
+    sub = np.sort(rng.choice(idx, size=min(k, 256), replace=False))
+    ref, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, sub, wl.codes)
+    check_codes_on(wl, T_np, sub, got, ref, info)
 
 
 @pytest.mark.parametrize("g,B,k", [(8, 6, 1), (8, 6, 16384), (8, 7, 13), (8, 8, 8191), (8, 8, 16385), (8, 9, 4095),
@@ -762,13 +798,13 @@ def test_reencode_m1_on_one_context_equals_fresh_contexts():
 
 
 @pytest.mark.parametrize("g", [8, 16])
-@pytest.mark.parametrize("B", [5, 10, 11, 14])
+@pytest.mark.parametrize("B", [5, 7, 10, 11, 13, 14])
 @pytest.mark.parametrize("norms", ["one", "spread", "tiny"])
 def test_reencode_m1_codebook_preparation(g, B, norms):
-    """Both ways of taking the codebook's statistics (1024 codewords, and more), and norms on which
-    the norm ordering is put to the test: all alike, far beyond a sample's, at the bottom of float32."""
-    # (1024 codewords: more groups than one launch takes, which prepares nothing)
-    wl = workloads.make(256 if B == 10 else 64, 64 * g, g, 1, B, seed=71, sigma_g=4e-3, tau=0.55)
+    """Every way of taking the codebook's statistics (in the preparing launch, in one before it, or all in one launch: 10 and
+    11 bits), and norms on which the norm ordering is put to the test: all alike, far beyond a sample's, at the bottom of float32."""
+    # (128 and 1024 codewords: more groups than the launch that evaluates everything takes)
+    wl = workloads.make({7: 512, 10: 256}.get(B, 64), 64 * g, g, 1, B, seed=71, sigma_g=4e-3, tau=0.55)
     if norms == "one":
         wl.codebooks[:] = np.float32(0.02) * np.sign(wl.codebooks)
     if norms == "spread":
@@ -780,6 +816,8 @@ def test_reencode_m1_codebook_preparation(g, B, norms):
         wl.scales *= np.float32(1e14)
     run, *_ = reencode_case(wl, 0)
     check_route(run, wl.k, filtered=True)
+    T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+    check_launches(run, T_np, oracle.select_topk_groups(T_np, wl.W, g, wl.k), several=B not in (10, 11))
 
 
 @pytest.mark.parametrize("B,rows", [(5, 64), (6, 64), (9, 64), (13, 64), (16, 64), (6, 256), (9, 256)])
@@ -792,14 +830,14 @@ def test_reencode_m1_codebook_sizes_with_long_lists(B, rows):
     check_route(run, wl.k, filtered=rows == 256 or B not in (6, 9))
 
 
-@pytest.mark.parametrize("seed", range(8))
+@pytest.mark.parametrize("seed", range(14))
 def test_reencode_m1_filter_agrees_with_the_exact_scan_on_large_lists(seed):
     """Tens of thousands of groups per case, varied gradient sizes, scale and codebook spreads:
-    the matrix-core filter with its certificate (mode 0) and the exact scan (mode 1) must
-    write identical codes; a sample is checked against the oracle as well."""
+    the matrix-core filter with its certificate (mode 0; one launch below 13 bits, g = 16: 12, several from there) and the
+    exact scan (mode 1) must write identical codes; a sample is checked against the oracle as well."""
     rng = np.random.default_rng(2000 + seed)
     g = 8 if seed % 2 == 0 else 16
-    B = int(rng.integers(9, 14))
+    B = int(rng.integers(9, 14)) if seed < 8 else int(rng.integers(13, 15)) if g == 8 else int(rng.integers(12, 15))
     wl = workloads.make(256, 128 * g, g, 1, B, seed=90 + seed, sigma_g=float(10.0 ** rng.uniform(-4, -2)),
                         sigma_c=float(10.0 ** rng.uniform(-2.5, -1.0)), tau=0.7)
     wl.scales *= np.float32(10.0 ** rng.uniform(-1, 1))
@@ -816,13 +854,15 @@ def test_reencode_m1_filter_agrees_with_the_exact_scan_on_large_lists(seed):
     st = run.ctx.pv_reencode_stats()
     assert np.array_equal(fast, exact) and n_fast == n_exact
     assert st["filtered"] + st["fallback"] == wl.k
+    check_launches(run, T_np, idx, several=B >= (13 if g == 8 else 12))
     sub = np.sort(rng.choice(idx, size=512, replace=False))
     want, info = oracle.reencode_groups(T_np, wl.codebooks, wl.scales, sub, wl.codes)
     check_codes_on(wl, T_np, sub, fast, want, info)
 
 
 @pytest.mark.parametrize("mode", [1, 0])
-@pytest.mark.parametrize("g,B", [(8, 10), (8, 11), (16, 11)])     # one launch, the filter twice
+# everything evaluated in one launch, the filter in one (twice), the filter in several (twice)
+@pytest.mark.parametrize("g,B", [(8, 10), (8, 11), (16, 11), (8, 13), (16, 12)])
 def test_reencode_m1_scale_edge_cases(mode, g, B):
     wl = workloads.make(32, 64 * g, g, 1, B, seed=8, sigma_g=2e-3, tau=1.0)
     wl.scales[3] = 0.0          # every code ties: previous code kept
@@ -831,29 +871,35 @@ def test_reencode_m1_scale_edge_cases(mode, g, B):
     wl.scales[9] = 300.0
     run, got, want, _ = reencode_case(wl, mode)
     if mode == 0:
-        check_route(run, wl.k, filtered=B == 11)
+        check_route(run, wl.k, filtered=B >= 11)
+    if B >= 11:
+        T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+        check_launches(run, T_np, oracle.select_topk_groups(T_np, wl.W, g, wl.k), several=B >= 12)
     gpr = wl.layout.groups_per_row
     assert np.array_equal(got.reshape(-1)[3 * gpr:4 * gpr], wl.codes.reshape(-1)[3 * gpr:4 * gpr])
 
 
 @pytest.mark.parametrize("mode", [1, 0])
-@pytest.mark.parametrize("g,B", [(8, 8), (8, 11), (16, 11)])      # one launch, the filter twice
+@pytest.mark.parametrize("g,B", [(8, 8), (8, 11), (16, 11), (8, 13), (16, 12)])      # as above
 def test_reencode_m1_duplicate_codewords_tie_rule(mode, g, B):
     wl = workloads.make(16, 32 * g, g, 1, B, seed=9, sigma_g=2e-3, tau=1.0)
     half = 1 << (B - 1)
     wl.codebooks[0, half:] = wl.codebooks[0, :half]     # every codeword exists twice
     run, got, want, info = reencode_case(wl, mode)
     if mode == 0:
-        check_route(run, wl.k, filtered=B == 11)
+        check_route(run, wl.k, filtered=B >= 11)
+    if B >= 11:
+        T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha)
+        check_launches(run, T_np, oracle.select_topk_groups(T_np, wl.W, g, wl.k), several=B >= 12)
     assert np.array_equal(got, want)                     # exact ties resolve identically
 
 
-@pytest.mark.parametrize("g,B", [(8, 10), (16, 9), (8, 11), (16, 11), (16, 13)])   # one launch, then the filter
+@pytest.mark.parametrize("g,B", [(8, 10), (16, 9), (8, 11), (16, 11), (16, 13), (8, 13)])   # as above
 @pytest.mark.parametrize("case", ["targets_on_codewords", "mixed_magnitudes", "tiny_values", "huge_values",
                                   "clustered_codebook", "one_dimension_dominates"])
 def test_reencode_m1_inputs_that_stress_the_filter(g, B, case):
-    """Inputs chosen against the fp16 filter and its bounds; the decision must stay the oracle's (and, below
-    2048 codewords, that of the one launch that takes so little work)."""
+    """Inputs chosen against the fp16 filter and its bounds, in one launch (11 bits) and in several; the decision must stay the
+    oracle's (and, below 2048 codewords, that of the one launch that takes so little work)."""
     wl = workloads.make(24, 64 * g, g, 1, B, seed=12, sigma_g=2e-3, tau=1.0)
     rng = np.random.default_rng(12)
     T_np = None
@@ -879,6 +925,9 @@ def test_reencode_m1_inputs_that_stress_the_filter(g, B, case):
         wl.W[:, ::g] *= np.float32(1000.0)
     run, got, want, info = reencode_case(wl, 0, T_np=T_np)
     check_route(run, wl.k, filtered=B >= 11)
+    if B >= 11:
+        T_np = oracle.encode_targets(wl.W, wl.G, wl.alpha) if T_np is None else T_np
+        check_launches(run, T_np, oracle.select_topk_groups(T_np, wl.W, g, wl.k), several=B >= 13)
     if case == "targets_on_codewords":
         assert (info["obj_new"] <= 1e-12).all()
 
