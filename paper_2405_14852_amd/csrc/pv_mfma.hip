@@ -2024,11 +2024,13 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
             const int su_end = su_begin + split_count(split, ncyc, nsplit) * kResidues;
             const int row = 8 * (qq >> 2) + 4 * hw + (qq & 3);
             constexpr int kBatch = G == 8 ? 4 : 2;
-            // a lane's super-units: su0, su0 + step, ..; up to 64 / kU of them are looked at before the exact objectives
+            // A lane's super-units: su0, su0 + step, ..; up to kPass of them are looked at before the exact objectives.  (Those are
+            // all: make_plan leaves a partition 64 super-units at most.)
+            constexpr int kPass = 32 / kU;
             const int step = 4 * (int)share * per_half;
-            for (int su0 = su_begin + (p % per_half) + slot * per_half; su0 < su_end; su0 += (64 / kU) * step) {
-                unsigned long long todo = 0;
-                for (int c = 0; c < 64 / kU && su0 + c * step < su_end; c += kBatch) {
+            for (int su0 = su_begin + (p % per_half) + slot * per_half; su0 < su_end; su0 += kPass * step) {
+                unsigned todo = 0;
+                for (int c = 0; c < kPass && su0 + c * step < su_end; c += kBatch) {
                     // unconditional loads (a row of the split's last super-unit stands in past its end), all of a
                     // lane's batch on their way before the first is looked at
                     row_t rows[kBatch][kU];
@@ -2053,11 +2055,11 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
                             bits |= (unsigned)in << (bb * kU + uu);
                         }
                     }
-                    todo |= (unsigned long long)bits << (c * kU);
+                    todo |= bits << (c * kU);
                 }
                 while (todo) {
-                    const int i = __ffsll(todo) - 1;
-                    todo &= todo - 1ull;
+                    const int i = __ffs((int)todo) - 1;
+                    todo &= todo - 1u;
                     const int pos = (((su0 + (i / kU) * step) * 2 + hw) * kU + i % kU) * 16 + qq;
                     const int cw = G == 8 ? pos : (int)perm[pos];
                     two_insert(mine, exact_obj<G>(codebook + (int64_t)cw * G, rec.s, rec.t), cw);
@@ -2125,10 +2127,12 @@ plan_t make_plan(const pv_layout *l, int64_t k, bool two_nearest)
     // 3 and 5 splits cost the scoring 25 to 37 us).
     const int slots = 256 * PV_OCC;
     int want = slots / p.gblocks;
-    // The rounding over the two nearest codewords keeps the finer cut (4 items a slot): its
+    // The rounding over the two nearest codewords keeps the finer cut (4 items a slot) at g = 8: its
     // cut comes from the second best objective, more keys reach it, and with 32 records a group
-    // a third more groups were left to the block-wide scan (352 against 338 us there).
-    if (want < 4 && two_nearest) want = (4 * slots + p.gblocks - 1) / p.gblocks;
+    // twice as many groups are left open.  Whole calls, finer / power of two: g = 8, 16 bits, 146 800 groups 363 / 379 us,
+    // 73 400 203 / 206, 14 bits, 146 800 170 / 168; g = 16, where the records are what the rounding waits for, 183 500
+    // groups, 12 bits 300 / 274, 14 bits 336 / 312, 16 bits 588 / 594 and, far from every codeword, 680 / 660.
+    if (want < 4 && two_nearest && l->group_size == 8) want = (4 * slots + p.gblocks - 1) / p.gblocks;
     if (want < 4) {
         const int least = (2 * slots + p.gblocks - 1) / p.gblocks;
         want = 4;

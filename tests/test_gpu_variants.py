@@ -232,10 +232,12 @@ def test_stochastic_rounding_on_inputs_that_strain_the_filter(g, B):
 
 
 @pytest.mark.parametrize("shape,g,B", [((64, 1024), 8, 13), ((256, 2048), 8, 16), ((1024, 2048), 8, 16),
-                                       ((64, 2048), 16, 14), ((512, 4096), 16, 13)])
+                                       ((64, 2048), 16, 14), ((512, 4096), 16, 13),
+                                       # more than 65 536 groups: the codebook in four parts, or more (g = 8)
+                                       ((264, 4096), 16, 12), ((272, 4096), 16, 16), ((136, 4096), 8, 13)])
 def test_stochastic_rounding_filtered_like_the_scan(shape, g, B):
-    """Few and many groups (the codebook in many parts and in few, so that a part has up to hundreds of
-    positions a lane), rows without a usable scale (every position of every part), twins; the scan in
+    """Few and many groups (the codebook in many parts and in few: up to 64 super-units a part, 16 of them a lane of the
+    wave that scans it, 32 positions; one or two open groups a block share its waves), rows without a usable scale (every position of every part), twins; the scan in
     double precision is the reference, code by code."""
     wl = workloads.make(shape[0], shape[1], g, 1, B, sigma_g=5e-3, seed=900 + B)
     cb = wl.codebooks
