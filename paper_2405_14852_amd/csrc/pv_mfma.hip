@@ -1180,6 +1180,45 @@ __device__ __forceinline__ float fast_rcp(float v) { return __builtin_amdgcn_rcp
 // applied before the root takes over
 __device__ __forceinline__ float float_above(double v) { return (float)v * 1.0000002f; }
 
+// The certificate, the same in every kernel that decides from keys.  A codeword reaches the objective e only if
+// || c_hi - x_hi ||^2 <= (P sqrt(e) / |s| + dC + dx)^2, of which this is an upper bound in fp32, every rounding covered.
+__device__ __forceinline__ float reach2_of(double e, float p_over_s, float dC, float dx)
+{
+    const float ef = float_above(e);
+    // (a NaN passes the floor and the root, and is caught below)
+    const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + dC + dx;
+    const float r2 = rr * rr * 1.000002f;
+    return r2 == r2 ? r2 : __builtin_huge_valf();   // NaN: nothing can be excluded
+}
+// Such a codeword, if it was not evaluated, sits behind a key whose upper bound is at least `at`: a lower bound of
+// SHIFT + ||x_hi||^2 - reach2 - E1 (meta: x_meta's, fp32, every rounding covered).
+struct key_cut {
+    float at;
+    bool none;                                      // also for NaN: nothing can be excluded
+    __device__ __forceinline__ key_cut(const pv_f4 &meta, float reach2)
+    {
+        const float base = meta.x + meta.y;
+        at = (base * 0.999999f - reach2 * 1.000001f) - meta.z - 1.0e-6f * (base + reach2);
+        none = !(at > -3.0e38f);
+    }
+    __device__ __forceinline__ bool open(int key) const { return none || key_upper(key) >= at; }
+};
+// best of a team; all its lanes get it
+template <int TEAM>
+__device__ __forceinline__ cand_t cand_team_min(cand_t c)
+{
+    pv_team_stages<TEAM>([&](auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        const double o = pv_dpp_f64<C>(c.obj);
+        const int i = pv_dpp<C>(c.idx);
+        if (cand_better(o, i, c.obj, c.idx)) {
+            c.obj = o;
+            c.idx = i;
+        }
+    });
+    return c;
+}
+
 // WIDE from two rounds of blocks on, where the instructions issued count; below, the chain of one block does, which the
 // sums over a row make longer.  Whole searches, 14 bits: 7 864 groups 64.6 us (a lane a codeword: 62.2), 16 252 71.4 (70.7),
 // 32 505 96.0 (96.2), 65 536 115.9 (118.8); 16 bits: 32 505 133.8 (135.7), 183 500 508.7 (520.2); 12 bits: 183 500 143 (157).
@@ -1331,18 +1370,6 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                 c.idx = cw;
             }
         };
-        auto team_min = [&](cand_t c) {
-            pv_team_stages<kTeam>([&](auto ctrl) {
-                constexpr int C = decltype(ctrl)::value;
-                const double o = pv_dpp_f64<C>(c.obj);
-                const int i = pv_dpp<C>(c.idx);
-                if (cand_better(o, i, c.obj, c.idx)) {
-                    c.obj = o;
-                    c.idx = i;
-                }
-            });
-            return c;
-        };
         // Exact objectives of every lane's positions in `todo`.  kWide: those of up to kRowMost lanes one after the other for
         // the team, those of more by each lane alone, which then has a best of its own.
         unsigned exact_evals = 1;                      // the previous code
@@ -1384,14 +1411,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                     }
             }
         };
-        // upper bound, in fp32 with every rounding covered, of (P sqrt(E) / |s| + dC + dx)^2
-        auto reach2_of = [&](double e_star) {
-            const float ef = float_above(e_star);
-            // (a NaN passes the floor and the root, and is caught below)
-            const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + dC + meta.w;
-            const float r2 = rr * rr * 1.000002f;
-            return r2 == r2 ? r2 : __builtin_huge_valf();   // NaN: nothing can be excluded
-        };
+        auto reach2 = [&](double e) { return reach2_of(e, p_over_s, dC, meta.w); };
 
         cand_t mine;
         mine.obj = __builtin_huge_val();
@@ -1433,36 +1453,31 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                 o0 = __shfl(mine.obj, (int)(pick & 15u), kTeam);
             }
             if (o0 < e_star) e_star = o0;
-            const float r2f = reach2_of(e_star);
+            const float r2f = reach2(e_star);
             unsigned todo = 0;
 #pragma unroll
             for (int uu = 0; uu < kMine; ++uu)
                 if (!(chosen && uu == wu) && dd[uu] - dabs <= r2f && dd[uu] < 3.0e38f) todo |= 1u << uu;
             exact_of(todo, cwd, mine);
         }
-        cand_t first = alike ? mine : team_min(mine);
+        cand_t first = alike ? mine : cand_team_min<kTeam>(mine);
         if (first.obj < e_star) e_star = first.obj;
 
-        // every codeword that was not evaluated and could still reach E* sits behind a key
-        // whose upper bound is at least kcut
-        const float reach2f = reach2_of(e_star);
-        // lower bound of SHIFT + ||x_hi||^2 - reach2 - E1 (fp32, every rounding covered)
-        const float base = meta.x + meta.y;
-        const float kcut = (base * 0.999999f - reach2f * 1.000001f) - meta.z - 1.0e-6f * (base + reach2f);
-        const bool no_bound = !(kcut > -3.0e38f);      // also true for NaN: nothing can be excluded
+        // what was not evaluated and could still reach E*
+        const float reach2f = reach2(e_star);
+        const key_cut cut(meta, reach2f);
         unsigned pending = 0;                         // bit u: rec[u].x needs evaluation
-        unsigned long long open = 0;                  // partitions with a second key at or above kcut
+        unsigned long long open = 0;                  // partitions with a second key at or above the cut
 #pragma unroll
         for (int u = 0; u < kMaxRec; ++u) {
             int p = q + kTeam * u;
             if (p < P) {
-                if (rec[u].y != kNoKey && (no_bound || key_upper(rec[u].y) >= kcut)) open |= 1ull << p;
-                if (p != best_p && rec[u].x != kNoKey && (no_bound || key_upper(rec[u].x) >= kcut))
-                    pending |= 1u << u;
+                if (rec[u].y != kNoKey && cut.open(rec[u].y)) open |= 1ull << p;
+                if (p != best_p && rec[u].x != kNoKey && cut.open(rec[u].x)) pending |= 1u << u;
             }
         }
         open = pv_team_or_u64<kTeam>(open);
-        // the best key of every other partition at or above kcut: its positions are evaluated here
+        // the best key of every other partition at or above the cut: its positions are evaluated here
         for (;;) {
             const unsigned long long pb = __ballot(pending != 0);
             const unsigned team = (unsigned)((pb >> team_shift) & ((1ull << kTeam) - 1ull));
@@ -1488,14 +1503,14 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
             if (q == src) pending &= ~(1u << u);
         }
         if (!kWide) exact_evals = pv_team_sum_u32<kTeam>(exact_evals);
-        const cand_t win = alike ? mine : team_min(mine);
+        const cand_t win = alike ? mine : cand_team_min<kTeam>(mine);
         if (q == 0) {
             if (open) {
-                // a partition may hide further codewords at or above kcut: all of its
+                // a partition may hide further codewords at or above the cut: all of its
                 // positions are evaluated by the block, which also takes the decision
                 open_rec_t r;
                 r.obj = win.obj;
-                r.reach2 = no_bound ? __builtin_huge_valf() : reach2_of(o_prev < win.obj ? o_prev : win.obj);
+                r.reach2 = cut.none ? __builtin_huge_valf() : reach2(o_prev < win.obj ? o_prev : win.obj);
                 r.mask = open;
                 r.idx = win.idx;
                 r.n = n;
@@ -1845,12 +1860,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
         const bool next_is_best = (bk2 & 1ll) != 0;      // the best key of its partition (else its runner-up)
         const float p_over_s = Pscale * fast_rcp(fabsf(s));
         const float dC = fast_sqrt(__uint_as_float(cb_meta[2])) * 1.0001f + 1e-30f;
-        auto reach2_of = [&](double e) {
-            const float ef = float_above(e);   // a NaN passes the floor and the root, and is caught below
-            const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + dC + meta.w;
-            const float r2 = rr * rr * 1.000002f;
-            return r2 == r2 ? r2 : __builtin_huge_valf();
-        };
+        auto reach2_at = [&](double e) { return reach2_of(e, p_over_s, dC, meta.w); };
         two_t mine;
         two_clear(mine);
         unsigned exact_evals = 0;
@@ -1918,7 +1928,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
             todo &= ok;
             evaluate(todo, a, b);
             first = two_team<kTeam>(mine);
-            const float reach2 = first.i2 == kPvNoCode ? __builtin_huge_valf() : reach2_of(first.o2);
+            const float reach2 = first.i2 == kPvNoCode ? __builtin_huge_valf() : reach2_at(first.o2);
             unsigned more = 0;
 #pragma unroll
             for (int i = 0; i < 2 * kMine; ++i)
@@ -1929,20 +1939,17 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
                 first = two_team<kTeam>(mine);
             }
         }
-        // every codeword that was not evaluated and could still reach E2 sits behind a key at or above kcut
-        const float reach2f = first.i2 == kPvNoCode ? __builtin_huge_valf() : reach2_of(first.o2);
-        const float base = meta.x + meta.y;
-        const float kcut = (base * 0.999999f - reach2f * 1.000001f) - meta.z - 1.0e-6f * (base + reach2f);
-        const bool no_bound = !(kcut > -3.0e38f);
+        // what was not evaluated and could still reach E2
+        const float reach2f = first.i2 == kPvNoCode ? __builtin_huge_valf() : reach2_at(first.o2);
+        const key_cut cut(meta, reach2f);
         unsigned pending = 0;
         unsigned long long open = 0;
 #pragma unroll
         for (int u = 0; u < kMaxRec; ++u) {
             int p = q + kTeam * u;
             if (p < P) {
-                if (rec[u].y != kNoKey && (no_bound || key_upper(rec[u].y) >= kcut)) open |= 1ull << p;
-                if (p != best_p && !(next_is_best && p == next_p) && rec[u].x != kNoKey &&
-                    (no_bound || key_upper(rec[u].x) >= kcut))
+                if (rec[u].y != kNoKey && cut.open(rec[u].y)) open |= 1ull << p;
+                if (p != best_p && !(next_is_best && p == next_p) && rec[u].x != kNoKey && cut.open(rec[u].x))
                     pending |= 1u << u;
             }
         }
@@ -1976,7 +1983,7 @@ __global__ __launch_bounds__(kBlock, PV_RR_OCC) void k_round_top2(
         const two_t win = two_team<kTeam>(mine);
         if (q == 0) {
             if (open) {
-                leave_open(win, (no_bound || win.i2 == kPvNoCode) ? __builtin_huge_valf() : reach2_of(win.o2), open);
+                leave_open(win, (cut.none || win.i2 == kPvNoCode) ? __builtin_huge_valf() : reach2_at(win.o2), open);
             } else {
                 decide(win, n, prev);
                 atomicAdd(&s_cnt[0], 1u);

@@ -335,18 +335,6 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
         }
         return !(dd > limit);
     };
-    auto team_min = [](auto team, cand_t c) {
-        pv_team_stages<decltype(team)::value>([&](auto ctrl) {
-            constexpr int C = decltype(ctrl)::value;
-            const double o = pv_dpp_f64<C>(c.obj);
-            const int i = pv_dpp<C>(c.idx);
-            if (cand_better(o, i, c.obj, c.idx)) {
-                c.obj = o;
-                c.idx = i;
-            }
-        });
-        return c;
-    };
     auto decide = [&](int g, const cand_t &win, unsigned evals, bool scanned) {
         const int prev = s_prev[g];
         int pick = win.idx;
@@ -398,25 +386,17 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
                                             8 * (qq >> 2) + 4 * (best_p & 1) + (qq & 3), mine);
                     }
                 evals = 16 * kU / kTeam;                  // a lane
-                mine = team_min(std::integral_constant<int, kTeam>{}, mine);
+                mine = cand_team_min<kTeam>(mine);
                 if (mine.obj < e_star) e_star = mine.obj;
             }
-            // every codeword that was not evaluated and could still reach E* sits behind a key whose upper bound is at
-            // least kcut (see rerank), and not behind a negative one
-            const float p_over_s = P * fast_rcp(fabsf(sg));
-            const float ef = float_above(e_star);
-            const float rr = fast_sqrt(ef < 1.2e-38f ? 1.2e-38f : ef) * p_over_s * 1.000002f + dC + m.w;
-            float r2 = rr * rr * 1.000002f;
-            if (!(r2 == r2)) r2 = __builtin_huge_valf();
-            const float base = m.x + m.y;
-            const float kcut = (base * 0.999999f - r2 * 1.000001f) - m.z - 1.0e-6f * (base + r2);
-            const bool no_bound = !(kcut > -3.0e38f);
+            // what was not evaluated and could still reach E*; never what is behind a negative key
+            const key_cut cut(m, reach2_of(e_star, P * fast_rcp(fabsf(sg)), dC, m.w));
             unsigned pending = 0, units = 0;              // bit u: the key of rec[u]; bit 16 + u: all of its partition
 #pragma unroll
             for (int u = 0; u < kRecs; ++u) {
                 const int p = q + kTeam * u;
-                if (rec[u].y >= 0 && (no_bound || key_upper(rec[u].y) >= kcut)) pending |= 1u << (16 + u);
-                else if (rec[u].x >= 0 && p != best_p && (no_bound || key_upper(rec[u].x) >= kcut)) pending |= 1u << u;
+                if (rec[u].y >= 0 && cut.open(rec[u].y)) pending |= 1u << (16 + u);
+                else if (rec[u].x >= 0 && p != best_p && cut.open(rec[u].x)) pending |= 1u << u;
             }
             if (__ballot(pending != 0u))
                 units = pv_team_sum_u32<kTeam>((unsigned)(__popc(pending & 0xFFFFu) + kSu * __popc(pending >> 16)));
@@ -467,7 +447,7 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
                     }
                     if (q == src) pending &= ~(1u << bit);
                 }
-                mine = team_min(std::integral_constant<int, kTeam>{}, mine);
+                mine = cand_team_min<kTeam>(mine);
             }
         }
         evals = pv_team_sum_u32<kTeam>(evals);
@@ -521,7 +501,7 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
         evals = pv_team_sum_u32<16>(evals);
         evals += (unsigned)__shfl_xor((int)evals, 16);
         evals += (unsigned)__shfl_xor((int)evals, 32);
-        cand_t win = team_min(std::integral_constant<int, 16>{}, mine);
+        cand_t win = cand_team_min<16>(mine);
 #pragma unroll
         for (int mask = 16; mask < 64; mask <<= 1) {
             const double o = __shfl_xor(win.obj, mask);
