@@ -34,10 +34,10 @@ static_assert(small_blocks(8, 8) <= kCountedBlocks, "a block's counters have a p
 
 // Super-units (32 codewords) beside the best key's that a team looks at by itself.  A group with more of them would keep the
 // block waiting, and goes to a wave; unless three quarters of a wave's groups have more and none more than twice that, up to
-// kAlikeUnits: then no team waits for another.  Whole searches, teams alone with every codeword in double / waves from 4 on /
-// from 16 on / as it is.  104 857 groups of 8, 4096 codewords, one of them 100 times the others 437 / 124 / 128 / 122 us,
-// lengths over three decades 859 / 422 / 432 / 412; 1024 codewords in 64 tight clusters 138 / 162 / 102 / 117; 52 428 groups of
-// 16, 2048 codewords over three decades 501 / 164 / 185 / 155, in clusters 252 / 163 / 164 / 161.
+// kAlikeUnits: then no team waits for another.  Whole searches: teams alone, every codeword in double / more than 4 to a wave /
+// more than 16 / as it is.  104 857 groups of 8, 4096 codewords, one of them 100 times the others 437 / 134 / 153 / 138 us,
+// lengths over three decades 859 / 415 / 429 / 417; 1024 codewords in 64 tight clusters 138 / 159 / 95 / 98; 52 428 groups of
+// 16, 2048 codewords over three decades 501 / 160 / 179 / 161, in clusters 252 / 161 / 187 / 163.
 constexpr unsigned kTeamUnits = 4, kAlikeUnits = 16;
 
 // SHIFT makes kv non-negative for every codeword that is no farther than D, the smaller of the current codeword's distance and
@@ -57,14 +57,14 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
     __shared__ pv_f4 s_cb[kCsize * (G / 4)];
     __shared__ h8 s_x[kGroups * (G == 8 ? 2 : 3)];        // operand B: x_hi, {-1, -1, -1, pieces of SHIFT}
     __shared__ pv_f4 s_meta[kGroups], s_t[kGroups * (G / 4)], s_tmp[kWaves];
-    __shared__ float s_s[kGroups], s_err[kWaves];
+    __shared__ float s_s[kGroups];
     __shared__ double s_oprev[kGroups];
     __shared__ int s_prev[kGroups], s_n[kGroups];
     __shared__ int s_rec[2][kParts][kGroups];
     __shared__ double s_best[kGroups];                    // of a group left open: the best objective so far, its codeword
     __shared__ int s_best_idx[kGroups], s_open[kGroups];
     __shared__ unsigned s_nopen, s_cnt[4];
-    static_assert((sizeof(s_cb) + sizeof(s_x) + sizeof(s_meta) + sizeof(s_t) + sizeof(s_tmp) + sizeof(s_s) + sizeof(s_err) +
+    static_assert((sizeof(s_cb) + sizeof(s_x) + sizeof(s_meta) + sizeof(s_t) + sizeof(s_tmp) + sizeof(s_s) +
                    sizeof(s_oprev) + sizeof(s_prev) + sizeof(s_n) + sizeof(s_rec) + sizeof(s_best) + sizeof(s_best_idx) +
                    sizeof(s_open) + 64) * (small_blocks(G, NBITS) / 256) <= 160 * 1024, "the LDS holds small_blocks");
     pv_counts_clear(counts);
@@ -142,24 +142,16 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
         first = __builtin_bit_cast(h8, f);
         second = __builtin_bit_cast(h8, g);
     };
-    float err = 0.0f;                                     // largest ||P c - c_hi||^2
 #pragma unroll
     for (int i = 0; i < kTiles / 2; ++i) {
         h8 c[G / 8], nrm, zero;
-        float n2 = 0.0f, e2 = 0.0f;
+        float n2 = 0.0f;
 #pragma unroll
         for (int v = 0; v < G / 4; ++v) {
             const pv_f4 cw = s_cb[row_at(row0 + 64 * i, v)];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float pc = ok ? P * cw[e] : 0.0f;
-                const _Float16 hv = (_Float16)(2.0f * pc);
-                const float d = fmaf(-0.5f, (float)hv, pc);
-                c[v / 2][v % 2 * 4 + e] = hv;
-                e2 = fmaf(d, d, e2);
-            }
+            for (int e = 0; e < 4; ++e) c[v / 2][v % 2 * 4 + e] = (_Float16)(ok ? 2.0f * P * cw[e] : 0.0f);
         }
-        err = fmaxf(err, e2);
 #pragma unroll
         for (int h = 0; h < G / 8; ++h)
 #pragma unroll
@@ -181,9 +173,8 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
             exchange(nrm, zero, an[2 * i], an[2 * i + 1]);
         }
     }
-    err = wave_max_f(err);
-    if (lane == 0) s_err[wave] = err;
-    float dC = 0.0f;                                      // >= every ||P c - c_hi||
+    // >= every ||P c - c_hi||: half an fp16 ulp of each element, and what the matrix core flushes (below 2^-15 each)
+    const float dC = P * sqrtf(all.z) * 4.8838e-4f + 1.3e-4f;
     for (int batch = blockIdx.x; batch < nbatch; batch += gridDim.x) {
     const int have = min(per_block, k - batch * per_block);
     if (tid < kGroups) {
@@ -258,9 +249,6 @@ __global__ __launch_bounds__(64 * small_waves(NBITS), small_occupancy(G, NBITS))
     if (tid == 0) s_nopen = 0u;
     __syncthreads();
 
-    if (batch == (int)blockIdx.x)                         // (elements that the matrix core flushes: below 2^-15 each)
-        dC = __int_as_float(__builtin_amdgcn_readfirstlane(
-            __float_as_int(fast_sqrt(wave_max_f(s_err[lane % kWaves])) * 1.0001f + 1.3e-4f)));
     // ---- contraction: the wave's codewords with 32 groups at a time
     unsigned vmask = ~kKeyMask;
     asm volatile("" : "+v"(vmask));   // keep the mask in a vector register
