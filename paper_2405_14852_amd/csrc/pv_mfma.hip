@@ -1220,14 +1220,15 @@ __device__ __forceinline__ cand_t cand_team_min(cand_t c)
 }
 
 // WIDE from two rounds of blocks on, where the instructions issued count; below, the chain of one block does, which the
-// sums over a row make longer.  Whole searches, 14 bits: 7 864 groups 64.6 us (a lane a codeword: 62.2), 16 252 71.4 (70.7),
-// 32 505 96.0 (96.2), 65 536 115.9 (118.8); 16 bits: 32 505 133.8 (135.7), 183 500 508.7 (520.2); 12 bits: 183 500 143 (157).
+// sums over a row make longer.  Kernels of a search, a lane a codeword / WIDE, 14 bits: 7 864 groups 48.3 / 48.8 us, 16 252
+// 57.2 / 56.1, 32 505 76.0 / 76.0, 65 536 111.4 / 109.1; 16 bits: 32 505 115.7 / 115.5, 183 500 524 / 512; 12 bits: 183 500
+// 153 / 143.
 constexpr int64_t kWideFrom = 32768;
 // A row of lanes a codeword pays only where few codewords need their exact objective: with more than kRowMost lanes of a
-// team in need, each takes its own.  Whole searches with a lane a codeword throughout / the row throughout / the row up to
-// one lane / up to two.  12 bits, 52 428 groups: 30 % of the codewords zero 406 / 1737 / 412 / 416 us, one codeword 100
-// times the others 168 / 252 / 172 / 177, targets far from every codeword 137 / 187 / 134 / 135, ordinary ones 77.6 / 73.3 /
-// 74.6 / 75.4; 16 bits, 183 500 ordinary ones 518.9 / 507.2 / 512.2 / 512.6.
+// team in need, each takes its own.  Whole searches with a lane a codeword throughout / the row throughout / as it is.  12 bits,
+// 52 428 groups: 30 % of the codewords zero 405 / 1737 / 405 us, one codeword 100 times the others 167 / 252 / 167, targets
+// far from every codeword 136 / 187 / 131, ordinary ones 76.9 / 73.3 / 72.7; 16 bits, 183 500 ordinary ones 519 / 507 / 507.
+// (Two lanes one after the other: 177 with the one large codeword.)
 constexpr int kRowMost = 1;
 template <int G, bool CELLS, bool WIDE = false>
 __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
@@ -1556,9 +1557,16 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                 own[v4 * 4 + 3] = v.w;
             }
         }
-        const float *t;
-        if constexpr (kWide) t = s_tgt[rec.j - (int)blockIdx.x * kTeams];
-        else t = own;
+        const int team_of = kWide ? rec.j - (int)blockIdx.x * kTeams : 0;
+        auto exact = [&](int cw) {
+            if constexpr (kWide) {
+                int at = team_of;
+                asm volatile("" : "+v"(at));             // (else the targets are kept over the loop)
+                return exact_obj<G>(codebook + (int64_t)cw * G, s, s_tgt[at]);
+            } else {
+                return exact_obj<G>(codebook + (int64_t)cw * G, s, own);
+            }
+        };
         constexpr int kSlots = kBlock / 16;
         // the group's fp16 operand as the matrix cores saw it
         h8 xq[G / 8];
@@ -1611,7 +1619,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                         if (su < su_end && (CELLS ? dd[bb][uu] < 3.0e38f : pos < csize) &&
                             (!test || dd[bb][uu] - dabs <= r2f)) {
                             const int cw = G == 8 && !CELLS ? pos : (int)perm[pos];
-                            const double obj = exact_obj<G>(codebook + (int64_t)cw * G, s, t);
+                            const double obj = exact(cw);
                             if (cand_better(obj, cw, mine.obj, mine.idx)) {
                                 mine.obj = obj;
                                 mine.idx = cw;
@@ -1646,7 +1654,7 @@ __global__ __launch_bounds__(kBlock, WIDE ? 5 : PV_RR_OCC) void k_rerank(
                     win.obj = s_obj[w];
                     win.idx = s_idx[w];
                 }
-            const double o_prev = exact_obj<G>(codebook + (int64_t)prev * G, s, t);
+            const double o_prev = exact(prev);
             int pick = win.idx;
             if (o_prev <= win.obj || pick == 0x7fffffff) pick = prev;
             if (pick != prev) {
