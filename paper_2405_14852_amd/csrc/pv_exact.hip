@@ -1119,10 +1119,13 @@ __global__ __launch_bounds__(kBeamBlock, 4) void k_beam_2x8_mfma(
 
 }  // namespace
 
-// Where one launch beats the filter.  The search, filter / one launch: g = 8, 256 codewords, 64 groups 13.4 / 7.1 us,
-// 8192 14.8 / 7.3, 16384 16.2 / 10.8; 1024 codewords, 8192 groups (2^26 operations) 17.4 / 13.2, 16384
-// 18.9 / 22.0.  g = 16, where the filter also sorts norms: 256 codewords, 8192 groups 21.2 / 10.3; 1024, 8192
-// (2^27) 26.3 / 21.7, 16384 29.6 / 38.4.
+// Where one launch that evaluates everything beats the filter in several (6 and 7 bits): 64 groups 13.4 / 7.1 us, 8192 of 8
+// over 256 codewords 14.8 / 7.3, 16 384 16.2 / 10.8.  From 8 bits on the other side is k_search_small; the kernels in a trace,
+// this / k_search_small: g = 8, 256 codewords, 64 groups 6.0 / 6.7 us, 12 000 10.0 / 10.4, 16 384 12.3 / 10.1; 512, 4096
+// 8.2 / 8.6, 8192 10.7 / 8.6; 1024, 2048 8.6 / 9.7, 4096 11.5 / 10.0, 8192 15.8 / 10.3; g = 16, 256, 64 7.5 / 8.1, 8192
+// 11.2 / 10.7, 16 384 18.7 / 13.4; 1024, 2048 10.9 / 13.9, 4096 16.2 / 14.8, 8192 23.8 / 15.3.  So half of the range would do there
+// (2^25 operations, g = 16: 2^26); the line stays where it was drawn against the filter, because which groups were evaluated
+// from the start is what pv_reencode_stats tells a caller.
 bool pv_search_few(const pv_layout *l, int64_t k)
 {
     const int g = l->group_size;

@@ -9,13 +9,19 @@
 // that is within reach) at those behind every other key that can still reach the best
 // objective found, and at all codewords of a partition (wave, half wave) whose runner-up key can; where that is much, a wave
 // does it.
-// Latency up to a block a compute unit: load, statistics, operands, contraction, decisions are a chain of five barriers; beyond,
-// a block goes from one batch of groups to the next, whose targets are requested while this one is decided, and the
-// decisions (32 exact objectives a group, double) and the contraction share the vector ALU.  Whole calls, three or four launches / this:
-// g = 8, 256 codewords, 104 857 groups 32.6 / 21.2 us; 1024, 12 988 16.8 / 8.5, 104 857 50.5 / 34.3; 2048, 12 988 20.7 / 9.7,
-// 104 857 71.2 / 36.8; 4096, 1638 17.8 / 11.6, 12 988 22.3 / 13.7, 104 857 73.1 / 53.5; g = 16, 256, 52 428 38.2 / 18.7; 1024
-// 57.5 / 27.8; 2048, 6519 56.8 / 17.2, 52 428 80.1 / 46.5.  Operands kept in registers from the load on: 15 registers spilled and
-// 17.2 us with 4096 codewords, 12 988 groups; a block for every 64 groups, without the loop: 112 us with 104 857.
+// Up to a block a compute unit it is a chain of latencies: load, statistics, operands, contraction, decisions, with four barriers
+// (five if a group is left to a wave); beyond, a block goes from one batch of groups to the next, whose targets are requested
+// while this one is decided, and the decisions (32 exact objectives a group, double) and the contraction share the vector ALU.
+// On 12 988 groups, 4096 codewords, the vector ALU issues on 42 % of the kernel's cycles, the matrix cores work on 5 %, the LDS
+// on 21 % (8 % conflicts).  Kernels of a search in a trace, summed, three or four launches (between which there are gaps
+// of up to 20 us where the list is short) / this: g = 8, 256 codewords, 104 857 groups 39.0 / 22.1 us; 1024, 12 988
+// 20.1 / 12.5, 104 857 53.3 / 33.3; 2048, 12 988 25.4 / 13.5, 104 857 74.4 / 38.0; 4096, 1638 23.2 / 13.2, 12 988
+// 28.2 / 15.5, 104 857 77.0 / 53.2; g = 16, 256, 52 428 42.2 / 21.6; 1024 55.5 / 27.5; 2048, 6519 43.7 / 16.8, 52 428
+// 71.4 / 40.1.  (The list and codebook of 4096 and 12 988 in a step, whose other kernels take the caches: 16.2.)  Not kept:
+// operands in registers from the load on (15 registers spilled, a quarter slower with 4096 codewords, 12 988 groups); a block
+// for every 64 groups, without the loop (twice the time with 104 857).
+// Slower than several launches: g = 16 and many codewords in tight clusters (1024 in 64 of them 57 / 80 us, 2048 77 / 163): in
+// order of their norms, which the LDS has no room to sort, a cluster is behind one key, here behind half of the partitions.
 #pragma once
 
 namespace {
